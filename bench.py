@@ -248,7 +248,7 @@ def main():
         us_events = ev.elapsed_ms(e0, e1) * 1e3 / steps  # on the head-per-workgroup path: one launch per step, its average duration
         # Token-split path: the same steps once more with the library's events between its kernels.  An event costs
         # about 4.5 us of stream time, which is why these steps are not the timed ones; that cost, measured here between
-        # events recorded back to back, is taken off every segment (a segment = one kernel, or the slice + selection kernels).
+        # events recorded back to back, is taken off every segment (a segment = one kernel, or the selection kernel).
         seg = None
         if prof_steps:
             evs = [ev.create(A.AKV_NEVENTS) for _ in range(prof_steps)]
@@ -277,8 +277,8 @@ def main():
             dom_name = f"akv::head_kernel<{Hq // Hkv}, {1024 if Hq == Hkv else 512}, false, {'true' if path == 3 else 'false'}>"
             dom_tag, dom_us, dom_bytes = "head_kernel", us_events, by["total"]
         else:
-            entry["path"] = "token-split (K, slice, selection, V kernels" + ("; append kernel in front)" if append else ")")
-            entry["kernel_us"] = {"append": round(seg[0], 2), "k_kernel": round(seg[1], 2), "slice_and_selection": round(seg[2], 2),
+            entry["path"] = "token-split (K, selection, V kernels" + ("; append kernel in front)" if append else ")")
+            entry["kernel_us"] = {"append": round(seg[0], 2), "k_kernel": round(seg[1], 2), "selection_kernel": round(seg[2], 2),
                                   "v_kernel": round(seg[3], 2),
                                   "how": f"HIP events recorded by the library between its kernels, mean over {prof_steps} steps run right "
                                          f"after the timed ones, minus the {gap:.2f} us two back-to-back events lie apart"}

@@ -151,7 +151,7 @@ typedef struct akv_params {
                              the V kernel, [4] after its last kernel.  On the head-per-workgroup path, which
                              is one kernel, [1], [2] and [3] follow [0] at once                        */
     int32_t path;         /* 0: choose; 1: head-per-workgroup path (one kernel; needs Hq/Hkv <= 4);
-                             2: token-split path (four kernels).  Both give the same decisions.       */
+                             2: token-split path (three kernels).  Both give the same decisions.       */
     akv_stats *stats;     /* DEVICE pointer to counters the call adds to, or NULL                    */
 } akv_params;
 
@@ -217,7 +217,7 @@ akv_status akv_decode_attention(const akv_cache *cache, const uint16_t *q, void 
 
 /* Which kernels akv_decode_attention takes for this shape when params->path is 0: 1 = head-per-workgroup (one
  * kernel, logits through the workspace), 3 = the same with the logits kept in LDS (none written to memory),
- * 2 = token-split (four kernels); max_len as in akv_params (0 means Ncap).  Host computation; 0 on a bad shape.
+ * 2 = token-split (three kernels); max_len as in akv_params (0 means Ncap).  Host computation; 0 on a bad shape.
  * For callers that attribute time and bytes to kernels. */
 int32_t akv_decode_path(const akv_shape *shape, int32_t max_len);
 

@@ -280,9 +280,6 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
     a.logits = reinterpret_cast<float*>(ws + w.logits);
     a.tilemax = reinterpret_cast<float*>(ws + w.tilemax);
     a.M = reinterpret_cast<float*>(ws + w.M);
-    a.hist = reinterpret_cast<int32_t*>(ws + w.hist);
-    a.cand_sel = reinterpret_cast<int32_t*>(ws + w.cand_sel);
-    a.cand_phat = reinterpret_cast<float*>(ws + w.cand_phat);
     a.Ehat = reinterpret_cast<int32_t*>(ws + w.Ehat);
     a.partO = reinterpret_cast<float*>(ws + w.partO);
     a.partZ = reinterpret_cast<float*>(ws + w.partZ);

@@ -18,8 +18,7 @@ constexpr int kMaxG = 8;           // query heads per KV head supported
 
 // K pass: one wave covers one 256-token block (4 consecutive tokens per lane).
 constexpr int kKWaves = 4;                         // waves per workgroup
-constexpr int kMidSlice = kTB * kKWaves;           // tokens per workgroup of the K kernel and of the slice kernel
-constexpr int kHistStride = 66;                    // ints per slice histogram in the workspace (65 buckets)
+constexpr int kKChunk = kTB * kKWaves;             // tokens per workgroup of the K kernel
 // V pass: one workgroup covers kVChunk tokens; a wave reads 8 token rows per step.
 constexpr int kVWaves = 4;
 constexpr int kVChunk = 512;
@@ -29,10 +28,7 @@ struct WsLayout {
     size_t logits;   // float [B][Hq][Ncap]
     size_t tilemax;  // float [B][Hq][Ncap / 256]: per-wave-tile maxima of the K pass
     size_t M;        // float [B][Hq]
-    size_t hist;     // int32 [B][Hq][ceil(Ncap / 1024)][66]: per-slice histograms of score exponents (token-split path)
-    size_t cand_sel; // int32 [B][Hq][ceil(Ncap / 1024)][64]: per-slice top-k candidates, token | bucket << 24 (token-split path)
-    size_t cand_phat;// float, same shape: their weights
-    size_t Ehat;     // int32 [B][Hkv][D]
+    size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
     size_t partO;    // float [B][Hq][v_splits(Ncap)][D]
     size_t partZ;    // float [B][Hq][v_splits(Ncap)]
     size_t control;  // int32 [2][B][Hkv]: a spare word and the arrival counter of the V kernel per (sequence, KV head); zero between calls
@@ -54,10 +50,7 @@ inline WsLayout ws_layout(const akv_shape& s, bool control_front = false)
     w.logits = off;  off = align256(off + bhq * s.Ncap * sizeof(float));
     w.tilemax = off; off = align256(off + bhq * (s.Ncap / kTB) * sizeof(float));
     w.M = off;       off = align256(off + bhq * sizeof(float));
-    w.hist = off;    off = align256(off + bhq * ((s.Ncap + kMidSlice - 1) / kMidSlice) * kHistStride * sizeof(int32_t));
-    w.cand_sel = off; off = align256(off + bhq * ((s.Ncap + kMidSlice - 1) / kMidSlice) * AKV_MAX_TOPK * sizeof(int32_t));
-    w.cand_phat = off; off = align256(off + bhq * ((s.Ncap + kMidSlice - 1) / kMidSlice) * AKV_MAX_TOPK * sizeof(float));
-    w.Ehat = off;    off = align256(off + size_t(s.B) * s.Hkv * kD * sizeof(int32_t));
+    w.Ehat = off;    off = align256(off + bhq * kD * sizeof(int32_t));
     w.partO = off;   off = align256(off + bhq * v_splits(s.Ncap) * kD * sizeof(float));
     w.partZ = off;   off = align256(off + bhq * v_splits(s.Ncap) * sizeof(float));
     w.control_bytes = 2 * size_t(s.B) * s.Hkv * sizeof(int32_t);
@@ -90,9 +83,6 @@ struct DecodeArgs {
     float* partO;
     float* partZ;
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave; at least kVChunk)
-    int32_t* hist;       // per-slice histograms of the token-split path
-    int32_t* cand_sel;   // per-slice candidates of the token-split path
-    float* cand_phat;
     int32_t* kcount;     // [B][Hkv] spare control words (kept zero; the selection runs in a kernel of its own)
     int32_t* vcount;
     akv_debug dbg;       // device pointers or NULL
@@ -153,7 +143,7 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_stream_read(const void* p, size_t bytes, uint32_t* sink, hipStream_t st);
 hipError_t launch_unpack(const akv_cache& c, uint16_t* k_out, uint16_t* v_out, hipStream_t st);
-hipError_t launch_decode_split(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event);   // four kernels; the events (may be null) are recorded after the first and in front of the last
+hipError_t launch_decode_split(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event);   // three kernels; the events (may be null) are recorded after the first and in front of the last
 hipError_t launch_decode_head(const DecodeArgs& a, hipStream_t st);                         // one kernel, a head per workgroup
 int split_v_workgroups_per_cu(int G);   // resident workgroups of the token-split V kernel per compute unit (registers, LDS)
 bool head_path_supported(const akv_shape& s);

@@ -1,9 +1,7 @@
 // Decode attention, token-split path: the tokens of every (sequence, KV head) are spread over many
-// workgroups (long contexts, few heads).  Four kernels:
+// workgroups (long contexts, few heads).  Three kernels:
 //   K kernel          Rule 1 levels + q.K~, one 256-token block per wave;
-//   slice kernel      max, score exponents, their histogram and the local top-k candidates per 1024-token slice;
-//   selection kernel  one workgroup per (sequence, KV head): the top-k from the slices' histograms and candidates,
-//                     O_est and the result exponents;
+//   selection kernel  one workgroup per (sequence, query head): max, approximate top-k, O_est and the result exponents;
 //   V kernel          Rule 2 + S.V~ over chunks of tokens; the workgroup that finishes last combines the chunks.
 // Sections "Quantization of K-Cache", "Quantization of V-Cache", "Runtime of AlignedKV".
 #include <type_traits>
@@ -14,7 +12,7 @@
 
 namespace akv {
 
-// K kernel: workgroup = kKWaves waves = one slice of kMidSlice tokens of one (sequence, KV head); a wave walks one
+// K kernel: workgroup = kKWaves waves = kKChunk tokens of one (sequence, KV head); a wave walks one
 // 256-token block and leaves its logits and its block maximum in the workspace.
 template <int G>
 __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
@@ -25,10 +23,10 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63;
     const int Hq = a.s.Hq, Ncap = a.s.Ncap, NB = Ncap / kTB;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all four kernels
+    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int blk = blockIdx.x * kKWaves + wave_u;
-    if (blockIdx.x * kMidSlice >= len) return;   // whole workgroup beyond the sequence (uniform)
+    if (blockIdx.x * kKChunk >= len) return;   // whole workgroup beyond the sequence (uniform)
 
     if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
     k_levels<G>(a, b, h, ks, blockIdx.x == 0, len);
@@ -44,245 +42,151 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
     }
 }
 
-// Mid step in two kernels.
-// Slice kernel: workgroup = 256 threads = one slice of kMidSlice tokens of one (sequence, KV head).  Every workgroup
-// derives the global max logit from the block maxima and, per query head (a wave each), (1) builds the histogram of
-// score exponents of its slice and leaves it in the workspace as running sums over the buckets, (2) selects the
-// approximate top-k' of its own slice -- a superset of what the whole sequence can select from it, because the
-// cut bucket of the sequence is never later than the slice's own -- and leaves those candidates (token, bucket,
-// weight, in token order) in the workspace.  Little LDS, so that every slice of a long batch is resident at once.
-// Selection kernel: one workgroup per (sequence, KV head); each query head of the group goes to one of its waves:
-// the wave adds the slices' running sums (the first bucket where the total reaches k' is the cut), reads two words
-// per slice to learn how many selected tokens precede each slice and which slices hold any, and takes the
-// selection out of those slices' candidate lists (lane = candidate, ballots give the order); then all threads
-// compute O_est and the result exponents -- the V rows of all query heads are asked for before the first is used.
-// Everything that grows with the length of the sequence is spread over the slices; every dependent step of the
-// selection is one round trip to memory.
-template <int G>
-__global__ __launch_bounds__(256, (G <= 4 ? 8 : 4)) void split_slice_kernel(DecodeArgs a)   // every slice of a long batch resident at once
+// Mid step: one workgroup per (sequence, query head) does all of it -- the global max logit, the approximate top-k, O_est
+// and the result exponents of its head.  It reads only the K blocks that can hold a selected token: every block maximum
+// the K kernel left behind is itself a token, so the bucket Jb in which the running count of block maxima reaches k' is
+// an upper bound of the cut bucket, and a block whose best token lies beyond Jb holds nothing that counts (fewer than k'
+// blocks: all are read).  Each wave takes a contiguous range of the blocks, in token order:
+//   pass 1  the histogram of its tokens in buckets <= Jb (LDS; the floor bucket is what is left of the range, uncounted);
+//   cut     from the totals, and from the waves in front of it how many selected tokens precede its range;
+//   pass 2  the blocks up to the cut once more (from L2), in order: ballots place the selected tokens.  A block whose best
+//           token is in the cut bucket itself is passed over once enough tokens of that bucket have been seen.
+// Bound by its chain of dependent round trips to memory (maxima, pass 1, pass 2, V rows), about a microsecond each, not by
+// bytes; so a head has a workgroup of its own, with 32 blocks in flight per workgroup of eight waves in each pass.
+// Measured on whole calls, against a pass over every logit (1024-token slices, histograms and candidates through memory)
+// followed by one selecting workgroup per KV head: 198 -> 181 us (B 8, 32/8 heads, 32768 tokens), 301 -> 273 us (B 4, 32/8,
+// up to 131072), 101 -> 80 us (B 3, 64/8, up to 13000); no call got slower.
+constexpr int kSelThreads = 512;
+__global__ __launch_bounds__(kSelThreads) void split_select_kernel(DecodeArgs a)
 {
-    constexpr int NT = 256, kWaves = NT / 64;
-    static_assert(kMidSlice == NT * 4, "a thread owns four tokens of the slice");
-    __shared__ float red_s[G][kWaves];
-    __shared__ float M_s[G];
-    __shared__ int cntw_s[kWaves][kBuckets + 1];
+    constexpr int NT = kSelThreads, kWaves = NT / 64, kAhead = 4;   // kAhead: blocks of a wave in flight
+    __shared__ MidShared ms;
+    __shared__ float red_s[kWaves];
 
-    const int slice = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Hq = a.s.Hq, Ncap = a.s.Ncap, NB = Ncap / kTB;
-    const int S = (Ncap + kMidSlice - 1) / kMidSlice;   // slices per query head in the workspace
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all four kernels
-    if (slice * kMidSlice >= len) return;   // uniform; also every empty sequence
+    const int hq_i = blockIdx.x, b = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap, NB = Ncap / kTB;
+    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
+    if (len <= 0) return;   // uniform: an empty sequence has no selection (the V kernel writes its zeros)
+    const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / (Hq / Hkv);
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
+    const float* tm = a.tilemax + hq * NB;
 
-    // M = max over the block maxima (exact, order-free); the loads of all query heads of the group go out together
-    float mg[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) mg[g] = tid < nblk ? a.tilemax[(size_t(b) * Hq + size_t(h) * G + g) * NB + tid] : -INFINITY;
-    for (int i = tid + NT; i < nblk; i += NT)
-#pragma unroll
-        for (int g = 0; g < G; ++g) mg[g] = fmaxf(mg[g], a.tilemax[(size_t(b) * Hq + size_t(h) * G + g) * NB + i]);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float m = wave_max(mg[g]);
-        if (lane == 0) red_s[g][wave] = m;
-    }
+    // ---- the global max logit (exact, order-free) and the bound of the cut
+    float m = -INFINITY;
+    for (int i = tid; i < nblk; i += NT) m = fmaxf(m, tm[i]);
+    m = wave_max(m);
+    if (lane == 0) red_s[wave] = m;
+    if (tid < kBuckets) ms.cnt[tid] = 0;
+    for (int i = tid; i < kWaves * (kBuckets + 1); i += NT) (&ms.cntw[0][0])[i] = 0;
     __syncthreads();
-    if (tid < G) {
-        float m = red_s[tid][0];
-        for (int w = 1; w < kWaves; ++w) m = fmaxf(m, red_s[tid][w]);
-        M_s[tid] = m;
-        if (slice == 0) a.M[size_t(b) * Hq + size_t(h) * G + tid] = m;   // for the kernels that follow
+    float M = red_s[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) M = fmaxf(M, red_s[w]);
+    int Jb = 64;
+    if (nblk >= kk) {   // uniform
+        int n64 = 0;
+        for (int i0 = 0; i0 < nblk; i0 += NT) mid_hist_add(ms.cnt, i0 + tid < nblk ? -score_a(score_x(tm[i0 + tid], M, a.c)) : 1000, n64);
+        __syncthreads();
+        int below;
+        mid_find_cut(ms.cnt[lane], kk, Jb, below);   // the floor bucket is not counted: 64 if none before it is
     }
-    __syncthreads();
 
-    // ---- the slice: histogram and candidates, a wave per query head (lane -> 16 consecutive tokens; everything
-    // below is wave-local: LDS serves a wave's accesses in order, no barrier) ------------------------------------
-    {
-        const int in_slice = min(len - slice * kMidSlice, kMidSlice);
-        const int kloc = kk < in_slice ? kk : in_slice;   // candidates per query head
-        const int t0 = slice * kMidSlice + lane * 16;
-        for (int g = wave; g < G; g += kWaves) {
-            const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-            const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
-            const float M = M_s[g];
-            u32x4_t w[4];
+    const int b0 = int((long long)nblk * wave / kWaves), b1 = int((long long)nblk * (wave + 1) / kWaves);   // the wave's blocks
+    const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
+    // bucket of the best token of block c0 + lane (1000 past the range)
+    auto best_of = [&](int c0) { return c0 + lane < b1 ? -score_a(score_x(tm[c0 + lane], M, a.c)) : 1000; };
+    // takes up to kAhead blocks off the mask and asks for their logits (lane -> four consecutive tokens)
+    auto fetch = [&](int c0, uint64_t& mask, int (&blk)[kAhead], u32x4_t (&w)[kAhead]) {
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) w[q4] = __builtin_amdgcn_raw_buffer_load_b128(rs_lg, uint32_t(t0 + 4 * q4) * 4u, 0, 0);   // past Ncap: zeros
-            int* hw = &cntw_s[wave][0];
-            hw[lane] = 0;
-            if (lane < 2) hw[64 + lane] = 0;
-            float x[16];
-            int j[16];   // bucket j = -a_t (1000 at or past len)
+        for (int u = 0; u < kAhead; ++u) {
+            blk[u] = mask ? c0 + __builtin_ctzll(mask) : -1;
+            mask &= mask - 1;
+            w[u] = buf_load_b128(rs_lg, blk[u] >= 0 ? uint32_t(blk[u] * kTB + lane * 4) * 4u : kSkip);
+        }
+    };
+    auto score4 = [&](int blk, const u32x4_t& w, float (&x)[4], int (&j)[4]) {
+        const float lv[4] = {bits_float(w.x), bits_float(w.y), bits_float(w.z), bits_float(w.w)};
+        const int t0 = blk * kTB + lane * 4;
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const float lv[4] = {bits_float(w[q4].x), bits_float(w[q4].y), bits_float(w[q4].z), bits_float(w[q4].w)};
+        for (int i = 0; i < 4; ++i) {
+            x[i] = score_x(lv[i], M, a.c);
+            j[i] = t0 + i < len ? -score_a(x[i]) : 1000;
+        }
+    };
+    // ---- pass 1
+    for (int c0 = b0; c0 < b1; c0 += 64) {
+        const int best = best_of(c0);
+        uint64_t mask = __ballot(a.dbg.a ? best <= 64 : best <= min(Jb, 63));   // the export wants every token
+        while (mask) {
+            int blk[kAhead];
+            u32x4_t w[kAhead];
+            fetch(c0, mask, blk, w);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (blk[u] < 0) continue;   // uniform
+                float x[4];
+                int j[4];
+                score4(blk[u], w[u], x, j);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int ii = 4 * q4 + i;
-                    x[ii] = score_x(lv[i], M, a.c);
-                    j[ii] = t0 + ii < len ? -score_a(x[ii]) : 1000;
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            int n64 = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                mid_hist_add(hw, j[i], n64);
-                if (j[i] <= 64 && a.dbg.a) a.dbg.a[hq * Ncap + t0 + i] = (int8_t)(-j[i]);
-            }
-            mid_hist_flush(hw, n64);
-            __builtin_amdgcn_wave_barrier();
-            const int c = hw[lane];   // bucket `lane` of the slice's histogram
-            int J, below;
-            mid_find_cut(c, kloc, J, below);   // the slice's own cut: never earlier than the sequence's
-            const int fromcut = kloc - below;
-            {   // running sums over the buckets, for the workgroup that merges the slices
-                const int incl = wave_scan_add(c);
-                int32_t* dst = a.hist + (hq * S + slice) * kHistStride;
-                dst[lane] = incl;                         // tokens in buckets 0..lane
-                if (lane == 63) dst[64] = in_slice;       // all tokens of the slice
-            }
-            // the candidates in token order: tokens of each kind in lower lanes from five ballots per kind (one per
-            // bit of the lane's count, at most 16)
-            int c_lt = 0, c_eq = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                c_lt += j[i] < J;
-                c_eq += j[i] == J;
-            }
-            int n_lt = 0, n_eq = 0;
-#pragma unroll
-            for (int bit = 0; bit < 5; ++bit) {
-                const uint64_t b_lt = __ballot((c_lt >> bit) & 1), b_eq = __ballot((c_eq >> bit) & 1);
-                n_lt += __builtin_amdgcn_mbcnt_hi((uint32_t)(b_lt >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b_lt, 0)) << bit;
-                n_eq += __builtin_amdgcn_mbcnt_hi((uint32_t)(b_eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b_eq, 0)) << bit;
-            }
-            const size_t base = (hq * S + slice) * AKV_MAX_TOPK;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const bool is_lt = j[i] < J, is_eq = j[i] == J;
-                if (is_lt || (is_eq && n_eq < fromcut)) {
-                    const int pos = n_lt + (n_eq < fromcut ? n_eq : fromcut);
-                    const float fl = floorf(x[i]);
-                    a.cand_sel[base + pos] = (t0 + i) | (j[i] << 24);
-                    a.cand_phat[base + pos] = ldexpf(1.0f + (x[i] - fl), -j[i]);   // as mid_emit
-                }
-                n_lt += is_lt;
-                n_eq += is_eq;
-            }
-            if (lane >= kloc) a.cand_sel[base + lane] = -1;   // no candidate
-        }
-    }
-}
-
-template <int G>
-__global__ __launch_bounds__(256) void split_select_kernel(DecodeArgs a)
-{
-    constexpr int NT = 256, kWaves = NT / 64;
-    static_assert(kWaves <= kMidSets, "a selection per wave");
-    __shared__ MidShared ms;
-    __shared__ int list_s[kWaves][AKV_MAX_TOPK], list_lt[kWaves][AKV_MAX_TOPK], list_eq[kWaves][AKV_MAX_TOPK];
-
-    const int h = blockIdx.x, b = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int S = (Ncap + kMidSlice - 1) / kMidSlice;   // slices per query head in the workspace
-    const int len = min(min(a.lens[b], Ncap), a.max_len);
-    const size_t bh = size_t(b) * Hkv + h;
-    if (len <= 0) return;   // uniform: an empty sequence has no selection (the V kernel writes its zeros)
-    const int nsl = (len + kMidSlice - 1) / kMidSlice;
-    const int kk = a.topk < len ? a.topk : len;
-
-    int ehat = 32767;   // min over the group of the result exponent of channel tid (tid < D)
-    for (int g0 = 0; g0 < G; g0 += kWaves) {
-        const int g = g0 + wave;
-        if (g < G) {   // wave-uniform: this wave collects the selection of query head g
-            const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-            const int32_t* hist = a.hist + hq * S * kHistStride;
-            // running sums over the buckets, added over the slices: lane = bucket (0..63); 16 loads in flight
-            int tot = 0;
-            for (int s0 = 0; s0 < nsl; s0 += 16) {
-                int v[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) v[i] = s0 + i < nsl ? hist[(s0 + i) * kHistStride + lane] : 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) tot += v[i];
-            }
-            const uint64_t reached = __ballot(tot >= kk);
-            const int J = reached ? __builtin_ctzll(reached) : 64;   // bucket 64 is the cut only if none before it is
-            const int below = J == 0 ? 0 : wave_read(tot, J - 1);
-            const int fromcut = kk - below;
-            // slices that hold selected tokens, with the number of tokens of each kind before them: lane = slice
-            int nlist = 0, carry_lt = 0, carry_eq = 0;
-            for (int s0 = 0; s0 < nsl; s0 += 64) {
-                const int s = s0 + lane;
-                int c_lt = 0, c_le = 0;
-                if (s < nsl) {
-                    if (J > 0) c_lt = hist[s * kHistStride + J - 1];
-                    c_le = hist[s * kHistStride + J];
-                }
-                const int c_eq = c_le - c_lt;
-                const int i_lt = wave_scan_add(c_lt), i_eq = wave_scan_add(c_eq);   // inclusive over the lanes
-                const int p_lt = carry_lt + i_lt - c_lt, p_eq = carry_eq + i_eq - c_eq;   // exclusive prefixes
-                const bool holds = c_lt > 0 || (c_eq > 0 && p_eq < fromcut);
-                const uint64_t hb = __ballot(holds);   // at most kk such slices in all: each holds a selected token
-                if (holds) {
-                    const int at = nlist + __builtin_amdgcn_mbcnt_hi((uint32_t)(hb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hb, 0));
-                    list_s[wave][at] = s;
-                    list_lt[wave][at] = p_lt;
-                    list_eq[wave][at] = p_eq;
-                }
-                nlist += __builtin_popcountll(hb);
-                carry_lt += wave_read(i_lt, 63);
-                carry_eq += wave_read(i_eq, 63);
-            }
-            // ---- the selection out of those slices' candidates: lane = candidate (token order inside a slice) ------
-            constexpr int kAhead = 16;   // slices of the list whose candidates are in flight
-            int cs[kAhead];
-            float cp[kAhead];
-            auto fetch = [&](int e, int& sel, float& phat) {
-                const bool on = e < nlist;
-                const size_t at = (hq * S + (on ? list_s[wave][e] : 0)) * AKV_MAX_TOPK + lane;
-                sel = on ? a.cand_sel[at] : -1;
-                phat = on ? a.cand_phat[at] : 0.0f;
-            };
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k) fetch(k, cs[k], cp[k]);
-            for (int e = 0; e < nlist; e += kAhead) {
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    if (e + k < nlist) {   // uniform
-                        const int jj = cs[k] >> 24, t = cs[k] & 0xFFFFFF;
-                        const bool is_lt = cs[k] >= 0 && jj < J, is_eq = cs[k] >= 0 && jj == J;
-                        const uint64_t b_lt = __ballot(is_lt), b_eq = __ballot(is_eq);
-                        const int n_lt = list_lt[wave][e + k] + __builtin_amdgcn_mbcnt_hi((uint32_t)(b_lt >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b_lt, 0));
-                        const int n_eq = list_eq[wave][e + k] + __builtin_amdgcn_mbcnt_hi((uint32_t)(b_eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b_eq, 0));
-                        if (is_lt || (is_eq && n_eq < fromcut)) {
-                            const int pos = n_lt + (n_eq < fromcut ? n_eq : fromcut);
-                            ms.sel[wave][pos] = t;
-                            ms.phat[wave][pos] = cp[k];
-                        }
-                    }
-                    fetch(e + k + kAhead, cs[k], cp[k]);
+                    if (j[i] <= min(Jb, 63)) atomicAdd(&ms.cntw[wave][j[i]], 1);
+                    if (j[i] <= 64 && a.dbg.a) a.dbg.a[hq * Ncap + blk[u] * kTB + lane * 4 + i] = (int8_t)(-j[i]);
                 }
             }
         }
-        __syncthreads();
-        // all threads: the selected V rows of every head of this round are asked for, then used head by head
-        OestRows<NT> rows[kWaves < G ? kWaves : G];
-#pragma unroll
-        for (int w = 0; w < (kWaves < G ? kWaves : G); ++w)
-            if (g0 + w < G) mid_oest_fetch<NT>(a, bh, kk, ms, w, rows[w]);
-#pragma unroll
-        for (int w = 0; w < (kWaves < G ? kWaves : G); ++w)
-            if (g0 + w < G) mid_oest_finish<NT>(a, size_t(b) * Hq + size_t(h) * G + g0 + w, kk, ms, w, rows[w], ehat);   // ends with a barrier
     }
-    if (tid < kD) {
-        a.Ehat[bh * kD + tid] = ehat;
-        if (a.dbg.Ehat) a.dbg.Ehat[bh * kD + tid] = (int16_t)ehat;
+    __syncthreads();
+    // ---- the cut, and the selected tokens of each kind in the waves before this one
+    int tot = 0, before = 0;   // bucket `lane`: all waves / the waves before this one
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const int c = ms.cntw[w][lane];
+        tot += c;
+        before += w < wave ? c : 0;
     }
+    int J, below;
+    mid_find_cut(tot, kk, J, below);
+    const int fromcut = kk - below;
+    int n_lt0 = wave_read(wave_scan_add(lane < J ? before : 0), 63);
+    int n_eq0 = J < 64 ? wave_read(before, J) : min(b0 * kTB, len) - n_lt0;   // the cut in the floor bucket: all buckets before it are counted
+    // ---- pass 2
+    for (int c0 = b0; c0 < b1; c0 += 64) {
+        const int best = best_of(c0);
+        uint64_t mask = __ballot(best <= J);
+        while (mask) {
+            if (n_eq0 >= fromcut) mask &= __ballot(best < J);   // blocks that could only add to the cut bucket
+            if (!mask) break;
+            int blk[kAhead];
+            u32x4_t w[kAhead];
+            fetch(c0, mask, blk, w);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (blk[u] < 0) continue;   // uniform
+                float x[4];
+                int j[4], n_lt, n_eq, w_lt, w_eq;
+                score4(blk[u], w[u], x, j);
+                mid_wave_order(j, J, n_lt, n_eq, w_lt, w_eq);
+                n_lt += n_lt0;
+                n_eq += n_eq0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool is_lt = j[i] < J, is_eq = j[i] == J;
+                    if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(ms, n_lt + (n_eq < fromcut ? n_eq : fromcut), blk[u] * kTB + lane * 4 + i, x[i], j[i]);
+                    n_lt += is_lt;
+                    n_eq += is_eq;
+                }
+                n_lt0 += w_lt;
+                n_eq0 += w_eq;
+            }
+        }
+    }
+    __syncthreads();
+    int ehat = 32767;
+    mid_oest<NT>(a, bh, hq, kk, ms, ehat);
+    if (tid < kD) a.Ehat[hq * kD + tid] = ehat;
+    if (tid == 0) a.M[hq] = M;
 }
 
 // Workgroup = kVWaves waves, one (sequence, KV head, kVChunk-token chunk); wave w takes the batches of rows
@@ -299,13 +203,14 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     struct Shared { union { VShare<G, RB> rows; float red[G][kD]; }; };   // the sums are laid down when the last round has been read
     __shared__ std::conditional_t<SHARED, Shared, Private> lds_s;
     __shared__ float z_s[kVWaves][G];
+    __shared__ int ehat_s[kD];
     __shared__ int last_s;
 
     const int h = blockIdx.y, b = blockIdx.z, split = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane >> 3, cl = lane & 7;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all four kernels
+    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of kVChunk chosen at launch
     const int c0 = split * vchunk;
     const size_t bh = size_t(b) * Hkv + h;
@@ -317,11 +222,19 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
         return;
     }
 
-    VRule vr;
-    v_rule_setup(a.Ehat + bh * kD, a.guard_bits, a.force_level, vr);
+    if (tid < kD) {   // Rule 2 aligns to the smallest result exponent of the group
+        int e = 32767;
+#pragma unroll
+        for (int g = 0; g < G; ++g) e = min(e, a.Ehat[(size_t(b) * Hq + size_t(h) * G + g) * kD + tid]);
+        ehat_s[tid] = e;
+        if (a.dbg.Ehat && split == 0) a.dbg.Ehat[bh * kD + tid] = (int16_t)e;
+    }
     float Mg[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) Mg[g] = a.M[size_t(b) * Hq + size_t(h) * G + g];
+    __syncthreads();
+    VRule vr;
+    v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
     float acc[SHARED ? 1 : G][SHARED ? 8 : 16], z[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) z[g] = 0.0f;
@@ -420,15 +333,12 @@ int split_v_workgroups_per_cu(int G)
 template <int G>
 static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event)
 {
-    const int tile = kTB * kKWaves;   // tokens per workgroup of the K kernel: one 256-token block per wave
-    const dim3 kgrid((a.max_len + tile - 1) / tile, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
+    const dim3 kgrid((a.max_len + kKChunk - 1) / kKChunk, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
     hipLaunchKernelGGL((split_k_kernel<G>), kgrid, kblock, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;
-    hipLaunchKernelGGL((split_slice_kernel<G>), kgrid, dim3(256), 0, st, a);   // one workgroup per slice here as well
-    if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL((split_select_kernel<G>), dim3(a.s.Hkv, a.s.B), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(split_select_kernel, dim3(a.s.Hq, a.s.B), dim3(kSelThreads), 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (mid_event)
         if (hipError_t e = hipEventRecord(mid_event, st)) return e;

@@ -8,7 +8,6 @@
 namespace akv {
 
 constexpr int kMidMaxWaves = 16;
-constexpr int kMidSets = 4;   // selections that can be held at once
 
 // LDS of the mid step (declared __shared__ by the kernel that runs it)
 struct MidShared {
@@ -17,20 +16,18 @@ struct MidShared {
     int cnt[kBuckets];           // histogram of score exponents (several chunks of tokens per thread)
     int cntw[kMidMaxWaves][kBuckets + 1];   // ... per wave (one chunk: every thread owns four tokens)
     int wlt[kMidMaxWaves], weq[kMidMaxWaves];
-    int sel[kMidSets][AKV_MAX_TOPK];                  // selected tokens, ascending (several query heads at a time
-    alignas(16) float phat[kMidSets][AKV_MAX_TOPK];   // in the token-split kernel, else set 0)
-    int selj[kMidSets][AKV_MAX_TOPK];                 // their buckets
+    int sel[AKV_MAX_TOPK];                   // selected tokens of one query head, ascending
+    alignas(16) float phat[AKV_MAX_TOPK];    // their weights
     alignas(16) uint32_t v2[AKV_MAX_TOPK / 2][kD];   // fp16 bits of the selected V rows: rows 2i (low half) and 2i+1 of channel d
 };
 
 // position pos of a selected token: its index and piecewise-linear weight go to LDS
-__device__ __forceinline__ void mid_emit(MidShared& sm, int set, int pos, int t, float x, int j)
+__device__ __forceinline__ void mid_emit(MidShared& sm, int pos, int t, float x, int j)
 {
     const float fl = floorf(x);
     const float f = x - fl;
-    sm.sel[set][pos] = t;
-    sm.selj[set][pos] = j;
-    sm.phat[set][pos] = ldexpf(1.0f + f, -j);   // 2^x with a linear mantissa, the exponent floored at -64
+    sm.sel[pos] = t;
+    sm.phat[pos] = ldexpf(1.0f + f, -j);   // 2^x with a linear mantissa, the exponent floored at -64
 }
 
 // One token per lane into a histogram in LDS (buckets 0..64; a token that does not count has j > 64; called by all
@@ -76,9 +73,9 @@ __device__ __forceinline__ void mid_wave_order(const int (&j)[4], int J, int& n_
 // bucket j, 1000 for a token that does not count), called by all NT threads; sm.cntw must be zero on entry (and a
 // barrier must lie between the zeroing and this call).  Per-wave histograms (LDS atomics) give every wave the cut
 // bucket and the number of selected tokens in the waves before it with one barrier; ballots order the tokens
-// inside a wave.  The selection goes to set `set` of sm; returns the cut bucket.
+// inside a wave.
 template <int NT>
-__device__ __forceinline__ int mid_select_chunk(MidShared& sm, int set, const float (&x)[4], const int (&j)[4], int t0, int kk)
+__device__ __forceinline__ void mid_select_chunk(MidShared& sm, const float (&x)[4], const int (&j)[4], int t0, int kk)
 {
     constexpr int kWaves = NT / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -113,14 +110,13 @@ __device__ __forceinline__ int mid_select_chunk(MidShared& sm, int set, const fl
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const bool is_lt = j[i] < J, is_eq = j[i] == J;
-        if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(sm, set, n_lt + (n_eq < fromcut ? n_eq : fromcut), t0 + i, x[i], j[i]);
+        if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(sm, n_lt + (n_eq < fromcut ? n_eq : fromcut), t0 + i, x[i], j[i]);
         n_lt += is_lt;
         n_eq += is_eq;
     }
-    return J;
 }
 
-// O_est of one query head from the kk selected tokens in sm.sel[set] / sm.phat[set] (all threads of the workgroup;
+// O_est of one query head from the kk selected tokens in sm.sel / sm.phat (all threads of the workgroup;
 // contains barriers, the last one after the LDS rows have been read): the selected V rows at full 16 bits go to LDS (8 threads per row, all rows in flight together, so
 // that this costs one memory latency), then each channel runs its ordered FMA chain from operands fetched 16 rows
 // at a time.  ehat (thread d < 128: channel d) is lowered to the exponent of the result.
@@ -132,17 +128,16 @@ struct OestRows {
     uint4 hi[kPasses];
     uint2 mid[kPasses], lo[kPasses];
 };
-// issue the loads of the rows sm.sel[set][0 .. kk-1] (nothing waits for them here: a caller with several query
-// heads asks for all of them before it uses the first)
+// issue the loads of the rows sm.sel[0 .. kk-1]
 template <int NT>
-__device__ __forceinline__ void mid_oest_fetch(const DecodeArgs& a, size_t bh, int kk, const MidShared& sm, int set, OestRows<NT>& R)
+__device__ __forceinline__ void mid_oest_fetch(const DecodeArgs& a, size_t bh, int kk, const MidShared& sm, OestRows<NT>& R)
 {
     const int tid = threadIdx.x, cl = tid & 7;
 #pragma unroll
     for (int p = 0; p < OestRows<NT>::kPasses; ++p) {
         const int row = (tid >> 3) + p * (NT / 8);
         if (row < kk) {
-            const size_t vrow = bh * a.s.Ncap + sm.sel[set][row];
+            const size_t vrow = bh * a.s.Ncap + sm.sel[row];
             R.hi[p] = *reinterpret_cast<const uint4*>(a.v_hi + vrow * kD + cl * 16);
             R.mid[p] = *reinterpret_cast<const uint2*>(a.v_mid + vrow * (kD / 2) + cl * 8);
             R.lo[p] = *reinterpret_cast<const uint2*>(a.v_lo + vrow * (kD / 2) + cl * 8);
@@ -151,7 +146,7 @@ __device__ __forceinline__ void mid_oest_fetch(const DecodeArgs& a, size_t bh, i
 }
 // rows -> LDS (two rows per word), then each channel runs its ordered FMA chain; ends with a barrier
 template <int NT>
-__device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, int kk, MidShared& sm, int set, const OestRows<NT>& R,
+__device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, int kk, MidShared& sm, const OestRows<NT>& R,
                                                 int& ehat)
 {
     const int tid = threadIdx.x, cl = tid & 7;
@@ -184,7 +179,7 @@ __device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, 
             uint32_t vv[8];
 #pragma unroll
             for (int i = 0; i < 16; i += 4) {
-                const float4 p4 = *reinterpret_cast<const float4*>(&sm.phat[set][i0 + i]);
+                const float4 p4 = *reinterpret_cast<const float4*>(&sm.phat[i0 + i]);
                 pv[i] = p4.x; pv[i + 1] = p4.y; pv[i + 2] = p4.z; pv[i + 3] = p4.w;
             }
 #pragma unroll
@@ -199,15 +194,15 @@ __device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, 
         ehat = E < ehat ? E : ehat;
         if (a.dbg.oest) a.dbg.oest[hq * kD + d] = acc;
     }
-    if (a.dbg.sel && tid < a.topk) a.dbg.sel[hq * a.topk + tid] = tid < kk ? sm.sel[set][tid] : -1;
+    if (a.dbg.sel && tid < a.topk) a.dbg.sel[hq * a.topk + tid] = tid < kk ? sm.sel[tid] : -1;
     __syncthreads();
 }
 template <int NT>
-__device__ __forceinline__ void mid_oest(const DecodeArgs& a, size_t bh, size_t hq, int kk, MidShared& sm, int set, int& ehat)
+__device__ __forceinline__ void mid_oest(const DecodeArgs& a, size_t bh, size_t hq, int kk, MidShared& sm, int& ehat)
 {
     OestRows<NT> R;
-    mid_oest_fetch<NT>(a, bh, kk, sm, set, R);
-    mid_oest_finish<NT>(a, hq, kk, sm, set, R, ehat);
+    mid_oest_fetch<NT>(a, bh, kk, sm, R);
+    mid_oest_finish<NT>(a, hq, kk, sm, R, ehat);
 }
 
 // Run by one workgroup of NT threads for one (sequence b, KV head h) of len tokens, after every logit of the pair is
@@ -219,7 +214,7 @@ __device__ __forceinline__ void mid_oest(const DecodeArgs& a, size_t bh, size_t 
 // per-wave histograms give every wave the cut bucket and the number of selected tokens in the waves before it
 // without a second barrier; ballots order the tokens inside the wave.  The selected V rows are fetched by all
 // threads at once into LDS so that O_est costs one memory latency, then each channel runs its ordered FMA chain
-// from operands fetched up front.  Results: a.M, a.Ehat (global, for a later kernel) and sm.ehat (LDS).
+// from operands fetched up front.  Result: sm.ehat (LDS).
 // lds_lg / lds_stride: the logits in LDS as k_tile left them, or NULL (they are read from a.logits).
 template <int G, int NT>
 __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int len, MidShared& sm,
@@ -247,10 +242,7 @@ __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int 
             const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(rs_lg, uint32_t(t0) * 4u, 0, 0);
             return make_float4(bits_float(w.x), bits_float(w.y), bits_float(w.z), bits_float(w.w));
         };
-        if (len == 0) {
-            if (tid == 0) a.M[hq] = 0.0f;
-            continue;
-        }
+        if (len == 0) continue;
         const float M = sm.M[g];
         const int kk = a.topk < len ? a.topk : len;
         // score exponents of four tokens: x, and the bucket j = -a_t (1000 for tokens at or past len)
@@ -291,7 +283,7 @@ __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int 
                 for (int i = 0; i < 4; ++i)
                     if (j[i] <= 64) a.dbg.a[hq * Ncap + t0 + i] = (int8_t)(-j[i]);
             }
-            mid_select_chunk<NT>(sm, 0, x, j, t0, kk);
+            mid_select_chunk<NT>(sm, x, j, t0, kk);
         } else {
             // ---- histogram of score exponents over all chunks -----------------------------------------
             if (tid < kBuckets) cnt_s[tid] = 0;
@@ -343,7 +335,7 @@ __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const bool is_lt = j[i] < J, is_eq = j[i] == J;
-                    if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(sm, 0, n_lt + (n_eq < fromcut ? n_eq : fromcut), t0 + i, x[i], j[i]);
+                    if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(sm, n_lt + (n_eq < fromcut ? n_eq : fromcut), t0 + i, x[i], j[i]);
                     n_lt += is_lt;
                     n_eq += is_eq;
                 }
@@ -356,12 +348,10 @@ __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int 
         __syncthreads();
 
         // ---- O_est from the selected rows, result exponents -------------------------------------------
-        mid_oest<NT>(a, bh, hq, kk, sm, 0, ehat);
-        if (tid == 0) a.M[hq] = M;
+        mid_oest<NT>(a, bh, hq, kk, sm, ehat);
     }
     if (tid < kD) {
         sm.ehat[tid] = ehat;
-        a.Ehat[bh * kD + tid] = ehat;
         if (a.dbg.Ehat) a.dbg.Ehat[bh * kD + tid] = (int16_t)ehat;
     }
     __syncthreads();
