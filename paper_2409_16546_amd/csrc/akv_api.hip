@@ -200,20 +200,28 @@ void* static_scratch_for_current_device(hipStream_t s)
 
 // Head-per-workgroup or token-split kernels, when the caller leaves the choice to the library.  One head kernel
 // workgroup occupies a compute unit, so `pairs` (sequence, KV head) pairs run in ceil(pairs / CUs) rounds of equal
-// length: the path pays when there is one round and it is nearly full, or when the sequences are so short that the
-// single launch outweighs idle units; for single query heads also at two nearly full rounds, as long as the logits of
-// a pair fit its LDS (the token-split kernels write theirs to memory, and written bytes cost several times what read
-// bytes cost).  The thresholds are where the two paths crossed when timed over pairs = 64..1024, lengths 1024..12288
-// and group sizes 1, 2, 4 on MI355X.
+// length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
+// that the single launch outweighs idle units; for single query heads also at two nearly full rounds, as long as the logits
+// of a pair fit its LDS (the token-split kernels write theirs to memory, and written bytes cost several times what read
+// bytes cost).  The thresholds are where the two paths crossed when timed on MI355X over 8..512 pairs, 256..8192 tokens and
+// group sizes 1, 2, 4 (head / split, us): single heads 8 pairs 1024 tokens 22.0/22.5, 2048 30.7/23.5; 128 pairs 4096
+// 52.9/51.7, 160 pairs 54.1/61.6; 160 pairs 8192 102/102; 512 pairs 1024 55/52, 4096 135/145.  Groups of two: 128 pairs 2048
+// 39.6/38.6, 192 pairs 41.2/50.5, 4096 71.6/79.1, 8192 141/132.  Groups of four: 64 pairs 256 30.4/25.8, 128 pairs 30.6/32.4;
+// 192 pairs 1024 41.9/44.7, 2048 59.2/58.2; 256 pairs 4096 110/114, 6144 159/158.
 bool head_path_pays(long pairs, int G, int max_len)
 {
     const long cus = compute_units();
-    if (pairs > cus) return G == 1 && pairs <= 2 * cus && double(pairs) / double(2 * cus) >= 0.85 && max_len <= 8192;
-    if (max_len <= (G == 1 ? 2048 : 1024)) return true;
+    if (pairs > cus) return G == 1 && pairs <= 2 * cus && double(pairs) / double(2 * cus) >= 0.85 && max_len > 1536 && max_len <= 8192;
     const double fill = double(pairs) / double(cus);
-    if (G == 1) return (max_len <= 8192 && fill >= 0.72) || (max_len <= 12288 && fill >= 0.85);
-    if (G == 2) return max_len <= 8192 && fill >= 0.9;
-    return (max_len <= 2048 && fill >= 0.6) || (max_len <= 4096 && fill >= 0.85) || (max_len <= 6144 && fill >= 0.97);
+    struct Rule { int len; double fill; };   // up to len tokens from this fill on
+    static constexpr Rule g1[] = {{1024, 0.0}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}}, g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},
+                          g4[] = {{512, 0.47}, {1024, 0.65}, {2048, 0.8}, {4096, 0.95}};
+    auto pays = [&](const Rule* r, int n) {
+        for (int i = 0; i < n; ++i)
+            if (max_len <= r[i].len) return fill >= r[i].fill;
+        return false;
+    };
+    return G == 1 ? pays(g1, 4) : (G == 2 ? pays(g2, 5) : pays(g4, 4));
 }
 
 // decode attention, optionally preceded by the append of one token per sequence (k_new, v_new: [B][Hkv][D])
@@ -274,7 +282,19 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         const long per_pair = std::max(1L, long(cus) * per_cu / pairs);
         long chunk = (a.max_len + per_pair - 1) / per_pair;
         chunk = (chunk + 63) / 64 * 64;                       // whole batches of rows for every wave
-        a.vchunk = int(std::max(long(akv::kVChunk), chunk));
+        // few pairs of small capacity: chunks down to 128 tokens, at most 16 per pair (the workgroup that combines them pays
+        // for each; by the capacity, so that a bound of the lengths does not change the order of the sums): 36.2 -> 31.9 us
+        // at 2048 tokens, 8 pairs of four heads; with 32 and 64 chunks (4096, 8192 tokens) slower again
+        long shortest = akv::kVChunk;
+        if (pairs <= akv::kVFewPairs)
+            shortest = std::min(shortest, std::max(long(akv::kVMinChunk), ((a.s.Ncap / akv::kVFewChunks + 63) / 64) * 64L));
+        a.vslots = akv::v_slots(a.s);
+        a.vchunk = int(std::max(shortest, chunk));
+        // K kernel: half blocks where whole ones would leave the device short of waves (the time is then one wave's walk through
+        // its unit): below three waves per compute unit (8 pairs of four heads: 36.2 -> 32.0 us at 2048 tokens, 40.8 -> 36.0 at
+        // 8192; 32 single heads at 4096: 31.0 -> 28.4; from 8 waves per unit on whole blocks are 1-5 % faster, in between equal)
+        const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
+        a.kunit = waves < 3L * cus ? akv::kMinUnit : akv::kTB;
     }
     char* ws = static_cast<char*>(workspace);
     a.logits = reinterpret_cast<float*>(ws + w.logits);

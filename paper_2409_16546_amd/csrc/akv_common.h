@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/akv.h"
 
 namespace akv {
@@ -16,28 +18,35 @@ constexpr int kAMin = -64;         // floor of the score exponent
 constexpr int kBuckets = 65;       // exponent buckets 0..64 of the approximate top-k
 constexpr int kMaxG = 8;           // query heads per KV head supported
 
-// K pass: one wave covers one 256-token block (4 consecutive tokens per lane).
+// K pass: one wave covers one unit of tokens, a 256-token block (4 consecutive tokens per lane) or half of one.
 constexpr int kKWaves = 4;                         // waves per workgroup
-constexpr int kKChunk = kTB * kKWaves;             // tokens per workgroup of the K kernel
-// V pass: one workgroup covers kVChunk tokens; a wave reads 8 token rows per step.
+constexpr int kMinUnit = kTB / 2;                  // tokens of the smaller unit
+// V pass: one workgroup covers a chunk of tokens; a wave reads 8 token rows per step.
 constexpr int kVWaves = 4;
-constexpr int kVChunk = 512;
+constexpr int kVChunk = 512;                       // chunks are at least this long where they are many
+constexpr int kVMinChunk = 128;                    // ... and at least this long where a call has few pairs of short sequences:
+constexpr int kVFewPairs = 64, kVFewChunks = 16;   // then up to this many chunks per pair
 
 // Offsets (bytes) into the decode workspace.
 struct WsLayout {
     size_t logits;   // float [B][Hq][Ncap]
-    size_t tilemax;  // float [B][Hq][Ncap / 256]: per-wave-tile maxima of the K pass
+    size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the units of the K pass
     size_t M;        // float [B][Hq]
     size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
-    size_t partO;    // float [B][Hq][v_splits(Ncap)][D]
-    size_t partZ;    // float [B][Hq][v_splits(Ncap)]
+    size_t partO;    // float [B][Hq][v_slots][D]
+    size_t partZ;    // float [B][Hq][v_slots]
     size_t control;  // int32 [2][B][Hkv]: a spare word and the arrival counter of the V kernel per (sequence, KV head); zero between calls
     size_t control_bytes;
     size_t total;
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-inline __host__ __device__ int v_splits(int ntok) { return (ntok + kVChunk - 1) / kVChunk; }   // V-pass chunks covering ntok
+// chunks per (sequence, KV head) the workspace has room for
+inline int v_slots(const akv_shape& s)
+{
+    const int n = (s.Ncap + kVChunk - 1) / kVChunk;
+    return long(s.B) * s.Hkv <= kVFewPairs ? std::max(n, std::min(kVFewChunks, s.Ncap / kVMinChunk)) : n;
+}
 
 // control_front: the control words come first, inside a reserved block of kCtlReserve bytes whose place does not
 // depend on the shape (the layout of the library's own static scratch array, shared by calls of every shape)
@@ -48,11 +57,11 @@ inline WsLayout ws_layout(const akv_shape& s, bool control_front = false)
     size_t off = control_front ? kCtlReserve : 0;
     const size_t bhq = size_t(s.B) * s.Hq;
     w.logits = off;  off = align256(off + bhq * s.Ncap * sizeof(float));
-    w.tilemax = off; off = align256(off + bhq * (s.Ncap / kTB) * sizeof(float));
+    w.tilemax = off; off = align256(off + bhq * (s.Ncap / kMinUnit) * sizeof(float));
     w.M = off;       off = align256(off + bhq * sizeof(float));
     w.Ehat = off;    off = align256(off + bhq * kD * sizeof(int32_t));
-    w.partO = off;   off = align256(off + bhq * v_splits(s.Ncap) * kD * sizeof(float));
-    w.partZ = off;   off = align256(off + bhq * v_splits(s.Ncap) * sizeof(float));
+    w.partO = off;   off = align256(off + bhq * v_slots(s) * kD * sizeof(float));
+    w.partZ = off;   off = align256(off + bhq * v_slots(s) * sizeof(float));
     w.control_bytes = 2 * size_t(s.B) * s.Hkv * sizeof(int32_t);
     if (control_front) {
         w.control = 0;
@@ -82,7 +91,9 @@ struct DecodeArgs {
     int32_t* Ehat;
     float* partO;
     float* partZ;
-    int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave; at least kVChunk)
+    int kunit;           // tokens per wave of the K kernel of the token-split path: kTB or kMinUnit
+    int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
+    int vslots;          // chunks per (sequence, KV head) in partO and partZ
     int32_t* kcount;     // [B][Hkv] spare control words (kept zero; the selection runs in a kernel of its own)
     int32_t* vcount;
     akv_debug dbg;       // device pointers or NULL
@@ -245,6 +256,10 @@ __device__ __forceinline__ void store_agent(float* p, float v)
 __device__ __forceinline__ float load_agent(const float* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u32x4_t buf_load_b128_agent(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAuxSc1);
 }
 __device__ __forceinline__ void store_agent(int32_t* p, int32_t v)
 {

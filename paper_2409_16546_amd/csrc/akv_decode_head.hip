@@ -38,7 +38,7 @@ template <int G, int NT> constexpr int head_v_groups() { return NT <= 512 && G <
 // (16 MB of logits written during a 0.8 GB stream cost as much time as 100 MB of reads on this machine).
 extern __shared__ __align__(16) float head_lds_logits[];
 
-template <int G, int NT, bool DEBUG, bool LDSLG>
+template <int G, int NT, bool DEBUG, bool LDSLG, int TPL>
 __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
 {
     constexpr int kWaves = NT / 64;
@@ -94,7 +94,8 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     // ---- K side: levels, then the 256-token blocks of the head dealt over the waves ---------------------
     // in contiguous, balanced ranges (sizes differ by at most one block)
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int nblk = (len_k + kTB - 1) / kTB;   // the tokens already stored
+    constexpr int kUnit = 64 * TPL, kPerBlk = kTB / kUnit;
+    const int nblk = (len_k + kUnit - 1) / kUnit;   // the tokens already stored
     const int per = nblk / kWaves, extra = nblk % kWaves;
     int blk = wave_u * per + min(wave_u, extra);
     const int blk_end = blk + per + (wave_u < extra ? 1 : 0);
@@ -106,8 +107,8 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     // the block the new token goes into is read without the non-temporal hint: its lines stay in L2 for the stores
     const int keep_blk = appended ? len_old / kTB : -1;
     if (pre_any) {
-        if (blk == keep_blk) k_tile_pre<false>(a, b, h, blk, kpre);
-        else k_tile_pre<true>(a, b, h, blk, kpre);
+        if (blk / kPerBlk == keep_blk) k_tile_pre<false, TPL>(a, b, h, blk, kpre);
+        else k_tile_pre<true, TPL>(a, b, h, blk, kpre);
     }
     const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, true, k_new_bits, lin, len);
     float wm[G];
@@ -119,23 +120,23 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     };
     // own[g][i]: logit of token 4*tid + i if the wave's only block was block `wave` (at most kWaves blocks: the
     // mid step then takes its logits from these registers instead of reading them back)
-    float own[G][4];
+    float own[G][TPL];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) own[g][i] = 0.0f;
+        for (int i = 0; i < TPL; ++i) own[g][i] = 0.0f;
     uint8_t* stage = &kstage[wave_u][0];
     if (pre_any) {   // the block whose first HI bytes are already in flight
         float tm[G];
-        if (blk == keep_blk) k_tile<G, false>(a, b, h, blk, len_k, ks, 0, tm, kpre, true, own, stage, lds_lg, lds_tokens);
-        else k_tile<G, true>(a, b, h, blk, len_k, ks, 0, tm, kpre, true, own, stage, lds_lg, lds_tokens);
+        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
+        else k_tile<G, true, TPL>(a, b, h, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
         blk += 1;
         fold(tm);
     }
     while (blk < blk_end) {
-        float tm[G], later[G][4];
-        if (blk == keep_blk) k_tile<G, false>(a, b, h, blk, len_k, ks, 0, tm, kpre, false, later, stage, lds_lg, lds_tokens);
-        else k_tile<G, true>(a, b, h, blk, len_k, ks, 0, tm, kpre, false, later, stage, lds_lg, lds_tokens);
+        float tm[G], later[G][TPL];
+        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
+        else k_tile<G, true, TPL>(a, b, h, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
         blk += 1;
         fold(tm);
     }
@@ -179,15 +180,20 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     __syncthreads();
 
     // ---- mid step -----------------------------------------------------------------------------------
-    const bool own_ok = nblk <= kWaves;   // then wave w < nblk has walked exactly block w, four tokens per lane
-    if (own_ok && attend_new && (len_old >> 2) == tid) {   // the new token's logit did not come from a tile
+    if constexpr (TPL == 4) {
+        const bool own_ok = nblk <= kWaves;   // then wave w < nblk has walked exactly block w, four tokens per lane
+        if (own_ok && attend_new && (len_old >> 2) == tid) {   // the new token's logit did not come from a tile
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+            for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((len_old & 3) == i) own[g][i] = ks.new_logit[g];
+                for (int i = 0; i < 4; ++i)
+                    if ((len_old & 3) == i) own[g][i] = ks.new_logit[g];
+        }
+        mid_step<G, NT>(a, b, h, len, ms, own, own_ok, lds_lg, lds_tokens);
+    } else {
+        const float none[G][4] = {};
+        mid_step<G, NT>(a, b, h, len, ms, none, false, lds_lg, lds_tokens);   // the logits are in LDS
     }
-    mid_step<G, NT>(a, b, h, len, ms, own, own_ok, lds_lg, lds_tokens);
 
     // ---- V side: each wave walks its range of batches of 8*KG rows -------------------------------------
     VRule vr;
@@ -239,8 +245,8 @@ bool head_logits_in_lds(const akv_shape& s, int max_len)
     return bytes <= (G == 1 ? head_lds_logit_budget<1024>() : head_lds_logit_budget<512>());
 }
 
-template <int G, int NT>
-static hipError_t launch_head_g(const DecodeArgs& a, hipStream_t st)
+template <int G, int NT, int TPL>
+static hipError_t launch_head_t(const DecodeArgs& a, hipStream_t st)
 {
     const dim3 grid(xcd_grid(size_t(a.s.B) * a.s.Hkv)), block(NT);
     const bool debug = a.dbg.needV || a.dbg.appliedV || a.stats;
@@ -248,8 +254,8 @@ static hipError_t launch_head_g(const DecodeArgs& a, hipStream_t st)
     const size_t lds_bytes = size_t(G) * lds_tokens * sizeof(float);
     if (head_logits_in_lds(a.s, a.max_len)) {
         static bool raised[64] = {};   // per instantiation and device: allow the dynamic part beside the static arrays
-        auto kd = head_kernel<G, NT, true, true>;
-        auto kp = head_kernel<G, NT, false, true>;
+        auto kd = head_kernel<G, NT, true, true, TPL>;
+        auto kp = head_kernel<G, NT, false, true, TPL>;
         int dev = 0;
         if (hipError_t e = hipGetDevice(&dev)) return e;
         if (dev < 0 || dev >= 64 || !raised[dev]) {
@@ -260,10 +266,17 @@ static hipError_t launch_head_g(const DecodeArgs& a, hipStream_t st)
         if (debug) hipLaunchKernelGGL(kd, grid, block, lds_bytes, st, a, lds_tokens);
         else hipLaunchKernelGGL(kp, grid, block, lds_bytes, st, a, lds_tokens);
     } else {
-        if (debug) hipLaunchKernelGGL((head_kernel<G, NT, true, false>), grid, block, 0, st, a, 0);
-        else hipLaunchKernelGGL((head_kernel<G, NT, false, false>), grid, block, 0, st, a, 0);
+        if (debug) hipLaunchKernelGGL((head_kernel<G, NT, true, false, 4>), grid, block, 0, st, a, 0);
+        else hipLaunchKernelGGL((head_kernel<G, NT, false, false, 4>), grid, block, 0, st, a, 0);
     }
     return hipGetLastError();
+}
+
+// half blocks per wave where whole ones would leave half of the waves without one
+template <int G, int NT>
+static hipError_t launch_head_g(const DecodeArgs& a, hipStream_t st)
+{
+    return a.max_len <= 2 * NT ? launch_head_t<G, NT, 2>(a, st) : launch_head_t<G, NT, 4>(a, st);
 }
 
 bool head_path_supported(const akv_shape& s) { return s.Hq / s.Hkv <= 4; }

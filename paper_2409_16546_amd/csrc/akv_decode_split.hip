@@ -12,33 +12,34 @@
 
 namespace akv {
 
-// K kernel: workgroup = kKWaves waves = kKChunk tokens of one (sequence, KV head); a wave walks one
-// 256-token block and leaves its logits and its block maximum in the workspace.
-template <int G>
+// K kernel: workgroup = kKWaves waves = kKWaves units of 64*TPL tokens (k_tile) of one (sequence, KV head); a wave walks one
+// unit and leaves its logits and the unit's maximum in the workspace.
+template <int G, int TPL>
 __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 {
     __shared__ __align__(16) uint8_t kstage[kKWaves][kKStage];
     __shared__ KShared<G> ks;
+    constexpr int kUnit = 64 * TPL;
 
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63;
-    const int Hq = a.s.Hq, Ncap = a.s.Ncap, NB = Ncap / kTB;
+    const int Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int blk = blockIdx.x * kKWaves + wave_u;
-    if (blockIdx.x * kKChunk >= len) return;   // whole workgroup beyond the sequence (uniform)
+    const int unit = blockIdx.x * kKWaves + wave_u;
+    if (blockIdx.x * kKWaves * kUnit >= len) return;   // whole workgroup beyond the sequence (uniform)
 
     if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
     k_levels<G>(a, b, h, ks, blockIdx.x == 0, len);
-    if (blk * kTB < len) {                       // else this wave's block is beyond the sequence
+    if (unit * kUnit < len) {                    // else this wave's unit is beyond the sequence
         float tm[G];
         const u32x4_t zero4 = {0u, 0u, 0u, 0u};
         const u32x4_t none[6] = {zero4, zero4, zero4, zero4, zero4, zero4};
-        float lg[G][4];
-        k_tile<G>(a, b, h, blk, len, ks, 0, tm, none, false, lg, &kstage[wave_u][0]);
+        float lg[G][TPL];
+        k_tile<G, true, TPL>(a, b, h, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
         if (lane == 0)
 #pragma unroll
-            for (int g = 0; g < G; ++g) a.tilemax[(size_t(b) * Hq + size_t(h) * G + g) * NB + blk] = tm[g];
+            for (int g = 0; g < G; ++g) a.tilemax[(size_t(b) * Hq + size_t(h) * G + g) * (Ncap / kMinUnit) + unit] = tm[g];
     }
 }
 
@@ -65,17 +66,23 @@ __global__ __launch_bounds__(kSelThreads) void split_select_kernel(DecodeArgs a)
 
     const int hq_i = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap, NB = Ncap / kTB;
+    const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     if (len <= 0) return;   // uniform: an empty sequence has no selection (the V kernel writes its zeros)
     const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / (Hq / Hkv);
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
-    const float* tm = a.tilemax + hq * NB;
+    const float* tm = a.tilemax + hq * (Ncap / kMinUnit);
+    const int upb = kTB / a.kunit;   // units of the K kernel per block: 1 or 2
+    auto block_max = [&](int i) {
+        float m = tm[i * upb];
+        if (upb == 2 && (2 * i + 1) * kMinUnit < len) m = fmaxf(m, tm[2 * i + 1]);
+        return m;
+    };
 
     // ---- the global max logit (exact, order-free) and the bound of the cut
     float m = -INFINITY;
-    for (int i = tid; i < nblk; i += NT) m = fmaxf(m, tm[i]);
+    for (int i = tid; i < nblk; i += NT) m = fmaxf(m, block_max(i));
     m = wave_max(m);
     if (lane == 0) red_s[wave] = m;
     if (tid < kBuckets) ms.cnt[tid] = 0;
@@ -87,7 +94,7 @@ __global__ __launch_bounds__(kSelThreads) void split_select_kernel(DecodeArgs a)
     int Jb = 64;
     if (nblk >= kk) {   // uniform
         int n64 = 0;
-        for (int i0 = 0; i0 < nblk; i0 += NT) mid_hist_add(ms.cnt, i0 + tid < nblk ? -score_a(score_x(tm[i0 + tid], M, a.c)) : 1000, n64);
+        for (int i0 = 0; i0 < nblk; i0 += NT) mid_hist_add(ms.cnt, i0 + tid < nblk ? -score_a(score_x(block_max(i0 + tid), M, a.c)) : 1000, n64);
         __syncthreads();
         int below;
         mid_find_cut(ms.cnt[lane], kk, Jb, below);   // the floor bucket is not counted: 64 if none before it is
@@ -96,7 +103,7 @@ __global__ __launch_bounds__(kSelThreads) void split_select_kernel(DecodeArgs a)
     const int b0 = int((long long)nblk * wave / kWaves), b1 = int((long long)nblk * (wave + 1) / kWaves);   // the wave's blocks
     const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
     // bucket of the best token of block c0 + lane (1000 past the range)
-    auto best_of = [&](int c0) { return c0 + lane < b1 ? -score_a(score_x(tm[c0 + lane], M, a.c)) : 1000; };
+    auto best_of = [&](int c0) { return c0 + lane < b1 ? -score_a(score_x(block_max(c0 + lane), M, a.c)) : 1000; };
     // takes up to kAhead blocks off the mask and asks for their logits (lane -> four consecutive tokens)
     auto fetch = [&](int c0, uint64_t& mask, int (&blk)[kAhead], u32x4_t (&w)[kAhead]) {
 #pragma unroll
@@ -199,9 +206,11 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 {
     constexpr bool SHARED = v_shared<G>();
     constexpr int KG = G >= 8 ? 1 : 2, RB = 8 * KG;         // one lane per (row of the batch, query head): at most 64 / G rows
-    struct Private { float red[kVWaves][G][kD]; };
-    struct Shared { union { VShare<G, RB> rows; float red[G][kD]; }; };   // the sums are laid down when the last round has been read
-    __shared__ std::conditional_t<SHARED, Shared, Private> lds_s;
+    // the combining workgroup: a thread sums four neighbouring outputs over every kSub-th chunk
+    constexpr int kCols = G * kD / 4, kSub = 64 * kVWaves / kCols;
+    struct Private { union { float red[kVWaves][G][kD]; f32x4_t comb[kSub][kCols]; }; };
+    struct Shared { union { VShare<G, RB> rows; float red[G][kD]; f32x4_t comb[kSub][kCols]; }; };   // the sums are laid down when the last round has been read
+    __shared__ __align__(16) std::conditional_t<SHARED, Shared, Private> lds_s;
     __shared__ float z_s[kVWaves][G];
     __shared__ int ehat_s[kD];
     __shared__ int last_s;
@@ -214,7 +223,7 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of kVChunk chosen at launch
     const int c0 = split * vchunk;
     const size_t bh = size_t(b) * Hkv + h;
-    const int nsplit = v_splits(Ncap);
+    const int nsplit = a.vslots;
     if (c0 >= len) {                                    // uniform: chunk beyond the sequence
         if (len == 0 && split == 0)                     // an empty sequence attends to nothing: zeros
             for (int idx = tid; idx < G * kD; idx += 64 * kVWaves)
@@ -293,32 +302,44 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     }
 
     // ---- the workgroup that finishes last for this (sequence, KV head) combines the chunks -------------
-    // out = sum_chunks O / sum_chunks Z: every chunk used the same global max, so nothing is rescaled.
+    // out = sum_chunks O / sum_chunks Z: every chunk used the same global max, so nothing is rescaled.  All threads take part
+    // with 16-byte loads, eight chunks each in flight (one word per thread and output before: 5-7 us at the end of a call of
+    // eight heads per group, now 4; the round trips of stores, ticket and loads are what is left).
     const int used = (len + vchunk - 1) / vchunk;
     stores_done();
     __syncthreads();
     if (tid == 0) last_s = take_ticket(&a.vcount[bh]) == used - 1;
     __syncthreads();
     if (!last_s) return;
-    for (int idx = tid; idx < G * kD; idx += 64 * kVWaves) {
-        const int g = idx / kD, d = idx % kD;
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-        float o = 0.0f, zsum = 0.0f;
-        for (int sp0 = 0; sp0 < used; sp0 += 8) {   // eight chunks' words in flight; the additions stay in chunk order
-            float po[8], pz[8];
+    const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
+    const int c = tid % kCols, sub = tid / kCols, g_out = c / (kD / 4);
+    const __amdgpu_buffer_rsrc_t rs_o = make_rsrc(a.partO + hq0 * nsplit * kD, uint32_t(G) * uint32_t(nsplit) * kD * 4u);
+    f32x4_t o = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int sp0 = sub; sp0 < used; sp0 += 8 * kSub) {   // eight chunks' words in flight; the additions stay in chunk order
+        u32x4_t po[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bool on = sp0 + i < used;
-                po[i] = on ? load_agent(&a.partO[(hq * nsplit + sp0 + i) * kD + d]) : 0.0f;
-                pz[i] = on ? load_agent(&a.partZ[hq * nsplit + sp0 + i]) : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                o += po[i];
-                zsum += pz[i];
-            }
+        for (int i = 0; i < 8; ++i) {
+            const int sp = sp0 + i * kSub;
+            po[i] = buf_load_b128_agent(rs_o, sp < used ? (uint32_t(g_out) * uint32_t(nsplit) + uint32_t(sp)) * (kD * 4u) + uint32_t(c % (kD / 4)) * 16u : kSkip);
         }
-        store_out(a, hq, d, o / zsum);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] += bits_float(po[i][k]);
+    }
+    for (int g = wave; g < G; g += kVWaves) {   // the weights' sums: a wave per query head, lane -> chunks
+        float zs = 0.0f;
+        for (int sp = lane; sp < used; sp += 64) zs += load_agent(&a.partZ[(hq0 + g) * nsplit + sp]);
+        for (int k = 1; k < 64; k <<= 1) zs += __shfl_xor(zs, k);
+        if (lane == 0) z_s[0][g] = zs;
+    }
+    if (kSub > 1) lds_s.comb[sub][c] = o;
+    __syncthreads();
+    if (sub == 0) {
+#pragma unroll
+        for (int u = 1; u < kSub; ++u) o += lds_s.comb[u][c];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) store_out(a, hq0 + g_out, (c % (kD / 4)) * 4 + k, o[k] / z_s[0][g_out]);
     }
     if (tid == 0) store_agent(&a.vcount[bh], 0);   // ready for the next call
 }
@@ -333,8 +354,10 @@ int split_v_workgroups_per_cu(int G)
 template <int G>
 static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event)
 {
-    const dim3 kgrid((a.max_len + kKChunk - 1) / kKChunk, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
-    hipLaunchKernelGGL((split_k_kernel<G>), kgrid, kblock, 0, st, a);
+    const int tile = a.kunit * kKWaves;   // tokens per workgroup of the K kernel
+    const dim3 kgrid((a.max_len + tile - 1) / tile, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
+    if (a.kunit == kMinUnit) hipLaunchKernelGGL((split_k_kernel<G, 2>), kgrid, kblock, 0, st, a);
+    else hipLaunchKernelGGL((split_k_kernel<G, 4>), kgrid, kblock, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;

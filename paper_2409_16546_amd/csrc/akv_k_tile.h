@@ -3,6 +3,8 @@
 // "Quantization of K-Cache": from q and K_colmax estimate the magnitude of the 128 addends of one logit,
 // align them to the coarsest one (Rule 1), read each column of K at the bit width its addend needs.
 #pragma once
+#include <type_traits>
+
 #include "akv_common.h"
 
 namespace akv {
@@ -139,9 +141,11 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     return (uint64_t(hi32) << 32) | uint64_t(lo32);
 }
 
-// One wave, one 256-token block blk of (b, h): lane -> tokens 4*lane .. 4*lane+3 of the block; the logit of a token
-// is accumulated in fp32 over channels in ascending order inside its lane (no reduction).
-// Channels are processed 8 at a time.  Per group the wave fetches the 2-KB run of K_hi (8 columns x 256 B,
+// One wave, one unit of 64*TPL tokens of (b, h): lane -> tokens TPL*lane .. TPL*lane+TPL-1 of the unit; the logit of a
+// token is accumulated in fp32 over channels in ascending order inside its lane (no reduction).  TPL = 4: a unit is a
+// 256-token block, the form that streams best (2-KB and 1-KB runs).  TPL = 2: half a block, for calls with so few blocks
+// that the time is one wave's walk through its unit: twice the waves, half as many dependent groups each (the call above: 24.8 -> 22.3 us).
+// Channels are processed U = 32 / TPL at a time, 4 KB per group in either form.  For TPL = 4 the wave fetches per group the 2-KB run of K_hi (8 columns x 256 B,
 // contiguous in the channel-major block) with two 16-B loads per lane, and the 1-KB runs of K_mid / K_lo with one
 // 16-B load per lane each, lane -> (column lane/8, 16 bytes): a column whose level does not ask for a plane is
 // left out by sending its 8 lanes out of range (nothing is fetched, zeros come back).  Four vector-memory
@@ -152,24 +156,35 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 // wave-private LDS area and read back in "token order" (lane -> its 4 tokens of every column: two words per column, the
 // reads of the whole group issued before the first is used).  q comes through scalar loads as fp16 pairs and goes into the
 // multiply-adds as it is.  No branch in a group: a branch per column on its level had made every LDS read wait for the one
-// before.  Measured against that form: one wave's block 13.9 -> 9 us (B 1, 32 heads, 1024 tokens: 29.1 -> 24.8 us a call),
+// before (13.9 us for one wave's block).  Measured against that form: B 1, 32 heads, 1024 tokens 29.1 -> 24.8 us a call;
 // groups of eight heads 172 -> 106 registers; calls bound by memory 1-2 % faster.
-// Logits go to a.logits with cache policy `aux` (kAuxSc1 when another workgroup of the same kernel will read
-// them) and are left in acc; the maximum over the tile's valid tokens is returned for every query head of the
+// Logits go to a.logits and are left in acc; the maximum over the unit's valid tokens is returned for every query head of the
 // group (same value in all lanes).
-constexpr int kKU = 8;            // columns per group
 constexpr int kKStage = 4096;     // bytes of LDS staging per wave
 
-// HI bytes of the first three groups of a tile, issued before the levels are known (they are always read):
-// pre[] is handed to k_tile (use_pre = true) for the same block.
-template <bool NT = true>
-__device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, int blk, u32x4_t (&pre)[6])
+// Byte offset (inside a block's HI plane) of the 16-byte piece this lane fetches of the first half of a group that starts at
+// column 0; the second half lies kHiHalf<TPL> further, column d0 starts at d0 * 256.
+template <int TPL>
+__device__ __forceinline__ uint32_t k_hi_lane_offset(int unit)
 {
-    const int lane = threadIdx.x & 63;
+    const uint32_t lane = threadIdx.x & 63, sub = uint32_t(unit) % (4 / TPL);
+    return (lane / (4 * TPL)) * kTB + sub * (64 * TPL) + (lane % (4 * TPL)) * 16;
+}
+template <int TPL> constexpr uint32_t kHiHalf = (16 / TPL) * kTB;
+
+// HI bytes of the first three groups of a unit, issued before the levels are known (they are always read):
+// pre[] is handed to k_tile (use_pre = true) for the same unit.
+template <bool NT = true, int TPL = 4>
+__device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, int unit, u32x4_t (&pre)[6])
+{
     const size_t bh = size_t(b) * a.s.Hkv + h;
-    const __amdgpu_buffer_rsrc_t rh = make_rsrc(a.k_hi + (bh * a.s.Ncap + size_t(blk) * kTB) * kD, uint32_t(kTB) * kD);
+    const __amdgpu_buffer_rsrc_t rh = make_rsrc(a.k_hi + (bh * a.s.Ncap + size_t(unit / (4 / TPL)) * kTB) * kD, uint32_t(kTB) * kD);
+    const uint32_t off = k_hi_lane_offset<TPL>(unit);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) pre[i] = NT ? buf_load_b128_nt(rh, uint32_t(lane) * 16 + i * 1024) : buf_load_b128(rh, uint32_t(lane) * 16 + i * 1024);
+    for (int i = 0; i < 6; ++i) {
+        const uint32_t at = off + i * kHiHalf<TPL>;
+        pre[i] = NT ? buf_load_b128_nt(rh, at) : buf_load_b128(rh, at);
+    }
 }
 
 // NT: the block's bytes are read with the non-temporal hint (they are read once per step); a caller that is about to
@@ -177,29 +192,32 @@ __device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, in
 // lds_lg: where a kernel keeps the logits of its (sequence, KV head) in LDS (query head g at lds_lg + g * lds_stride
 // floats, token t at index t), or NULL: they go to a.logits.  With LDS logits a.logits is written as well only if it
 // is the caller's export buffer (a.dbg.logits).
-template <int G, bool NT = true>
-__device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int blk, int len, const KShared<G>& ks,
-                                       int aux, float (&tile_max)[G], const u32x4_t (&pre)[6], bool use_pre,
-                                       float (&acc)[G][4], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0)
+template <int G, bool NT = true, int TPL = 4>
+__device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int unit, int len, const KShared<G>& ks,
+                                       float (&tile_max)[G], const u32x4_t (&pre)[6], bool use_pre,
+                                       float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0)
 {
-    constexpr int U = kKU;
+    static_assert(TPL == 4 || TPL == 2, "");
+    constexpr int U = 32 / TPL;       // columns per group
+    constexpr int kUnit = 64 * TPL;   // tokens of the unit
     constexpr int kAux = NT ? kAuxNt : 0;
     const int lane = threadIdx.x & 63;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
     const size_t bh = size_t(b) * Hkv + h;
-    blk = __builtin_amdgcn_readfirstlane(blk);   // wave-uniform by contract: scalar addressing
+    unit = __builtin_amdgcn_readfirstlane(unit);   // wave-uniform by contract: scalar addressing
+    const int blk = unit / (4 / TPL), sub = unit % (4 / TPL);
 
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[g][i] = 0.0f;
+        for (int i = 0; i < TPL; ++i) acc[g][i] = 0.0f;
 
     // the level masks live in scalar registers for the whole loop
     const uint64_t nm0 = uniform64(ks.need_mid[0]), nm1 = uniform64(ks.need_mid[1]);
     const uint64_t nl0 = uniform64(ks.need_lo[0]), nl1 = uniform64(ks.need_lo[1]);
     // bits of the U columns starting at d0 (d0 % U == 0, so a group never straddles the two words)
     auto bits_at = [&](uint64_t w0, uint64_t w1, int d0) -> uint32_t {
-        return d0 < kD ? (uint32_t)((d0 < 64 ? w0 : w1) >> (d0 & 63)) & ((1u << U) - 1) : 0u;
+        return d0 < kD ? (uint32_t)((d0 < 64 ? w0 : w1) >> (d0 & 63)) & (uint32_t)((1ull << U) - 1) : 0u;
     };
     const uint8_t* hi_blk = a.k_hi + (bh * Ncap + size_t(blk) * kTB) * kD;
     const uint8_t* mid_blk = a.k_mid + (bh * Ncap + size_t(blk) * kTB) * (kD / 2);
@@ -209,23 +227,25 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int bl
 #pragma unroll
     for (int g = 0; g < G; ++g) qw[g] = (const uint32_t __attribute__((address_space(4)))*)(uintptr_t)(a.q + (size_t(b) * Hq + size_t(h) * G + g) * kD);
     const uint32_t voff = uint32_t(lane) * 16;
-    const uint32_t col = uint32_t(lane) >> 3;   // the column of the group this lane fetches nibbles of
+    const uint32_t hoff = k_hi_lane_offset<TPL>(unit);
+    const uint32_t col = uint32_t(lane) / (2 * TPL);   // the column of the group this lane fetches nibbles of (32 tokens of it)
+    const uint32_t noff = col * (kTB / 2) + uint32_t(sub) * (kUnit / 2) + (uint32_t(lane) % (2 * TPL)) * 16;
 
     struct Group {
-        u32x4_t h0, h1;   // bytes 16*lane .. +15 of the first / second KB of the HI run (columns 0..3 / 4..7)
-        u32x4_t m, l;     // bytes 16*lane .. +15 of the MID / LO run (column lane/8)
+        u32x4_t h0, h1;   // 16 HI bytes of a column of the first / second half of the group
+        u32x4_t m, l;     // 16 MID / LO bytes of column col
     };
     // groups past the last column are issued through descriptors of size zero: nothing is fetched
     auto issue_hi = [&](Group& gr, int d0) {
         const __amdgpu_buffer_rsrc_t rh = make_rsrc(hi_blk, d0 < kD ? uint32_t(kTB) * kD : 0u);
-        gr.h0 = __builtin_amdgcn_raw_buffer_load_b128(rh, voff, d0 * kTB, kAux);
-        gr.h1 = __builtin_amdgcn_raw_buffer_load_b128(rh, voff + 1024, d0 * kTB, kAux);
+        gr.h0 = __builtin_amdgcn_raw_buffer_load_b128(rh, hoff, d0 * kTB, kAux);
+        gr.h1 = __builtin_amdgcn_raw_buffer_load_b128(rh, hoff + kHiHalf<TPL>, d0 * kTB, kAux);
     };
     auto issue_nib = [&](Group& gr, int d0) {
         const uint32_t bm = bits_at(nm0, nm1, d0), bl = bits_at(nl0, nl1, d0);
         const uint32_t size = d0 < kD ? uint32_t(kTB) * (kD / 2) : 0u;
         const __amdgpu_buffer_rsrc_t rm = make_rsrc(mid_blk, size), rl = make_rsrc(lo_blk, size);
-        const uint32_t base = voff + uint32_t(d0 < kD ? d0 : 0) * (kTB / 2);
+        const uint32_t base = noff + uint32_t(d0 < kD ? d0 : 0) * (kTB / 2);
         gr.m = __builtin_amdgcn_raw_buffer_load_b128(rm, ((bm >> col) & 1u) ? base : kSkip, 0, kAux);
         gr.l = __builtin_amdgcn_raw_buffer_load_b128(rl, ((bl >> col) & 1u) ? base : kSkip, 0, kAux);
     };
@@ -234,7 +254,7 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int bl
         issue_nib(gr, d0);
     };
     auto compute = [&](const Group& gr, int d0) {
-        // the low bytes of the lane's 32 tokens of column lane/8, from their nibbles (planes that were not read came back
+        // the low bytes of the lane's 32 tokens of column col, from their nibbles (planes that were not read came back
         // as zeros) and the column's fill, in token order
         const uint32_t bm = bits_at(nm0, nm1, d0) >> col, bl = bits_at(nl0, nl1, d0) >> col;
         const uint32_t fill = (bl & 1u) ? 0u : ((bm & 1u) ? 0x08080808u : 0x80808080u);
@@ -254,24 +274,31 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int bl
         *reinterpret_cast<u32x4_t*>(stage + 2048 + 2 * voff) = u32x4_t{low[0], low[1], low[2], low[3]};
         *reinterpret_cast<u32x4_t*>(stage + 2048 + 2 * voff + 16) = u32x4_t{low[4], low[5], low[6], low[7]};
         __builtin_amdgcn_wave_barrier();
+        typedef std::conditional_t<TPL == 4, uint32_t, uint16_t> word_t;   // TPL bytes
         uint32_t hh[U], ll[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            hh[u] = *reinterpret_cast<const uint32_t*>(stage + u * kTB + lane * 4);
-            ll[u] = *reinterpret_cast<const uint32_t*>(stage + 2048 + u * kTB + lane * 4);
+            hh[u] = *reinterpret_cast<const word_t*>(stage + u * kUnit + lane * TPL);
+            ll[u] = *reinterpret_cast<const word_t*>(stage + 2048 + u * kUnit + lane * TPL);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            float k[TPL];
             const uint32_t p0 = __builtin_amdgcn_perm(hh[u], ll[u], 0x05010400u);   // tokens (0,1)
-            const uint32_t p1 = __builtin_amdgcn_perm(hh[u], ll[u], 0x07030602u);   // tokens (2,3)
-            const float k[4] = {lo_half(p0), hi_half(p0), lo_half(p1), hi_half(p1)};
+            k[0] = lo_half(p0);
+            k[1] = hi_half(p0);
+            if constexpr (TPL == 4) {
+                const uint32_t p1 = __builtin_amdgcn_perm(hh[u], ll[u], 0x07030602u);   // tokens (2,3)
+                k[2] = lo_half(p1);
+                k[3] = hi_half(p1);
+            }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const uint32_t qp = qw[g][(d0 + u) >> 1];
                 const float qd = (u & 1) ? hi_half(qp) : lo_half(qp);
                 // q*k is exact in fp32, so the fused form rounds exactly like multiply-then-add
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[g][i] = fmaf(qd, k[i], acc[g][i]);
+                for (int i = 0; i < TPL; ++i) acc[g][i] = fmaf(qd, k[i], acc[g][i]);
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -305,22 +332,23 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int bl
     }
 
     // ---- logits out, tile maxima -----------------------------------------------------------------
-    const int t0 = blk * kTB + lane * 4;
+    const int t0 = unit * kUnit + lane * TPL;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
         const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
-        u32x4_t w;
-        w.x = float_bits(acc[g][0]); w.y = float_bits(acc[g][1]);
-        w.z = float_bits(acc[g][2]); w.w = float_bits(acc[g][3]);
-        if (lds_lg) *reinterpret_cast<u32x4_t*>(lds_lg + g * lds_stride + t0) = w;
+        typedef std::conditional_t<TPL == 4, u32x4_t, u32x2_t> vec_t;
+        vec_t w;
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) w[i] = float_bits(acc[g][i]);
+        if (lds_lg) *reinterpret_cast<vec_t*>(lds_lg + g * lds_stride + t0) = w;
         if (!lds_lg || a.dbg.logits) {
-            if (aux) __builtin_amdgcn_raw_buffer_store_b128(w, rs_lg, uint32_t(t0) * 4u, 0, kAuxSc1);
-            else __builtin_amdgcn_raw_buffer_store_b128(w, rs_lg, uint32_t(t0) * 4u, 0, 0);
+            if constexpr (TPL == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs_lg, uint32_t(t0) * 4u, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b64(w, rs_lg, uint32_t(t0) * 4u, 0, 0);
         }
         float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TPL; ++i)
             if (t0 + i < len) m = fmaxf(m, acc[g][i]);
         tile_max[g] = wave_max(m);
     }

@@ -46,3 +46,26 @@ def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     assert np.array_equal(dbg.Ehat.cpu().numpy(), r.Ehat)
     bound = T.out_tolerance(r, lens, scale)
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= bound)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_token_split_with_whole_blocks_per_wave(T, G):
+    """Enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks), and more pairs than
+    those the V kernel cuts into short chunks; ragged lengths down to one token."""
+    from paper_2409_16546_amd import workloads
+    lens = [2048, 1, 1027, 300]
+    print(f"token-split path, whole blocks: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=2048, seed=500 + G)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
+    T.assert_decode_equal(out, dbg, r, lens, G, f"whole blocks G{G}")
+
+
+@pytest.mark.parametrize("G,lens", [(1, [1024, 129]), (2, [2048, 127]), (4, [4100, 128]), (8, [700, 385])])
+def test_token_split_with_half_blocks_and_short_chunks(T, G, lens):
+    """Few pairs of short sequences: half a block per wave of the K kernel (lengths around 128), chunks of the V kernel below
+    512 tokens (128, 128, 320 and 128 of them)."""
+    from paper_2409_16546_amd import workloads
+    print(f"token-split path, half blocks: G{G} lens {lens}", flush=True)
+    w = workloads.make(4, B=2, Hq=2 * G, Hkv=2, N=max(lens), seed=600 + G)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
+    T.assert_decode_equal(out, dbg, r, lens, G, f"half blocks G{G}")
