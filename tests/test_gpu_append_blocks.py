@@ -1,0 +1,82 @@
+"""GPU parity of the block-wise append and of unpack at the edges of their tiles: ranges that begin and end inside a nibble byte,
+a 16-byte piece, a 64-token wave or a block, onto planes that hold older tokens behind the length (they stay), ragged counts
+with none and with a refusal; each output of unpack alone."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def T():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import akv_oracle
+    akv_oracle.build()
+    import akv_testlib
+    return akv_testlib
+
+
+@pytest.mark.parametrize("n,lens,counts", [
+    (16, [0, 1, 255, 241], None),                    # inside one block, into the next, up to its end
+    (33, [15, 16, 17, 480], [33, 0, 32, 33]),        # pieces of 16 and 32 tokens; the last one fits exactly no more (refused at 512)
+    (256, [0, 256, 1, 255], None),                   # whole blocks and every split of one
+    (257, [0, 255, 254, 63], [257, 257, 1, 200]),
+    (300, [100, 212, 213, 31], None),                # 212 + 300 fills the capacity, 213 + 300 is refused
+])
+def test_append_blocks_match_oracle_and_leave_the_rest(T, n, lens, counts):
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A, workloads
+    print(f"append blocks: n {n} lens {lens} counts {counts}", flush=True)
+    B, Hkv, Ncap = len(lens), 3, 512
+    k, v = workloads.edge_patterns(B, Hkv, Ncap + n, seed=n)
+    full = [Ncap] * B
+    oc = T.oracle_cache(k[:, :, :Ncap], v[:, :, :Ncap], full, Ncap)
+    gc = T.gpu_cache(k[:, :, :Ncap], v[:, :, :Ncap], full, Hkv, Ncap)
+    T.assert_cache_equal(gc, oc)
+    oc.lens[:] = lens
+    gc.lens.copy_(torch.tensor(lens, dtype=torch.int32))
+    kn, vn = k[:, :, Ncap:].contiguous(), v[:, :, Ncap:].contiguous()
+    n_new = np.array([n] * B if counts is None else counts, np.int32)
+    refused = O.append(oc, T.bits(kn), T.bits(vn), n_new)
+    A.akv_append(gc, kn.to(DEV), vn.to(DEV), torch.from_numpy(n_new).to(DEV) if counts is not None else None)
+    torch.cuda.synchronize()
+    T.assert_cache_equal(gc, oc)
+    assert int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == refused and not gc.flags.cpu()[A.AKV_NFLAGS:].any()
+    # unpack: both outputs, and each alone
+    ku, vu = A.akv_unpack(gc)
+    k1, v1 = torch.zeros_like(ku), torch.zeros_like(vu)
+    s, st = gc.struct(), torch.cuda.current_stream().cuda_stream
+    assert A.lib().akv_unpack(C.byref(s), k1.data_ptr(), None, st) == A.AKV_OK
+    assert A.lib().akv_unpack(C.byref(s), None, v1.data_ptr(), st) == A.AKV_OK
+    torch.cuda.synchronize()
+    full16 = lambda hi, mid, lo: (hi.astype(np.uint16) << 8) | (mid << 4) | lo
+    vm, vl = (x.reshape(B, Hkv, Ncap, 64) for x in (oc.v_mid, oc.v_lo))
+    nib = lambda x: np.stack([x & 15, x >> 4], axis=-1).reshape(*x.shape[:-1], -1).astype(np.uint16)
+    assert np.array_equal(T.bits(vu), full16(oc.v_hi.reshape(B, Hkv, Ncap, 128), nib(vm), nib(vl)))
+    kh = oc.k_hi.reshape(B, Hkv, Ncap // 256, 128, 256)
+    km, kl = (nib(x.reshape(B, Hkv, Ncap // 256, 128, 128)) for x in (oc.k_mid, oc.k_lo))
+    assert np.array_equal(T.bits(ku), full16(kh, km, kl).transpose(0, 1, 2, 4, 3).reshape(B, Hkv, Ncap, 128))
+    assert torch.equal(k1.view(torch.int16), ku.view(torch.int16)) and torch.equal(v1.view(torch.int16), vu.view(torch.int16))
+
+
+def test_append_of_few_tokens_for_many_heads(T):
+    """Enough (sequence, head) pairs that four tokens already go block by block."""
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A, workloads
+    B, Hkv, Ncap, n = 32, 32, 256, 4
+    print(f"append blocks: {B * Hkv} pairs, {n} tokens", flush=True)
+    k, v = workloads.edge_patterns(B, Hkv, 2 * n + 3, seed=9)
+    lens = [i % 8 for i in range(B)]
+    oc = T.oracle_cache(k[:, :, :7], v[:, :, :7], lens, Ncap)
+    gc = T.gpu_cache(k[:, :, :7], v[:, :, :7], lens, Hkv, Ncap)
+    kn, vn = k[:, :, 7:7 + n].contiguous(), v[:, :, 7:7 + n].contiguous()
+    assert O.append(oc, T.bits(kn), T.bits(vn), np.array([n] * B, np.int32)) == 0
+    A.akv_append(gc, kn.to(DEV), vn.to(DEV))
+    torch.cuda.synchronize()
+    T.assert_cache_equal(gc, oc)
