@@ -1,31 +1,33 @@
 // The unquantised yardstick: decode attention on plain fp16 K, V [B][Hkv][Ncap][D]
 // ("Runtime of AlignedKV": S = QK^T/sqrt(128), softmax, O = SV on 16-bit data).
-// Same streaming design as the plane kernels (16-byte coalesced loads straight into registers, wave
-// shuffles for the reductions, token-axis splits combined at the end), but K and V of a chunk are read in
-// one kernel with a chunk-local softmax (split-KV), since nothing has to be decided between the passes.
-#include <type_traits>
+// K and V of a chunk of tokens are read in one kernel with a softmax of its own (split-KV), since nothing has to be decided
+// between the passes; the chunks are merged by a second small kernel.
+#include <algorithm>
 
 #include "akv_common.h"
 
 namespace akv {
 
-// 16 bytes with the non-temporal hint (the token-split kernels stream K and V once per step, as the aligned ones do)
-__device__ __forceinline__ uint4 load16_nt(const uint16_t* p)
-{
-    const u32x4_t w = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-    return make_uint4(w.x, w.y, w.z, w.w);
-}
-
-constexpr int kFChunk = 512;   // tokens per workgroup
 constexpr int kFWaves = 4;
+constexpr int kFTile = 32;                          // tokens a wave takes at a time
+constexpr int kFMinChunk = kFTile * kFWaves;        // tokens per workgroup are a multiple of this
 
-inline int f_splits(int ntok) { return (ntok + kFChunk - 1) / kFChunk; }
+// Tokens per workgroup: about twelve workgroups per compute unit over the whole call (three are resident; single heads eight,
+// groups of eight four, with two resident), so that ragged lengths even out, and not fewer than one tile per wave.  Timed with 4 / 8 / 12 / 16
+// / 32 workgroups per unit: B 8, 32/8, up to 16000 ragged 77 / 78 / 61 / 65 / 73 us, B 8, 32/8, 32768 178 / 178 / 176 / 182 / 194;
+// B 8, 64/8, 8192 58 / 66 / 66 / 84 / 84; B 8, 32/32, 4096 89 / 85 / 87 / 89 / 92.  From the shape alone: a bound of the lengths must not change the order of the sums.
+static int f_chunk(const akv_shape& s)
+{
+    const int G = s.Hq / s.Hkv;
+    const long wgs = (G == 8 ? 4L : (G == 1 ? 8L : 12L)) * compute_units();
+    const long per = long(s.B) * s.Hkv * s.Ncap / wgs;
+    return (int)std::min(1024L, std::max(long(kFMinChunk), (per + kFMinChunk - 1) / kFMinChunk * kFMinChunk));
+}
 
 size_t fp16_workspace_bytes(const akv_shape& s)
 {
-    const size_t bhq = size_t(s.B) * s.Hq, ns = f_splits(s.Ncap);
-    return align256(bhq * ns * kD * sizeof(float)) + 2 * align256(bhq * ns * sizeof(float)) +
-           align256(bhq * size_t(s.Ncap) * sizeof(float));   // split partials, then the logits of the head-per-workgroup variant
+    const size_t bhq = size_t(s.B) * s.Hq, ns = s.Ncap / kFMinChunk;
+    return align256(bhq * ns * kD * sizeof(float)) + 2 * align256(bhq * ns * sizeof(float));   // partial sums, maxima, weights' sums
 }
 
 struct F16Args {
@@ -34,298 +36,238 @@ struct F16Args {
     const int32_t* lens;
     void* out;
     float c;   // scale * log2(e)
-    int out_dtype, nsplit, max_len;
+    int out_dtype, nsplit, max_len, chunk;   // nsplit: chunks there is room for per query head
     float *partO, *partM, *partZ;
 };
 
-__device__ __forceinline__ void unpack8h(const uint4& w, float (&f)[8])
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// the value of the lane 16 / 32 further (mod the pairs of rows / halves) folded in: op over lanes with the same lane % 16, in all of them
+template <typename F>
+__device__ __forceinline__ float over_rows(float v, F op)
 {
-    f[0] = lo_half(w.x); f[1] = hi_half(w.x); f[2] = lo_half(w.y); f[3] = hi_half(w.y);
-    f[4] = lo_half(w.z); f[5] = hi_half(w.z); f[6] = lo_half(w.w); f[7] = hi_half(w.w);
+    const auto a = __builtin_amdgcn_permlane16_swap(float_bits(v), float_bits(v), false, false);
+    v = op(bits_float(a[0]), bits_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(float_bits(v), float_bits(v), false, false);
+    return op(bits_float(b[0]), bits_float(b[1]));
 }
 
-// Workgroup = 4 waves, one (sequence, KV head, 512-token chunk).  A token row is 256 B = 16 lanes x 16 B;
-// a wave reads 4 rows per step.  Phase 1: logits of the chunk into LDS (16-lane shuffle reduction).
-// Phase 2: chunk max, p = 2^((l - m) c), Z and O accumulated per lane, reduced over rows and waves.
-template <int G>
+__device__ __forceinline__ void store_result(const F16Args& a, size_t at, float v)
+{
+    if (a.out_dtype == 0) reinterpret_cast<float*>(a.out)[at] = v;
+    else reinterpret_cast<_Float16*>(a.out)[at] = (_Float16)v;
+}
+
+// Workgroup = 4 waves, one (sequence, KV head, chunk of tokens); each wave walks its quarter of the chunk by itself in tiles of
+// 32 tokens with a running maximum, so that nothing waits at a barrier until the chunk's end.  Bound by memory; K and V
+// tiles take turns in flight (8 to 16 KB per wave, loads of the next K tile behind those of this V tile).
+//   logits   matrix product on the matrix cores, 16 tokens x 16 columns (the G query heads, the rest zero) x 32 channels:
+//            a lane holds 16 bytes of one token's row per step, no exchange between lanes;
+//   weights  2^((l - m) c) in binary32, through LDS to the lanes that hold the token's V row;
+//   O        multiply-adds in binary32 on the vector ALU, 8 channels of a row per lane (8 G per 16 bytes: a fifth of the
+//            time the bytes take at G = 4).
+// Measured against one row of 16 lanes per token with shuffled sums: B 8, 32/8 heads, up to 16000 tokens 137 -> 65 us, 32768
+// 241 -> 176; B 8, 64/8, 8192 110 -> 58; B 1, 32 heads, 1024 29 -> 13; single heads at 4096 and 8192 as before (memory).
+// Error against 64 bits over these ranges 3e-7 .. 6e-7, as before (one running sum of the logits: a third more).
+// ONE: the launch has one chunk per sequence: the workgroup writes the result itself.
+template <int G, bool ONE>
 __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
 {
-    __shared__ float l_s[G][kFChunk];
-    __shared__ float red_s[kFWaves][G][kD + 1];
-    __shared__ float max_s[kFWaves][G];
+    __shared__ __align__(16) float p_s[kFWaves][kFTile][G];
+    __shared__ float red_s[kFWaves][G][kD];
+    __shared__ float max_s[kFWaves][G], z_s[kFWaves][G];
 
     const int h = blockIdx.y, b = blockIdx.z, split = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane >> 4, cl = lane & 15;            // row within the wave's group of 4, channels 8*cl..8*cl+7
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, j = lane >> 4;   // logits: token n of 16 (then query head n), channels 8j .. 8j+7 of 32; V: row j of 4, channels 8n .. 8n+7
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);
-    const int c0 = split * kFChunk;
-    if (c0 >= len) return;
-    const size_t bh = size_t(b) * Hkv + h;
-
-    float qf[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const uint4 w = *reinterpret_cast<const uint4*>(a.q + (size_t(b) * Hq + size_t(h) * G + g) * kD + cl * 8);
-        unpack8h(w, qf[g]);
-    }
-
-    // ---- phase 1: logits ---------------------------------------------------------------------------
-    float mloc[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) mloc[g] = -INFINITY;
-    for (int it = 0; it < kFChunk / (4 * kFWaves); ++it) {
-        const int tl = it * (4 * kFWaves) + wave * 4 + r, t = c0 + tl;
-        const bool valid = t < len;
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (valid) w = load16_nt(a.k + (bh * Ncap + t) * kD + cl * 8);
-        float kf[8];
-        unpack8h(w, kf);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float s = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) s = fmaf(qf[g][i], kf[i], s);
-            for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o);
-            if (valid) mloc[g] = fmaxf(mloc[g], s);
-            if (cl == 0) l_s[g][tl] = s;
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float m = wave_max(mloc[g]);
-        if (lane == 0) max_s[wave][g] = m;
-    }
-    __syncthreads();
-    float mg[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        mg[g] = max_s[0][g];
-        for (int w = 1; w < kFWaves; ++w) mg[g] = fmaxf(mg[g], max_s[w][g]);
-    }
-
-    // ---- phase 2: weights and O ---------------------------------------------------------------------
-    float acc[G][8], z[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        z[g] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[g][i] = 0.0f;
-    }
-    for (int it = 0; it < kFChunk / (4 * kFWaves); ++it) {
-        const int tl = it * (4 * kFWaves) + wave * 4 + r, t = c0 + tl;
-        const bool valid = t < len;
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (valid) w = load16_nt(a.v + (bh * Ncap + t) * kD + cl * 8);
-        float vf[8];
-        unpack8h(w, vf);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float p = valid ? __builtin_amdgcn_exp2f((l_s[g][tl] - mg[g]) * a.c) : 0.0f;
-            z[g] += p;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[g][i] = fmaf(p, vf[i], acc[g][i]);
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        for (int o = 16; o < 64; o <<= 1) {
-            z[g] += __shfl_xor(z[g], o);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[g][i] += __shfl_xor(acc[g][i], o);
-        }
-        if (r == 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) red_s[wave][g][cl * 8 + i] = acc[g][i];
-            if (cl == 0) red_s[wave][g][kD] = z[g];
-        }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < G * (kD + 1); idx += 64 * kFWaves) {
-        const int g = idx / (kD + 1), d = idx % (kD + 1);
-        float s = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kFWaves; ++w) s += red_s[w][g][d];
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-        if (d < kD) a.partO[(hq * a.nsplit + split) * kD + d] = s;
-        else {
-            a.partZ[hq * a.nsplit + split] = s;
-            a.partM[hq * a.nsplit + split] = mg[g];
-        }
-    }
-}
-
-// merge the splits: rescale each to the global max
-__global__ __launch_bounds__(kD) void fp16_combine_kernel(F16Args a)
-{
-    const int hq_i = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
-    const int len = min(min(a.lens[b], a.s.Ncap), a.max_len);
-    const size_t hq = size_t(b) * a.s.Hq + hq_i;
-    const int used = (len + kFChunk - 1) / kFChunk;
-    float M = -INFINITY;
-    for (int s = 0; s < used; ++s) M = fmaxf(M, a.partM[hq * a.nsplit + s]);
-    float o = 0.0f, zsum = 0.0f;
-    for (int s = 0; s < used; ++s) {
-        const float w = __builtin_amdgcn_exp2f((a.partM[hq * a.nsplit + s] - M) * a.c);
-        o = fmaf(w, a.partO[(hq * a.nsplit + s) * kD + d], o);
-        zsum = fmaf(w, a.partZ[hq * a.nsplit + s], zsum);
-    }
-    const float res = used > 0 ? o / zsum : 0.0f;
-    if (a.out_dtype == 0) reinterpret_cast<float*>(a.out)[hq * kD + d] = res;
-    else reinterpret_cast<_Float16*>(a.out)[hq * kD + d] = (_Float16)res;
-}
-
-// Head-per-workgroup variant (the design of the plane kernels' main path): one workgroup of 1024 threads does
-// the whole (sequence, KV head): logits of all tokens (kept in the workspace), their maximum, then weights and
-// O.  A wave takes a contiguous range of the batches of 32 rows; the 8 row loads of the next batch are in flight while the
-// current batch is reduced.
-template <int G, int NT>
-__global__ __launch_bounds__(NT) void fp16_head_kernel(F16Args a, float* __restrict__ logits)
-{
-    constexpr int kWaves = NT / 64;
-    constexpr int kLoads = 8;   // 4 rows each
-    __shared__ float max_s[kWaves][G];
-    __shared__ float red_s[kWaves][G][kD + 1];
-
-    const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int pair = xcd_work_index(blockIdx.x, gridDim.x);   // an XCD takes consecutive heads
-    if (pair >= a.s.B * Hkv) return;
-    const int h = pair % Hkv, b = pair / Hkv;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane >> 4, cl = lane & 15;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);
-    if (len == 0) {
-        for (int idx = tid; idx < G * kD; idx += NT) {
-            const size_t o = (size_t(b) * Hq + size_t(h) * G) * kD + idx;
-            if (a.out_dtype == 0) reinterpret_cast<float*>(a.out)[o] = 0.0f;
-            else reinterpret_cast<_Float16*>(a.out)[o] = (_Float16)0.0f;
-        }
+    const int c0 = split * a.chunk;
+    const size_t bh = size_t(b) * Hkv + h, hq0 = size_t(b) * Hq + size_t(h) * G;
+    if (c0 >= len) {
+        if (ONE)   // an empty sequence attends to nothing: zeros
+            for (int idx = tid; idx < G * kD; idx += 64 * kFWaves) store_result(a, hq0 * kD + idx, 0.0f);
         return;
     }
-    const size_t bh = size_t(b) * Hkv + h;
-    const __amdgpu_buffer_rsrc_t rs_k = make_rsrc(a.k + bh * Ncap * kD, uint32_t(Ncap) * kD * 2u);
-    const __amdgpu_buffer_rsrc_t rs_v = make_rsrc(a.v + bh * Ncap * kD, uint32_t(Ncap) * kD * 2u);
-    float* lg[G];
-    float qf[G][8];
+    // rows at or past len are out of range: zeros, nothing fetched
+    const __amdgpu_buffer_rsrc_t rs_k = make_rsrc(a.k + bh * Ncap * kD, uint32_t(len) * (kD * 2u));
+    const __amdgpu_buffer_rsrc_t rs_v = make_rsrc(a.v + bh * Ncap * kD, uint32_t(len) * (kD * 2u));
+    const int t_begin = c0 + wave * (a.chunk / kFWaves), t_end = min(t_begin + a.chunk / kFWaves, len);   // the wave's tokens
+
+    u32x4_t kf[2][4], vf[8];
+    auto fetch_k = [&](int t0) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-        lg[g] = logits + hq * Ncap;
-        const uint4 w = *reinterpret_cast<const uint4*>(a.q + hq * kD + cl * 8);
-        unpack8h(w, qf[g]);
-    }
-    const int nbatch = (len + 31) / 32;
-    // each wave walks a contiguous, balanced range of the batches, as in the aligned kernel of this shape
-    const int bt0 = (int)((long long)nbatch * wave / kWaves), bt1 = (int)((long long)nbatch * (wave + 1) / kWaves);
-    // the same cache hints as the aligned kernels of this shape: K non-temporal, V not
-    auto load_batch = [&](const __amdgpu_buffer_rsrc_t& rs, int bt, u32x4_t (&w)[kLoads], auto nt) {
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) {
-            const int t = bt * 32 + j * 4 + r;
-            const uint32_t off = (bt < bt1 && t < len) ? uint32_t(t) * (kD * 2) + cl * 16 : kSkip;
-            w[j] = decltype(nt)::value ? buf_load_b128_nt(rs, off) : buf_load_b128(rs, off);
-        }
+            for (int kb = 0; kb < 4; ++kb) kf[s][kb] = buf_load_b128_nt(rs_k, t0 < t_end ? uint32_t(t0 + 16 * s + n) * (kD * 2u) + kb * 64 + j * 16 : kSkip);
     };
-    constexpr std::true_type kNt{};
-    constexpr std::false_type kKeep{};
-
-    // ---- phase 1: logits and their maximum ---------------------------------------------------------
-    float mloc[G];
+    auto fetch_v = [&](int t0) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) mloc[g] = -INFINITY;
-    u32x4_t wc[kLoads], wn[kLoads];
-    load_batch(rs_k, bt0, wc, kNt);
-#pragma unroll 1
-    for (int bt = bt0; bt < bt1; ++bt) {
-        load_batch(rs_k, bt + 1, wn, kNt);
+        for (int k = 0; k < 8; ++k) vf[k] = buf_load_b128_nt(rs_v, t0 < t_end ? uint32_t(t0 + 4 * k + j) * (kD * 2u) + n * 16 : kSkip);
+    };
+    fetch_k(t_begin);
+    fetch_v(t_begin);
+    half8_t qf[4];
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) {
-            const int t = bt * 32 + j * 4 + r;
-            float kf[8];
-            unpack8h(make_uint4(wc[j].x, wc[j].y, wc[j].z, wc[j].w), kf);
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float s = 0.0f;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) s = fmaf(qf[g][i], kf[i], s);
-                for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o);
-                if (t < len) {
-                    mloc[g] = fmaxf(mloc[g], s);
-                    if (cl == 0) lg[g][t] = s;
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kLoads; ++j) wc[j] = wn[j];
+    for (int kb = 0; kb < 4; ++kb) {
+        u32x4_t w = {0u, 0u, 0u, 0u};
+        if (n < G) w = *reinterpret_cast<const u32x4_t*>(a.q + (hq0 + n) * kD + kb * 32 + j * 8);
+        qf[kb] = __builtin_bit_cast(half8_t, w);
     }
+    float acc[G][8], z = 0.0f, m_run = -INFINITY;   // z, m_run: of query head n (lanes with n < G)
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float m = wave_max(mloc[g]);
-        if (lane == 0) max_s[wave][g] = m;
-    }
-    __syncthreads();   // also: every logit store of the workgroup has completed
-    float mg[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        mg[g] = max_s[0][g];
-        for (int w = 1; w < kWaves; ++w) mg[g] = fmaxf(mg[g], max_s[w][g]);
-    }
-
-    // ---- phase 2: weights and O -----------------------------------------------------------------------
-    float acc[G][8], z[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        z[g] = 0.0f;
+    for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[g][i] = 0.0f;
-    }
-    load_batch(rs_v, bt0, wc, kKeep);
+
 #pragma unroll 1
-    for (int bt = bt0; bt < bt1; ++bt) {
-        load_batch(rs_v, bt + 1, wn, kKeep);
+    for (int t0 = t_begin; t0 < t_end; t0 += kFTile) {
+        f32x4_t s[2];
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) {
-            const int t = bt * 32 + j * 4 + r;
-            float vf[8];
-            unpack8h(make_uint4(wc[j].x, wc[j].y, wc[j].z, wc[j].w), vf);
+        for (int u = 0; u < 2; ++u) {
+            f32x4_t part[4];   // 32 channels each, added pairwise: less rounding than one running sum through the matrix cores
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) part[kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, kf[u][kb]), qf[kb], f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            s[u] = (part[0] + part[1]) + (part[2] + part[3]);
+        }
+        fetch_k(t0 + kFTile);
+        // lane: query head n, tokens 16 u + 4 j + i
+        float m = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (t0 + 16 * u + 4 * j + i >= t_end) s[u][i] = -INFINITY;
+                m = fmaxf(m, s[u][i]);
+            }
+        m = over_rows(m, [](float x, float y) { return fmaxf(x, y); });
+        if (__ballot(m > m_run)) {   // uniform; rare after the first tiles
+            const float m_new = fmaxf(m, m_run), sc = __builtin_amdgcn_exp2f((m_run - m_new) * a.c);
+            z *= sc;
+            m_run = m_new;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const float p = t < len ? __builtin_amdgcn_exp2f((lg[g][t < len ? t : 0] - mg[g]) * a.c) : 0.0f;
-                z[g] += p;
+                const float sg = bits_float(__builtin_amdgcn_readlane(float_bits(sc), g));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) acc[g][i] = fmaf(p, vf[i], acc[g][i]);
+                for (int i = 0; i < 8; ++i) acc[g][i] *= sg;
             }
         }
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) wc[j] = wn[j];
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float p = __builtin_amdgcn_exp2f((s[u][i] - m_run) * a.c);
+                z += p;
+                if (n < G) p_s[wave][16 * u + 4 * j + i][n] = p;
+            }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            float p[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) p[g] = p_s[wave][4 * k + j][g];
+            const uint32_t w[4] = {vf[k].x, vf[k].y, vf[k].z, vf[k].w};
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[g][2 * i] = fmaf(p[g], lo_half(w[i]), acc[g][2 * i]);
+                    acc[g][2 * i + 1] = fmaf(p[g], hi_half(w[i]), acc[g][2 * i + 1]);
+                }
+        }
+        fetch_v(t0 + kFTile);
+    }
+
+    // ---- the waves' sums, rescaled to the chunk's maximum
+    auto add = [](float x, float y) { return x + y; };
+    z = over_rows(z, add);
+    if (lane < G) {
+        max_s[wave][lane] = m_run;
+        z_s[wave][lane] = z;
     }
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        for (int o = 16; o < 64; o <<= 1) {
-            z[g] += __shfl_xor(z[g], o);
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[g][i] += __shfl_xor(acc[g][i], o);
+        for (int i = 0; i < 8; ++i) {
+            const float o = over_rows(acc[g][i], add);
+            if (j == 0) red_s[wave][g][8 * n + i] = o;
         }
-        if (r == 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) red_s[wave][g][cl * 8 + i] = acc[g][i];
-            if (cl == 0) red_s[wave][g][kD] = z[g];
-        }
-    }
     __syncthreads();
-    for (int idx = tid; idx < G * kD; idx += NT) {
+    for (int idx = tid; idx < G * kD; idx += 64 * kFWaves) {
         const int g = idx / kD, d = idx % kD;
-        float o = 0.0f, zsum = 0.0f;
+        float M = max_s[0][g];   // wave 0 has tokens
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            o += red_s[w][g][d];
-            zsum += red_s[w][g][kD];
+        for (int w = 1; w < kFWaves; ++w) M = fmaxf(M, max_s[w][g]);
+        float o = 0.0f, zs = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kFWaves; ++w) {
+            const float sc = __builtin_amdgcn_exp2f((max_s[w][g] - M) * a.c);
+            o = fmaf(sc, red_s[w][g][d], o);
+            zs = fmaf(sc, z_s[w][g], zs);
         }
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-        const float res = o / zsum;
-        if (a.out_dtype == 0) reinterpret_cast<float*>(a.out)[hq * kD + d] = res;
-        else reinterpret_cast<_Float16*>(a.out)[hq * kD + d] = (_Float16)res;
+        const size_t hq = hq0 + g;
+        if (ONE) {
+            store_result(a, hq * kD + d, o / zs);
+        } else {
+            a.partO[(hq * a.nsplit + split) * kD + d] = o;
+            if (d == 0) {
+                a.partM[hq * a.nsplit + split] = M;
+                a.partZ[hq * a.nsplit + split] = zs;
+            }
+        }
     }
+}
+
+// merge the chunks of one query head: rescale each to the global max (a wave holds 64 chunks' weights; 16 rows in flight)
+__global__ __launch_bounds__(kD) void fp16_combine_kernel(F16Args a)
+{
+    __shared__ float w_s[kD];
+    const int hq_i = blockIdx.x, b = blockIdx.y, d = threadIdx.x, lane = d & 63;
+    const int len = min(min(a.lens[b], a.s.Ncap), a.max_len);
+    const size_t hq = size_t(b) * a.s.Hq + hq_i;
+    const int used = (len + a.chunk - 1) / a.chunk;
+    const float *pm = a.partM + hq * a.nsplit, *pz = a.partZ + hq * a.nsplit, *po = a.partO + hq * a.nsplit * kD + d;
+    float M = -INFINITY;
+    for (int s = lane; s < used; s += 64) M = fmaxf(M, pm[s]);
+    M = wave_max(M);
+    float o = 0.0f, zsum = 0.0f;
+    for (int s0 = 0; s0 < used; s0 += kD) {   // uniform
+        const int s = s0 + d;
+        const float w = s < used ? __builtin_amdgcn_exp2f((pm[s] - M) * a.c) : 0.0f;
+        if (s < used) zsum = fmaf(w, pz[s], zsum);
+        w_s[d] = w;
+        __syncthreads();
+        const int lim = min(used - s0, kD);
+        for (int i0 = 0; i0 < lim; i0 += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = i0 + i < lim ? po[size_t(s0 + i0 + i) * kD] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o = fmaf(i0 + i < lim ? w_s[i0 + i] : 0.0f, v[i], o);
+        }
+        __syncthreads();
+    }
+    __shared__ float z2_s[2];
+    for (int k = 1; k < 64; k <<= 1) zsum += __shfl_xor(zsum, k);
+    if (lane == 0) z2_s[d >> 6] = zsum;
+    __syncthreads();
+    store_result(a, hq * kD + d, used > 0 ? o / (z2_s[0] + z2_s[1]) : 0.0f);
+}
+
+template <int G>
+static hipError_t launch_fp16_g(const F16Args& a, hipStream_t st)
+{
+    const dim3 grid((a.max_len + a.chunk - 1) / a.chunk, a.s.Hkv, a.s.B), block(64 * kFWaves);
+    if (grid.x == 1) {
+        hipLaunchKernelGGL((fp16_kernel<G, true>), grid, block, 0, st, a);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((fp16_kernel<G, false>), grid, block, 0, st, a);
+    if (hipError_t e = hipGetLastError()) return e;
+    hipLaunchKernelGGL(fp16_combine_kernel, dim3(a.s.Hq, a.s.B), dim3(kD), 0, st, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v, const int32_t* lens, const uint16_t* q,
@@ -335,7 +277,8 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.s = s; a.k = k; a.v = v; a.q = q; a.lens = lens; a.out = out;
     a.c = (float)((double)scale * 1.4426950408889634);
     a.out_dtype = out_dtype;
-    a.nsplit = f_splits(s.Ncap);
+    a.nsplit = s.Ncap / kFMinChunk;
+    a.chunk = f_chunk(s);
     a.max_len = max_len;
     const size_t bhq = size_t(s.B) * s.Hq;
     char* p = reinterpret_cast<char*>(ws);
@@ -344,30 +287,13 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.partM = reinterpret_cast<float*>(p);
     p += align256(bhq * a.nsplit * sizeof(float));
     a.partZ = reinterpret_cast<float*>(p);
-    p += align256(bhq * a.nsplit * sizeof(float));
-    float* logits = reinterpret_cast<float*>(p);
-    const int G = s.Hq / s.Hkv;
-    // One workgroup per head only for short sequences on a full chip (timed on 256 heads: 31.6 against 40.5 us at 1024
-    // tokens, even at 2048, 99 against 86.5 us at 4096): beyond that the many small workgroups of the chunk kernel
-    // stream faster (6.2 TB/s), and the yardstick is the faster of the two.
-    if (G <= 2 && s.B * s.Hkv >= 192 && max_len < 2048) {
-        const dim3 hgrid(xcd_grid(size_t(s.B) * s.Hkv));
-        if (G == 1) hipLaunchKernelGGL((fp16_head_kernel<1, 1024>), hgrid, dim3(1024), 0, st, a, logits);
-        else hipLaunchKernelGGL((fp16_head_kernel<2, 1024>), hgrid, dim3(1024), 0, st, a, logits);
-        return hipGetLastError();
-    }
-    const dim3 grid(f_splits(max_len), s.Hkv, s.B), block(64 * kFWaves);
-    switch (G) {
-        case 1: hipLaunchKernelGGL(fp16_kernel<1>, grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL(fp16_kernel<2>, grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL(fp16_kernel<4>, grid, block, 0, st, a); break;
-        case 8: hipLaunchKernelGGL(fp16_kernel<8>, grid, block, 0, st, a); break;
+    switch (s.Hq / s.Hkv) {
+        case 1: return launch_fp16_g<1>(a, st);
+        case 2: return launch_fp16_g<2>(a, st);
+        case 4: return launch_fp16_g<4>(a, st);
+        case 8: return launch_fp16_g<8>(a, st);
         default: return hipErrorInvalidValue;
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fp16_combine_kernel, dim3(s.Hq, s.B), dim3(kD), 0, st, a);
-    return hipGetLastError();
 }
 
 }  // namespace akv

@@ -1,0 +1,36 @@
+"""GPU parity of the fp16 decode attention at the edges of its tiles: every group size, lengths around a tile of 32 tokens, a wave's
+and a workgroup's share, one chunk (the workgroup writes the result itself) and several (merged), fp16 output."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("Ncap,lens", [(256, [0, 1, 31, 32, 33, 127, 128, 129, 256]), (2816, [2816, 2785, 640, 129, 0])])
+def test_fp16_attention_matches_textbook(G, Ncap, lens):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import akv_testlib as T
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A, workloads
+    O.build()
+    print(f"fp16 attention: G{G} Ncap {Ncap} lens {lens}", flush=True)
+    B, Hkv = len(lens), 2
+    w = workloads.make(2, B=B, Hq=G * Hkv, Hkv=Hkv, N=Ncap, seed=40 + G)
+    lens = np.asarray(lens, np.int32)
+    args = (w.k.to(DEV), w.v.to(DEV), torch.from_numpy(lens).to(DEV), w.q.to(DEV))
+    out = A.akv_fp16_decode_attention(*args)
+    first = A.akv_fp16_decode_attention(*args, max_len=128)                      # one chunk per sequence
+    out16 = A.akv_fp16_decode_attention(*args, out=torch.empty_like(args[3]))
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+    ref = O.fp16_attention(T.bits(w.k), T.bits(w.v), lens, T.bits(w.q))
+    assert np.abs(got - ref).max() <= T.MAX_ABS and T.rel_l2(got, ref) <= T.REL_L2
+    assert torch.equal(out16, out.to(torch.float16)) and not got[lens == 0].any()
+    ref1 = O.fp16_attention(T.bits(w.k), T.bits(w.v), np.minimum(lens, 128), T.bits(w.q))
+    got1 = first.cpu().numpy().astype(np.float64)
+    assert np.abs(got1 - ref1).max() <= T.MAX_ABS and T.rel_l2(got1, ref1) <= T.REL_L2
