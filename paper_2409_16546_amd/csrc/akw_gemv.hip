@@ -9,9 +9,13 @@
 // level does not need a plane is asked for out of range and fetches nothing).  All of a wave's loads are in flight
 // at once: the HI bytes go first, before anything is known about the levels.  Every workgroup derives the largest
 // addend exponent of each activation row from x and rowmax itself (K products, from L2) -- cheaper than a launch
-// of its own in front of a kernel that runs for a few microseconds.  The sums over the 8 row lanes meet by lane
-// exchange, the waves' sums in LDS, the slabs' sums (K/512 of them) in the workspace: the workgroup that draws
+// of its own in front of a kernel that runs for a few microseconds.  One activation row is multiplied on the vector ALU, two
+// to four by 4x4x4 matrix products (the weights stay where the lanes hold them; four fp16 rows of a column are two byte
+// permutes).  The sums over the 8 row lanes meet in the vector ALU, the waves' sums in LDS, the slabs' sums (K/512 of them) in the workspace: the workgroup that draws
 // the last ticket of a strip adds them in slab order, so the result does not depend on timing.
+// Measured against multiply-adds for every activation row and row sums through lane exchange (1 / 2 / 4 rows, us):
+// 4096x4096 10.7 / 13.2 / 18.9 -> 10.0 / 11.2 / 13.0, 4096x11008 16.8 / 23.1 / 34.1 ->
+// 15.7 / 19.3 / 21.9, 11008x4096 17.8 / 28.5 / 43.5 -> 17.6 / 23.0 / 28.2.
 #include <cstdarg>
 
 #include "../../include/akw.h"
@@ -36,13 +40,49 @@ struct GemvArgs {
     uint8_t* lvl_out;
 };
 
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Sums over the 8 row lanes of a wave (lane / 8) in the vector ALU, two values per exchange: afterwards a lane holds the
+// totals of columns row_lane_column(lane), + 1 of its 16, v[0] and v[1].  (24 instead of 48 exchanges through the LDS unit for
+// 16 values: that unit is shared by the whole compute unit.)
+__device__ __forceinline__ int row_lane_column(int lane) { return 8 * (lane >> 5) + 4 * ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1); }
+__device__ __forceinline__ void sum_row_lanes(const float (&acc)[16], float (&v)[2])
+{
+    float a[8], b[4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {   // lower half of the wave: columns 0..7, upper half: 8..15
+        const auto x = __builtin_amdgcn_permlane32_swap(float_bits(acc[i]), float_bits(acc[i + 8]), false, false);
+        a[i] = bits_float(x[0]) + bits_float(x[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto x = __builtin_amdgcn_permlane16_swap(float_bits(a[i]), float_bits(a[i + 4]), false, false);
+        b[i] = bits_float(x[0]) + bits_float(x[1]);
+    }
+    const bool up = threadIdx.x & 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = up ? b[i + 2] : b[i], send = up ? b[i] : b[i + 2];
+        v[i] = keep + bits_float(__builtin_amdgcn_update_dpp(0, float_bits(send), 0x128, 0xF, 0xF, false));   // row_ror:8
+    }
+}
+
+// two fp16 magnitudes, each at least the smallest normal
+__device__ __forceinline__ uint32_t at_least_smallest_normal(uint32_t w)
+{
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, w), u16x2_t{0x0400, 0x0400}));
+}
+
 template <int B>
 __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two workgroups per compute unit at least
 {
-    __shared__ int emax_s[B][kWWaves];
+    __shared__ float pmax_s[B][kWWaves];
     __shared__ int lvl_s[kWSlab];
-    __shared__ float xs[B][kWSlab];
-    __shared__ float red_s[kWWaves][B][kWCols];
+    __shared__ float xs[B == 1 ? kWSlab : 1];
+    __shared__ __align__(16) uint16_t xh[4][kWWaves][8][kWGroups];   // B > 1: x of row (group g, row lane r) of a wave, as the matrix instruction takes it
+    __shared__ __align__(16) float red_s[kWWaves][B][kWCols];
     __shared__ int last_s;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -68,57 +108,63 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
         H[g] = buf_load_b128(rs_hi, lane_ok && k < K ? uint32_t(k) * uint32_t(N) + uint32_t(col) : kSkip);
     }
 
-    // ---- Rule 1: largest addend exponent of every activation row, over all K input features (8 per thread and round)
-    int emax[B];
+    // rowmax and x of this thread's row of the slab: used once the exponents are known, asked for now
+    const int k_row = k0 + tid;
+    uint32_t r16_row = 0, x16_row[B];
 #pragma unroll
-    for (int b = 0; b < B; ++b) emax[b] = -1;
+    for (int b = 0; b < B; ++b) x16_row[b] = 0;
+    if (k_row < K) {
+        r16_row = a.rowmax[k_row];
+#pragma unroll
+        for (int b = 0; b < B; ++b) x16_row[b] = a.x[size_t(b) * K + k_row];
+    }
+
+    // ---- Rule 1: largest addend exponent of every activation row, over all K input features (8 per thread and round)
+    if (B > 1 && B < 4)   // activation rows that are not there
+        for (int i = tid; i < (4 - B) * kWSlab; i += kWThreads) (&xh[B][0][0][0])[i] = 0;
+    // (the exponent of the largest product: one multiply and one maximum per product)
+    float pmax[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) pmax[b] = 0.0f;
     const int nvec = K / 8;
     for (int v = tid; v < nvec; v += kWThreads) {
         const uint4 rm = reinterpret_cast<const uint4*>(a.rowmax)[v];
-        const uint32_t rw[4] = {rm.x, rm.y, rm.z, rm.w};
+        const uint32_t rw[4] = {at_least_smallest_normal(rm.x), at_least_smallest_normal(rm.y), at_least_smallest_normal(rm.z), at_least_smallest_normal(rm.w)};
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const uint4 xv = reinterpret_cast<const uint4*>(a.x)[size_t(b) * nvec + v];
             const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t r16 = (rw[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-                const uint32_t x16 = (xw[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-                const float P = half_bits_to_float(x16) * half_bits_to_float(r16 < 0x0400u ? 0x0400u : r16);   // exact
-                const int e = float_exp_field(P);
-                emax[b] = (P != 0.0f && e > emax[b]) ? e : emax[b];
-            }
+            for (int i = 0; i < 4; ++i)                             // exact products
+                pmax[b] = fmaxf(pmax[b], fmaxf(fabsf(lo_half(xw[i]) * lo_half(rw[i])), fabsf(hi_half(xw[i]) * hi_half(rw[i]))));
         }
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-        const int m = (int)wave_max((float)emax[b]);                // small integers: exact as floats
-        if (lane == 0) emax_s[b][wave] = m;
+        const float m = wave_max(pmax[b]);
+        if (lane == 0) pmax_s[b][wave] = m;
     }
     __syncthreads();
     {                                                               // thread -> row k0 + tid of the slab: level and activations
-        const int k = k0 + tid;
         int level = 0;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            int em = -1;
+            float pm = pmax_s[b][0];
 #pragma unroll
-            for (int w = 0; w < kWWaves; ++w) em = emax_s[b][w] > em ? emax_s[b][w] : em;
-            float xf = 0.0f;
-            if (k < K) {
-                const uint32_t x16 = a.x[size_t(b) * K + k], r16 = a.rowmax[k];
-                xf = half_bits_to_float(x16);
-                const float P = xf * half_bits_to_float(r16 < 0x0400u ? 0x0400u : r16);
-                if (P != 0.0f) {
-                    const int l = level_for_mantissa_bits(10 + a.guard_bits - (em - float_exp_field(P)));
-                    level = l > level ? l : level;
-                }
+            for (int w = 1; w < kWWaves; ++w) pm = fmaxf(pm, pmax_s[b][w]);
+            const int em = float_exp_field(pm);
+            const float xf = half_bits_to_float(x16_row[b]);        // rows at or past K: 0
+            const float P = xf * half_bits_to_float(r16_row < 0x0400u ? 0x0400u : r16_row);
+            if (P != 0.0f) {
+                const int l = level_for_mantissa_bits(10 + a.guard_bits - (em - float_exp_field(P)));
+                level = l > level ? l : level;
             }
-            xs[b][tid] = xf;                                        // rows at or past K: 0
+            if (B == 1) xs[B == 1 ? tid : 0] = xf;
+            else xh[b][tid >> 6][tid & 7][(tid >> 3) & 7] = (uint16_t)x16_row[b];
         }
         if (a.force_level >= 0) level = a.force_level;
         lvl_s[tid] = level;
-        if (a.lvl_out && strip == 0 && k < K) a.lvl_out[k] = (uint8_t)level;
+        if (a.lvl_out && strip == 0 && k_row < K) a.lvl_out[k_row] = (uint8_t)level;
     }
     __syncthreads();
 
@@ -135,41 +181,69 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
         L[g] = buf_load_b64(rs_lo, in && lv[g] >= 2 ? off : kSkip);
     }
     float acc[B][16];
-#pragma unroll
-    for (int b = 0; b < B; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
-#pragma unroll
-    for (int g = 0; g < kWGroups; ++g) {
+    auto assemble = [&](int g, uint32_t (&pa)[4], uint32_t (&pb)[4]) {
         const uint32_t fill = fill_for_level(lv[g]);
-        uint32_t pa[4], pb[4];
         assemble8_fill(H[g].x, H[g].y, M[g].x, L[g].x, fill, pa);   // columns 0..7 of the lane
         assemble8_fill(H[g].z, H[g].w, M[g].y, L[g].y, fill, pb);   // columns 8..15
-        const float v[16] = {lo_half(pa[0]), lo_half(pa[1]), hi_half(pa[0]), hi_half(pa[1]),
-                             lo_half(pa[2]), lo_half(pa[3]), hi_half(pa[2]), hi_half(pa[3]),
-                             lo_half(pb[0]), lo_half(pb[1]), hi_half(pb[0]), hi_half(pb[1]),
-                             lo_half(pb[2]), lo_half(pb[3]), hi_half(pb[2]), hi_half(pb[3])};
-        const int lr = local_row(g);
+    };
+    if constexpr (B == 1) {
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const float xf = xs[b][lr];
+        for (int i = 0; i < 16; ++i) acc[0][i] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[b][i] = fmaf(xf, v[i], acc[b][i]);
+        for (int g = 0; g < kWGroups; ++g) {
+            uint32_t pa[4], pb[4];
+            assemble(g, pa, pb);
+            const float v[16] = {lo_half(pa[0]), lo_half(pa[1]), hi_half(pa[0]), hi_half(pa[1]),
+                                 lo_half(pa[2]), lo_half(pa[3]), hi_half(pa[2]), hi_half(pa[3]),
+                                 lo_half(pb[0]), lo_half(pb[1]), hi_half(pb[0]), hi_half(pb[1]),
+                                 lo_half(pb[2]), lo_half(pb[3]), hi_half(pb[2]), hi_half(pb[3])};
+            const float xf = xs[local_row(g)];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = fmaf(xf, v[i], acc[0][i]);
         }
-    }
-
-    // ---- sums: over the 8 row lanes by lane exchange, over the waves in LDS, over the slabs in the workspace
+    } else {
+        // Two to four activation rows: sixteen 4x4x4 products per instruction.  A block is four lanes of one row lane r, its
+        // four k are four groups' rows, its four columns one column of each of the four lanes, its four rows the activation
+        // rows (those that are not there are zero): D[b] of the instruction for column i is this lane's acc[b][i].
+        const u32x4_t xa = *reinterpret_cast<const u32x4_t*>(&xh[lane & 3][wave][r][0]);   // A: activation row lane % 4, eight groups
+        f32x4_t d[16];
 #pragma unroll
-    for (int b = 0; b < B; ++b)
-        for (int o = 8; o < 64; o <<= 1) {
+        for (int i = 0; i < 16; ++i) d[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[b][i] += __shfl_xor(acc[b][i], o);
+        for (int q = 0; q < kWGroups / 4; ++q) {
+            const half4_t x4 = __builtin_bit_cast(half4_t, u32x2_t{xa[2 * q], xa[2 * q + 1]});
+            uint32_t p[4][8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t pa[4], pb[4];
+                assemble(4 * q + i, pa, pb);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    p[i][w] = pa[w];
+                    p[i][4 + w] = pb[w];
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {   // word w: columns c, c + 2
+                const int c = 8 * (w >> 2) + 4 * ((w >> 1) & 1) + (w & 1);
+                const u32x2_t lo = {__builtin_amdgcn_perm(p[1][w], p[0][w], 0x05040100u), __builtin_amdgcn_perm(p[3][w], p[2][w], 0x05040100u)};
+                const u32x2_t hi = {__builtin_amdgcn_perm(p[1][w], p[0][w], 0x07060302u), __builtin_amdgcn_perm(p[3][w], p[2][w], 0x07060302u)};
+                d[c] = __builtin_amdgcn_mfma_f32_4x4x4f16(x4, __builtin_bit_cast(half4_t, lo), d[c], 0, 0, 0);
+                d[c + 2] = __builtin_amdgcn_mfma_f32_4x4x4f16(x4, __builtin_bit_cast(half4_t, hi), d[c + 2], 0, 0, 0);
+            }
         }
-    if (r == 0) {
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) red_s[wave][b][cl * 16 + i] = acc[b][i];
+            for (int i = 0; i < 16; ++i) acc[b][i] = d[i][b];
+    }
+
+    // ---- sums: over the 8 row lanes in the vector ALU, over the waves in LDS, over the slabs in the workspace
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        float v[2];
+        sum_row_lanes(acc[b], v);
+        *reinterpret_cast<float2*>(&red_s[wave][b][cl * 16 + row_lane_column(lane)]) = make_float2(v[0], v[1]);
     }
     __syncthreads();
     const int nslab = a.nslab;

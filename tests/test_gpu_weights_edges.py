@@ -1,0 +1,34 @@
+"""GPU parity of the weight GEMV where two to four activation rows go through the matrix cores: the smallest shapes, ragged strips and
+slabs, subnormal weights and activations (they must not be flushed), an activation row of zeros."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 4])
+@pytest.mark.parametrize("K,N,tiny", [(8, 16, False), (520, 144, False), (64, 128, True), (1032, 272, True)])
+def test_gemv_edges_match_oracle(K, N, tiny, B):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import akw_oracle as OW
+    from paper_2409_16546_amd import binding as A, workloads
+    OW.build()
+    print(f"gemv edges: K{K} N{N} B{B} subnormal {tiny}", flush=True)
+    bits = lambda t: np.ascontiguousarray(t.contiguous().view(torch.int16).numpy().view(np.uint16))
+    wl = workloads.make_weights((K, N), B, outliers=2, seed=K + B)
+    W, x = (wl.W.float() * 2.0 ** -16).half() if tiny else wl.W, (wl.x.float() * 2.0 ** -16).half() if tiny else wl.x
+    if B > 2:
+        x[1] = 0
+    gw = A.Weights.allocate(K, N, DEV)
+    A.akw_pack(gw, W.to(DEV))
+    lvl = torch.empty(K, dtype=torch.uint8, device=DEV)
+    y = A.akw_gemv(gw, x.to(DEV), lvl_out=lvl)
+    torch.cuda.synchronize()
+    r = OW.gemv(OW.pack(bits(W)), bits(x))
+    assert np.array_equal(lvl.cpu().numpy(), r.lvl)
+    # at most 19 + K/512 binary32 additions of a running sum no larger than S_n = sum |x w| (2^-24 of it each): below 1.3e-6
+    assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - r.y) <= 1.3e-6 * r.abs_sum)
