@@ -76,26 +76,29 @@ __device__ __forceinline__ void v_prefetch_hi(const DecodeArgs& a, int b, int h,
         for (int gr = 0; gr < KG; ++gr) hi[n][gr] = buf_load_b128(rs_hi, voff + uint32_t(n * batch_stride + gr * 8) * kD);
 }
 
-// LDS of the shared mode of v_rows: the rows all waves of a workgroup assembled in one round, transposed -- line L
-// holds one of the 128 values of a row (as fp16) for every row of the round, so that four consecutive rows of a line
-// are one 8-byte read, the operand layout of the 16x16x16 matrix instruction -- and the weights of these rows, line
-// g the high part and line G + g the low part of query head g's weight (two fp16 numbers whose sum carries 22 bits).
-// Two buffers alternate by round.  Lines are kStride halves apart: 8-byte aligned, neighbouring lines two banks apart.
-// Which channel a line holds: line_channel().
+// LDS of the shared mode of v_rows: the rows all waves of a workgroup assembled in one round, row after row, each as the
+// sixteen 16-byte words its eight lanes hold (word cl: the first eight channels of slice cl, word 8 + cl: the second eight),
+// and the weights of these rows, line g the high part and line G + g the low part of query head g's weight (two fp16
+// numbers whose sum carries 22 bits).  The matrix instruction wants four consecutive rows of one value per lane: the
+// transposing LDS read turns them on the way out, so that a lane lays a row down with two 16-byte stores (sixteen 4-byte
+// stores for two rows, and as many byte permutes, where they were transposed on the way in: B 8, 32/8, 32768 tokens 174.2 ->
+// 173.1 us a call, B 4, 32/8, up to 131072 276.9 -> 273.4).  The words of a row are
+// permuted by its number, so that neither side has bank conflicts.  Two buffers alternate by round.
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 template <int G, int RB> struct VShare {
     static constexpr int kRows = kVWaves * RB;   // rows of a round
-    static constexpr int kStride = kRows + 4;
-    alignas(16) uint16_t vt[2][kD][kStride];
-    alignas(16) uint16_t pt[2][16][kStride];
+    alignas(16) u32x4_t vr[2][kRows][16];
+    alignas(16) uint16_t pt[2][16][kRows + 8];
 };
-// assemble8_fill leaves channels (0,2), (1,3), (4,6), (5,7) of eight in its four words; the lane of channel slice cl
-// stores half hf of word wi of its first eight channels in line 8 * (2 * wi + hf) + cl, of its second eight 64 lines on
+// the channel of value `line` (0..127) of a row as it lies in VShare::vr: assemble8_fill leaves channels (0,2), (1,3), (4,6),
+// (5,7) of eight in its four words
 __device__ __forceinline__ int line_channel(int line)
 {
-    const int c = (line & 63) >> 3, cl = line & 7, wi = c >> 1, hf = c & 1;
-    return 16 * cl + 8 * (line >> 6) + (wi & 1) + 4 * (wi >> 1) + 2 * hf;
+    const int word = line >> 3, pos = line & 7;
+    return 16 * (word & 7) + 8 * (word >> 3) + ((pos >> 1) & 1) + 4 * (pos >> 2) + 2 * (pos & 1);
 }
 constexpr float kVWeightScale = 16384.0f;   // weights are at most 1: scaled by 2^14 their fp16 parts reach down to 2^-38
 // workgroup barrier that waits for this wave's LDS traffic only: the loads from memory that are in flight stay in flight
@@ -122,7 +125,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // and the chunk partials of other workgroups share the caches, and costs in the head-per-workgroup kernel); the MID
 // and LO bytes always are (it pays in both).
 // SHARED, sh: the shared mode for groups of query heads (the token-split V kernel).  Every wave of the workgroup still
-// fetches, tests and assembles its own rows, once, but leaves them in LDS (transposed) with their weights; after a
+// fetches, tests and assembles its own rows, once, but leaves them in LDS with their weights; after a
 // barrier the sum over the rows of the round, for all query heads at once, is a matrix product on the matrix cores:
 // D[m][line] += sum_rows W[m][row] * V[row][line], wave w taking lines 32 w .. 32 w + 31.  acc then holds the wave's two
 // 16x16 result tiles (four words each: rows 4 * (lane / 16) .. + 3 of W, line 16 * (2 w + tile) + lane % 16), scaled by
@@ -292,38 +295,23 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
         }
     };
 
-    // shared mode: A leaves the wave's rows of batch bt, transposed, and their weights in the round's buffer; Fs is the
-    // wave's share of the matrix product over the rows of the round
+    // shared mode: A leaves the wave's rows of batch bt and their weights in the round's buffer; Fs is the wave's share of the matrix product over the rows of the round
     auto A = [&](const Batch& X, int bt) {
         const int buf = bt & 1;
-        uint32_t pa[KG][4], pb[KG][4];
 #pragma unroll
         for (int gr = 0; gr < KG; ++gr) {
-            assemble8_fill(X.hi[gr].x, X.hi[gr].y, X.mid[gr].x, X.lo[gr].x, X.fill[gr], pa[gr]);
-            assemble8_fill(X.hi[gr].z, X.hi[gr].w, X.mid[gr].y, X.lo[gr].y, X.fill[gr], pb[gr]);
-        }
-        // the order of the rows inside a round is free (the weights follow it): the lane's two rows, 8 apart in the
-        // batch, are neighbours in the buffer, so that one 32-bit store lays down both
-        const int row = wave * RB + KG * r;
-#pragma unroll
-        for (int wi = 0; wi < 4; ++wi) {
-            if (KG == 2) {
-                *reinterpret_cast<uint32_t*>(&sh->vt[buf][8 * (2 * wi) + cl][row]) = __builtin_amdgcn_perm(pa[KG - 1][wi], pa[0][wi], 0x05040100u);
-                *reinterpret_cast<uint32_t*>(&sh->vt[buf][8 * (2 * wi + 1) + cl][row]) = __builtin_amdgcn_perm(pa[KG - 1][wi], pa[0][wi], 0x07060302u);
-                *reinterpret_cast<uint32_t*>(&sh->vt[buf][64 + 8 * (2 * wi) + cl][row]) = __builtin_amdgcn_perm(pb[KG - 1][wi], pb[0][wi], 0x05040100u);
-                *reinterpret_cast<uint32_t*>(&sh->vt[buf][64 + 8 * (2 * wi + 1) + cl][row]) = __builtin_amdgcn_perm(pb[KG - 1][wi], pb[0][wi], 0x07060302u);
-            } else {
-                sh->vt[buf][8 * (2 * wi) + cl][row] = (uint16_t)pa[0][wi];
-                sh->vt[buf][8 * (2 * wi + 1) + cl][row] = (uint16_t)(pa[0][wi] >> 16);
-                sh->vt[buf][64 + 8 * (2 * wi) + cl][row] = (uint16_t)pb[0][wi];
-                sh->vt[buf][64 + 8 * (2 * wi + 1) + cl][row] = (uint16_t)(pb[0][wi] >> 16);
-            }
+            uint32_t pa[4], pb[4];
+            assemble8_fill(X.hi[gr].x, X.hi[gr].y, X.mid[gr].x, X.lo[gr].x, X.fill[gr], pa);
+            assemble8_fill(X.hi[gr].z, X.hi[gr].w, X.mid[gr].y, X.lo[gr].y, X.fill[gr], pb);
+            u32x4_t* row = sh->vr[buf][wave * RB + gr * 8 + r];
+            row[cl ^ (r << 1)] = u32x4_t{pa[0], pa[1], pa[2], pa[3]};
+            row[(8 + cl) ^ (r << 1)] = u32x4_t{pb[0], pb[1], pb[2], pb[3]};
         }
         if (jlane) {
             const float ws = X.pj * kVWeightScale;
             const _Float16 whi = (_Float16)ws;
             const _Float16 wlo = (_Float16)(ws - (float)whi);
-            const int wrow = wave * RB + KG * (jrow & 7) + (jrow >> 3);
+            const int wrow = wave * RB + jrow;
             sh->pt[buf][jg][wrow] = __builtin_bit_cast(uint16_t, whi);
             sh->pt[buf][G + jg][wrow] = __builtin_bit_cast(uint16_t, wlo);
         }
@@ -331,20 +319,28 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     f32x4_t d0 = {0.0f, 0.0f, 0.0f, 0.0f}, d1 = {0.0f, 0.0f, 0.0f, 0.0f};   // the wave's two result tiles
     auto Fs = [&](int bt) {
         const int buf = bt & 1;
-        const int n = lane & 15, kq = 4 * (lane >> 4);
+        const int n = lane & 15, kq = lane >> 4;
 #pragma unroll
-        for (int kb = 0; kb < (kVWaves * RB) / 16; ++kb) {
-            const half4_t w4 = *reinterpret_cast<const half4_t*>(&sh->pt[buf][n][kb * 16 + kq]);
-            const half4_t v0 = *reinterpret_cast<const half4_t*>(&sh->vt[buf][32 * wave + n][kb * 16 + kq]);
-            const half4_t v1 = *reinterpret_cast<const half4_t*>(&sh->vt[buf][32 * wave + 16 + n][kb * 16 + kq]);
-            d0 = __builtin_amdgcn_mfma_f32_16x16x16f16(w4, v0, d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_16x16x16f16(w4, v1, d1, 0, 0, 0);
+        for (int kb = 0; kb < (kVWaves * RB) / 32; ++kb) {   // 32 rows: a lane's k are rows 8 kq .. 8 kq + 7
+            const half8_t w8 = *reinterpret_cast<const half8_t*>(&sh->pt[buf][n][kb * 32 + 8 * kq]);
+            short4_t v[2][2];   // [tile][rows 0..3, 4..7 of the lane's eight]
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {   // lane n of sixteen reads four values of row n / 4 and receives value n of all four rows
+                    const int row = kb * 32 + 8 * kq + 4 * e + (n >> 2), word = 4 * wave + 2 * t + ((n >> 1) & 1);
+                    typedef __attribute__((address_space(3))) short4_t* lds_ptr;
+                    v[t][e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(reinterpret_cast<short4_t*>(&sh->vr[buf][row][word ^ ((row & 7) << 1)]) + (n & 1)));
+                }
+            d0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[0][0], v[0][1], 0, 1, 2, 3, 4, 5, 6, 7)), d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[1][0], v[1][1], 0, 1, 2, 3, 4, 5, 6, 7)), d1, 0, 0, 0);
         }
     };
     if constexpr (SHARED && 2 * G < 16) {   // the rows of W no head uses stay zero in both buffers (ordered before the first read by the first barrier)
-        for (int idx = threadIdx.x; idx < 2 * (16 - 2 * G) * VShare<G, RB>::kStride; idx += 64 * kVWaves) {
-            const int bf = idx / ((16 - 2 * G) * VShare<G, RB>::kStride), rest = idx % ((16 - 2 * G) * VShare<G, RB>::kStride);
-            sh->pt[bf][2 * G + rest / VShare<G, RB>::kStride][rest % VShare<G, RB>::kStride] = 0;
+        constexpr int kRows = VShare<G, RB>::kRows;
+        for (int idx = threadIdx.x; idx < 2 * (16 - 2 * G) * kRows; idx += 64 * kVWaves) {
+            const int bf = idx / ((16 - 2 * G) * kRows), rest = idx % ((16 - 2 * G) * kRows);
+            sh->pt[bf][2 * G + rest / kRows][rest % kRows] = 0;
         }
     }
 
