@@ -294,7 +294,10 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         // its unit): below three waves per compute unit (8 pairs of four heads: 36.2 -> 32.0 us at 2048 tokens, 40.8 -> 36.0 at
         // 8192; 32 single heads at 4096: 31.0 -> 28.4; from 8 waves per unit on whole blocks are 1-5 % faster, in between equal)
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
-        a.kunit = waves < 3L * cus ? akv::kMinUnit : akv::kTB;
+        a.kunit = waves < 3L * cus && G < 8 ? akv::kMinUnit : akv::kTB;
+        // groups of eight heads: two waves per block instead, four heads each, below six waves per unit (24 pairs: 73.3 -> 69.5
+        // us at 13000 tokens, 56.7 -> 55.7 at 8000; 8 pairs 4096: 40.7 (half blocks) -> 39.4; 32 pairs 16384, 8 per unit: 89.9 -> 92.1)
+        a.khs = G == 8 && waves < 6L * cus ? 2 : 1;
     }
     char* ws = static_cast<char*>(workspace);
     a.logits = reinterpret_cast<float*>(ws + w.logits);

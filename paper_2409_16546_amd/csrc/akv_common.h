@@ -92,6 +92,7 @@ struct DecodeArgs {
     float* partO;
     float* partZ;
     int kunit;           // tokens per wave of the K kernel of the token-split path: kTB or kMinUnit
+    int khs;             // waves per unit there, each for its share of the query heads: 1 or 2
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
     int vslots;          // chunks per (sequence, KV head) in partO and partZ
     int32_t* kcount;     // [B][Hkv] spare control words (kept zero; the selection runs in a kernel of its own)

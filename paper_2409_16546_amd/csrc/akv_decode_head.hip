@@ -107,8 +107,8 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     // the block the new token goes into is read without the non-temporal hint: its lines stay in L2 for the stores
     const int keep_blk = appended ? len_old / kTB : -1;
     if (pre_any) {
-        if (blk / kPerBlk == keep_blk) k_tile_pre<false, TPL>(a, b, h, blk, kpre);
-        else k_tile_pre<true, TPL>(a, b, h, blk, kpre);
+        if (blk / kPerBlk == keep_blk) k_tile_pre<false, TPL>(a, b, h, blk, len_k, kpre);
+        else k_tile_pre<true, TPL>(a, b, h, blk, len_k, kpre);
     }
     const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, true, k_new_bits, lin, len);
     float wm[G];
@@ -126,17 +126,18 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
 #pragma unroll
         for (int i = 0; i < TPL; ++i) own[g][i] = 0.0f;
     uint8_t* stage = &kstage[wave_u][0];
+    const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
     if (pre_any) {   // the block whose first HI bytes are already in flight
         float tm[G];
-        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
-        else k_tile<G, true, TPL>(a, b, h, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
+        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, hq0, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
+        else k_tile<G, true, TPL>(a, b, h, hq0, blk, len_k, ks, tm, kpre, true, own, stage, lds_lg, lds_tokens);
         blk += 1;
         fold(tm);
     }
     while (blk < blk_end) {
         float tm[G], later[G][TPL];
-        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
-        else k_tile<G, true, TPL>(a, b, h, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
+        if (blk / kPerBlk == keep_blk) k_tile<G, false, TPL>(a, b, h, hq0, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
+        else k_tile<G, true, TPL>(a, b, h, hq0, blk, len_k, ks, tm, kpre, false, later, stage, lds_lg, lds_tokens);
         blk += 1;
         fold(tm);
     }

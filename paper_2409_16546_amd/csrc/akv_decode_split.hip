@@ -12,34 +12,37 @@
 
 namespace akv {
 
-// K kernel: workgroup = kKWaves waves = kKWaves units of 64*TPL tokens (k_tile) of one (sequence, KV head); a wave walks one
-// unit and leaves its logits and the unit's maximum in the workspace.
-template <int G, int TPL>
+// K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one unit of 64*TPL tokens (k_tile) for G / HS
+// of the query heads and leaves its logits and the unit's maxima in the workspace.  HS = 2: neighbouring waves take the same
+// unit for half of the heads each (its bytes come from the caches the second time): a group of eight heads is bound by its
+// multiply-adds, and where a call has fewer units than SIMDs a second wave per unit halves them.
+template <int G, int TPL, int HS>
 __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 {
     __shared__ __align__(16) uint8_t kstage[kKWaves][kKStage];
     __shared__ KShared<G> ks;
-    constexpr int kUnit = 64 * TPL;
+    constexpr int kUnit = 64 * TPL, kUnits = kKWaves / HS, GW = G / HS;   // units per workgroup, heads per wave
 
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63;
     const int Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int unit = blockIdx.x * kKWaves + wave_u;
-    if (blockIdx.x * kKWaves * kUnit >= len) return;   // whole workgroup beyond the sequence (uniform)
+    const int unit = blockIdx.x * kUnits + wave_u / HS;
+    if (blockIdx.x * kUnits * kUnit >= len) return;   // whole workgroup beyond the sequence (uniform)
 
     if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
     k_levels<G>(a, b, h, ks, blockIdx.x == 0, len);
     if (unit * kUnit < len) {                    // else this wave's unit is beyond the sequence
-        float tm[G];
+        float tm[GW];
         const u32x4_t zero4 = {0u, 0u, 0u, 0u};
         const u32x4_t none[6] = {zero4, zero4, zero4, zero4, zero4, zero4};
-        float lg[G][TPL];
-        k_tile<G, true, TPL>(a, b, h, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
+        float lg[GW][TPL];
+        const size_t hq0 = size_t(b) * Hq + size_t(h) * G + (wave_u % HS) * GW;
+        k_tile<GW, HS == 1, TPL>(a, b, h, hq0, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
         if (lane == 0)
 #pragma unroll
-            for (int g = 0; g < G; ++g) a.tilemax[(size_t(b) * Hq + size_t(h) * G + g) * (Ncap / kMinUnit) + unit] = tm[g];
+            for (int g = 0; g < GW; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + unit] = tm[g];
     }
 }
 
@@ -354,10 +357,11 @@ int split_v_workgroups_per_cu(int G)
 template <int G>
 static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event)
 {
-    const int tile = a.kunit * kKWaves;   // tokens per workgroup of the K kernel
+    const int tile = a.kunit * kKWaves / a.khs;   // tokens per workgroup of the K kernel
     const dim3 kgrid((a.max_len + tile - 1) / tile, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
-    if (a.kunit == kMinUnit) hipLaunchKernelGGL((split_k_kernel<G, 2>), kgrid, kblock, 0, st, a);
-    else hipLaunchKernelGGL((split_k_kernel<G, 4>), kgrid, kblock, 0, st, a);
+    // groups of eight take two waves per block where the others take half blocks
+    if (G == 8 ? a.khs == 2 : a.kunit == kMinUnit) hipLaunchKernelGGL((split_k_kernel<G, G == 8 ? 4 : 2, G == 8 ? 2 : 1>), kgrid, kblock, 0, st, a);
+    else hipLaunchKernelGGL((split_k_kernel<G, 4, 1>), kgrid, kblock, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;

@@ -163,26 +163,27 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 constexpr int kKStage = 4096;     // bytes of LDS staging per wave
 
 // Byte offset (inside a block's HI plane) of the 16-byte piece this lane fetches of the first half of a group that starts at
-// column 0; the second half lies kHiHalf<TPL> further, column d0 starts at d0 * 256.
+// column 0; the second half lies kHiHalf<TPL> further, column d0 starts at d0 * 256.  A piece whose tokens all lie at or
+// past len is out of range: nothing of it is fetched (8193 tokens: 3 % of the bytes).
 template <int TPL>
-__device__ __forceinline__ uint32_t k_hi_lane_offset(int unit)
+__device__ __forceinline__ uint32_t k_hi_lane_offset(int unit, int len)
 {
-    const uint32_t lane = threadIdx.x & 63, sub = uint32_t(unit) % (4 / TPL);
-    return (lane / (4 * TPL)) * kTB + sub * (64 * TPL) + (lane % (4 * TPL)) * 16;
+    const uint32_t lane = threadIdx.x & 63, sub = uint32_t(unit) % (4 / TPL), t = (lane % (4 * TPL)) * 16;
+    return unit * (64 * TPL) + int(t) < len ? (lane / (4 * TPL)) * kTB + sub * (64 * TPL) + t : kSkip;
 }
 template <int TPL> constexpr uint32_t kHiHalf = (16 / TPL) * kTB;
 
 // HI bytes of the first three groups of a unit, issued before the levels are known (they are always read):
 // pre[] is handed to k_tile (use_pre = true) for the same unit.
 template <bool NT = true, int TPL = 4>
-__device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, int unit, u32x4_t (&pre)[6])
+__device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, int unit, int len, u32x4_t (&pre)[6])
 {
     const size_t bh = size_t(b) * a.s.Hkv + h;
     const __amdgpu_buffer_rsrc_t rh = make_rsrc(a.k_hi + (bh * a.s.Ncap + size_t(unit / (4 / TPL)) * kTB) * kD, uint32_t(kTB) * kD);
-    const uint32_t off = k_hi_lane_offset<TPL>(unit);
+    const uint32_t off = k_hi_lane_offset<TPL>(unit, len);
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-        const uint32_t at = off + i * kHiHalf<TPL>;
+        const uint32_t at = off + i * kHiHalf<TPL>;   // past the end of the buffer (nothing is fetched) if off is kSkip
         pre[i] = NT ? buf_load_b128_nt(rh, at) : buf_load_b128(rh, at);
     }
 }
@@ -192,8 +193,9 @@ __device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, in
 // lds_lg: where a kernel keeps the logits of its (sequence, KV head) in LDS (query head g at lds_lg + g * lds_stride
 // floats, token t at index t), or NULL: they go to a.logits.  With LDS logits a.logits is written as well only if it
 // is the caller's export buffer (a.dbg.logits).
-template <int G, bool NT = true, int TPL = 4>
-__device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int unit, int len, const KShared<G>& ks,
+// hq0: first of the G consecutive query heads whose logits are computed (all heads of the group, or part of it).
+template <int G, bool NT = true, int TPL = 4, typename KS>
+__device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t hq0, int unit, int len, const KS& ks,
                                        float (&tile_max)[G], const u32x4_t (&pre)[6], bool use_pre,
                                        float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0)
 {
@@ -202,7 +204,7 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int un
     constexpr int kUnit = 64 * TPL;   // tokens of the unit
     constexpr int kAux = NT ? kAuxNt : 0;
     const int lane = threadIdx.x & 63;
-    const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
+    const int Hkv = a.s.Hkv, Ncap = a.s.Ncap;
     const size_t bh = size_t(b) * Hkv + h;
     unit = __builtin_amdgcn_readfirstlane(unit);   // wave-uniform by contract: scalar addressing
     const int blk = unit / (4 / TPL), sub = unit % (4 / TPL);
@@ -225,10 +227,11 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int un
     // q of the group as fp16 pairs: uniform addresses in constant memory space, scalar loads
     const uint32_t __attribute__((address_space(4)))* qw[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) qw[g] = (const uint32_t __attribute__((address_space(4)))*)(uintptr_t)(a.q + (size_t(b) * Hq + size_t(h) * G + g) * kD);
+    for (int g = 0; g < G; ++g) qw[g] = (const uint32_t __attribute__((address_space(4)))*)(uintptr_t)(a.q + (hq0 + g) * kD);
     const uint32_t voff = uint32_t(lane) * 16;
-    const uint32_t hoff = k_hi_lane_offset<TPL>(unit);
+    const uint32_t hoff = k_hi_lane_offset<TPL>(unit, len);
     const uint32_t col = uint32_t(lane) / (2 * TPL);   // the column of the group this lane fetches nibbles of (32 tokens of it)
+    const bool nib_in = unit * kUnit + int(uint32_t(lane) % (2 * TPL)) * 32 < len;   // some of the lane's 32 tokens are inside the sequence
     const uint32_t noff = col * (kTB / 2) + uint32_t(sub) * (kUnit / 2) + (uint32_t(lane) % (2 * TPL)) * 16;
 
     struct Group {
@@ -246,8 +249,8 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int un
         const uint32_t size = d0 < kD ? uint32_t(kTB) * (kD / 2) : 0u;
         const __amdgpu_buffer_rsrc_t rm = make_rsrc(mid_blk, size), rl = make_rsrc(lo_blk, size);
         const uint32_t base = noff + uint32_t(d0 < kD ? d0 : 0) * (kTB / 2);
-        gr.m = __builtin_amdgcn_raw_buffer_load_b128(rm, ((bm >> col) & 1u) ? base : kSkip, 0, kAux);
-        gr.l = __builtin_amdgcn_raw_buffer_load_b128(rl, ((bl >> col) & 1u) ? base : kSkip, 0, kAux);
+        gr.m = __builtin_amdgcn_raw_buffer_load_b128(rm, nib_in && ((bm >> col) & 1u) ? base : kSkip, 0, kAux);
+        gr.l = __builtin_amdgcn_raw_buffer_load_b128(rl, nib_in && ((bl >> col) & 1u) ? base : kSkip, 0, kAux);
     };
     auto issue = [&](Group& gr, int d0) {
         issue_hi(gr, d0);
@@ -335,7 +338,7 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, int un
     const int t0 = unit * kUnit + lane * TPL;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
+        const size_t hq = hq0 + g;
         const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
         typedef std::conditional_t<TPL == 4, u32x4_t, u32x2_t> vec_t;
         vec_t w;

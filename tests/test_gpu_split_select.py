@@ -62,7 +62,8 @@ def test_token_split_with_whole_blocks_per_wave(T, G):
 
 @pytest.mark.parametrize("G,lens", [(1, [1024, 129]), (2, [2048, 127]), (4, [4100, 128]), (8, [700, 385])])
 def test_token_split_with_half_blocks_and_short_chunks(T, G, lens):
-    """Few pairs of short sequences: half a block per wave of the K kernel (lengths around 128), chunks of the V kernel below
+    """Few pairs of short sequences: half a block per wave of the K kernel (lengths around 128; groups of eight: two waves per
+    block, four heads each), chunks of the V kernel below
     512 tokens (128, 128, 320 and 128 of them)."""
     from paper_2409_16546_amd import workloads
     print(f"token-split path, half blocks: G{G} lens {lens}", flush=True)
