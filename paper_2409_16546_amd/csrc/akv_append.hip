@@ -55,8 +55,7 @@ __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t
 //      bytes that are there: no other workgroup writes that block.
 // K_colmax: two channels at a time by compare-and-swap on their word, at the very end, when nothing of the workgroup waits for
 // it (all blocks of a head meet there: per channel and between the halves it had cost a third of the launch).  The length
-// moves in a launch of its own behind this one: every workgroup reads the old one, and a ticket per workgroup on one cache
-// line costs more than the launch.  Plain loads and non-temporal stores measured best of the four combinations.
+// moves in a launch of its own behind this one (every workgroup reads the old one), or by ticket where the workgroups are few.  Plain loads and non-temporal stores measured best of the four combinations.
 // B 16, 32 heads, 8192 tokens (2.1 GB in, 2.1 GB out): 1510 -> 800 us, 5.4 TB/s (a plain copy reaches 4.9); chunks of up to 777
 // tokens onto 6 x 8 heads: 155 -> 17 us (partly covered blocks used to be walked token by token).
 constexpr int kHalf = kD / 2;   // channels per turn
@@ -112,7 +111,7 @@ __device__ __forceinline__ void store_piece(uint8_t* dst, u32x4_t v, int t, int 
 
 __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const uint16_t* __restrict__ k_new,
                                                            const uint16_t* __restrict__ v_new,
-                                                           const int32_t* __restrict__ n_new, int n)
+                                                           const int32_t* __restrict__ n_new, int n, int ticketed)
 {
     __shared__ u32x4_t hi_s[kHalf][kTB / 16], mid_s[kHalf][kTB / 32], lo_s[kHalf][kTB / 32];
     __shared__ uint32_t max_s[4][kD / 2];
@@ -121,10 +120,23 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
     const int len = c.lens[b];
     int cnt = n_new ? n_new[b] : n;
     cnt = cnt < 0 ? 0 : (cnt > n ? n : cnt);
-    if (cnt == 0 || len + cnt > Ncap) return;   // nothing to do, or the sequence is left unchanged
+    if (cnt == 0) return;
+    if (len + cnt > Ncap) {                     // the sequence is left unchanged
+        if (ticketed && blockIdx.x == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
+        return;
+    }
     const int blk = len / kTB + (blockIdx.x >> 1);
     const int t_lo = max(len, blk * kTB), t_hi = min(len + cnt, (blk + 1) * kTB);   // tokens of this block: [t_lo, t_hi)
     if (t_lo >= t_hi) return;
+    // ticketed: drawn as soon as the length has been read (the test keeps the atomic behind that read), looked at on leaving
+    int ticket = -1;
+    if (ticketed && tid == 0 && len >= 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
+    auto leave = [&] {
+        if (ticket == 2 * ((len % kTB + cnt + kTB - 1) / kTB) * Hkv - 1) {   // the last of the sequence's workgroups to have read the length
+            c.flags[AKV_NFLAGS + b] = 0;
+            c.lens[b] = len + cnt;
+        }
+    };
     const size_t bh = size_t(b) * Hkv + h;
     const bool is_v = blockIdx.x & 1;
     // row i of the input is token len + i; rows outside the range are asked for out of range and read as zeros
@@ -164,6 +176,7 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
                 __builtin_nontemporal_store(lo, reinterpret_cast<u32x2_t*>(c.v_lo + row * (kD / 2) + cl * 8));
             }
         }
+        leave();
         return;
     }
 
@@ -226,6 +239,7 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
     }
     if (tid < kD / 2)   // last, when nothing of this workgroup waits for it any more
         colmax_update(reinterpret_cast<uint32_t*>(c.colmax + bh * kD) + tid, max_halves(max_halves(max_s[0][tid], max_s[1][tid]), max_halves(max_s[2][tid], max_s[3][tid])));
+    leave();
 }
 
 // behind the bulk append: the lengths move, refusals are counted
@@ -250,7 +264,12 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
     if (n < 16 && long(c.shape.B) * c.shape.Hkv * n < 3072) {
         hipLaunchKernelGGL(append_kernel, dim3(c.shape.Hkv, c.shape.B), dim3(128), 0, st, c, k_new, v_new, n_new, n);
     } else {        // n tokens touch at most (n + 254) / 256 + 1 blocks
-        hipLaunchKernelGGL(append_block_kernel, dim3(2 * ((n + kTB - 2) / kTB + 1), c.shape.Hkv, c.shape.B), dim3(256), 0, st, c, k_new, v_new, n_new, n);
+        const dim3 grid(2 * ((n + kTB - 2) / kTB + 1), c.shape.Hkv, c.shape.B);
+        // few workgroups move the length by ticket: a launch less (80 workgroups: 15.2 -> 12.6 us, 320: 15.0 -> 12.2), but tickets
+        // on one cache line cost more than the launch where they are many (480: 16.7 -> 18.0, 768: 20.3 -> 24.9)
+        const bool ticketed = long(grid.x) * grid.y * grid.z <= 384;
+        hipLaunchKernelGGL(append_block_kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0);
+        if (ticketed) return hipGetLastError();
         if (hipError_t e = hipGetLastError()) return e;
         hipLaunchKernelGGL(append_lens_kernel, dim3(1), dim3(256), 0, st, c, n_new, n);
     }

@@ -65,18 +65,25 @@ def test_append_blocks_match_oracle_and_leave_the_rest(T, n, lens, counts):
     assert torch.equal(k1.view(torch.int16), ku.view(torch.int16)) and torch.equal(v1.view(torch.int16), vu.view(torch.int16))
 
 
-def test_append_of_few_tokens_for_many_heads(T):
-    """Enough (sequence, head) pairs that four tokens already go block by block."""
+@pytest.mark.parametrize("B,Hkv,n", [(32, 32, 4), (4, 32, 60)])
+def test_append_of_few_tokens_for_many_heads(T, B, Hkv, n):
+    """Enough (sequence, head) pairs that four tokens already go block by block; enough workgroups that the lengths move in a launch
+    of their own (the cases above draw tickets), with a refused sequence."""
     from oracle import akv_oracle as O
     from paper_2409_16546_amd import binding as A, workloads
-    B, Hkv, Ncap, n = 32, 32, 256, 4
+    Ncap = 256
     print(f"append blocks: {B * Hkv} pairs, {n} tokens", flush=True)
     k, v = workloads.edge_patterns(B, Hkv, 2 * n + 3, seed=9)
     lens = [i % 8 for i in range(B)]
-    oc = T.oracle_cache(k[:, :, :7], v[:, :, :7], lens, Ncap)
-    gc = T.gpu_cache(k[:, :, :7], v[:, :, :7], lens, Hkv, Ncap)
-    kn, vn = k[:, :, 7:7 + n].contiguous(), v[:, :, 7:7 + n].contiguous()
-    assert O.append(oc, T.bits(kn), T.bits(vn), np.array([n] * B, np.int32)) == 0
+    if n == 60:
+        k, v = workloads.edge_patterns(B, Hkv, 200 + n, seed=9)
+        lens = [0, 7, 196, 200]                      # 196 + 60 fills the capacity, 200 + 60 is refused
+    m = max(lens)
+    oc = T.oracle_cache(k[:, :, :m], v[:, :, :m], lens, Ncap)
+    gc = T.gpu_cache(k[:, :, :m], v[:, :, :m], lens, Hkv, Ncap)
+    kn, vn = k[:, :, m:m + n].contiguous(), v[:, :, m:m + n].contiguous()
+    refused = O.append(oc, T.bits(kn), T.bits(vn), np.array([n] * B, np.int32))
     A.akv_append(gc, kn.to(DEV), vn.to(DEV))
     torch.cuda.synchronize()
     T.assert_cache_equal(gc, oc)
+    assert int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == refused == (1 if n == 60 else 0)
