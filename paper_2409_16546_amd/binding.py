@@ -137,7 +137,8 @@ def _check(st: int):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device as a raw handle (no Stream object: that cost 2.5 us of every call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: torch.Tensor | None) -> int | None:
@@ -419,6 +420,8 @@ def akw_gemv(w: Weights, x: torch.Tensor, y: torch.Tensor | None = None, *, guar
     if lvl_out is not None:
         assert lvl_out.dtype == torch.uint8 and lvl_out.numel() == w.K
     ws = w.workspace if workspace is None else workspace
-    s, p = w.struct(), akw_params(guard_bits, force_level, _ptr(lvl_out))
-    _check(lib().akw_gemv(C.byref(s), _ptr(x), B, _ptr(y), C.byref(p), _ptr(ws), ws.numel(), _stream()))
+    p = None   # the library's defaults
+    if guard_bits != 0 or force_level != -1 or lvl_out is not None:
+        p = C.byref(akw_params(guard_bits, force_level, _ptr(lvl_out)))
+    _check(lib().akw_gemv(C.byref(w.struct()), _ptr(x), B, _ptr(y), p, _ptr(ws), ws.numel(), _stream()))
     return y
