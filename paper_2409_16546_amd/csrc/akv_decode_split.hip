@@ -350,7 +350,7 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 // what the register and LDS budgets of split_v_kernel<G> leave room for
 int split_v_workgroups_per_cu(int G)
 {
-    if (G >= kVWaves) return 4;   // shared mode: 104 registers, 39 KB of LDS
+    if (G >= kVWaves) return 4;   // shared mode: 106 registers, 38 KB of LDS
     return G <= 1 ? 4 : (G <= 2 ? 3 : (G <= 4 ? 2 : 1));
 }
 
