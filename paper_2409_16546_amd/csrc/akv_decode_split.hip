@@ -56,14 +56,17 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 //   pass 2  the blocks up to the cut once more (from L2), in order: ballots place the selected tokens.  A block whose best
 //           token is in the cut bucket itself is passed over once enough tokens of that bucket have been seen.
 // Bound by its chain of dependent round trips to memory (maxima, pass 1, pass 2, V rows), about a microsecond each, not by
-// bytes; so a head has a workgroup of its own, with 32 blocks in flight per workgroup of eight waves in each pass.
+// bytes; so a head has a workgroup of its own, with 32 blocks in flight in each pass.
 // Measured on whole calls, against a pass over every logit (1024-token slices, histograms and candidates through memory)
 // followed by one selecting workgroup per KV head: 198 -> 181 us (B 8, 32/8 heads, 32768 tokens), 301 -> 273 us (B 4, 32/8,
 // up to 131072), 101 -> 80 us (B 3, 64/8, up to 13000); no call got slower.
-constexpr int kSelThreads = 512;
-__global__ __launch_bounds__(kSelThreads) void split_select_kernel(DecodeArgs a)
+// NT: 512 threads, or 1024 where every head can have a compute unit to itself and has more than 16 blocks (B 8, 32/8, 32768
+// tokens 173.4 -> 171.6 us a call, B 3, 64/8, up to 13000 69.8 -> 68.9; with 512 heads of 33 blocks 283.3 -> 284.7, with 32 heads
+// of 8 blocks 27.2 -> 28.0).
+template <int NT>
+__global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
 {
-    constexpr int NT = kSelThreads, kWaves = NT / 64, kAhead = 4;   // kAhead: blocks of a wave in flight
+    constexpr int kWaves = NT / 64, kAhead = 32 / kWaves;   // kAhead: blocks of a wave in flight
     __shared__ MidShared ms;
     __shared__ float red_s[kWaves];
 
@@ -365,7 +368,8 @@ static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;
-    hipLaunchKernelGGL(split_select_kernel, dim3(a.s.Hq, a.s.B), dim3(kSelThreads), 0, st, a);
+    if (a.max_len > 16 * kTB && long(a.s.B) * a.s.Hq <= compute_units()) hipLaunchKernelGGL(split_select_kernel<1024>, dim3(a.s.Hq, a.s.B), dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(split_select_kernel<512>, dim3(a.s.Hq, a.s.B), dim3(512), 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (mid_event)
         if (hipError_t e = hipEventRecord(mid_event, st)) return e;

@@ -48,6 +48,23 @@ def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= bound)
 
 
+def test_selection_of_many_heads(T):
+    """More query heads than compute units: the selection runs with 512 threads per head (1024 in the cases above)."""
+    from paper_2409_16546_amd import binding as A, workloads
+    from oracle import akv_oracle as O
+    B, Hkv, lens = 5, 64, [8300, 8192, 1, 4097, 6000]
+    print(f"split selection: {B * Hkv} heads, lens {lens}", flush=True)
+    w = workloads.make(3, B=B, Hq=Hkv, Hkv=Hkv, N=max(lens), seed=91)
+    oc = T.oracle_cache(w.k, w.v, lens, 8448)
+    r = O.decode_attention(oc, T.bits(w.q))
+    gc = T.gpu_cache(w.k, w.v, lens, Hkv, 8448)
+    dbg = A.DebugBuffers.allocate(gc, want_needV=False)
+    dbg.a = None
+    A.akv_decode_attention(gc, w.q.to(DEV), dbg=dbg, path=2)
+    torch.cuda.synchronize()
+    assert np.array_equal(dbg.sel.cpu().numpy(), r.sel) and np.array_equal(dbg.Ehat.cpu().numpy(), r.Ehat)
+
+
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_token_split_with_whole_blocks_per_wave(T, G):
     """Enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks), and more pairs than
