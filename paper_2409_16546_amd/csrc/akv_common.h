@@ -306,7 +306,9 @@ __device__ __forceinline__ float lo_half(uint32_t p) { return (float)__builtin_b
 __device__ __forceinline__ float hi_half(uint32_t p) { return (float)__builtin_bit_cast(half2_t, p).y; }
 
 // Score exponent of a logit ("Quantization of V-Cache": the scores span many orders of magnitude):
-// x = (l - M) * c in two separately rounded fp32 operations, a = max(floor(x), -64).
+// x = (l - M) * c in two separately rounded fp32 operations, a = max(floor(x), -64).  A score that is not a number
+// (infinite or NaN keys: results are unspecified) has a = -64: maxima of logits pass over NaN, so the best score of a
+// block of tokens then still bounds every one of them, and a selection that goes by block maxima stays in range.
 __device__ __forceinline__ float score_x(float l, float M, float c)
 {
     const float diff = l - M;
@@ -315,7 +317,7 @@ __device__ __forceinline__ float score_x(float l, float M, float c)
 __device__ __forceinline__ int score_a(float x)
 {
     const float fl = floorf(x);
-    return fl < (float)kAMin ? kAMin : (int)fl;
+    return fl >= (float)kAMin ? (int)fl : kAMin;
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave in the vector ALU (six data-parallel-primitive steps: shifts by

@@ -48,6 +48,29 @@ def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= bound)
 
 
+@pytest.mark.parametrize("n", [700, 9000])
+def test_selection_stays_in_range_on_infinite_keys(T, n):
+    """One sequence holds infinities in K (its logits are infinite or not numbers: results unspecified), the other does not: the
+    selection of the first still names stored tokens only, the second's result is that of finite data."""
+    from paper_2409_16546_amd import binding as A, workloads
+    print(f"split selection: infinite keys, {n} tokens", flush=True)
+    w = workloads.make(3, B=2, Hq=4, Hkv=2, N=n, seed=5)
+    Ncap = (n + 255) // 256 * 256
+    q = w.q.to(DEV)
+    good = A.akv_decode_attention(T.gpu_cache(w.k, w.v, [n, n], 4, Ncap), q, path=2)
+    k = w.k.clone()
+    k[0, :, ::3, ::5] = float("inf")
+    k[0, :, 1::7, 2] = float("-inf")
+    gc = T.gpu_cache(k, w.v, [n, n], 4, Ncap)
+    dbg = A.DebugBuffers.allocate(gc, want_needV=False)
+    dbg.a = None
+    out = A.akv_decode_attention(gc, q, dbg=dbg, path=2)
+    torch.cuda.synchronize()
+    sel = dbg.sel.cpu().numpy()
+    assert sel.min() >= 0 and sel.max() < n
+    assert torch.equal(out[1], good[1])
+
+
 def test_selection_of_many_heads(T):
     """More query heads than compute units: the selection runs with 512 threads per head (1024 in the cases above)."""
     from paper_2409_16546_amd import binding as A, workloads
