@@ -1,9 +1,12 @@
 // Append tokens into the split-plane cache and its inverse.
 // "Dynamic Quantization": the cache keeps all 16 bits of every element, the first 8 / next 4 / last 4
 // bits in separately contiguous planes; "Quantization of K-Cache": K_colmax is kept while storing.
+#include "akv_append_plan.h"
 #include "akv_common.h"
 
 namespace akv {
+
+static_assert(kPlanTB == kTB, "one block size");
 
 // One workgroup per (sequence, KV head), 128 threads: thread d owns K channel d (so it is the only writer
 // of that column's nibble bytes and of colmax[d]); threads 0..63 own the V nibble byte of channels 2d, 2d+1.
@@ -125,18 +128,26 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
         if (ticketed && blockIdx.x == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
         return;
     }
-    const int blk = len / kTB + (blockIdx.x >> 1);
-    const int t_lo = max(len, blk * kTB), t_hi = min(len + cnt, (blk + 1) * kTB);   // tokens of this block: [t_lo, t_hi)
-    if (t_lo >= t_hi) return;
-    // ticketed: drawn as soon as the length has been read (the test keeps the atomic behind that read), looked at on leaving
+    // ticketed: every workgroup of the sequence draws one once all its waves have read the length (each has taken the branches
+    // above on it, then they meet at the barrier), and looks at it on leaving.  In a sequence that takes nothing or is refused
+    // no length moves and none draws.
     int ticket = -1;
-    if (ticketed && tid == 0 && len >= 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
+    if (ticketed) {
+        __syncthreads();
+        if (tid == 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
+    }
     auto leave = [&] {
-        if (ticket == 2 * ((len % kTB + cnt + kTB - 1) / kTB) * Hkv - 1) {   // the last of the sequence's workgroups to have read the length
+        if (ticket == append_tickets(gridDim.x / 2, Hkv) - 1) {   // the last: every wave of the sequence's workgroups has read the length
             c.flags[AKV_NFLAGS + b] = 0;
             c.lens[b] = len + cnt;
         }
     };
+    const AppendBlock ab = append_block(len, cnt, blockIdx.x >> 1);
+    const int blk = ab.blk, t_lo = ab.t_lo, t_hi = ab.t_hi;   // tokens of this block: [t_lo, t_hi)
+    if (t_lo >= t_hi) {
+        leave();
+        return;
+    }
     const size_t bh = size_t(b) * Hkv + h;
     const bool is_v = blockIdx.x & 1;
     // row i of the input is token len + i; rows outside the range are asked for out of range and read as zeros
@@ -263,11 +274,12 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
     // 14.9/14.6; 512 pairs 4 tokens 27.4/31.2, 8 tokens 50.3/31.5.
     if (n < 16 && long(c.shape.B) * c.shape.Hkv * n < 3072) {
         hipLaunchKernelGGL(append_kernel, dim3(c.shape.Hkv, c.shape.B), dim3(128), 0, st, c, k_new, v_new, n_new, n);
-    } else {        // n tokens touch at most (n + 254) / 256 + 1 blocks
-        const dim3 grid(2 * ((n + kTB - 2) / kTB + 1), c.shape.Hkv, c.shape.B);
-        // few workgroups move the length by ticket: a launch less (80 workgroups: 15.2 -> 12.6 us, 320: 15.0 -> 12.2), but tickets
-        // on one cache line cost more than the launch where they are many (480: 16.7 -> 18.0, 768: 20.3 -> 24.9)
-        const bool ticketed = long(grid.x) * grid.y * grid.z <= 384;
+    } else {
+        const dim3 grid(2 * append_grid_blocks(n), c.shape.Hkv, c.shape.B);
+        // few workgroups move the length by ticket: a launch less, but tickets on one cache line cost more than the launch where they
+        // are many (launch / tickets, us with the copy that sets the lengths: 32 workgroups 12.8/10.0, 128 13.7/11.7, 256 15.3/15.3,
+        // 320 on one sequence 13.4/12.4, 384 17.4/18.7, 480 16.5/19.0, 1024 22.7/31.1)
+        const bool ticketed = long(grid.x) * grid.y * grid.z <= 320;
         hipLaunchKernelGGL(append_block_kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0);
         if (ticketed) return hipGetLastError();
         if (hipError_t e = hipGetLastError()) return e;

@@ -87,3 +87,41 @@ def test_append_of_few_tokens_for_many_heads(T, B, Hkv, n):
     torch.cuda.synchronize()
     T.assert_cache_equal(gc, oc)
     assert int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == refused == (1 if n == 60 else 0)
+
+
+def _append_beside_busy_stream(T, Hkv, B, counts):
+    """Appends of counts[0], counts[1], ... tokens, one after another onto empty sequences, while products on a second stream hold the
+    compute units, so that workgroups of a launch start late and far apart; eight times, each against the oracle's cache."""
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A, workloads
+    n = sum(counts)
+    Ncap = (n + 255) // 256 * 256
+    k, v = workloads.edge_patterns(B, Hkv, n, seed=n)
+    oc = O.Cache.empty(B, Hkv, 128, Ncap)
+    at, parts = 0, []
+    for c in counts:
+        kn, vn = k[:, :, at:at + c].contiguous(), v[:, :, at:at + c].contiguous()
+        assert O.append(oc, T.bits(kn), T.bits(vn)) == 0
+        parts.append((kn.to(DEV), vn.to(DEV)))
+        at += c
+    a = torch.randn(4096, 4096, device=DEV, dtype=torch.float16)
+    y = torch.empty_like(a)
+    side = torch.cuda.Stream()
+    gcs = [A.Cache.allocate(B, Hkv, Hkv, 128, Ncap, DEV) for _ in range(8)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(60):
+            torch.mm(a, a, out=y)
+    for gc in gcs:
+        for kn, vn in parts:
+            A.akv_append(gc, kn, vn)
+    torch.cuda.synchronize()
+    for gc in gcs:
+        T.assert_cache_equal(gc, oc)
+        assert not gc.flags.cpu().numpy().any()
+
+
+def test_block_append_beside_a_busy_stream(T):
+    """The lengths move by ticket (256 workgroups); every launch but the third has workgroups whose block no token falls into."""
+    print("append blocks: 200 tokens and more beside a busy stream", flush=True)
+    _append_beside_busy_stream(T, 32, 2, [200, 40, 250, 16])
