@@ -10,7 +10,7 @@ static_assert(kPlanTB == kTB, "one block size");
 
 // One workgroup per (sequence, KV head), 128 threads: thread d owns K channel d (so it is the only writer
 // of that column's nibble bytes and of colmax[d]); threads 0..63 own the V nibble byte of channels 2d, 2d+1.
-// flags[AKV_NFLAGS + b] counts the workgroups of sequence b that are done (zero between calls).
+// flags[AKV_NFLAGS + b] counts the workgroups of sequence b that have read its length (zero between calls).
 __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t* __restrict__ k_new,
                                                      const uint16_t* __restrict__ v_new,
                                                      const int32_t* __restrict__ n_new, int n)
@@ -20,15 +20,19 @@ __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t
     const int len = c.lens[b];
     int cnt = n_new ? n_new[b] : n;
     cnt = cnt < 0 ? 0 : (cnt > n ? n : cnt);
-    const bool fits = len + cnt <= Ncap;   // else the sequence is left unchanged and the refusal is counted
+    if (len + cnt > Ncap) {   // the sequence is left unchanged and the refusal is counted
+        if (h == 0 && d == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
+        return;
+    }
+    if (cnt == 0) return;
     const size_t bh = size_t(b) * Hkv + h;
-    // The ticket is drawn as soon as this workgroup has read the length (the test keeps the atomic behind that read):
-    // its round trip then runs beside the loads and stores below instead of after them.  Whoever draws the last one
-    // moves the length at its end -- every head of the sequence has read the old one by then, and nothing in this
-    // kernel reads the planes.
+    // The ticket is drawn as soon as both waves of this workgroup have read the length (each has taken the branches above on
+    // it, then they meet at the barrier): its round trip then runs beside the loads and stores below instead of after them.
+    // Whoever draws the last one moves the length at its end -- every wave of the sequence's heads has read the old one by
+    // then, and nothing in this kernel reads the planes.
+    __syncthreads();
     int ticket = -1;
-    if (d == 0 && len >= 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
-    if (fits) {
+    if (d == 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
     const uint16_t* kn = k_new + bh * n * kD;
     const uint16_t* vn = v_new + bh * n * kD;
     uint32_t cm = c.colmax[bh * kD + d];
@@ -38,11 +42,9 @@ __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t
         cm = mag > cm ? mag : cm;
     }
     c.colmax[bh * kD + d] = (uint16_t)cm;
-    }
     if (d == 0 && ticket == Hkv - 1) {
         c.flags[AKV_NFLAGS + b] = 0;
-        if (fits) c.lens[b] = len + cnt;
-        else atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
+        c.lens[b] = len + cnt;
     }
 }
 

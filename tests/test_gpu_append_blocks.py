@@ -125,3 +125,9 @@ def test_block_append_beside_a_busy_stream(T):
     """The lengths move by ticket (256 workgroups); every launch but the third has workgroups whose block no token falls into."""
     print("append blocks: 200 tokens and more beside a busy stream", flush=True)
     _append_beside_busy_stream(T, 32, 2, [200, 40, 250, 16])
+
+
+def test_walking_append_beside_a_busy_stream(T):
+    """A few tokens per call: one workgroup of two waves per head, ticket drawn in front of the stores."""
+    print("append: one to fifteen tokens beside a busy stream", flush=True)
+    _append_beside_busy_stream(T, 8, 3, [1, 2, 15, 1, 1, 8, 3, 1, 15])
