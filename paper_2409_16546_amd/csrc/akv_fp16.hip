@@ -3,6 +3,7 @@
 // K and V of a chunk of tokens are read in one kernel with a softmax of its own (split-KV), since nothing has to be decided
 // between the passes; the chunks are merged by a second small kernel.
 #include <algorithm>
+#include <cfloat>
 
 #include "akv_common.h"
 
@@ -115,7 +116,9 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
         if (n < G) w = *reinterpret_cast<const u32x4_t*>(a.q + (hq0 + n) * kD + kb * 32 + j * 8);
         qf[kb] = __builtin_bit_cast(half8_t, w);
     }
-    float acc[G][8], z = 0.0f, m_run = -INFINITY;   // z, m_run: of query head n (lanes with n < G)
+    // z, m_run: of query head n (lanes with n < G).  The maximum starts at the lowest finite number and not at minus infinity: a
+    // logit of minus infinity (a key that must not be attended) then has weight zero also where a wave has seen no other yet.
+    float acc[G][8], z = 0.0f, m_run = -FLT_MAX;
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll

@@ -34,3 +34,35 @@ def test_fp16_attention_matches_textbook(G, Ncap, lens):
     ref1 = O.fp16_attention(T.bits(w.k), T.bits(w.v), np.minimum(lens, 128), T.bits(w.q))
     got1 = first.cpu().numpy().astype(np.float64)
     assert np.abs(got1 - ref1).max() <= T.MAX_ABS and T.rel_l2(got1, ref1) <= T.REL_L2
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_fp16_minus_infinite_logits_have_weight_zero(G):
+    """Keys of minus infinity (positive queries): the first tiles of a wave, whole shares and chunks, scattered tokens; a sequence of
+    nothing else is not a number, as in the textbook form."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import akv_testlib as T
+    from paper_2409_16546_amd import binding as A
+    print(f"fp16 attention, minus infinity: G{G}", flush=True)
+    g = torch.Generator().manual_seed(G)
+    B, Hkv, N = 3, 2, 1024
+    q = (torch.rand(B, Hkv * G, 128, generator=g) + 0.1).half()
+    k, v = torch.randn(B, Hkv, N, 128, generator=g).half(), torch.randn(B, Hkv, N, 128, generator=g).half()
+    k[0, :, :650] = float("-inf")              # whole chunks, then a share that begins with them
+    k[1, :, 32:64, 5] = float("-inf")
+    k[1, :, 300::7, 9] = float("-inf")
+    k[2] = float("-inf")
+    args = [t.to(DEV) for t in (k, v, torch.tensor([1024, 650, 700], dtype=torch.int32), q)]
+    got = A.akv_fp16_decode_attention(*args).cpu().double()
+    one = A.akv_fp16_decode_attention(*args, max_len=128).cpu().double()   # one chunk per sequence
+    torch.cuda.synchronize()
+    for out, lens in ((got, [1024, 650]), (one, [128, 128])):
+        for b, n in enumerate(lens):
+            kk, vv = (t[b, :, :n].double().repeat_interleave(G, 0) for t in (k, v))
+            ref = torch.softmax((q[b].double()[:, None] * kk).sum(-1) / 128 ** 0.5, -1)[:, None] @ vv
+            if out is one and b == 0:
+                assert torch.isnan(out[b]).all()
+            else:
+                assert (out[b] - ref[:, 0]).abs().max() <= T.MAX_ABS and T.rel_l2(out[b].numpy(), ref[:, 0].numpy()) <= T.REL_L2
+    assert torch.isnan(got[2]).all()
