@@ -203,25 +203,35 @@ void* static_scratch_for_current_device(hipStream_t s)
 // length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
 // that the single launch outweighs idle units; for single query heads also at two nearly full rounds, as long as the logits
 // of a pair fit its LDS (the token-split kernels write theirs to memory, and written bytes cost several times what read
-// bytes cost).  The thresholds are where the two paths crossed when timed on MI355X over 8..512 pairs, 256..8192 tokens and
-// group sizes 1, 2, 4 (head / split, us): single heads 8 pairs 1024 tokens 22.0/22.5, 2048 30.7/23.5; 128 pairs 4096
-// 52.9/51.7, 160 pairs 54.1/61.6; 160 pairs 8192 102/102; 512 pairs 1024 55/52, 4096 135/145.  Groups of two: 128 pairs 2048
-// 39.6/38.6, 192 pairs 41.2/50.5, 4096 71.6/79.1, 8192 141/132.  Groups of four: 64 pairs 256 30.4/25.8, 128 pairs 30.6/32.4;
-// 192 pairs 1024 41.9/44.7, 2048 59.2/58.2; 256 pairs 4096 110/114, 6144 159/158.
+// bytes cost).
+// The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
+// path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step
+// (append and attention in one call) costs it a launch more; the head kernel stores the new token itself.  So the lines lie
+// where the head kernel wins on attention over full sequences, or where it is behind by a few per cent there and ahead by more
+// over sequences a third full and in steps.  Timed on MI355X over 8..512 pairs, bounds 256..8192, group sizes 1, 2, 4 (head /
+// split, us, full and a third):
+//   single heads  8 pairs 1024 22.0/22.5; 64 pairs 2048 36.2/34.6 and 23.4/29.7, step 37.0/39.5; 96 pairs 1536 32.5/33.5 and
+//                 22.7/28.0; 128 pairs 2048 37.7/38.3 and 24.0/33.5; 128 pairs 4096 52.9/51.7, 160 pairs 58.5/69.9; 160 pairs 8192
+//                 102/102; 512 pairs 512 44.4/37.9, 768 49.5/50.5 (step 54.7/60.1), 1536 70.5/78.3, 4096 135/145
+//   groups of 2   128 pairs 2048 39.6/38.6, 192 pairs 41.2/50.5, 4096 71.6/79.1, 8192 141/132
+//   groups of 4   64 pairs 256 32.3/27.4; 128 pairs 512 30.6/32.4; 160 pairs 2048 61.7/57.8 and 43.2/50.2, step 62.7/63.4 and
+//                 46.2/55.6; 192 pairs 1024 43.8/44.7, 2048 62.2/60.1 and 43.7/50.8, step 63.2/67.2; 200 pairs 2048 63.0/66.5; 224 pairs 4096 106/113 and 56/88; 256 pairs 6144 166/165 and 65/104
+// (two rounds: timed up to 8192 tokens, where the head kernel still wins)
 bool head_path_pays(long pairs, int G, int max_len)
 {
     const long cus = compute_units();
-    if (pairs > cus) return G == 1 && pairs <= 2 * cus && double(pairs) / double(2 * cus) >= 0.85 && max_len > 1536 && max_len <= 8192;
+    if (pairs > cus) return G == 1 && pairs <= 2 * cus && double(pairs) / double(2 * cus) >= 0.85 && max_len > 512 && max_len <= 8192;
     const double fill = double(pairs) / double(cus);
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
-    static constexpr Rule g1[] = {{1024, 0.0}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}}, g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},
-                          g4[] = {{512, 0.47}, {1024, 0.65}, {2048, 0.8}, {4096, 0.95}};
+    static constexpr Rule g1[] = {{1024, 0.0}, {2048, 0.2}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
+                          g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},
+                          g4[] = {{512, 0.47}, {2048, 0.6}, {4096, 0.85}, {6144, 0.97}};
     auto pays = [&](const Rule* r, int n) {
         for (int i = 0; i < n; ++i)
             if (max_len <= r[i].len) return fill >= r[i].fill;
         return false;
     };
-    return G == 1 ? pays(g1, 4) : (G == 2 ? pays(g2, 5) : pays(g4, 4));
+    return G == 1 ? pays(g1, 5) : (G == 2 ? pays(g2, 5) : pays(g4, 4));
 }
 
 // decode attention, optionally preceded by the append of one token per sequence (k_new, v_new: [B][Hkv][D])
