@@ -16,13 +16,19 @@ constexpr int kFMinChunk = kFTile * kFWaves;        // tokens per workgroup are 
 // Tokens per workgroup: about twelve workgroups per compute unit over the whole call (three are resident; single heads eight,
 // groups of eight four, with two resident), so that ragged lengths even out, and not fewer than one tile per wave.  Timed with 4 / 8 / 12 / 16
 // / 32 workgroups per unit: B 8, 32/8, up to 16000 ragged 77 / 78 / 61 / 65 / 73 us, B 8, 32/8, 32768 178 / 178 / 176 / 182 / 194;
-// B 8, 64/8, 8192 58 / 66 / 66 / 84 / 84; B 8, 32/32, 4096 89 / 85 / 87 / 89 / 92.  From the shape alone: a bound of the lengths must not change the order of the sums.
-static int f_chunk(const akv_shape& s)
+// B 8, 64/8, 8192 58 / 66 / 66 / 84 / 84; B 8, 32/32, 4096 89 / 85 / 87 / 89 / 92.  By the capacity and not by a bound of the
+// lengths, which then does not change the order of the sums.
+// Except: as many pairs as compute units, and a bound of at most 1024: one workgroup for the whole pair, no merge (chunks / one, us:
+// 256 single heads 512 18.0/13.7, 1024 28.6/24.7, 512 of them 1024 47.5/46.3, a third full 26.0/18.4; 256 groups of four 1024
+// 33.1/26.1; 384 single heads 1024, the one call behind, 37.5/39.1).
+static int f_chunk(const akv_shape& s, int max_len)
 {
     const int G = s.Hq / s.Hkv;
+    const long pairs = long(s.B) * s.Hkv;
+    auto whole = [](long n) { return (n + kFMinChunk - 1) / kFMinChunk * kFMinChunk; };
+    if (pairs >= compute_units() && max_len <= 1024) return (int)whole(max_len);
     const long wgs = (G == 8 ? 4L : (G == 1 ? 8L : 12L)) * compute_units();
-    const long per = long(s.B) * s.Hkv * s.Ncap / wgs;
-    return (int)std::min(1024L, std::max(long(kFMinChunk), (per + kFMinChunk - 1) / kFMinChunk * kFMinChunk));
+    return (int)std::min(1024L, std::max(long(kFMinChunk), whole(pairs * s.Ncap / wgs)));
 }
 
 size_t fp16_workspace_bytes(const akv_shape& s)
@@ -38,6 +44,7 @@ struct F16Args {
     void* out;
     float c;   // scale * log2(e)
     int out_dtype, nsplit, max_len, chunk;   // nsplit: chunks there is room for per query head
+    int turn_shift, turn_mask;               // which chunk a workgroup takes: launch_fp16_g
     float *partO, *partM, *partZ;
 };
 
@@ -79,7 +86,8 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
     __shared__ float red_s[kFWaves][G][kD];
     __shared__ float max_s[kFWaves][G], z_s[kFWaves][G];
 
-    const int h = blockIdx.y, b = blockIdx.z, split = blockIdx.x;
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int split = blockIdx.x ^ (((b * a.s.Hkv + h) >> a.turn_shift) & a.turn_mask);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, j = lane >> 4;   // logits: token n of 16 (then query head n), channels 8j .. 8j+7 of 32; V: row j of 4, channels 8n .. 8n+7
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
@@ -260,9 +268,17 @@ __global__ __launch_bounds__(kD) void fp16_combine_kernel(F16Args a)
 }
 
 template <int G>
-static hipError_t launch_fp16_g(const F16Args& a, hipStream_t st)
+static hipError_t launch_fp16_g(F16Args a, hipStream_t st)
 {
     const dim3 grid((a.max_len + a.chunk - 1) / a.chunk, a.s.Hkv, a.s.B), block(64 * kFWaves);
+    // Workgroups are dealt to the eight XCDs in turn, and inside an XCD to its four shader engines.  Where the chunks of a pair are
+    // a multiple of two, four ... 32, the first chunks of all pairs would fall on 16, 8 ... one of the 32 engines; and where
+    // sequences are shorter than their bound, those are the only ones with work.  So chunks change places inside groups of that
+    // many, by pair: single heads 8 x 32, 8192 tokens of room, 1029 stored 122 -> 53 us; 16 x 32, 1024, 133 stored 27 -> 15.  (Pairs
+    // varying fastest instead: even there, but full sequences 3..17 % slower.)
+    const int two = __builtin_ctz(grid.x | 32u);
+    a.turn_mask = (1 << two) - 1;
+    a.turn_shift = 5 - two;
     if (grid.x == 1) {
         hipLaunchKernelGGL((fp16_kernel<G, true>), grid, block, 0, st, a);
         return hipGetLastError();
@@ -281,7 +297,7 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.c = (float)((double)scale * 1.4426950408889634);
     a.out_dtype = out_dtype;
     a.nsplit = s.Ncap / kFMinChunk;
-    a.chunk = f_chunk(s);
+    a.chunk = f_chunk(s, max_len);
     a.max_len = max_len;
     const size_t bhq = size_t(s.B) * s.Hq;
     char* p = reinterpret_cast<char*>(ws);

@@ -66,3 +66,42 @@ def test_fp16_minus_infinite_logits_have_weight_zero(G):
             else:
                 assert (out[b] - ref[:, 0]).abs().max() <= T.MAX_ABS and T.rel_l2(out[b].numpy(), ref[:, 0].numpy()) <= T.REL_L2
     assert torch.isnan(got[2]).all()
+
+
+@pytest.mark.parametrize("G,B,Hkv,Ncap,lens", [
+    # chunks of 256 tokens, 32 per pair (64 of them for groups of eight: 16 per pair): two tiles per wave; tails inside a share
+    (1, 8, 8, 8192, [8192, 8191, 4100, 257, 225, 33, 0, 6000]),
+    (2, 8, 8, 8192, [8192, 8095, 300, 256, 1, 5000, 7777, 2048]),
+    (4, 8, 8, 8192, [8000, 8192, 161, 97, 3000, 129, 513, 1]),
+    (8, 8, 8, 4096, [4096, 4001, 224, 2049, 1000, 31, 4095, 300]),
+    # as many pairs as compute units: one workgroup takes the whole pair, up to eight tiles per wave
+    (1, 32, 8, 1024, [1024, 1023, 1000, 600, 257, 256, 33, 0] * 4),
+    (2, 32, 8, 768, [768, 767, 500, 385, 193, 192, 191, 1] * 4),
+    (4, 32, 8, 1024, [1024, 993, 900, 513, 255, 129, 97, 2] * 4),
+    (8, 32, 8, 512, [512, 480, 511, 300, 129, 128, 65, 0] * 4),
+    # more chunks (130) than the merge takes at a time
+    (1, 1, 1, 16640, [16640]),
+    (4, 1, 1, 16640, [16500]),
+])
+def test_fp16_walks_of_several_tiles_match_textbook(G, B, Hkv, Ncap, lens):
+    """A wave's maximum rises late in the first sequence (its last tokens hold the largest keys), falls in the second, and wanders in
+    the others: sums are rescaled, left as they are, and merged."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import akv_testlib as T
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A
+    O.build()
+    print(f"fp16 attention, several tiles: G{G} {B}x{Hkv} Ncap {Ncap}", flush=True)
+    g = torch.Generator().manual_seed(100 * G + B)
+    q = torch.randn(B, Hkv * G, 128, generator=g).half()
+    k, v = torch.randn(B, Hkv, Ncap, 128, generator=g).half(), torch.randn(B, Hkv, Ncap, 128, generator=g).half()
+    ramp = torch.linspace(0.05, 2.0, Ncap)[:, None]
+    k[0] *= ramp.half()
+    if B > 1:
+        k[1] *= ramp.flip(0).half()
+    lens = np.asarray(lens, np.int32)
+    got = A.akv_fp16_decode_attention(k.to(DEV), v.to(DEV), torch.from_numpy(lens).to(DEV), q.to(DEV)).cpu().numpy().astype(np.float64)
+    ref = O.fp16_attention(T.bits(k), T.bits(v), lens, T.bits(q))
+    assert np.abs(got - ref).max() <= T.MAX_ABS and T.rel_l2(got, ref) <= T.REL_L2
+    assert not got[lens == 0].any()
