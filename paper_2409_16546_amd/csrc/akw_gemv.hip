@@ -78,7 +78,7 @@ __device__ __forceinline__ uint32_t at_least_smallest_normal(uint32_t w)
 template <int B>
 __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two workgroups per compute unit at least
 {
-    __shared__ float pmax_s[B][kWWaves];
+    __shared__ int pmax_s[B][kWWaves];   // bits of magnitudes: integer order
     __shared__ int lvl_s[kWSlab];
     __shared__ float xs[B == 1 ? kWSlab : 1];
     __shared__ __align__(16) uint16_t xh[4][kWWaves][8][kWGroups];   // B > 1: x of row (group g, row lane r) of a wave, as the matrix instruction takes it
@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
     // ---- Rule 1: largest addend exponent of every activation row, over all K input features (8 per thread and round)
     if (B > 1 && B < 4)   // activation rows that are not there
         for (int i = tid; i < (4 - B) * kWSlab; i += kWThreads) (&xh[B][0][0][0])[i] = 0;
-    // (the exponent of the largest product: one multiply and one maximum per product)
+    // (the exponent of the largest product: one multiply and one maximum per product; a product that is not a number, of an infinite
+    // weight and a zero, counts as larger than all, as its exponent says: the maximum that returns such an operand)
     float pmax[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) pmax[b] = 0.0f;
@@ -136,12 +137,12 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
             const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i)                             // exact products
-                pmax[b] = fmaxf(pmax[b], fmaxf(fabsf(lo_half(xw[i]) * lo_half(rw[i])), fabsf(hi_half(xw[i]) * hi_half(rw[i]))));
+                pmax[b] = __builtin_elementwise_maximum(pmax[b], __builtin_elementwise_maximum(fabsf(lo_half(xw[i]) * lo_half(rw[i])), fabsf(hi_half(xw[i]) * hi_half(rw[i]))));
         }
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-        const float m = wave_max(pmax[b]);
+        const int m = wave_max_int((int)(float_bits(pmax[b]) & 0x7FFFFFFFu));
         if (lane == 0) pmax_s[b][wave] = m;
     }
     __syncthreads();
@@ -149,10 +150,10 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
         int level = 0;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            float pm = pmax_s[b][0];
+            int pm = pmax_s[b][0];
 #pragma unroll
-            for (int w = 1; w < kWWaves; ++w) pm = fmaxf(pm, pmax_s[b][w]);
-            const int em = float_exp_field(pm);
+            for (int w = 1; w < kWWaves; ++w) pm = max(pm, pmax_s[b][w]);
+            const int em = pm >> 23;
             const float xf = half_bits_to_float(x16_row[b]);        // rows at or past K: 0
             const float P = xf * half_bits_to_float(r16_row < 0x0400u ? 0x0400u : r16_row);
             if (P != 0.0f) {

@@ -32,3 +32,32 @@ def test_gemv_edges_match_oracle(K, N, tiny, B):
     assert np.array_equal(lvl.cpu().numpy(), r.lvl)
     # at most 19 + K/512 binary32 additions of a running sum no larger than S_n = sum |x w| (2^-24 of it each): below 1.3e-6
     assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - r.y) <= 1.3e-6 * r.abs_sum)
+
+
+@pytest.mark.parametrize("B", [1, 2, 4])
+def test_gemv_levels_with_infinite_weights_match_oracle(B):
+    """An infinite weight makes its row's products infinite or, where the activation is zero, not a number; either has the largest
+    exponent there is, so that the other rows are read at level 0.  Columns without the infinity stay finite."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import akw_oracle as OW
+    from paper_2409_16546_amd import binding as A
+    OW.build()
+    print(f"gemv infinite weights: B{B}", flush=True)
+    bits = lambda t: np.ascontiguousarray(t.contiguous().view(torch.int16).numpy().view(np.uint16))
+    g = torch.Generator().manual_seed(B)
+    K, N = 1040, 160
+    W, x = torch.randn(K, N, generator=g).half(), torch.randn(B, K, generator=g).half()
+    W[3, 5], W[700, 150] = float("inf"), float("-inf")
+    for zeros in ([3, 700], [3], []):                       # both products are no numbers, one, none
+        x[:, 3], x[:, 700] = 0.5, -0.25
+        x[:, zeros] = 0
+        gw = A.Weights.allocate(K, N, DEV)
+        A.akw_pack(gw, W.to(DEV))
+        lvl = torch.empty(K, dtype=torch.uint8, device=DEV)
+        y = A.akw_gemv(gw, x.to(DEV), lvl_out=lvl).cpu().numpy().astype(np.float64)
+        r = OW.gemv(OW.pack(bits(W)), bits(x))
+        assert np.array_equal(lvl.cpu().numpy(), r.lvl)
+        fin = np.isfinite(r.y)
+        assert np.array_equal(np.isnan(y), np.isnan(r.y)) and np.array_equal(y[~fin & ~np.isnan(r.y)], r.y[~fin & ~np.isnan(r.y)])
+        assert fin.sum() == B * (N - 2) and np.all(np.abs(y - r.y)[fin] <= 1.3e-6 * r.abs_sum[fin])
