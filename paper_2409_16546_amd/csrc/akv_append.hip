@@ -271,10 +271,13 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
                          hipStream_t st)
 {
     if (n == 0) return hipSuccess;
-    // a few tokens: one workgroup per (sequence, KV head) walks them, a round trip to memory each; from there on a block at a
-    // time.  Timed with 1000 tokens stored, walk / block: 8 pairs 8 tokens 12.5/15.0, 31 tokens 22.6/15.0 us; 48 pairs 16 tokens
-    // 14.9/14.6; 512 pairs 4 tokens 27.4/31.2, 8 tokens 50.3/31.5.
-    if (n < 16 && long(c.shape.B) * c.shape.Hkv * n < 3072) {
+    // A few tokens: one workgroup per (sequence, KV head) walks them, a round trip to memory each; from there on a block at a
+    // time, which moves whole 16-byte pieces of every channel for however few tokens.  Timed with 1000 tokens stored, walk / block,
+    // us: 8 pairs 8 tokens 10.2/10.3, 15 13.1/10.5; 128 pairs 16 tokens 15.8/15.9, 256 18.6/19.4, 24 tokens 24.1/19.4; 512 pairs 8
+    // tokens 25.6/30.2, 12 34.0/30.1; 1024 pairs 1 token 19.3/30.6, 4 41.9/50.3, 6 56.5/50.3; 3072 pairs 1 token 47/111, 6
+    // 164/186, 8 207/186; 8192 pairs 1 token 165/278, 6 454/486, 8 622/487.
+    const long pairs = long(c.shape.B) * c.shape.Hkv;
+    if (n <= (pairs >= 3072 ? 6 : 5) || (n <= (pairs < 128 ? 15 : 16) && pairs * n <= 4608)) {
         hipLaunchKernelGGL(append_kernel, dim3(c.shape.Hkv, c.shape.B), dim3(128), 0, st, c, k_new, v_new, n_new, n);
     } else {
         const dim3 grid(2 * append_grid_blocks(n), c.shape.Hkv, c.shape.B);

@@ -65,10 +65,10 @@ def test_append_blocks_match_oracle_and_leave_the_rest(T, n, lens, counts):
     assert torch.equal(k1.view(torch.int16), ku.view(torch.int16)) and torch.equal(v1.view(torch.int16), vu.view(torch.int16))
 
 
-@pytest.mark.parametrize("B,Hkv,n", [(32, 32, 4), (4, 32, 60)])
+@pytest.mark.parametrize("B,Hkv,n", [(32, 32, 4), (32, 32, 6), (4, 32, 60)])
 def test_append_of_few_tokens_for_many_heads(T, B, Hkv, n):
-    """Enough (sequence, head) pairs that four tokens already go block by block; enough workgroups that the lengths move in a launch
-    of their own (the cases above draw tickets), with a refused sequence."""
+    """Enough (sequence, head) pairs that six tokens already go block by block and four do not; enough workgroups that the lengths of a
+    block launch move in a launch of their own (the cases above draw tickets), with a refused sequence."""
     from oracle import akv_oracle as O
     from paper_2409_16546_amd import binding as A, workloads
     Ncap = 256
