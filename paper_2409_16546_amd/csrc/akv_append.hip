@@ -295,29 +295,34 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
 
 // planes -> fp16 [B][Hkv][Ncap][D], the bulk append run backwards (B 8, 32 heads, 4096 tokens: 1466 -> 236 us, 4.5 TB/s; single
 // bytes per lane before): a workgroup of 256 threads per 256-token block of K, and
-// one per block of V.  Bound by memory; K goes through LDS 64 channels at a time (16-byte pieces of the channel-major runs in,
+// VP per block of V.  Bound by memory; K goes through LDS 64 channels at a time (16-byte pieces of the channel-major runs in,
 // rows of 128 bytes out), with the same placement as there.
+// VP: workgroups per block of V.  V alone takes eight of 32 rows, so that a small call has waves enough (2 x 8 heads, 4096 tokens,
+// one / eight / single bytes per lane: 9.7 / 7.5 / 8.2 us; 8 x 32, 4096: 157 / 98 / 176).
+template <int VP>
 __global__ __launch_bounds__(256) void unpack_kernel(akv_cache c, uint16_t* __restrict__ k_out,
                                                      uint16_t* __restrict__ v_out)
 {
     __shared__ u32x4_t hi_s[kHalf][kTB / 16], mid_s[kHalf][kTB / 32], lo_s[kHalf][kTB / 32];
     const int tid = threadIdx.x;
-    const bool both = k_out && v_out;
-    const size_t item = both ? blockIdx.x >> 1 : blockIdx.x;   // (b * Hkv + h) * NB + blk: the token rows item * 256 .. + 255
-    if (both ? blockIdx.x & 1 : v_out != nullptr) {   // thread -> (row tid/8 + 32 i, 16 channels)
+    const bool both = VP == 1 && k_out && v_out;
+    const size_t item = VP > 1 ? blockIdx.x / VP : (both ? blockIdx.x >> 1 : blockIdx.x);   // (b * Hkv + h) * NB + blk: the token rows item * 256 .. + 255
+    if (VP > 1 || (both ? blockIdx.x & 1 : v_out != nullptr)) {   // thread -> (row tid/8 + 32 i of the part, 16 channels)
+        constexpr int kRows = kTB / VP / 32;
         const int cl = tid & 7;
-        u32x4_t hi[8];
-        u32x2_t mid[8], lo[8];
+        const size_t row0 = item * kTB + (blockIdx.x % VP) * (kTB / VP) + (tid >> 3);
+        u32x4_t hi[kRows];
+        u32x2_t mid[kRows], lo[kRows];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const size_t row = item * kTB + (tid >> 3) + 32 * i;
+        for (int i = 0; i < kRows; ++i) {
+            const size_t row = row0 + 32 * i;
             hi[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(c.v_hi + row * kD + cl * 16));
             mid[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(c.v_mid + row * (kD / 2) + cl * 8));
             lo[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(c.v_lo + row * (kD / 2) + cl * 8));
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const size_t row = item * kTB + (tid >> 3) + 32 * i;
+        for (int i = 0; i < kRows; ++i) {
+            const size_t row = row0 + 32 * i;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {   // channels 8e .. 8e + 7 of the slice
                 uint32_t w[4];
@@ -388,8 +393,9 @@ __global__ __launch_bounds__(256) void unpack_kernel(akv_cache c, uint16_t* __re
 
 hipError_t launch_unpack(const akv_cache& c, uint16_t* k_out, uint16_t* v_out, hipStream_t st)
 {
-    const size_t blocks = size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB) * (k_out && v_out ? 2 : 1);
-    hipLaunchKernelGGL(unpack_kernel, dim3((unsigned)blocks), dim3(256), 0, st, c, k_out, v_out);
+    const size_t blocks = size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB);
+    if (k_out) hipLaunchKernelGGL(unpack_kernel<1>, dim3((unsigned)(blocks * (v_out ? 2 : 1))), dim3(256), 0, st, c, k_out, v_out);
+    else hipLaunchKernelGGL(unpack_kernel<8>, dim3((unsigned)(blocks * 8)), dim3(256), 0, st, c, k_out, v_out);
     return hipGetLastError();
 }
 
