@@ -394,10 +394,10 @@ def test_fp16_yardstick_matches_textbook_attention(T, G):
 
 
 @pytest.mark.parametrize("G", [1, 2])
-def test_fp16_yardstick_head_per_workgroup_variant(T, G):
+def test_fp16_yardstick_many_short_sequences(T, G):
     from paper_2409_16546_amd import workloads, binding as A
     from oracle import akv_oracle as O
-    say(f"fp16 yardstick, many heads (one workgroup per head): G={G}, ragged lengths incl. 0 and 1")
+    say(f"fp16 yardstick, 192 pairs of up to 700 tokens: G={G}, ragged lengths incl. 0 and 1")
     B, Hkv, N, Ncap = 24, 8, 700, 768
     w = workloads.make(2, B=B, Hq=Hkv * G, Hkv=Hkv, N=N)
     rng = np.random.default_rng(3)

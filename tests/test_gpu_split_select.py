@@ -90,14 +90,26 @@ def test_selection_of_many_heads(T):
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_token_split_with_whole_blocks_per_wave(T, G):
-    """Enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks), and more pairs than
-    those the V kernel cuts into short chunks; ragged lengths down to one token."""
+    """Groups of one, two and four: enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks);
+    groups of eight still take two waves per block here.  More pairs than those the V kernel cuts into short chunks; ragged lengths
+    down to one token."""
     from paper_2409_16546_amd import workloads
     lens = [2048, 1, 1027, 300]
     print(f"token-split path, whole blocks: G{G} lens {lens}", flush=True)
     w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=2048, seed=500 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
     T.assert_decode_equal(out, dbg, r, lens, G, f"whole blocks G{G}")
+
+
+def test_token_split_with_one_wave_per_block_of_eight_heads(T):
+    """Groups of eight, 128 pairs of 12 blocks: six waves per compute unit, from where on a wave of the K kernel takes a block for all
+    eight heads."""
+    from paper_2409_16546_amd import workloads
+    lens = [3072, 1025, 256, 2817]
+    print(f"token-split path, one wave per block: G8 lens {lens}", flush=True)
+    w = workloads.make(3, B=4, Hq=256, Hkv=32, N=3072, seed=508)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
+    T.assert_decode_equal(out, dbg, r, lens, 8, "one wave per block G8")
 
 
 @pytest.mark.parametrize("G,lens", [(1, [1024, 129]), (2, [2048, 127]), (4, [4100, 128]), (8, [700, 385])])
