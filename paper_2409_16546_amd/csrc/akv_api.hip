@@ -293,8 +293,9 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         long chunk = (a.max_len + per_pair - 1) / per_pair;
         chunk = (chunk + 63) / 64 * 64;                       // whole batches of rows for every wave
         // few pairs of small capacity: chunks down to 128 tokens, at most 16 per pair (the workgroup that combines them pays
-        // for each; by the capacity, so that a bound of the lengths does not change the order of the sums): 36.2 -> 31.9 us
-        // at 2048 tokens, 8 pairs of four heads; with 32 and 64 chunks (4096, 8192 tokens) slower again
+        // for each; this lower limit goes by the capacity, `chunk` by the bound of the lengths, which so may change the order of
+        // the sums where there are more tokens than slots): 36.2 -> 31.9 us at 2048 tokens, 8 pairs of four heads; with 32 and
+        // 64 chunks (4096, 8192 tokens) slower again
         long shortest = akv::kVChunk;
         if (pairs <= akv::kVFewPairs)
             shortest = std::min(shortest, std::max(long(akv::kVMinChunk), ((a.s.Ncap / akv::kVFewChunks + 63) / 64) * 64L));
@@ -316,8 +317,7 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
     a.Ehat = reinterpret_cast<int32_t*>(ws + w.Ehat);
     a.partO = reinterpret_cast<float*>(ws + w.partO);
     a.partZ = reinterpret_cast<float*>(ws + w.partZ);
-    a.kcount = reinterpret_cast<int32_t*>(ws + w.control);
-    a.vcount = a.kcount + size_t(a.s.B) * a.s.Hkv;
+    a.vcount = reinterpret_cast<int32_t*>(ws + w.control) + size_t(a.s.B) * a.s.Hkv;
     a.stats = p.stats;
     if (p.dbg) {
         a.dbg = *p.dbg;

@@ -35,7 +35,7 @@ struct WsLayout {
     size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
     size_t partO;    // float [B][Hq][v_slots][D]
     size_t partZ;    // float [B][Hq][v_slots]
-    size_t control;  // int32 [2][B][Hkv]: a spare word and the arrival counter of the V kernel per (sequence, KV head); zero between calls
+    size_t control;  // int32 [2][B][Hkv]: unused words (they keep the sizes callers have been given), then the arrival counters of the V kernel per (sequence, KV head); zero between calls
     size_t control_bytes;
     size_t total;
 };
@@ -95,8 +95,7 @@ struct DecodeArgs {
     int khs;             // waves per unit there, each for its share of the query heads: 1 or 2
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
     int vslots;          // chunks per (sequence, KV head) in partO and partZ
-    int32_t* kcount;     // [B][Hkv] spare control words (kept zero; the selection runs in a kernel of its own)
-    int32_t* vcount;
+    int32_t* vcount;     // [B][Hkv] arrival counters of the V kernel of the token-split path
     akv_debug dbg;       // device pointers or NULL
     akv_stats* stats;    // device counters the kernels add to, or NULL
 };

@@ -1,7 +1,8 @@
 // Decode attention, head-per-workgroup path: ONE workgroup does everything for one (sequence, KV head) --
 // Rule 1 levels, q.K~ over all tiles, the mid step, Rule 2 + S.V~ over all rows, the final division --
 // so nothing is handed between workgroups and one launch covers the whole step.  Used when there are enough
-// (sequence, KV head) pairs to fill the chip.  Logits live in the workspace (they stay in this XCD's L2).
+// (sequence, KV head) pairs to fill the chip.  Logits stay in LDS where they fit, else they go through the workspace (this
+// XCD's L2).
 // Workgroup L of the launch runs on XCD L % 8; an XCD takes consecutive pairs (4.5 % faster than every eighth pair).
 // Sections "Quantization of K-Cache", "Quantization of V-Cache", "Runtime of AlignedKV".
 #include "akv_common.h"
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
 {
     constexpr int kWaves = NT / 64;
     float* const lds_lg = LDSLG ? head_lds_logits : nullptr;
-    __shared__ KShared<G> ks;
+    __shared__ KSharedNew<G> ks;
     __shared__ MidShared ms;
     __shared__ float wmax_s[G][kWaves];
     __shared__ float red_s[kWaves][G][kD + 1];

@@ -1,6 +1,6 @@
 // Decode attention, token-split path: the tokens of every (sequence, KV head) are spread over many
 // workgroups (long contexts, few heads).  Three kernels:
-//   K kernel          Rule 1 levels + q.K~, one 256-token block per wave;
+//   K kernel          Rule 1 levels + q.K~, a 256-token block per wave, half of one, or a block per two waves;
 //   selection kernel  one workgroup per (sequence, query head): max, approximate top-k, O_est and the result exponents;
 //   V kernel          Rule 2 + S.V~ over chunks of tokens; the workgroup that finishes last combines the chunks.
 // Sections "Quantization of K-Cache", "Quantization of V-Cache", "Runtime of AlignedKV".
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     if (tid == 0) a.M[hq] = M;
 }
 
-// Workgroup = kVWaves waves, one (sequence, KV head, kVChunk-token chunk); wave w takes the batches of rows
+// Workgroup = kVWaves waves, one (sequence, KV head, chunk of a.vchunk tokens); wave w takes the batches of rows
 // w, w + kVWaves, ... of the chunk.  Groups of four or eight query heads run v_rows in its shared mode: every wave
 // fetches and assembles its rows once, the rows pass through LDS, and the sums over rows for all heads of the group
 // are matrix products on the matrix cores.
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     const int r = lane >> 3, cl = lane & 7;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
-    const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of kVChunk chosen at launch
+    const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of 64 chosen at launch
     const int c0 = split * vchunk;
     const size_t bh = size_t(b) * Hkv + h;
     const int nsplit = a.vslots;
@@ -350,12 +350,10 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     if (tid == 0) store_agent(&a.vcount[bh], 0);   // ready for the next call
 }
 
-// what the register and LDS budgets of split_v_kernel<G> leave room for
-int split_v_workgroups_per_cu(int G)
-{
-    if (G >= kVWaves) return 4;   // shared mode: 106 registers, 38 KB of LDS
-    return G <= 1 ? 4 : (G <= 2 ? 3 : (G <= 4 ? 2 : 1));
-}
+// Workgroups of split_v_kernel<G> per compute unit that the chunks are sized for: what the registers leave room for (single heads
+// 117, groups of two 156; groups of four 106 and 38 KB of LDS).  Groups of eight (74 registers, 19.6 KB) have room for five; their
+// chunks are sized for four.
+int split_v_workgroups_per_cu(int G) { return G == 2 ? 3 : 4; }
 
 template <int G>
 static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event)

@@ -12,19 +12,25 @@ namespace akv {
 // LDS of the K side of one (sequence, KV head)
 template <int G>
 struct KShared {
-    float q[G][kD];
+    static constexpr bool kNew = false;
     int emax[2][G];                     // largest addend exponent per query head, of the columns of wave 0 / wave 1
     uint64_t need_mid[2], need_lo[2];   // bit d%64 of word d/64: column d is read at level >= 1 / = 2
-    float knew[kD];                     // fused append: the new token's K row as it will be read at the column levels
-    float new_logit[G];                 // fused append: q . knew, accumulated in channel order
+};
+// ... of a kernel that appends a token itself
+template <int G>
+struct KSharedNew : KShared<G> {
+    static constexpr bool kNew = true;
+    float q[G][kD];
+    float knew[kD];                     // the new token's K row as it will be read at the column levels
+    float new_logit[G];                 // q . knew, accumulated in channel order
 };
 
 // Rule 1 for the 128 columns of (b, h), in two steps so that a caller can put other loads in flight between the
 // issue of the loads here and their first use.  Both are called by every thread of a workgroup of at least 128
-// threads (the second contains barriers); afterwards ks holds q as fp32 and the level masks.
-// k_new_bits: fp16 bits of channel tid of a token that is being appended in the same kernel (fused append),
-// else -1: K_colmax then counts that token, and the token's row, read at the column levels, is left in
-// ks.knew for new_token_logit().
+// threads (the second contains barriers); afterwards ks holds the level masks.
+// k_new_bits: fp16 bits of channel tid of a token that is being appended in the same kernel (fused append; ks is a
+// KSharedNew), else -1: K_colmax then counts that token, and q as fp32 and the token's row, read at the column levels, are
+// left in ks.q and ks.knew for new_token_logit().
 template <int G>
 struct KLevelsIn {
     uint32_t cm;         // K_colmax of channel tid as stored
@@ -48,8 +54,8 @@ __device__ __forceinline__ void k_levels_load(const DecodeArgs& a, int b, int h,
 
 // Returns the K_colmax of channel tid (tid < 128) that the levels used.
 // stat_len: tokens of the sequence the levels apply to (for the counters of akv_stats; used with export_levels).
-template <int G>
-__device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, int h, KShared<G>& ks, bool export_levels,
+template <int G, typename KS>
+__device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, int h, KS& ks, bool export_levels,
                                                     int k_new_bits, const KLevelsIn<G>& in, int stat_len)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -65,7 +71,7 @@ __device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const float qf = half_bits_to_float(in.qbits[g]);
-            ks.q[g][tid] = qf;
+            if constexpr (KS::kNew) ks.q[g][tid] = qf;
             P[g] = qf * cmf;                             // exact: 11-bit x 11-bit significands
             // the maximum over the wave's 64 columns in the vector ALU (LDS atomics of 64 lanes on one address take a
             // cycle per lane of the LDS unit that all workgroups of the compute unit share)
@@ -97,9 +103,11 @@ __device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, 
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->k_elems[1]), n1 * n);
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->k_elems[2]), n2 * n);
         }
-        if (k_new_bits >= 0) {   // "Dynamic Quantization": bits that are not read are filled with 100...
-            const uint32_t kb = uint32_t(k_new_bits);
-            ks.knew[tid] = half_bits_to_float(lv == 2 ? kb : (lv == 1 ? ((kb & 0xFFF0u) | 0x0008u) : ((kb & 0xFF00u) | 0x0080u)));
+        if constexpr (KS::kNew) {
+            if (k_new_bits >= 0) {   // "Dynamic Quantization": bits that are not read are filled with 100...
+                const uint32_t kb = uint32_t(k_new_bits);
+                ks.knew[tid] = half_bits_to_float(lv == 2 ? kb : (lv == 1 ? ((kb & 0xFFF0u) | 0x0008u) : ((kb & 0xFF00u) | 0x0080u)));
+            }
         }
     }
     __syncthreads();
@@ -107,18 +115,17 @@ __device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, 
 }
 
 template <int G>
-__device__ __forceinline__ uint32_t k_levels(const DecodeArgs& a, int b, int h, KShared<G>& ks, bool export_levels,
-                                             int stat_len, int k_new_bits = -1)
+__device__ __forceinline__ void k_levels(const DecodeArgs& a, int b, int h, KShared<G>& ks, bool export_levels, int stat_len)
 {
     KLevelsIn<G> in;
     k_levels_load<G>(a, b, h, in);
-    return k_levels_finish<G>(a, b, h, ks, export_levels, k_new_bits, in, stat_len);
+    k_levels_finish<G>(a, b, h, ks, export_levels, -1, in, stat_len);
 }
 
 // Fused append: the logit of the token that is being appended, from ks.knew, with the same arithmetic as a
 // tile lane (fp32, channels ascending).  One thread per query head of the group.
 template <int G>
-__device__ __forceinline__ float new_token_logit(const KShared<G>& ks, int g)
+__device__ __forceinline__ float new_token_logit(const KSharedNew<G>& ks, int g)
 {
     float acc = 0.0f;
     for (int d0 = 0; d0 < kD; d0 += 16) {   // operands fetched 16 at a time, the additions stay in channel order

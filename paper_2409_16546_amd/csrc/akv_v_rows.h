@@ -84,7 +84,6 @@ __device__ __forceinline__ void v_prefetch_hi(const DecodeArgs& a, int b, int h,
 // stores for two rows, and as many byte permutes, where they were transposed on the way in: B 8, 32/8, 32768 tokens 174.2 ->
 // 173.1 us a call, B 4, 32/8, up to 131072 276.9 -> 273.4).  The words of a row are
 // permuted by its number, so that neither side has bank conflicts.  Two buffers alternate by round.
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
