@@ -128,7 +128,9 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
             j[i] = t0 + i < len ? -score_a(x[i]) : 1000;
         }
     };
-    // ---- pass 1
+    // ---- pass 1.  Bucket Jb is counted in the lanes: where scores are flat nearly all tokens are in it, and LDS atomics of a whole
+    // wave on one address take a cycle per lane (B 1, 32/8, 131072 tokens of equal scores: 214 -> 126 us a call; where scores spread, 0.2 to 0.9 % more).
+    int n_top = 0;
     for (int c0 = b0; c0 < b1; c0 += 64) {
         const int best = best_of(c0);
         uint64_t mask = __ballot(a.dbg.a ? best <= 64 : best <= min(Jb, 63));   // the export wants every token
@@ -144,12 +146,17 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
                 score4(blk[u], w[u], x, j);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    if (j[i] <= min(Jb, 63)) atomicAdd(&ms.cntw[wave][j[i]], 1);
+                    if (j[i] <= Jb) {
+                        if (j[i] == Jb) ++n_top;
+                        else atomicAdd(&ms.cntw[wave][j[i]], 1);
+                    }
                     if (j[i] <= 64 && a.dbg.a) a.dbg.a[hq * Ncap + blk[u] * kTB + lane * 4 + i] = (int8_t)(-j[i]);
                 }
             }
         }
     }
+    n_top = wave_read(wave_scan_add(n_top), 63);
+    if (lane == 0 && Jb < 64) ms.cntw[wave][Jb] = n_top;   // the floor bucket stays uncounted
     __syncthreads();
     // ---- the cut, and the selected tokens of each kind in the waves before this one
     int tot = 0, before = 0;   // bucket `lane`: all waves / the waves before this one

@@ -27,6 +27,7 @@ def T():
     (3, 4, 0.0, [20000, 9001]),         # peaked: the cut lies in the floor bucket, taken by position
     (4, 8, 0.02, [12288, 300]),
     (5, 1, 0.0, [33000, 16384]),
+    (2, 4, 1e-6, [33000, 8200]),        # all but the best token in one bucket
 ])
 def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     from paper_2409_16546_amd import binding as A, workloads
