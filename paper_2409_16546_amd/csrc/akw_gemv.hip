@@ -13,9 +13,9 @@
 // to four by 4x4x4 matrix products (the weights stay where the lanes hold them; four fp16 rows of a column are two byte
 // permutes).  The sums over the 8 row lanes meet in the vector ALU, the waves' sums in LDS, the slabs' sums (K/512 of them) in the workspace: the workgroup that draws
 // the last ticket of a strip adds them in slab order, so the result does not depend on timing.
-// Measured against multiply-adds for every activation row and row sums through lane exchange (1 / 2 / 4 rows, us):
-// 4096x4096 10.7 / 13.2 / 18.9 -> 10.0 / 11.2 / 13.0, 4096x11008 16.8 / 23.1 / 34.1 ->
-// 15.7 / 19.3 / 21.9, 11008x4096 17.8 / 28.5 / 43.5 -> 17.6 / 23.0 / 28.2.
+// Measured against multiply-adds for every activation row and row sums through lane exchange (1 / 2 / 4 rows, us a call, copies of
+// the matrix over 768 MB in turn): 4096x4096 10.9 / 14.0 / 19.6 -> 10.6 / 11.7 / 12.8, 4096x11008 19.0 / 25.8 / 36.5 ->
+// 17.9 / 22.7 / 25.0, 11008x4096 21.2 / 31.2 / 45.1 -> 20.2 / 25.8 / 28.3.
 #include <cstdarg>
 
 #include "../../include/akw.h"
