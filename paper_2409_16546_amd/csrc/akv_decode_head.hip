@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     }
 
     // ---- V side: each wave walks its range of batches of 8*KG rows -------------------------------------
-    VRule vr;
+    VRule<> vr;
     v_rule_setup(ms.ehat, a.guard_bits, a.force_level, vr);
     float Mg[G];
 #pragma unroll

@@ -218,11 +218,12 @@ template <int G, bool DEBUG>
 __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 {
     constexpr bool SHARED = v_shared<G>();
-    constexpr int KG = G >= 8 ? 1 : 2, RB = 8 * KG;         // one lane per (row of the batch, query head): at most 64 / G rows
+    constexpr int KG = 2, RB = 8 * KG;                      // rows of a batch
+    static_assert(RB == kSRows && (kVMinChunk % (RB * kVWaves)) == 0, "a chunk is whole rounds");
     // the combining workgroup: a thread sums four neighbouring outputs over every kSub-th chunk
     constexpr int kCols = G * kD / 4, kSub = 64 * kVWaves / kCols;
     struct Private { union { float red[kVWaves][G][kD]; f32x4_t comb[kSub][kCols]; }; };
-    struct Shared { union { VShare<G, RB> rows; float red[G][kD]; f32x4_t comb[kSub][kCols]; }; };   // the sums are laid down when the last round has been read
+    struct Shared { union { VShare rows; float red[G][kD]; f32x4_t comb[kSub][kCols]; }; };   // the sums are laid down when the last round has been read
     __shared__ __align__(16) std::conditional_t<SHARED, Shared, Private> lds_s;
     __shared__ float z_s[kVWaves][G];
     __shared__ int ehat_s[kD];
@@ -255,29 +256,26 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 #pragma unroll
     for (int g = 0; g < G; ++g) Mg[g] = a.M[size_t(b) * Hq + size_t(h) * G + g];
     __syncthreads();
-    VRule vr;
-    v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
-    float acc[SHARED ? 1 : G][SHARED ? 8 : 16], z[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) z[g] = 0.0f;
-#pragma unroll
-    for (int g = 0; g < (SHARED ? 1 : G); ++g)
-#pragma unroll
-        for (int i = 0; i < (SHARED ? 8 : 16); ++i) acc[g][i] = 0.0f;
     // HI bytes fetched three or four batches ahead in the private mode (few waves per SIMD: each keeps more bytes in
     // flight), two in the shared mode (four waves per SIMD; three and four measured 1.5 % and 3 % slower)
     constexpr int DL = SHARED ? 2 : (G == 2 ? 4 : 3);
-    const u32x4_t none[1][KG] = {};
     if constexpr (SHARED) {
-        v_rows<G, KG, DEBUG, 0, DL, true, true>(a, b, h, c0 + wave * RB, RB * kVWaves, vchunk / (RB * kVWaves), len, vr, Mg, acc, z, none, false, nullptr, 0, &lds_s.rows);
+        VRule<4> vr;
+        v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
+        float acc[8], z[G / 4];
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            for (int o = 1; o < 64; o <<= 1) z[g] += __shfl_xor(z[g], o);
+        for (int s = 0; s < G / 4; ++s) z[s] = 0.0f;
+        v_rows_shared<G, DEBUG, DL>(a, b, h, c0 + wave * RB, vchunk / (RB * kVWaves), len, vr, Mg, acc, z, lds_s.rows);
+#pragma unroll
+        for (int s = 0; s < G / 4; ++s) {   // over the lanes of the same query heads
+            for (int o = 4; o < 64; o <<= 1) z[s] += __shfl_xor(z[s], o);
+            if (lane < 4) z_s[wave][lane + 4 * s] = z[s];
+        }
         // a result tile holds the high parts of the weights in its rows 0 .. G-1 and the low parts in rows G .. 2G-1:
         // lanes 16 * (G / 4) apart hold the two parts of one (query head, line)
         float part[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) part[i] = (acc[0][i] + __shfl(acc[0][i], (lane + 4 * G) & 63)) * (1.0f / kVWeightScale);
+        for (int i = 0; i < 8; ++i) part[i] = (acc[i] + __shfl(acc[i], (lane + 4 * G) & 63)) * (1.0f / kVWeightScale);
         __syncthreads();   // every wave is done with the rows of the last round: the same LDS now takes the sums
         if (lane < 4 * G) {
 #pragma unroll
@@ -286,6 +284,16 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
                 for (int i = 0; i < 4; ++i) lds_s.red[4 * (lane >> 4) + i][line_channel(32 * wave + 16 * t + (lane & 15))] = part[4 * t + i];
         }
     } else {
+        VRule<> vr;
+        v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
+        float acc[G][16], z[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            z[g] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[g][i] = 0.0f;
+        }
+        const u32x4_t none[1][KG] = {};
         v_rows<G, KG, DEBUG, 0, DL, true>(a, b, h, c0 + wave * RB, RB * kVWaves, vchunk / (RB * kVWaves), len, vr, Mg, acc, z, none, false);
         v_reduce_rows<G>(acc, z);
         if (r == 0) {
@@ -294,10 +302,10 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) lds_s.red[wave][g][cl * 16 + i] = acc[g][i];
         }
-    }
-    if (lane == 0) {
+        if (lane == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) z_s[wave][g] = z[g];
+            for (int g = 0; g < G; ++g) z_s[wave][g] = z[g];
+        }
     }
     __syncthreads();
     for (int idx = tid; idx < G * (kD + 1); idx += 64 * kVWaves) {

@@ -16,25 +16,28 @@ namespace akv {
 // only for ev = 0, which adds the row-independent test 1 + max_d w_d + s >= 3 (resp. 7).
 __device__ __forceinline__ uint32_t clamp_byte(int v) { return (uint32_t)(v < 4 ? 4 : (v > 132 ? 132 : v)); }
 
-// Per-lane constants of Rule 2 for the lane's 16 channels (lane -> channel slice 16 * (lane % 8))
+// Per-lane constants of Rule 2 for the lane's 128 / LPR channels (LPR lanes per row: lane -> channel slice lane % LPR)
+template <int LPR = 8>
 struct VRule {
-    uint32_t B[4];
-    int ehat[16];   // only read by the variant that exports per-element needs
+    static constexpr int kWords = 32 / LPR;
+    uint32_t B[kWords];
+    int ehat[4 * kWords];   // only read by the variant that exports per-element needs
     int wmax;       // max over all 128 channels of w_d
     int force;      // -1, or the level every row is read at (then B = 4: no byte ever reaches bit 7)
 };
 
 // ehat: the 128 result exponents of the KV head (global memory or LDS)
-__device__ __forceinline__ void v_rule_setup(const int* ehat, int guard_bits, int force_level, VRule& vr)
+template <int LPR>
+__device__ __forceinline__ void v_rule_setup(const int* ehat, int guard_bits, int force_level, VRule<LPR>& vr)
 {
-    const int cl = threadIdx.x & 7;
+    const int cl = threadIdx.x % LPR;
     int wmax = -100000;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < vr.kWords; ++i) {
         vr.B[i] = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int e = ehat[cl * 16 + i * 4 + k];
+            const int e = ehat[(cl * vr.kWords + i) * 4 + k];
             vr.ehat[i * 4 + k] = e;
             const int w = guard_bits - 5 - e;
             wmax = w > wmax ? w : wmax;
@@ -42,7 +45,7 @@ __device__ __forceinline__ void v_rule_setup(const int* ehat, int guard_bits, in
         }
         if (force_level >= 0) vr.B[i] = 0x04040404u;
     }
-    for (int o = 1; o < 8; o <<= 1) {
+    for (int o = 1; o < LPR; o <<= 1) {
         const int other = __shfl_xor(wmax, o);
         wmax = other > wmax ? other : wmax;
     }
@@ -50,14 +53,42 @@ __device__ __forceinline__ void v_rule_setup(const int* ehat, int guard_bits, in
     vr.force = force_level;
 }
 
-// OR over the 8 lanes of a row (lanes 8r .. 8r+7), result in all of them: two exchanges inside the quads,
-// one with the mirrored lane of the 8-lane half row.
+// OR over the 8 (4) lanes of a row, result in all of them: two exchanges inside the quads, and one with the mirrored lane of
+// the 8-lane half row.
+template <int LPR = 8>
 __device__ __forceinline__ uint32_t or_over_row(uint32_t v)
 {
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);   // row_half_mirror
+    if (LPR == 8) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);   // row_half_mirror
     return v;
+}
+
+// the row-independent tests 1 + max_d w_d + Ahat >= 3 and >= 7 (or the forced level) as bounds of Ahat + 64 in every byte
+template <int LPR>
+__device__ __forceinline__ uint32_t v_bound_word(const VRule<LPR>& vr, int need, int level)
+{
+    const int at = vr.force >= 0 ? (vr.force >= level ? 0 : 127) : min(max(need + 63 - vr.wmax, 0), 127);
+    return (uint32_t)__builtin_amdgcn_readfirstlane(at * 0x01010101);
+}
+// levels >= 1 / = 2 needed by some element of the row, from the lane's words of HI bytes (result in all LPR lanes of the row);
+// ss: Ahat + 64 in every byte
+template <int LPR>
+__device__ __forceinline__ void v_row_needs(const uint32_t (&hw)[32 / LPR], const VRule<LPR>& vr, uint32_t ss, uint32_t row1, uint32_t row2,
+                                            bool& need1, bool& need2)
+{
+    uint32_t any1 = 0, any2 = 0;
+#pragma unroll
+    for (int i = 0; i < 32 / LPR; ++i) {
+        const uint32_t evp = (hw[i] >> 2) & 0x1F1F1F1Fu;
+        const uint32_t S = evp + vr.B[i] + ss;
+        any1 |= S;
+        any2 |= S - 0x04040404u;
+    }
+    // bit 7 of a byte: level >= 1 needed; bit 6: level 2 needed (which implies the former)
+    const uint32_t flags = or_over_row<LPR>((any1 & 0x80808080u) | ((any2 >> 1) & 0x40404040u));
+    need1 = flags != 0 || ss >= row1;
+    need2 = (flags & 0x40404040u) != 0 || ss >= row2;   // ss: the same byte four times
 }
 
 // HI bytes of the first NPRE batches of a wave, issued early by a caller that has idle time before the V side can
@@ -76,32 +107,55 @@ __device__ __forceinline__ void v_prefetch_hi(const DecodeArgs& a, int b, int h,
         for (int gr = 0; gr < KG; ++gr) hi[n][gr] = buf_load_b128(rs_hi, voff + uint32_t(n * batch_stride + gr * 8) * kD);
 }
 
-// LDS of the shared mode of v_rows: the rows all waves of a workgroup assembled in one round, row after row, each as the
-// sixteen 16-byte words its eight lanes hold (word cl: the first eight channels of slice cl, word 8 + cl: the second eight),
-// and the weights of these rows, line g the high part and line G + g the low part of query head g's weight (two fp16
-// numbers whose sum carries 22 bits).  The matrix instruction wants four consecutive rows of one value per lane: the
-// transposing LDS read turns them on the way out, so that a lane lays a row down with two 16-byte stores (sixteen 4-byte
-// stores for two rows, and as many byte permutes, where they were transposed on the way in: B 8, 32/8, 32768 tokens 174.2 ->
-// 173.1 us a call, B 4, 32/8, up to 131072 276.9 -> 273.4).  The words of a row are
-// permuted by its number, so that neither side has bank conflicts.  Two buffers alternate by round.
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-template <int G, int RB> struct VShare {
-    static constexpr int kRows = kVWaves * RB;   // rows of a round
-    alignas(16) u32x4_t vr[2][kRows][16];
-    alignas(16) uint16_t pt[2][16][kRows + 8];
-};
-// the channel of value `line` (0..127) of a row as it lies in VShare::vr: assemble8_fill leaves channels (0,2), (1,3), (4,6),
-// (5,7) of eight in its four words
-__device__ __forceinline__ int line_channel(int line)
+// DEBUG: what a lane has counted for akv_stats (rows at each level; elements in all and those that need levels 1 and 2), added
+// once per wave
+__device__ __forceinline__ void v_add_stats(const DecodeArgs& a, const unsigned (&rows)[3], const unsigned (&need)[3])
 {
-    const int word = line >> 3, pos = line & 7;
-    return 16 * (word & 7) + 8 * (word >> 3) + ((pos >> 1) & 1) + 4 * (pos >> 2) + 2 * (pos & 1);
+    unsigned v6[6] = {rows[0], rows[1], rows[2], need[0] - need[1] - need[2], need[1], need[2]};
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+        for (int o = 1; o < 64; o <<= 1) v6[i] += __shfl_xor(v6[i], o);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->v_row_elems[i]), (unsigned long long)v6[i] * kD);
+            atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->v_need_elems[i]), (unsigned long long)v6[3 + i]);
+        }
+    }
 }
-constexpr float kVWeightScale = 16384.0f;   // weights are at most 1: scaled by 2^14 their fp16 parts reach down to 2^-38
-// workgroup barrier that waits for this wave's LDS traffic only: the loads from memory that are in flight stay in flight
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// DEBUG: the exports of one lane for its W words of HI bytes of row t of (b, h): the level applied, the level each element needs
+template <int W>
+__device__ __forceinline__ void v_export(const DecodeArgs& a, size_t bh, int t, int cl, int applied, int ahat, const uint32_t (&hw)[W],
+                                         const int (&ehat)[4 * W], unsigned (&st_rows)[3], unsigned (&st_need)[3])
+{
+    if (a.dbg.appliedV && cl == 0) a.dbg.appliedV[bh * a.s.Ncap + t] = (uint8_t)applied;
+    if (cl == 0) {
+        st_rows[0] += applied == 0;
+        st_rows[1] += applied == 1;
+        st_rows[2] += applied == 2;
+    }
+    if (!a.dbg.needV && !a.stats) return;
+    uint32_t nv[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        nv[i] = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int ev = (int)((hw[i] >> (8 * k + 2)) & 31u);
+            ev = ev < 1 ? 1 : ev;
+            int need = level_for_mantissa_bits(10 + a.guard_bits - (ehat[i * 4 + k] - (ahat + ev - 15)));
+            if (a.force_level >= 0) need = a.force_level;
+            nv[i] |= (uint32_t)need << (8 * k);
+            st_need[1] += need == 1;
+            st_need[2] += need == 2;
+        }
+    }
+    st_need[0] += 4 * W;
+    if (a.dbg.needV)
+#pragma unroll
+        for (int i = 0; i < W; i += 4)
+            *reinterpret_cast<uint4*>(a.dbg.needV + (bh * a.s.Ncap + t) * kD + (cl * W + i) * 4) = make_uint4(nv[i], nv[i + 1], nv[i + 2], nv[i + 3]);
+}
 
 // One wave walks token rows of (b, h) in batches of 8*KG rows (KG groups of 8 rows; lane -> row lane/8 of the
 // group and the 16-channel slice lane%8): batch i covers rows t_first + i*batch_stride .. + 8*KG - 1,
@@ -123,22 +177,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // NT: the HI bytes are read with the non-temporal hint (measured: it pays in the token-split V kernel, where the logits
 // and the chunk partials of other workgroups share the caches, and costs in the head-per-workgroup kernel); the MID
 // and LO bytes always are (it pays in both).
-// SHARED, sh: the shared mode for groups of query heads (the token-split V kernel).  Every wave of the workgroup still
-// fetches, tests and assembles its own rows, once, but leaves them in LDS with their weights; after a
-// barrier the sum over the rows of the round, for all query heads at once, is a matrix product on the matrix cores:
-// D[m][line] += sum_rows W[m][row] * V[row][line], wave w taking lines 32 w .. 32 w + 31.  acc then holds the wave's two
-// 16x16 result tiles (four words each: rows 4 * (lane / 16) .. + 3 of W, line 16 * (2 w + tile) + lane % 16), scaled by
-// kVWeightScale.  A lane holds 8 sums instead of 16 * G, the multiply-adds leave the vector ALU.  All waves of the
-// workgroup must call with the same nbatches.
-template <int G, int KG, bool DEBUG, int NPRE, int DL = 2, bool NT = false, bool SHARED = false>
+template <int G, int KG, bool DEBUG, int NPRE, int DL = 2, bool NT = false>
 __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_first, int batch_stride, int nbatches,
-                                       int len, const VRule& vr, const float (&Mg)[G], float (&acc)[SHARED ? 1 : G][SHARED ? 8 : 16],
+                                       int len, const VRule<>& vr, const float (&Mg)[G], float (&acc)[G][16],
                                        float (&z)[G], const u32x4_t (&pre)[NPRE > 0 ? NPRE : 1][KG], bool pre_ok,
-                                       const float* lds_lg = nullptr, int lds_stride = 0, VShare<G, 8 * KG>* sh = nullptr)
+                                       const float* lds_lg = nullptr, int lds_stride = 0)
 {
     constexpr int RB = 8 * KG;
-    static_assert(!SHARED || (G >= 4 && 2 * G <= 16 && kVWaves * 32 == kD && KG <= 2), "shared mode: high and low parts of all heads are the 16 rows of W; four waves share the 128 lines");
-    const int wave = threadIdx.x >> 6;
     // wave-uniform by contract: scalar registers, scalar loop control
     nbatches = __builtin_amdgcn_readfirstlane(nbatches);
     t_first = __builtin_amdgcn_readfirstlane(t_first);
@@ -157,12 +202,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.v_hi + bh * Ncap * kD, uint32_t(len) * kD);
     const __amdgpu_buffer_rsrc_t rs_mid = make_rsrc(a.v_mid + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
     const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(a.v_lo + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
-    // the row-independent tests 1 + max_d w_d + Ahat >= 3 and >= 7 (or the forced level) as bounds of Ahat + 64 in every byte
-    auto bound_word = [&](int need, int level) {
-        const int at = vr.force >= 0 ? (vr.force >= level ? 0 : 127) : min(max(need + 63 - vr.wmax, 0), 127);
-        return (uint32_t)__builtin_amdgcn_readfirstlane(at * 0x01010101);
-    };
-    const uint32_t row1 = bound_word(3, 1), row2 = bound_word(7, 2);
+    const uint32_t row1 = v_bound_word(vr, 3, 1), row2 = v_bound_word(vr, 7, 2);
     const uint32_t voff_hi = uint32_t(r) * kD + uint32_t(cl) * 16;
     const uint32_t voff_nib = uint32_t(r) * (kD / 2) + uint32_t(cl) * 8;
     const uint32_t voff_lg = (uint32_t(jg) * uint32_t(Ncap) + uint32_t(jrow)) * 4u;
@@ -179,8 +219,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
         u32x4_t hi[KG];
         float lg;
         u32x2_t mid[KG], lo[KG];
-        float p[SHARED ? 1 : KG][SHARED ? 1 : G];
-        float pj;   // shared mode: the weight this lane computed, kept until the round of its batch
+        float p[KG][G];
         uint32_t fill[KG];
     };
     auto row0 = [&](int bt) { return t_first + bt * batch_stride; };
@@ -198,7 +237,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     // Single heads in a ring of four (SB): the scores of the four batches of a round of the ring are computed together, one row
     // per lane (lane / 16 = batch, lane % 16 = row), a quarter of the score instructions and of the logit loads: B 1, 32 heads,
     // 1024 tokens 22.7 -> 22.1 us a call, B 8 4096 71.9 -> 70.2, B 16 step of 8193 285.3 -> 282.
-    constexpr bool SB = G == 1 && !SHARED && KG == 2 && DL == 3;
+    constexpr bool SB = G == 1 && KG == 2 && DL == 3;
     float lg_n = 0.0f, sb_p = 0.0f;                // logits of the block to come; weights of the present one
     uint32_t sb_ss = 0;
     auto sb_load = [&](int b0) {                   // logits of batches b0 .. b0 + 3
@@ -233,7 +272,6 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
                 int ahat = score_a(x);                  // then the maximum over the G heads of the row (adjacent lanes)
                 pj = jlane && jrow < nvalid ? __builtin_amdgcn_exp2f(x) : 0.0f;
                 zl += pj;
-                X.pj = pj;
                 if (G >= 2) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
                 if (G >= 4) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
                 if (G >= 8) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0x141, 0xF, 0xF, false));   // row_half_mirror
@@ -243,23 +281,11 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
 #pragma unroll
             for (int gr = 0; gr < KG; ++gr) {
                 const uint32_t ss = (uint32_t)__builtin_amdgcn_ds_bpermute(src[gr] + sk, (int)ssw);
-                if (!SHARED) {
 #pragma unroll
-                    for (int g = 0; g < G; ++g)
-                        X.p[SHARED ? 0 : gr][SHARED ? 0 : g] = bits_float((uint32_t)__builtin_amdgcn_ds_bpermute(src[gr] + sk + 4 * g, (int)float_bits(pj)));
-                }
+                for (int g = 0; g < G; ++g) X.p[gr][g] = bits_float((uint32_t)__builtin_amdgcn_ds_bpermute(src[gr] + sk + 4 * g, (int)float_bits(pj)));
                 const uint32_t hw[4] = {X.hi[gr].x, X.hi[gr].y, X.hi[gr].z, X.hi[gr].w};
-                uint32_t any1 = 0, any2 = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t evp = (hw[i] >> 2) & 0x1F1F1F1Fu;
-                    const uint32_t S = evp + vr.B[i] + ss;
-                    any1 |= S;
-                    any2 |= S - 0x04040404u;
-                }
-                // bit 7 of a byte: level >= 1 needed; bit 6: level 2 needed (which implies the former)
-                const uint32_t flags = or_over_row((any1 & 0x80808080u) | ((any2 >> 1) & 0x40404040u));
-                const bool need1 = flags != 0 || ss >= row1, need2 = (flags & 0x40404040u) != 0 || ss >= row2;   // ss: the same byte four times
+                bool need1, need2;
+                v_row_needs<8>(hw, vr, ss, row1, row2, need1, need2);
                 const uint32_t off = voff_nib + uint32_t(t0) * (kD / 2) + gr * 8 * (kD / 2);
                 offm[gr] = need1 ? off : kSkip;
                 offl[gr] = need2 ? off : kSkip;
@@ -267,37 +293,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
 
                 if (DEBUG) {
                     const int t = t0 + gr * 8 + r;
-                    if (t < len) {
-                        const int applied = need2 ? 2 : (need1 ? 1 : 0);
-                        if (a.dbg.appliedV && cl == 0) a.dbg.appliedV[bh * Ncap + t] = (uint8_t)applied;
-                        if (cl == 0) {
-                            st_rows[0] += applied == 0;
-                            st_rows[1] += applied == 1;
-                            st_rows[2] += applied == 2;
-                        }
-                        if (a.dbg.needV || a.stats) {
-                            const int ah = int(ss & 0xFFu) - 64;
-                            uint32_t nv[4];
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                nv[i] = 0;
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) {
-                                    int ev = (int)((hw[i] >> (8 * k + 2)) & 31u);
-                                    ev = ev < 1 ? 1 : ev;
-                                    int need = level_for_mantissa_bits(10 + a.guard_bits - (vr.ehat[i * 4 + k] - (ah + ev - 15)));
-                                    if (a.force_level >= 0) need = a.force_level;
-                                    nv[i] |= (uint32_t)need << (8 * k);
-                                    st_need[1] += need == 1;
-                                    st_need[2] += need == 2;
-                                }
-                            }
-                            st_need[0] += 16;   // all of the lane's elements; those at levels 1 and 2 are taken off at the end
-                            if (a.dbg.needV)
-                                *reinterpret_cast<uint4*>(a.dbg.needV + (bh * Ncap + t) * kD + cl * 16) =
-                                    make_uint4(nv[0], nv[1], nv[2], nv[3]);
-                        }
-                    }
+                    if (t < len) v_export<4>(a, bh, t, cl, need2 ? 2 : (need1 ? 1 : 0), int(ss & 0xFFu) - 64, hw, vr.ehat, st_rows, st_need);
                 }
             }
         }
@@ -319,60 +315,11 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
                                  lo_half(pb[0]), lo_half(pb[1]), hi_half(pb[0]), hi_half(pb[1]),
                                  lo_half(pb[2]), lo_half(pb[3]), hi_half(pb[2]), hi_half(pb[3])};
 #pragma unroll
-            for (int g = 0; g < (SHARED ? 1 : G); ++g)
+            for (int g = 0; g < G; ++g)
 #pragma unroll
-                for (int i = 0; i < (SHARED ? 8 : 16); ++i) acc[g][i] = fmaf(X.p[SHARED ? 0 : gr][SHARED ? 0 : g], v[i], acc[g][i]);
+                for (int i = 0; i < 16; ++i) acc[g][i] = fmaf(X.p[gr][g], v[i], acc[g][i]);
         }
     };
-
-    // shared mode: A leaves the wave's rows of batch bt and their weights in the round's buffer; Fs is the wave's share of the matrix product over the rows of the round
-    auto A = [&](const Batch& X, int bt) {
-        const int buf = bt & 1;
-#pragma unroll
-        for (int gr = 0; gr < KG; ++gr) {
-            uint32_t pa[4], pb[4];
-            assemble8_fill(X.hi[gr].x, X.hi[gr].y, X.mid[gr].x, X.lo[gr].x, X.fill[gr], pa);
-            assemble8_fill(X.hi[gr].z, X.hi[gr].w, X.mid[gr].y, X.lo[gr].y, X.fill[gr], pb);
-            u32x4_t* row = sh->vr[buf][wave * RB + gr * 8 + r];
-            row[cl ^ (r << 1)] = u32x4_t{pa[0], pa[1], pa[2], pa[3]};
-            row[(8 + cl) ^ (r << 1)] = u32x4_t{pb[0], pb[1], pb[2], pb[3]};
-        }
-        if (jlane) {
-            const float ws = X.pj * kVWeightScale;
-            const _Float16 whi = (_Float16)ws;
-            const _Float16 wlo = (_Float16)(ws - (float)whi);
-            const int wrow = wave * RB + jrow;
-            sh->pt[buf][jg][wrow] = __builtin_bit_cast(uint16_t, whi);
-            sh->pt[buf][G + jg][wrow] = __builtin_bit_cast(uint16_t, wlo);
-        }
-    };
-    f32x4_t d0 = {0.0f, 0.0f, 0.0f, 0.0f}, d1 = {0.0f, 0.0f, 0.0f, 0.0f};   // the wave's two result tiles
-    auto Fs = [&](int bt) {
-        const int buf = bt & 1;
-        const int n = lane & 15, kq = lane >> 4;
-#pragma unroll
-        for (int kb = 0; kb < (kVWaves * RB) / 32; ++kb) {   // 32 rows: a lane's k are rows 8 kq .. 8 kq + 7
-            const half8_t w8 = *reinterpret_cast<const half8_t*>(&sh->pt[buf][n][kb * 32 + 8 * kq]);
-            short4_t v[2][2];   // [tile][rows 0..3, 4..7 of the lane's eight]
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {   // lane n of sixteen reads four values of row n / 4 and receives value n of all four rows
-                    const int row = kb * 32 + 8 * kq + 4 * e + (n >> 2), word = 4 * wave + 2 * t + ((n >> 1) & 1);
-                    typedef __attribute__((address_space(3))) short4_t* lds_ptr;
-                    v[t][e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(reinterpret_cast<short4_t*>(&sh->vr[buf][row][word ^ ((row & 7) << 1)]) + (n & 1)));
-                }
-            d0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[0][0], v[0][1], 0, 1, 2, 3, 4, 5, 6, 7)), d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[1][0], v[1][1], 0, 1, 2, 3, 4, 5, 6, 7)), d1, 0, 0, 0);
-        }
-    };
-    if constexpr (SHARED && 2 * G < 16) {   // the rows of W no head uses stay zero in both buffers (ordered before the first read by the first barrier)
-        constexpr int kRows = VShare<G, RB>::kRows;
-        for (int idx = threadIdx.x; idx < 2 * (16 - 2 * G) * kRows; idx += 64 * kVWaves) {
-            const int bf = idx / ((16 - 2 * G) * kRows), rest = idx % ((16 - 2 * G) * kRows);
-            sh->pt[bf][2 * G + rest / kRows][rest % kRows] = 0;
-        }
-    }
 
     // R = DL + 1 named buffers: round i runs D(i + 1), L(i + DL), F(i); the buffer L fills is the one F emptied in
     // the round before.  The loop is unrolled R times so that every buffer index is a constant.  Loads come back in
@@ -407,40 +354,12 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
             D(ring[(k + 1) % R], i + k + 1, (k + 1) % R);
             Lhi(ring[(k + DL) % R], i + k + DL);
             if (!SB) Llg(ring[(k + DL) % R], i + k + DL);
-            if (SHARED) {
-                if (i + k < nbatches) {   // the same for every wave of the workgroup
-                    A(ring[k], i + k);
-                    lds_barrier();
-                    Fs(i + k);
-                }
-            } else {
-                F(ring[k], i + k);
-            }
+            F(ring[k], i + k);
         }
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) z[g] += jg == g ? zl : 0.0f;
-    if (SHARED) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[0][i] = d0[i];
-            acc[0][SHARED ? 4 + i : 0] = d1[i];
-        }
-    }
-    if (DEBUG && a.stats) {   // uniform; one set of atomics per wave
-        st_need[0] -= st_need[1] + st_need[2];
-        unsigned v6[6] = {st_rows[0], st_rows[1], st_rows[2], st_need[0], st_need[1], st_need[2]};
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-            for (int o = 1; o < 64; o <<= 1) v6[i] += __shfl_xor(v6[i], o);
-        if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->v_row_elems[i]), (unsigned long long)v6[i] * kD);
-                atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->v_need_elems[i]), (unsigned long long)v6[3 + i]);
-            }
-        }
-    }
+    if (DEBUG && a.stats) v_add_stats(a, st_rows, st_need);
 }
 
 // sum acc over the 8 row lanes of a wave (lanes with the same lane % 8) and z over all lanes; afterwards
@@ -456,6 +375,192 @@ __device__ __forceinline__ void v_reduce_rows(float (&acc)[G][16], float (&z)[G]
             for (int i = 0; i < 16; ++i) acc[g][i] += __shfl_xor(acc[g][i], o);
         }
     }
+}
+
+// ---- Groups of four and eight query heads (the token-split V kernel): the rows of all waves of a workgroup are shared.
+// Every wave fetches, tests and assembles its own rows, once, and leaves them in LDS with their weights; after a barrier the
+// sum over the rows of the round, for all query heads at once, is a matrix product on the matrix cores:
+// D[m][line] += sum_rows W[m][row] * V[row][line], wave w taking lines 32 w .. 32 w + 31.
+constexpr int kSRows = 16;        // rows of a wave's batch: lane -> row lane / 4, 32-channel slice lane % 4
+// LDS: the rows of a round, each as sixteen 16-byte words (word 4 k + c: channels 32 c + 8 k .. + 7), and the weights of these
+// rows, line g the high part and line G + g the low part of query head g's weight (two fp16 numbers whose sum carries 22
+// bits).  The matrix instruction wants four consecutive rows of one value per lane: the transposing LDS read turns them on the
+// way out, so that a lane lays a row down with 16-byte stores.  The words of a row are permuted by its number
+// (v_word_turn), so that neither side has bank conflicts.  Two buffers alternate by round.
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+struct VShare {
+    static constexpr int kRows = kVWaves * kSRows;   // rows of a round
+    alignas(16) u32x4_t vr[2][kRows][16];
+    alignas(16) uint16_t pt[2][16][kRows + 8];
+};
+// a store takes rows 2 i, 2 i + 1 (four lanes each) at a time, a transposing read rows 4 i .. 4 i + 3 (two words each)
+__device__ __forceinline__ int v_word_turn(int row) { return ((row & 1) << 2) | (row & 2); }
+// the channel of value `line` (0..127) of a row as it lies in VShare::vr: assemble8_fill leaves channels (0,2), (1,3), (4,6),
+// (5,7) of eight in its four words
+__device__ __forceinline__ int line_channel(int line)
+{
+    const int word = line >> 3, pos = line & 7;
+    return 32 * (word & 3) + 8 * (word >> 2) + ((pos >> 1) & 1) + 4 * (pos >> 2) + 2 * (pos & 1);
+}
+constexpr float kVWeightScale = 16384.0f;   // weights are at most 1: scaled by 2^14 their fp16 parts reach down to 2^-38
+// workgroup barrier that waits for this wave's LDS traffic only: the loads from memory that are in flight stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Batch i of this wave covers rows t_first + i * kVWaves * kSRows .. + 15; all waves of the workgroup call with the same nbatches.
+// Stages L, D, A + matrix product as in v_rows.  Four lanes per row: they are also the lanes that compute the row's scores
+// (lane -> query heads lane % 4, + 4), so that nothing is exchanged but the maximum over a quad, and a MID or LO row takes one
+// 16-byte load per lane: five vector-memory instructions a batch instead of seven, a quarter of the vector instructions less.
+// Measured against eight lanes per row, scores handed over by lane permutes, batches of 8 rows for groups of eight (us a call):
+// B 4, 32/8, up to 131072 tokens 265 -> 257, B 3, 64/8, up to 13000 69.5 -> 65; B 8, 32/8, 32768, every slot of the device full,
+// 159.5 -> 161.  What bounds it now is the loads: without assembly, LDS and matrix products (timing only) the call takes as
+// long, without Rule 2's test and its MID / LO bytes 8 us less, without the logits 10 us less.  The two halves of a lane's 32 HI
+// bytes share a line, so the HI loads keep the line in the caches (temporal: 175 -> 168, at an earlier state).
+// acc: the wave's two 16x16 result tiles (four words each: rows 4 * (lane / 16) .. + 3 of W, line 16 * (2 w + tile) + lane % 16),
+// scaled by kVWeightScale.  z[s]: this lane's sum of the weights of head lane % 4 + 4 s.
+template <int G, bool DEBUG, int DL>
+__device__ __forceinline__ void v_rows_shared(const DecodeArgs& a, int b, int h, int t_first, int nbatches, int len, const VRule<4>& vr,
+                                              const float (&Mg)[G], float (&acc)[8], float (&z)[G / 4], VShare& sh)
+{
+    static_assert(G == 4 || G == 8, "high and low parts of all heads are the 16 rows of W");
+    static_assert(kVWaves * 32 == kD, "four waves share the 128 lines");
+    constexpr int S = G / 4, kStride = VShare::kRows;
+    nbatches = __builtin_amdgcn_readfirstlane(nbatches);
+    t_first = __builtin_amdgcn_readfirstlane(t_first);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane >> 2, c = lane & 3;
+    const int Hq = a.s.Hq, Ncap = a.s.Ncap;
+    const size_t bh = size_t(b) * a.s.Hkv + h;
+    // the logits of the G query heads of the group lie Ncap floats apart: one descriptor over all of them
+    const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + (size_t(b) * Hq + size_t(h) * G) * Ncap, uint32_t(G) * uint32_t(Ncap) * 4u);
+    // ... and the rows end at len: rows at or past it read as zeros, their weight is forced to zero
+    const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.v_hi + bh * Ncap * kD, uint32_t(len) * kD);
+    const __amdgpu_buffer_rsrc_t rs_mid = make_rsrc(a.v_mid + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
+    const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(a.v_lo + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
+    const uint32_t row1 = v_bound_word(vr, 3, 1), row2 = v_bound_word(vr, 7, 2);
+    const uint32_t voff_hi = uint32_t(r) * kD + uint32_t(c) * 32, voff_nib = uint32_t(r) * (kD / 2) + uint32_t(c) * 16;
+    const uint32_t voff_lg = (uint32_t(c) * uint32_t(Ncap) + uint32_t(r)) * 4u;
+    float Ml[S];                                   // the global max of this lane's query heads
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        Ml[s] = Mg[4 * s];
+#pragma unroll
+        for (int g = 1; g < 4; ++g) Ml[s] = c == g ? Mg[4 * s + g] : Ml[s];
+    }
+    unsigned st_rows[3] = {0u, 0u, 0u}, st_need[3] = {0u, 0u, 0u};   // DEBUG: this lane's counts for akv_stats
+
+    struct Batch {
+        u32x4_t hi[2], mid, lo;
+        float lg[S], p[S];
+        uint32_t fill;
+    };
+    auto row0 = [&](int bt) { return t_first + bt * kStride; };
+    // a batch past the wave's last one is issued out of range: nothing is fetched
+    auto L = [&](Batch& X, int bt) {
+        const uint32_t base = bt < nbatches ? uint32_t(row0(bt)) * kD : kSkip;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) X.hi[i] = buf_load_b128(rs_hi, voff_hi + base + 16 * i);
+        const bool on = bt < nbatches && row0(bt) + r < len;
+#pragma unroll
+        for (int s = 0; s < S; ++s) X.lg[s] = bits_float(buf_load_b32_nt(rs_lg, on ? voff_lg + (uint32_t(row0(bt)) + uint32_t(4 * s) * uint32_t(Ncap)) * 4u : kSkip));
+    };
+    auto D = [&](Batch& X, int bt) {
+        uint32_t offm = kSkip, offl = kSkip;
+        if (bt < nbatches) {   // uniform; arithmetic only -- the loads below are issued in any case
+            const int t = row0(bt) + r;
+            int ahat = kAMin;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const float x = score_x(X.lg[s], Ml[s], a.c);
+                ahat = max(ahat, score_a(x));
+                X.p[s] = t < len ? __builtin_amdgcn_exp2f(x) : 0.0f;
+                z[s] += X.p[s];
+            }
+            ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+            ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+            const uint32_t ss = __builtin_amdgcn_perm(0u, uint32_t(ahat + 64), 0x00000000u);     // (Ahat + 64) in every byte
+            const uint32_t hw[8] = {X.hi[0].x, X.hi[0].y, X.hi[0].z, X.hi[0].w, X.hi[1].x, X.hi[1].y, X.hi[1].z, X.hi[1].w};
+            bool need1, need2;
+            v_row_needs<4>(hw, vr, ss, row1, row2, need1, need2);
+            const uint32_t off = voff_nib + uint32_t(row0(bt)) * (kD / 2);
+            offm = need1 ? off : kSkip;
+            offl = need2 ? off : kSkip;
+            X.fill = need2 ? 0u : (need1 ? 0x08080808u : 0x80808080u);
+            if (DEBUG && t < len) v_export<8>(a, bh, t, c, need2 ? 2 : (need1 ? 1 : 0), ahat, hw, vr.ehat, st_rows, st_need);
+        }
+        X.mid = buf_load_b128_nt(rs_mid, offm);
+        X.lo = buf_load_b128_nt(rs_lo, offl);
+    };
+    const int turn = v_word_turn(r);
+    auto A = [&](const Batch& X, int bt) {
+        const int buf = bt & 1;
+        u32x4_t* row = sh.vr[buf][wave * kSRows + r];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // channels 8 k .. 8 k + 7 of the slice
+            uint32_t w[4];
+            assemble8_fill(X.hi[k >> 1][2 * (k & 1)], X.hi[k >> 1][2 * (k & 1) + 1], X.mid[k], X.lo[k], X.fill, w);
+            row[(4 * k + c) ^ turn] = u32x4_t{w[0], w[1], w[2], w[3]};
+        }
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const float ws = X.p[s] * kVWeightScale;
+            const _Float16 whi = (_Float16)ws;
+            const _Float16 wlo = (_Float16)(ws - (float)whi);
+            sh.pt[buf][c + 4 * s][wave * kSRows + r] = __builtin_bit_cast(uint16_t, whi);
+            sh.pt[buf][G + c + 4 * s][wave * kSRows + r] = __builtin_bit_cast(uint16_t, wlo);
+        }
+    };
+    f32x4_t d0 = {0.0f, 0.0f, 0.0f, 0.0f}, d1 = {0.0f, 0.0f, 0.0f, 0.0f};   // the wave's two result tiles
+    auto F = [&](int bt) {
+        const int buf = bt & 1;
+        const int n = lane & 15, kq = lane >> 4;
+#pragma unroll
+        for (int kb = 0; kb < VShare::kRows / 32; ++kb) {   // 32 rows: a lane's k are rows 8 kq .. 8 kq + 7
+            const half8_t w8 = *reinterpret_cast<const half8_t*>(&sh.pt[buf][n][kb * 32 + 8 * kq]);
+            short4_t v[2][2];   // [tile][rows 0..3, 4..7 of the lane's eight]
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {   // lane n of sixteen reads four values of row n / 4 and receives value n of all four rows
+                    const int row = kb * 32 + 8 * kq + 4 * e + (n >> 2), word = 4 * wave + 2 * t + ((n >> 1) & 1);
+                    typedef __attribute__((address_space(3))) short4_t* lds_ptr;
+                    v[t][e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(reinterpret_cast<short4_t*>(&sh.vr[buf][row][word ^ v_word_turn(row)]) + (n & 1)));
+                }
+            d0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[0][0], v[0][1], 0, 1, 2, 3, 4, 5, 6, 7)), d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[1][0], v[1][1], 0, 1, 2, 3, 4, 5, 6, 7)), d1, 0, 0, 0);
+        }
+    };
+    if constexpr (2 * G < 16) {   // the rows of W no head uses stay zero in both buffers (ordered before the first read by the first barrier)
+        constexpr int kRows = VShare::kRows;
+        for (int idx = threadIdx.x; idx < 2 * (16 - 2 * G) * kRows; idx += 64 * kVWaves) {
+            const int bf = idx / ((16 - 2 * G) * kRows), rest = idx % ((16 - 2 * G) * kRows);
+            sh.pt[bf][2 * G + rest / kRows][rest % kRows] = 0;
+        }
+    }
+    constexpr int R = DL + 1;   // rounds and buffers as in v_rows
+    Batch ring[R];
+#pragma unroll
+    for (int k = 0; k < DL; ++k) L(ring[k], k);
+    D(ring[0], 0);
+#pragma unroll 1
+    for (int i = 0; i < nbatches; i += R) {   // rounds past the last batch issue nothing and compute nothing
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            D(ring[(k + 1) % R], i + k + 1);
+            L(ring[(k + DL) % R], i + k + DL);
+            if (i + k < nbatches) {   // the same for every wave of the workgroup
+                A(ring[k], i + k);
+                lds_barrier();
+                F(i + k);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[i] = d0[i];
+        acc[4 + i] = d1[i];
+    }
+    if (DEBUG && a.stats) v_add_stats(a, st_rows, st_need);
 }
 
 // write out[b][h*G + g][:] = o / zsum for channel d (or zero for an empty sequence)
