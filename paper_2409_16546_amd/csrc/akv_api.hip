@@ -201,9 +201,9 @@ void* static_scratch_for_current_device(hipStream_t s)
 // Head-per-workgroup or token-split kernels, when the caller leaves the choice to the library.  One head kernel
 // workgroup occupies a compute unit, so `pairs` (sequence, KV head) pairs run in ceil(pairs / CUs) rounds of equal
 // length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
-// that the single launch outweighs idle units; for single query heads also at two nearly full rounds, as long as the logits
-// of a pair fit its LDS (the token-split kernels write theirs to memory, and written bytes cost several times what read
-// bytes cost).
+// that the single launch outweighs idle units; for single query heads also at two and more nearly full rounds, as long as the
+// logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written bytes cost several times
+// what read bytes cost).
 // The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
 // path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step
 // (append and attention in one call) costs it a launch more; the head kernel stores the new token itself.  So the lines lie
@@ -216,12 +216,15 @@ void* static_scratch_for_current_device(hipStream_t s)
 //   groups of 2   128 pairs 2048 39.6/38.6, 192 pairs 41.2/50.5, 4096 71.6/79.1, 8192 141/132
 //   groups of 4   64 pairs 256 32.3/27.4; 128 pairs 512 30.6/32.4; 160 pairs 2048 61.7/57.8 and 43.2/50.2, step 62.7/63.4 and
 //                 46.2/55.6; 192 pairs 1024 43.8/44.7, 2048 62.2/60.1 and 43.7/50.8, step 63.2/67.2; 200 pairs 2048 63.0/66.5; 224 pairs 4096 106/113 and 56/88; 256 pairs 6144 166/165 and 65/104
-// (two rounds: timed up to 8192 tokens, where the head kernel still wins)
+//   two rounds of single heads, step and attention over full sequences and partly full ones: 448 pairs 10000 298/307, 12288 354/367;
+//                 512 pairs 8448 291/300, 10000 321/335 (half full 172/236), 12288 384/401, step of 11000 0.7 full 291/323
+//   more rounds   640 pairs 4096 184/190, 768 pairs 4096 197/209, 8192 389/401, 1024 pairs 4096 273/278 (0.4 full 152/199), 1536
+//                 pairs 4096 395/410; but 1024 pairs 2048 172/152, 768 pairs 1024 79/70
 bool head_path_pays(long pairs, int G, int max_len)
 {
     const long cus = compute_units();
-    if (pairs > cus) return G == 1 && pairs <= 2 * cus && double(pairs) / double(2 * cus) >= 0.85 && max_len > 512 && max_len <= 8192;
-    const double fill = double(pairs) / double(cus);
+    const double rounds = double((pairs + cus - 1) / cus), fill = double(pairs) / (rounds * double(cus));
+    if (rounds > 1) return G == 1 && max_len <= 12288 && (rounds == 2 ? fill >= 0.85 && max_len > 512 : fill >= 0.83 && max_len >= 4096);
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
     static constexpr Rule g1[] = {{1024, 0.0}, {2048, 0.2}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
                           g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},

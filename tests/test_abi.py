@@ -151,6 +151,14 @@ def test_decode_path_keeps_the_head_kernel_where_sequences_may_be_short(A):
         assert A.akv_decode_path(B, Hkv * G, Hkv, 128, N) == 2, (B, Hkv, G, N)
 
 
+@pytest.mark.parametrize("B,Hkv,N,path", [
+    (16, 32, 8448, 3), (14, 32, 12288, 3), (16, 32, 12544, 2),        # two rounds: as long as the logits fit the LDS
+    (24, 32, 4096, 3), (20, 32, 4096, 3), (48, 32, 12288, 3),          # more rounds, the last one full enough
+    (18, 32, 4096, 2), (32, 32, 2048, 2), (24, 32, 3840, 2)])
+def test_decode_path_of_single_heads_in_several_rounds(A, B, Hkv, N, path):
+    assert A.akv_decode_path(B, Hkv, Hkv, 128, N) == path
+
+
 def test_misaligned_weight_arrays_are_refused(A):
     L = A.lib()
     w = A.akw_weights(64, 32, 0x10000, 0x20000, 0x30000, 0x40000)
