@@ -293,50 +293,46 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
     return hipGetLastError();
 }
 
-// planes -> fp16 [B][Hkv][Ncap][D], the bulk append run backwards (B 8, 32 heads, 4096 tokens: 1466 -> 236 us, 4.5 TB/s; single
-// bytes per lane before): a workgroup of 256 threads per 256-token block of K, and
-// VP per block of V.  Bound by memory; K goes through LDS 64 channels at a time (16-byte pieces of the channel-major runs in,
-// rows of 128 bytes out), with the same placement as there.
-// VP: workgroups per block of V.  V alone takes eight of 32 rows, so that a small call has waves enough (2 x 8 heads, 4096 tokens,
-// one / eight / single bytes per lane: 9.7 / 7.5 / 8.2 us; 8 x 32, 4096: 157 / 98 / 176).
-template <int VP>
+// planes -> fp16 [B][Hkv][Ncap][D], the bulk append run backwards: a workgroup of 256 threads per 256-token block of K, and VP per
+// block of V.  Bound by memory; K goes through LDS 64 channels at a time (16-byte pieces of the channel-major runs in, rows of 128
+// bytes out), with the same placement as there.  V: sixteen lanes per row, so that a store covers whole lines (eight lanes with two
+// stores each, and one workgroup per block of V as of K: 8 x 32 heads, 4096 tokens 235 -> 176 us, 6.1 TB/s; 4 x 8, 4096 30 -> 25).
+// KP: workgroups per block of K, 1 or 0 (V alone).
+template <int KP, int VP>
 __global__ __launch_bounds__(256) void unpack_kernel(akv_cache c, uint16_t* __restrict__ k_out,
                                                      uint16_t* __restrict__ v_out)
 {
-    __shared__ u32x4_t hi_s[kHalf][kTB / 16], mid_s[kHalf][kTB / 32], lo_s[kHalf][kTB / 32];
+    __shared__ u32x4_t hi_s[KP ? kHalf : 1][kTB / 16], mid_s[KP ? kHalf : 1][kTB / 32], lo_s[KP ? kHalf : 1][kTB / 32];
     const int tid = threadIdx.x;
-    const bool both = VP == 1 && k_out && v_out;
-    const size_t item = VP > 1 ? blockIdx.x / VP : (both ? blockIdx.x >> 1 : blockIdx.x);   // (b * Hkv + h) * NB + blk: the token rows item * 256 .. + 255
-    if (VP > 1 || (both ? blockIdx.x & 1 : v_out != nullptr)) {   // thread -> (row tid/8 + 32 i of the part, 16 channels)
-        constexpr int kRows = kTB / VP / 32;
-        const int cl = tid & 7;
-        const size_t row0 = item * kTB + (blockIdx.x % VP) * (kTB / VP) + (tid >> 3);
-        u32x4_t hi[kRows];
-        u32x2_t mid[kRows], lo[kRows];
+    const size_t item = blockIdx.x / (KP + VP);   // (b * Hkv + h) * NB + blk: the token rows item * 256 .. + 255
+    const int part = int(blockIdx.x % (KP + VP)) - KP;
+    if (VP > 0 && part >= 0) {   // thread -> (row tid / 16 + 16 i of the part, 8 channels)
+        constexpr int kRows = VP > 0 ? kTB / (VP > 0 ? VP : 1) / 16 : 1;
+        const int cl = tid & 15;
+        const size_t row0 = item * kTB + part * (16 * kRows) + (tid >> 4);
+        u32x2_t hi[kRows];
+        uint32_t mid[kRows], lo[kRows];
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
-            const size_t row = row0 + 32 * i;
-            hi[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(c.v_hi + row * kD + cl * 16));
-            mid[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(c.v_mid + row * (kD / 2) + cl * 8));
-            lo[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(c.v_lo + row * (kD / 2) + cl * 8));
+            const size_t row = row0 + 16 * i;
+            hi[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(c.v_hi + row * kD + cl * 8));
+            mid[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(c.v_mid + row * (kD / 2) + cl * 4));
+            lo[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(c.v_lo + row * (kD / 2) + cl * 4));
         }
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
-            const size_t row = row0 + 32 * i;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {   // channels 8e .. 8e + 7 of the slice
-                uint32_t w[4];
-                assemble8(hi[i][2 * e], hi[i][2 * e + 1], mid[i][e], lo[i][e], w);   // channels (0,2), (1,3), (4,6), (5,7)
-                u32x4_t o;
-                o.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100u);
-                o.y = __builtin_amdgcn_perm(w[1], w[0], 0x07060302u);
-                o.z = __builtin_amdgcn_perm(w[3], w[2], 0x05040100u);
-                o.w = __builtin_amdgcn_perm(w[3], w[2], 0x07060302u);
-                __builtin_nontemporal_store(o, reinterpret_cast<u32x4_t*>(v_out + row * kD + cl * 16 + 8 * e));
-            }
+            uint32_t w[4];
+            assemble8(hi[i].x, hi[i].y, mid[i], lo[i], w);   // channels (0,2), (1,3), (4,6), (5,7)
+            u32x4_t o;
+            o.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100u);
+            o.y = __builtin_amdgcn_perm(w[1], w[0], 0x07060302u);
+            o.z = __builtin_amdgcn_perm(w[3], w[2], 0x05040100u);
+            o.w = __builtin_amdgcn_perm(w[3], w[2], 0x07060302u);
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4_t*>(v_out + (row0 + 16 * i) * kD + cl * 8));
         }
         return;
     }
+    if constexpr (KP > 0) {
     const int lane = tid & 63, wave = tid >> 6;
     const int p = lane & 7, oct = wave * 8 + (lane >> 3);   // channels 8p .. 8p+7 of the half, tokens 8 oct .. 8 oct + 7 of the block
     const size_t colbase = item * kD;
@@ -389,13 +385,23 @@ __global__ __launch_bounds__(256) void unpack_kernel(akv_cache c, uint16_t* __re
         for (int i = 0; i < 8; ++i)
             __builtin_nontemporal_store(o[i], reinterpret_cast<u32x4_t*>(k_out + (item * kTB + 8 * oct + i) * kD + half * kHalf + 8 * p));
     }
+    }
 }
 
 hipError_t launch_unpack(const akv_cache& c, uint16_t* k_out, uint16_t* v_out, hipStream_t st)
 {
     const size_t blocks = size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB);
-    if (k_out) hipLaunchKernelGGL(unpack_kernel<1>, dim3((unsigned)(blocks * (v_out ? 2 : 1))), dim3(256), 0, st, c, k_out, v_out);
-    else hipLaunchKernelGGL(unpack_kernel<8>, dim3((unsigned)(blocks * 8)), dim3(256), 0, st, c, k_out, v_out);
+    auto launch = [&](auto kernel, int per) { hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks * per)), dim3(256), 0, st, c, k_out, v_out); };
+    // both: many short V workgroups between those of K keep reads and writes of the two mixed, but cost a launch that is over in a few
+    // rounds (one / sixteen per block of V, us: 256 blocks 13.7/15.4, 512 25.3/25.8, 1024 48.6/46.9, 2048 93/89, 4096 188/176, 8192 380/350)
+    if (k_out && v_out) {
+        if (blocks >= 1024) launch(unpack_kernel<1, 16>, 17);
+        else launch(unpack_kernel<1, 1>, 2);
+    } else if (k_out) {
+        launch(unpack_kernel<1, 0>, 1);
+    } else {   // one / two / four / eight per block: 256 blocks 7.5/7.5/7.5/7.6, 512 12.9/12.6/12.9/13.5, 4096 91/86/84/86
+        launch(unpack_kernel<0, 2>, 2);
+    }
     return hipGetLastError();
 }
 

@@ -131,3 +131,18 @@ def test_walking_append_beside_a_busy_stream(T):
     """A few tokens per call: one workgroup of two waves per head, ticket drawn in front of the stores."""
     print("append: one to fifteen tokens beside a busy stream", flush=True)
     _append_beside_busy_stream(T, 8, 3, [1, 2, 15, 1, 1, 8, 3, 1, 15])
+
+
+@pytest.mark.parametrize("B", [341, 342])            # 1023 and 1026 blocks: one workgroup per block of V, and sixteen
+def test_unpack_of_many_blocks_gives_back_what_was_stored(T, B):
+    from paper_2409_16546_amd import binding as A, workloads
+    print(f"unpack: {3 * B} blocks", flush=True)
+    k, v = (t.repeat(B, 1, 1, 1).to(DEV) for t in workloads.edge_patterns(1, 3, 256, seed=B))
+    k[:, :, :, 5] = torch.arange(B, device=DEV)[:, None, None].half()      # a block that lands in another's place is seen
+    v[:, :, :, 6] = torch.arange(256, device=DEV).half()
+    gc = A.Cache.allocate(B, 3, 3, 128, 256, DEV)
+    A.akv_append(gc, k, v)
+    ku, vu = A.akv_unpack(gc)
+    torch.cuda.synchronize()
+    for got, want in ((ku, k), (vu, v)):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
