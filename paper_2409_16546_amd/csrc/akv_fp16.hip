@@ -31,6 +31,9 @@ static int f_chunk(const akv_shape& s, int max_len)
     return (int)std::min(1024L, std::max(long(kFMinChunk), whole(pairs * s.Ncap / wgs)));
 }
 
+// workgroups of a compute unit at a time
+constexpr int f_resident(int G) { return G == 8 ? 2 : 3; }
+
 size_t fp16_workspace_bytes(const akv_shape& s)
 {
     const size_t bhq = size_t(s.B) * s.Hq, ns = s.Ncap / kFMinChunk;
@@ -45,6 +48,7 @@ struct F16Args {
     float c;   // scale * log2(e)
     int out_dtype, nsplit, max_len, chunk;   // nsplit: chunks there is room for per query head
     int turn_shift, turn_mask;               // which chunk a workgroup takes: launch_fp16_g
+    int workgroups;                          // of fp16_even_kernel, or 0: chunks
     float *partO, *partM, *partZ;
 };
 
@@ -60,6 +64,35 @@ __device__ __forceinline__ float over_rows(float v, F op)
     const auto b = __builtin_amdgcn_permlane32_swap(float_bits(v), float_bits(v), false, false);
     return op(bits_float(b[0]), bits_float(b[1]));
 }
+
+__device__ __forceinline__ int fp16_len(const F16Args& a, int b) { return max(min(min(a.lens[b], a.s.Ncap), a.max_len), 0); }
+
+// fp16_even_kernel: the tiles of all pairs numbered through, sequence after sequence (at most 64 of them: a lane per sequence), and
+// the tiles a workgroup takes.  A pair of n tiles has room for ceil(n / 4) partial results.  Shares of eight tiles and more may begin
+// anywhere: at most (n - 2) / share + 2 parts.  Below that every pair begins at a multiple of four (its last places may be empty) and
+// shares are a multiple of four: at most one part per four.
+constexpr int kFEvenSeqs = 64;
+struct F16Tiles {
+    int len, end;   // of sequence `lane`: its length, the tiles up to and with it
+    int share, unit;
+    __device__ __forceinline__ F16Tiles(const F16Args& a)
+    {
+        const int lane = threadIdx.x & 63;
+        len = lane < a.s.B ? fp16_len(a, lane) : 0;
+        unit = 1;
+        end = wave_scan_add(tiles(len) * a.s.Hkv);
+        share = (wave_read(end, 63) + a.workgroups - 1) / a.workgroups;
+        if (share < 8) {
+            unit = 4;
+            end = wave_scan_add(tiles(len) * a.s.Hkv);
+            share = (wave_read(end, 63) + 4 * a.workgroups - 1) / (4 * a.workgroups) * 4;
+        }
+    }
+    __device__ __forceinline__ int tiles(int n) const { return (n + kFTile * unit - 1) / (kFTile * unit) * unit; }
+    __device__ __forceinline__ int before(int b) const { return b > 0 ? wave_read(end, b - 1) : 0; }   // b uniform
+    __device__ __forceinline__ int len_of(int b) const { return wave_read(len, b); }
+    __device__ __forceinline__ int sequence_of(int tile) const { return __builtin_popcountll(__ballot(end <= tile)); }
+};
 
 __device__ __forceinline__ void store_result(const F16Args& a, size_t at, float v)
 {
@@ -78,32 +111,31 @@ __device__ __forceinline__ void store_result(const F16Args& a, size_t at, float 
 // Measured against one row of 16 lanes per token with shuffled sums: B 8, 32/8 heads, up to 16000 tokens 137 -> 65 us, 32768
 // 241 -> 176; B 8, 64/8, 8192 110 -> 58; B 1, 32 heads, 1024 29 -> 13; single heads at 4096 and 8192 as before (memory).
 // Error against 64 bits over these ranges 3e-7 .. 6e-7, as before (one running sum of the logits: a third more).
-// ONE: the launch has one chunk per sequence: the workgroup writes the result itself.
-template <int G, bool ONE>
-__global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
+// ONE: the workgroup has the whole sequence and writes the result itself; else a partial result into place `split` of the pair.
+// LONG: ranges may be long: rows are added four at a time in a sum of their own, so that the running sums are rounded a quarter as
+// often (error against 64 bits over B 2..16, 700..16384 tokens, groups of four and eight 4.1e-7; one row at a time 4.3e-7, up to 5.5e-7 at
+// 16 x 16384; chunks of at most 1024 tokens one row at a time 4.2e-7).
+// t_begin, t_end: the wave's tokens; some wave of the workgroup has some.
+template <int G>
+struct F16Shared {
+    alignas(16) float p[kFWaves][kFTile][G];
+    float red[kFWaves][G][kD];
+    float max[kFWaves][G], z[kFWaves][G];
+};
+template <int G, bool ONE, bool LONG>
+__device__ __forceinline__ void fp16_range(const F16Args& a, int b, int h, int split, int t_begin, int t_end, int len, F16Shared<G>& sm)
 {
-    __shared__ __align__(16) float p_s[kFWaves][kFTile][G];
-    __shared__ float red_s[kFWaves][G][kD];
-    __shared__ float max_s[kFWaves][G], z_s[kFWaves][G];
-
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int split = blockIdx.x ^ (((b * a.s.Hkv + h) >> a.turn_shift) & a.turn_mask);
+    auto& p_s = sm.p;
+    auto& red_s = sm.red;
+    auto& max_s = sm.max;
+    auto& z_s = sm.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, j = lane >> 4;   // logits: token n of 16 (then query head n), channels 8j .. 8j+7 of 32; V: row j of 4, channels 8n .. 8n+7
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);
-    const int c0 = split * a.chunk;
     const size_t bh = size_t(b) * Hkv + h, hq0 = size_t(b) * Hq + size_t(h) * G;
-    if (c0 >= len) {
-        if (ONE)   // an empty sequence attends to nothing: zeros
-            for (int idx = tid; idx < G * kD; idx += 64 * kFWaves) store_result(a, hq0 * kD + idx, 0.0f);
-        return;
-    }
     // rows at or past len are out of range: zeros, nothing fetched
     const __amdgpu_buffer_rsrc_t rs_k = make_rsrc(a.k + bh * Ncap * kD, uint32_t(len) * (kD * 2u));
     const __amdgpu_buffer_rsrc_t rs_v = make_rsrc(a.v + bh * Ncap * kD, uint32_t(len) * (kD * 2u));
-    const int t_begin = c0 + wave * (a.chunk / kFWaves), t_end = min(t_begin + a.chunk / kFWaves, len);   // the wave's tokens
-
     u32x4_t kf[2][4], vf[8];
     auto fetch_k = [&](int t0) {
 #pragma unroll
@@ -164,29 +196,43 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
                 for (int i = 0; i < 8; ++i) acc[g][i] *= sg;
             }
         }
+        float zt = LONG ? 0.0f : z;
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float p = __builtin_amdgcn_exp2f((s[u][i] - m_run) * a.c);
-                z += p;
+                zt += p;
                 if (n < G) p_s[wave][16 * u + 4 * j + i][n] = p;
             }
+        z = LONG ? z + zt : zt;
         __builtin_amdgcn_wave_barrier();
+        constexpr int kRows = LONG ? 4 : 1;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            float p[G];
+        for (int k0 = 0; k0 < 8; k0 += kRows) {
+            float p[kRows][G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) p[g] = p_s[wave][4 * k + j][g];
-            const uint32_t w[4] = {vf[k].x, vf[k].y, vf[k].z, vf[k].w};
+            for (int k = 0; k < kRows; ++k)
 #pragma unroll
-            for (int g = 0; g < G; ++g)
+                for (int g = 0; g < G; ++g) p[k][g] = p_s[wave][4 * (k0 + k) + j][g];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[g][2 * i] = fmaf(p[g], lo_half(w[i]), acc[g][2 * i]);
-                    acc[g][2 * i + 1] = fmaf(p[g], hi_half(w[i]), acc[g][2 * i + 1]);
+            for (int g = 0; g < G; ++g) {
+                float t[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) t[i] = LONG ? 0.0f : acc[g][i];
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) {
+                    const uint32_t w[4] = {vf[k0 + k].x, vf[k0 + k].y, vf[k0 + k].z, vf[k0 + k].w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        t[2 * i] = fmaf(p[k][g], lo_half(w[i]), t[2 * i]);
+                        t[2 * i + 1] = fmaf(p[k][g], hi_half(w[i]), t[2 * i + 1]);
+                    }
                 }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[g][i] = LONG ? acc[g][i] + t[i] : t[i];
+            }
         }
         fetch_v(t0 + kFTile);
     }
@@ -208,7 +254,7 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
     __syncthreads();
     for (int idx = tid; idx < G * kD; idx += 64 * kFWaves) {
         const int g = idx / kD, d = idx % kD;
-        float M = max_s[0][g];   // wave 0 has tokens
+        float M = max_s[0][g];
 #pragma unroll
         for (int w = 1; w < kFWaves; ++w) M = fmaxf(M, max_s[w][g]);
         float o = 0.0f, zs = 0.0f;
@@ -231,14 +277,63 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
     }
 }
 
+template <int G, bool ONE>
+__global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
+{
+    __shared__ F16Shared<G> sm;
+    const int h = blockIdx.y, b = blockIdx.z, split = blockIdx.x ^ (((b * a.s.Hkv + h) >> a.turn_shift) & a.turn_mask);
+    const int len = fp16_len(a, b), c0 = split * a.chunk;
+    if (c0 >= len) {
+        if (ONE)   // an empty sequence attends to nothing: zeros
+            for (int idx = threadIdx.x; idx < G * kD; idx += 64 * kFWaves) store_result(a, (size_t(b) * a.s.Hq + size_t(h) * G) * kD + idx, 0.0f);
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), per = a.chunk / kFWaves;
+    fp16_range<G, ONE, false>(a, b, h, split, c0 + wave * per, min(c0 + (wave + 1) * per, len), len, sm);
+}
+
+// More work than one round of workgroups: every workgroup of that round takes the same number of tiles of 32 tokens, wherever
+// they lie.  The tiles of all (sequence, KV head) pairs are numbered through, sequence after sequence; workgroup i takes tiles i *
+// share .. + share - 1, a range of one pair or the end of one and the beginning of the next.  Chunks by the shape end in a last round
+// that is nearly empty, all the more where lengths differ (times: launch_fp16).  Bound by memory: 5.8 TB/s where lengths are ragged,
+// 6.2 where they are equal.
+template <int G>
+__global__ __launch_bounds__(64 * kFWaves, f_resident(G)) void fp16_even_kernel(F16Args a)
+{
+    __shared__ F16Shared<G> sm;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), Hkv = a.s.Hkv;
+    const F16Tiles all(a);
+    const int total = all.before(64), share = all.share;
+    int tile = blockIdx.x * share;
+    const int tile_end = min(tile + share, total);
+    if (tile >= tile_end) return;   // uniform
+    for (int b = all.sequence_of(tile); tile < tile_end; ++b) {
+        const int len = all.len_of(b), per = all.tiles(len), first = all.before(b);
+        while (tile < tile_end && tile < first + Hkv * per) {   // the pairs of sequence b
+            const int h = (tile - first) / per, pair0 = first + h * per, t0 = tile - pair0, n = min(tile_end, pair0 + per) - tile;
+            fp16_range<G, false, true>(a, b, h, tile / share - pair0 / share, (t0 + n * wave / kFWaves) * kFTile, min((t0 + n * (wave + 1) / kFWaves) * kFTile, len), len, sm);
+            tile += n;
+            if (tile < tile_end) __syncthreads();   // the LDS areas are written again
+        }
+    }
+}
+
 // merge the chunks of one query head: rescale each to the global max (a wave holds 64 chunks' weights; 16 rows in flight)
 __global__ __launch_bounds__(kD) void fp16_combine_kernel(F16Args a)
 {
     __shared__ float w_s[kD];
     const int hq_i = blockIdx.x, b = blockIdx.y, d = threadIdx.x, lane = d & 63;
-    const int len = min(min(a.lens[b], a.s.Ncap), a.max_len);
+    const int len = fp16_len(a, b);
     const size_t hq = size_t(b) * a.s.Hq + hq_i;
-    const int used = (len + a.chunk - 1) / a.chunk;
+    int used;
+    if (a.workgroups) {   // uniform
+        const F16Tiles all(a);
+        const int share = all.share, per = all.tiles(len);
+        const int pair0 = all.before(b) + (hq_i / (a.s.Hq / a.s.Hkv)) * per;
+        used = per > 0 ? (pair0 + per - 1) / share - pair0 / share + 1 : 0;
+    } else {
+        used = (len + a.chunk - 1) / a.chunk;
+    }
     const float *pm = a.partM + hq * a.nsplit, *pz = a.partZ + hq * a.nsplit, *po = a.partO + hq * a.nsplit * kD + d;
     float M = -INFINITY;
     for (int s = lane; s < used; s += 64) M = fmaxf(M, pm[s]);
@@ -274,8 +369,8 @@ static hipError_t launch_fp16_g(F16Args a, hipStream_t st)
     // Workgroups are dealt to the eight XCDs in turn, and inside an XCD to its four shader engines.  Where the chunks of a pair are
     // a multiple of two, four ... 32, the first chunks of all pairs would fall on 16, 8 ... one of the 32 engines; and where
     // sequences are shorter than their bound, those are the only ones with work.  So chunks change places inside groups of that
-    // many, by pair: single heads 8 x 32, 8192 tokens of room, 1029 stored 122 -> 53 us; 16 x 32, 1024, 133 stored 27 -> 15.  (Pairs
-    // varying fastest instead: even there, but full sequences 3..17 % slower.)
+    // many, by pair: single heads 16 x 32, 1024 of room, 133 stored 27 -> 15 us.  (Pairs varying fastest instead: even there, but
+    // full sequences 3..17 % slower.)
     const int two = __builtin_ctz(grid.x | 32u);
     a.turn_mask = (1 << two) - 1;
     a.turn_shift = 5 - two;
@@ -283,7 +378,10 @@ static hipError_t launch_fp16_g(F16Args a, hipStream_t st)
         hipLaunchKernelGGL((fp16_kernel<G, true>), grid, block, 0, st, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((fp16_kernel<G, false>), grid, block, 0, st, a);
+    if constexpr (G >= 4) {
+        if (a.workgroups) hipLaunchKernelGGL(fp16_even_kernel<G>, dim3(a.workgroups), block, 0, st, a);
+    }
+    if (!a.workgroups) hipLaunchKernelGGL((fp16_kernel<G, false>), grid, block, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     hipLaunchKernelGGL(fp16_combine_kernel, dim3(a.s.Hq, a.s.B), dim3(kD), 0, st, a);
     return hipGetLastError();
@@ -299,6 +397,16 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.nsplit = s.Ncap / kFMinChunk;
     a.chunk = f_chunk(s, max_len);
     a.max_len = max_len;
+    // More chunks than one round of workgroups: even shares, where they are not cut by the pairs' ends too often.  Chunks / even, us:
+    // groups of four, ragged (a quarter to all of the bound): 16 pairs 8192 20.9/20.2, 40 pairs 4096 22.8/21.4, 64 pairs 16128
+    // 61..70/59..66, 128 pairs 16384 141/128; full: 8 pairs 16384 25.7/23.8, 32 pairs 54.9/55.8, 128 pairs 187/184, 64 pairs 32768 176/176;
+    // but 128 pairs 1024 17.4/18.5, 2048 full 34.0/36.9, 256 pairs 2048 53.7/56.7, 96 pairs 5888 40.3/40.9.  Groups of eight, ragged:
+    // 64 pairs 16384 88/75, 128 pairs 2048 33.7/34.3, 256 pairs 1280 38.3/38.8; full: 128 pairs 16384 194/183.  Single heads and groups
+    // of two lose (8 x 32 of 4096 88/94).
+    const int G = s.Hq / s.Hkv, round = f_resident(G) * compute_units();
+    const long pairs = long(s.B) * s.Hkv;
+    const bool even = ((G == 8 && max_len >= 32 * pairs) || (G == 4 && max_len >= 64 * pairs)) && s.B <= kFEvenSeqs && a.chunk < max_len && pairs * ((max_len + a.chunk - 1) / a.chunk) > round;
+    a.workgroups = even ? round : 0;
     const size_t bhq = size_t(s.B) * s.Hq;
     char* p = reinterpret_cast<char*>(ws);
     a.partO = reinterpret_cast<float*>(p);
@@ -308,7 +416,7 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.partZ = reinterpret_cast<float*>(p);
     switch (s.Hq / s.Hkv) {
         case 1: return launch_fp16_g<1>(a, st);
-        case 2: return launch_fp16_g<2>(a, st);
+        case 2: return launch_fp16_g<2>(a, st);   // a.workgroups is 0 for these two
         case 4: return launch_fp16_g<4>(a, st);
         case 8: return launch_fp16_g<8>(a, st);
         default: return hipErrorInvalidValue;

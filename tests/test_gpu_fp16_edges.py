@@ -105,3 +105,32 @@ def test_fp16_walks_of_several_tiles_match_textbook(G, B, Hkv, Ncap, lens):
     ref = O.fp16_attention(T.bits(k), T.bits(v), lens, T.bits(q))
     assert np.abs(got - ref).max() <= T.MAX_ABS and T.rel_l2(got, ref) <= T.REL_L2
     assert not got[lens == 0].any()
+
+
+@pytest.mark.parametrize("G,B,Hkv,Ncap,lens", [
+    (4, 2, 3, 32768, [32768, 31999]),                                     # shares of eight tiles that begin anywhere
+    (4, 3, 2, 16384, [16384, 0, 40]),                                     # shares of four tiles, pairs at multiples of four
+    (8, 64, 2, 2048, [2048, 0, 0, 1, 33, 129, 2047, 0] * 8),              # a lane per sequence, empty ones between
+    (8, 64, 8, 512, [0] * 63 + [512]),                                    # hardly any work: most workgroups have no tile
+    (8, 65, 2, 2048, [2048, 0, 0, 1, 33, 129, 2047, 0] * 8 + [77]),       # one sequence more: chunks
+])
+def test_fp16_even_shares_match_textbook(G, B, Hkv, Ncap, lens):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import akv_testlib as T
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A
+    O.build()
+    print(f"fp16 attention, even shares: G{G} {B}x{Hkv} Ncap {Ncap}", flush=True)
+    g = torch.Generator().manual_seed(G + B)
+    q = torch.randn(B, Hkv * G, 128, generator=g).half()
+    k, v = torch.randn(B, Hkv, Ncap, 128, generator=g).half(), torch.randn(B, Hkv, Ncap, 128, generator=g).half()
+    k *= torch.linspace(0.05, 2.0, Ncap)[:, None].half()
+    lens = np.asarray(lens, np.int32)
+    args = (k.to(DEV), v.to(DEV), torch.from_numpy(lens).to(DEV), q.to(DEV))
+    out = A.akv_fp16_decode_attention(*args)
+    got = out.cpu().numpy().astype(np.float64)
+    ref = O.fp16_attention(T.bits(k), T.bits(v), lens, T.bits(q))
+    assert np.abs(got - ref).max() <= T.MAX_ABS and T.rel_l2(got, ref) <= T.REL_L2
+    assert not got[lens == 0].any()
+    assert torch.equal(out, A.akv_fp16_decode_attention(*args))
