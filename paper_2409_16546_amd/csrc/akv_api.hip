@@ -309,9 +309,9 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         // 8192; 32 single heads at 4096: 31.0 -> 28.4; from 8 waves per unit on whole blocks are 1-5 % faster, in between equal)
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
         a.kunit = waves < 3L * cus && G < 8 ? akv::kMinUnit : akv::kTB;
-        // groups of eight heads: two waves per block instead, four heads each, below six waves per unit (24 pairs: 73.3 -> 69.5
-        // us at 13000 tokens, 56.7 -> 55.7 at 8000; 8 pairs 4096: 40.7 (half blocks) -> 39.4; 32 pairs 16384, 8 per unit: 89.9 -> 92.1)
-        a.khs = G == 8 && waves < 6L * cus ? 2 : 1;
+        // groups of eight heads: two waves per block instead, four heads each, below 3.5 waves per unit (one / two, us: 8 pairs 2048
+        // 35.8/33.8, 8192 44.4/41.8, 32 pairs 4096 (2 per unit) 43.9/41.8; 24 pairs 13000 (4.8) 65.1/66.7, 32 pairs 16384 (8) 76/85)
+        a.khs = G == 8 && waves < 7L * cus / 2 ? 2 : 1;
     }
     char* ws = static_cast<char*>(workspace);
     a.logits = reinterpret_cast<float*>(ws + w.logits);

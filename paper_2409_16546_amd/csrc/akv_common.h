@@ -212,6 +212,7 @@ __device__ __forceinline__ void assemble8(uint32_t H0, uint32_t H1, uint32_t M, 
 // kSkip instead of a branch, and every load of a loop can be issued unconditionally and early.
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr uint32_t kSkip = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
 {

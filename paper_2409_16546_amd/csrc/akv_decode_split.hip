@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
         const u32x4_t none[6] = {zero4, zero4, zero4, zero4, zero4, zero4};
         float lg[GW][TPL];
         const size_t hq0 = size_t(b) * Hq + size_t(h) * G + (wave_u % HS) * GW;
-        k_tile<GW, HS == 1, TPL>(a, b, h, hq0, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
+        k_tile<GW, HS == 1, TPL>(a, b, h, hq0, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0], nullptr, 0, (wave_u % HS) * GW);
         if (lane == 0)
 #pragma unroll
             for (int g = 0; g < GW; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + unit] = tm[g];

@@ -53,7 +53,6 @@ struct F16Args {
 };
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // the value of the lane 16 / 32 further (mod the pairs of rows / halves) folded in: op over lanes with the same lane % 16, in all of them
 template <typename F>

@@ -13,14 +13,15 @@ namespace akv {
 template <int G>
 struct KShared {
     static constexpr bool kNew = false;
+    static constexpr bool kMatrix = G == 8;   // k_tile multiplies on the matrix cores
     int emax[2][G];                     // largest addend exponent per query head, of the columns of wave 0 / wave 1
     uint64_t need_mid[2], need_lo[2];   // bit d%64 of word d/64: column d is read at level >= 1 / = 2
+    alignas(16) float q[G][kD + 4];     // as binary32, for kMatrix and kNew (rows of neighbouring heads four banks apart)
 };
 // ... of a kernel that appends a token itself
 template <int G>
 struct KSharedNew : KShared<G> {
     static constexpr bool kNew = true;
-    float q[G][kD];
     float knew[kD];                     // the new token's K row as it will be read at the column levels
     float new_logit[G];                 // q . knew, accumulated in channel order
 };
@@ -71,7 +72,7 @@ __device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const float qf = half_bits_to_float(in.qbits[g]);
-            if constexpr (KS::kNew) ks.q[g][tid] = qf;
+            if constexpr (KS::kNew || KS::kMatrix) ks.q[g][tid] = qf;
             P[g] = qf * cmf;                             // exact: 11-bit x 11-bit significands
             // the maximum over the wave's 64 columns in the vector ALU (LDS atomics of 64 lanes on one address take a
             // cycle per lane of the LDS unit that all workgroups of the compute unit share)
@@ -200,11 +201,11 @@ __device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, in
 // lds_lg: where a kernel keeps the logits of its (sequence, KV head) in LDS (query head g at lds_lg + g * lds_stride
 // floats, token t at index t), or NULL: they go to a.logits.  With LDS logits a.logits is written as well only if it
 // is the caller's export buffer (a.dbg.logits).
-// hq0: first of the G consecutive query heads whose logits are computed (all heads of the group, or part of it).
+// hq0, g0: first of the G consecutive query heads whose logits are computed (all heads of the group, or part of it), and its place in the group.
 template <int G, bool NT = true, int TPL = 4, typename KS>
 __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t hq0, int unit, int len, const KS& ks,
                                        float (&tile_max)[G], const u32x4_t (&pre)[6], bool use_pre,
-                                       float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0)
+                                       float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0, int g0 = 0)
 {
     static_assert(TPL == 4 || TPL == 2, "");
     constexpr int U = 32 / TPL;       // columns per group
@@ -236,6 +237,20 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
 #pragma unroll
     for (int g = 0; g < G; ++g) qw[g] = (const uint32_t __attribute__((address_space(4)))*)(uintptr_t)(a.q + (hq0 + g) * kD);
     const uint32_t voff = uint32_t(lane) * 16;
+    // Groups of eight heads: the multiply-adds on the matrix cores, a column at a time.  One 4x4x1 product is sixteen blocks of four
+    // lanes: its rows are four query heads, its columns the four lanes' tokens, and a lane receives its own token's sums for the four
+    // heads -- one binary32 multiply-add per element and column, in channel order, the same bits as the vector ALU's.  235 vector
+    // instructions a group of columns for four heads become 83 and 32 products of half a multiply-add's time.  Us a call, 64/8 heads:
+    // B 4 16384 tokens 79.9 -> 75.8, B 8 8192 78.6 -> 74.7, B 3 13000 64.1 -> 62.3, B 1 8192 42.3 -> 41.8.  Groups of four are bound by
+    // memory: -2 to +2 %, left on the vector ALU.
+    constexpr bool MX = KS::kMatrix;
+    static_assert(!MX || G % 4 == 0, "four heads per product");
+    constexpr int S = MX ? G / 4 : 1;
+    f32x4_t dx[MX ? TPL : 1][S];
+#pragma unroll
+    for (int i = 0; i < (MX ? TPL : 1); ++i)
+#pragma unroll
+        for (int s = 0; s < S; ++s) dx[i][s] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     const uint32_t hoff = k_hi_lane_offset<TPL>(unit, len);
     const uint32_t col = uint32_t(lane) / (2 * TPL);   // the column of the group this lane fetches nibbles of (32 tokens of it)
     const bool nib_in = unit * kUnit + int(uint32_t(lane) % (2 * TPL)) * 32 < len;   // some of the lane's 32 tokens are inside the sequence
@@ -291,6 +306,12 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
             hh[u] = *reinterpret_cast<const word_t*>(stage + u * kUnit + lane * TPL);
             ll[u] = *reinterpret_cast<const word_t*>(stage + 2048 + u * kUnit + lane * TPL);
         }
+        f32x4_t qx[S][U / 4];   // q of head lane % 4 (+ 4 s), the group's columns
+        if constexpr (MX)
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int v = 0; v < U / 4; ++v) qx[s][v] = *reinterpret_cast<const f32x4_t*>(&ks.q[g0 + 4 * s + (lane & 3)][d0 + 4 * v]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float k[TPL];
@@ -301,6 +322,13 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
                 const uint32_t p1 = __builtin_amdgcn_perm(hh[u], ll[u], 0x07030602u);   // tokens (2,3)
                 k[2] = lo_half(p1);
                 k[3] = hi_half(p1);
+            }
+            if constexpr (MX) {
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int i = 0; i < TPL; ++i) dx[i][s] = __builtin_amdgcn_mfma_f32_4x4x1f32(qx[s][u / 4][u % 4], k[i], dx[i][s], 0, 0, 0);
+                continue;
             }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -340,6 +368,12 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
         if (d0 + 2 * U < kD) compute(C, d0 + 2 * U);
         issue(C, d0 + 5 * U);
     }
+
+    if constexpr (MX)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < TPL; ++i) acc[g][i] = dx[i][g / 4][g % 4];
 
     // ---- logits out, tile maxima -----------------------------------------------------------------
     // (with the non-temporal hint, here and where the V kernel of a group of four or eight reads them: B 16, 32 heads, 8193 tokens

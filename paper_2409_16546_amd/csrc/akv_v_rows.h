@@ -389,7 +389,6 @@ constexpr int kSRows = 16;        // rows of a wave's batch: lane -> row lane / 
 // (v_word_turn), so that neither side has bank conflicts.  Two buffers alternate by round.
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 struct VShare {
     static constexpr int kRows = kVWaves * kSRows;   // rows of a round
     alignas(16) u32x4_t vr[2][kRows][16];

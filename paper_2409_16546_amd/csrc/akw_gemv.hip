@@ -41,7 +41,6 @@ struct GemvArgs {
 };
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // Sums over the 8 row lanes of a wave (lane / 8) in the vector ALU, two values per exchange: afterwards a lane holds the
 // totals of columns row_lane_column(lane), + 1 of its 16, v[0] and v[1].  (24 instead of 48 exchanges through the LDS unit for

@@ -92,7 +92,7 @@ def test_selection_of_many_heads(T):
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_token_split_with_whole_blocks_per_wave(T, G):
     """Groups of one, two and four: enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks);
-    groups of eight still take two waves per block here.  More pairs than those the V kernel cuts into short chunks; ragged lengths
+    groups of eight one for all eight heads.  More pairs than those the V kernel cuts into short chunks; ragged lengths
     down to one token."""
     from paper_2409_16546_amd import workloads
     lens = [2048, 1, 1027, 300]
@@ -103,8 +103,8 @@ def test_token_split_with_whole_blocks_per_wave(T, G):
 
 
 def test_token_split_with_one_wave_per_block_of_eight_heads(T):
-    """Groups of eight, 128 pairs of 12 blocks: six waves per compute unit, from where on a wave of the K kernel takes a block for all
-    eight heads."""
+    """Groups of eight, 128 pairs of 12 blocks: six waves per compute unit; a wave of the K kernel takes a block for all eight heads
+    (two waves share one below 3.5 per unit)."""
     from paper_2409_16546_amd import workloads
     lens = [3072, 1025, 256, 2817]
     print(f"token-split path, one wave per block: G8 lens {lens}", flush=True)
