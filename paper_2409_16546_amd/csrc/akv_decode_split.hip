@@ -68,7 +68,8 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
 {
     constexpr int kWaves = NT / 64, kAhead = 32 / kWaves;   // kAhead: blocks of a wave in flight
     __shared__ MidShared ms;
-    __shared__ float red_s[kWaves];
+    constexpr int kBest = 1024;
+    __shared__ float red_s[kWaves], best_s[kBest];
 
     const int hq_i = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -80,15 +81,22 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const int kk = a.topk < len ? a.topk : len;
     const float* tm = a.tilemax + hq * (Ncap / kMinUnit);
     const int upb = kTB / a.kunit;   // units of the K kernel per block: 1 or 2
-    auto block_max = [&](int i) {
+    auto block_max_of = [&](int i) {
         float m = tm[i * upb];
         if (upb == 2 && (2 * i + 1) * kMinUnit < len) m = fmaxf(m, tm[2 * i + 1]);
         return m;
     };
+    // the maxima are looked at up to four times, each a round trip in the chain: those of the first kBest blocks stay in LDS (B 1, 32/8,
+    // 8192 tokens 34.8 -> 34.1 us a call, B 4 45.8 -> 45.0, others 0 to 0.6 %)
+    auto block_max = [&](int i) { return i < kBest ? best_s[i] : block_max_of(i); };
 
     // ---- the global max logit (exact, order-free) and the bound of the cut
     float m = -INFINITY;
-    for (int i = tid; i < nblk; i += NT) m = fmaxf(m, block_max(i));
+    for (int i = tid; i < nblk; i += NT) {
+        const float bm = block_max_of(i);
+        if (i < kBest) best_s[i] = bm;
+        m = fmaxf(m, bm);
+    }
     m = wave_max(m);
     if (lane == 0) red_s[wave] = m;
     if (tid < kBuckets) ms.cnt[tid] = 0;
