@@ -92,6 +92,7 @@ struct DecodeArgs {
     float* partO;
     float* partZ;
     int kunit;           // tokens per wave of the K kernel of the token-split path: kTB or kMinUnit
+    int lg_nt;           // the K kernel of one or two heads stores its logits with the non-temporal hint
     int khs;             // waves per unit there, each for its share of the query heads: 1 or 2
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
     int vslots;          // chunks per (sequence, KV head) in partO and partZ

@@ -13,6 +13,7 @@ namespace akv {
 template <int G>
 struct KShared {
     static constexpr bool kNew = false;
+    static constexpr int kHeads = G;
     static constexpr bool kMatrix = G == 8;   // k_tile multiplies on the matrix cores
     int emax[2][G];                     // largest addend exponent per query head, of the columns of wave 0 / wave 1
     uint64_t need_mid[2], need_lo[2];   // bit d%64 of word d/64: column d is read at level >= 1 / = 2
@@ -376,8 +377,11 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
             for (int i = 0; i < TPL; ++i) acc[g][i] = dx[i][g / 4][g % 4];
 
     // ---- logits out, tile maxima -----------------------------------------------------------------
-    // (with the non-temporal hint, here and where the V kernel of a group of four or eight reads them: B 16, 32 heads, 8193 tokens
-    // with append 283.5 -> 274 us a call, B 8, 32/8, 32768 171 -> 160, B 4, 32/8, up to 131072 271 -> 265)
+    // Written for other workgroups they go with the non-temporal hint, which is also how the V kernel of a group of four or eight reads
+    // them: B 8, 32/8, 32768 tokens 171 -> 160 us a call, B 4, 32/8, up to 131072 271 -> 265; of one or two heads where there are many
+    // (a.lg_nt; 17 MB, B 16, 32 heads, 8193 with append 283.5 -> 274; 8 MB equal; 4 MB, which the caches hold until they are read
+    // again: B 4, 32 heads, 8192 84.2 -> 85.1).  The head kernel reads its own soon after: without.
+    const bool lg_nt = !KS::kNew && (KS::kHeads >= 4 || a.lg_nt);
     const int t0 = unit * kUnit + lane * TPL;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -389,8 +393,12 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
         for (int i = 0; i < TPL; ++i) w[i] = float_bits(acc[g][i]);
         if (lds_lg) *reinterpret_cast<vec_t*>(lds_lg + g * lds_stride + t0) = w;
         if (!lds_lg || a.dbg.logits) {
-            if constexpr (TPL == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs_lg, uint32_t(t0) * 4u, 0, kAuxNt);
-            else __builtin_amdgcn_raw_buffer_store_b64(w, rs_lg, uint32_t(t0) * 4u, 0, kAuxNt);
+            auto store = [&](auto aux) {
+                if constexpr (TPL == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs_lg, uint32_t(t0) * 4u, 0, aux());
+                else __builtin_amdgcn_raw_buffer_store_b64(w, rs_lg, uint32_t(t0) * 4u, 0, aux());
+            };
+            if (lg_nt) store(std::integral_constant<int, kAuxNt>());   // uniform
+            else store(std::integral_constant<int, 0>());
         }
         float m = -INFINITY;
 #pragma unroll
