@@ -14,8 +14,8 @@ namespace akv {
 
 // K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one unit of 64*TPL tokens (k_tile) for G / HS
 // of the query heads and leaves its logits and the unit's maxima in the workspace.  HS = 2: neighbouring waves take the same
-// unit for half of the heads each (its bytes come from the caches the second time): a group of eight heads is bound by its
-// multiply-adds, and where a call has fewer units than SIMDs a second wave per unit halves them.
+// unit for half of the heads each (its bytes come from the caches the second time): in calls of a group of eight heads with fewer
+// units than SIMDs, whose time is one wave's walk through its unit.
 template <int G, int TPL, int HS>
 __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
 }
 
 // Workgroup = kVWaves waves, one (sequence, KV head, chunk of a.vchunk tokens); wave w takes the batches of rows
-// w, w + kVWaves, ... of the chunk.  Groups of four or eight query heads run v_rows in its shared mode: every wave
+// w, w + kVWaves, ... of the chunk.  Groups of four or eight query heads run v_rows_shared: every wave
 // fetches and assembles its rows once, the rows pass through LDS, and the sums over rows for all heads of the group
 // are matrix products on the matrix cores.
 template <int G> constexpr bool v_shared() { return G >= kVWaves; }
@@ -374,8 +374,7 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
 }
 
 // Workgroups of split_v_kernel<G> per compute unit that the chunks are sized for: what the registers leave room for (single heads
-// 117, groups of two 156; groups of four 106 and 38 KB of LDS).  Groups of eight (74 registers, 19.6 KB) have room for five; their
-// chunks are sized for four.
+// 117, groups of two 156; groups of four 104 and of eight 112, with 38 KB of LDS).
 int split_v_workgroups_per_cu(int G) { return G == 2 ? 3 : 4; }
 
 template <int G>
