@@ -3,6 +3,7 @@
 // bits in separately contiguous planes; "Quantization of K-Cache": K_colmax is kept while storing.
 #include "akv_append_plan.h"
 #include "akv_common.h"
+#include "akv_unpack_plan.h"
 
 namespace akv {
 
@@ -390,18 +391,13 @@ __global__ __launch_bounds__(256) void unpack_kernel(akv_cache c, uint16_t* __re
 
 hipError_t launch_unpack(const akv_cache& c, uint16_t* k_out, uint16_t* v_out, hipStream_t st)
 {
-    const size_t blocks = size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB);
-    auto launch = [&](auto kernel, int per) { hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks * per)), dim3(256), 0, st, c, k_out, v_out); };
-    // both: many short V workgroups between those of K keep reads and writes of the two mixed, but cost a launch that is over in a few
-    // rounds (one / sixteen per block of V, us: 256 blocks 13.7/15.4, 512 25.3/25.8, 1024 48.6/46.9, 2048 93/89, 4096 188/176, 8192 380/350)
-    if (k_out && v_out) {
-        if (blocks >= 1024) launch(unpack_kernel<1, 16>, 17);
-        else launch(unpack_kernel<1, 1>, 2);
-    } else if (k_out) {
-        launch(unpack_kernel<1, 0>, 1);
-    } else {   // one / two / four / eight per block: 256 blocks 7.5/7.5/7.5/7.6, 512 12.9/12.6/12.9/13.5, 4096 91/86/84/86
-        launch(unpack_kernel<0, 2>, 2);
-    }
+    const UnpackPlan p = unpack_plan(size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB), k_out != nullptr, v_out != nullptr);
+    if (!p.workgroups) return hipErrorInvalidConfiguration;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)p.workgroups), dim3(256), 0, st, c, k_out, v_out); };
+    if (!k_out) launch(unpack_kernel<0, 2>);
+    else if (!v_out) launch(unpack_kernel<1, 0>);
+    else if (p.v_parts == 1) launch(unpack_kernel<1, 1>);
+    else launch(unpack_kernel<1, 16>);
     return hipGetLastError();
 }
 
