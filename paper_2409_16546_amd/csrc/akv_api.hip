@@ -201,9 +201,9 @@ void* static_scratch_for_current_device(hipStream_t s)
 // Head-per-workgroup or token-split kernels, when the caller leaves the choice to the library.  One head kernel
 // workgroup occupies a compute unit, so `pairs` (sequence, KV head) pairs run in ceil(pairs / CUs) rounds of equal
 // length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
-// that the single launch outweighs idle units; for single query heads also at two and more nearly full rounds, as long as the
-// logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written bytes cost several times
-// what read bytes cost).
+// that the single launch outweighs idle units; for single query heads also at two nearly full rounds, and at more whose last one is
+// full enough, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written
+// bytes cost several times what read bytes cost).
 // The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
 // path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step
 // (append and attention in one call) costs it a launch more; the head kernel stores the new token itself.  So the lines lie
@@ -218,13 +218,19 @@ void* static_scratch_for_current_device(hipStream_t s)
 //                 46.2/55.6; 192 pairs 1024 43.8/44.7, 2048 62.2/60.1 and 43.7/50.8, step 63.2/67.2; 200 pairs 2048 63.0/66.5; 224 pairs 4096 106/113 and 56/88; 256 pairs 6144 166/165 and 65/104
 //   two rounds of single heads, step and attention over full sequences and partly full ones: 448 pairs 10000 298/307, 12288 354/367;
 //                 512 pairs 8448 291/300, 10000 321/335 (half full 172/236), 12288 384/401, step of 11000 0.7 full 291/323
-//   more rounds   640 pairs 4096 184/190, 768 pairs 4096 197/209, 8192 389/401, 1024 pairs 4096 273/278 (0.4 full 152/199), 1536
-//                 pairs 4096 395/410; but 1024 pairs 2048 172/152, 768 pairs 1024 79/70
+//   more rounds, full / step / lengths a quarter to all of the bound: an idle part of the last round is shared by all rounds.  4096
+//                 tokens: 640 pairs 191/193, 207/221, 133/155; 860 255/258, 283/291, 170/202; 1100 322/321, 356/363, 218/244; 1312
+//                 374/377, 420/425, 261/286; 1536 400/413; but 1024 pairs 2048 172/152, 768 pairs 1024 79/70.  Above that full
+//                 sequences and steps lose where the last round is less than half full: 5000 tokens 860 pairs 315/302, 337/327, 209/231; 1312
+//                 459/443, 502/474; 6144 860 384/362, 1312 547/515; 8192 860 488/473, 527/508; 1312 742/712, 782/741; 12280 1312
+//                 1047/1008; from half full on they are even: 6144 704 293/300, 311/324, 210/229; 1408 568/570, 607/616, 376/426;
+//                 8192 704 377/371, 409/399, 275/288; 928 485/493, 538/530, 342/367; 1216 638/646, 692/676, 427/458; 1536 757/781
 bool head_path_pays(long pairs, int G, int max_len)
 {
-    const long cus = compute_units();
-    const double rounds = double((pairs + cus - 1) / cus), fill = double(pairs) / (rounds * double(cus));
-    if (rounds > 1) return G == 1 && max_len <= 12288 && (rounds == 2 ? fill >= 0.85 && max_len > 512 : fill >= 0.83 && max_len >= 4096);
+    const long cus = compute_units(), rounds = (pairs + cus - 1) / cus;
+    const double fill = double(pairs) / double(rounds * cus), last = double(pairs - (rounds - 1) * cus) / double(cus);   // of all rounds, of the last one
+    if (rounds == 2) return G == 1 && max_len <= 12288 && fill >= 0.85 && max_len > 512;
+    if (rounds > 2) return G == 1 && max_len <= 12288 && fill >= 0.83 && max_len >= 4096 && (max_len == 4096 || last >= 0.5);
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
     static constexpr Rule g1[] = {{1024, 0.0}, {2048, 0.2}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
                           g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},

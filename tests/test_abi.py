@@ -153,8 +153,12 @@ def test_decode_path_keeps_the_head_kernel_where_sequences_may_be_short(A):
 
 @pytest.mark.parametrize("B,Hkv,N,path", [
     (16, 32, 8448, 3), (14, 32, 12288, 3), (16, 32, 12544, 2),        # two rounds: as long as the logits fit the LDS
-    (24, 32, 4096, 3), (20, 32, 4096, 3), (48, 32, 12288, 3),          # more rounds, the last one full enough
-    (18, 32, 4096, 2), (32, 32, 2048, 2), (24, 32, 3840, 2)])
+    (24, 32, 4096, 3), (20, 32, 4096, 3), (48, 32, 12288, 3),          # more rounds, all of them 83 % full together
+    (18, 32, 4096, 2), (32, 32, 2048, 2), (24, 32, 3840, 2),
+    # a last round that is less than half full (860 pairs 36 %, 1100 30 %, 1312 12 %): up to 4096 tokens only
+    (215, 4, 4096, 3), (275, 4, 4096, 3), (41, 32, 4096, 3),
+    (215, 4, 4352, 2), (215, 4, 8192, 2), (275, 4, 8192, 2), (41, 32, 8192, 2), (41, 32, 12288, 2),
+    (176, 4, 8192, 3), (352, 4, 8192, 3), (20, 32, 8192, 3)])          # from half full on: longer ones too
 def test_decode_path_of_single_heads_in_several_rounds(A, B, Hkv, N, path):
     assert A.akv_decode_path(B, Hkv, Hkv, 128, N) == path
 
