@@ -317,8 +317,8 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         a.kunit = waves < 3L * cus && G < 8 ? akv::kMinUnit : akv::kTB;
         // groups of eight heads: two waves per block instead, four heads each, below 3.5 waves per unit (one / two, us: 8 pairs 2048
         // 35.8/33.8, 8192 44.4/41.8, 32 pairs 4096 (2 per unit) 43.9/41.8; 24 pairs 13000 (4.8) 65.1/66.7, 32 pairs 16384 (8) 76/85)
-        a.lg_nt = long(a.s.B) * a.s.Hq * a.max_len * long(sizeof(float)) >= (8L << 20);   // figures: k_tile
         a.khs = G == 8 && waves < 7L * cus / 2 ? 2 : 1;
+        a.lg_nt = long(a.s.B) * a.s.Hq * a.max_len * long(sizeof(float)) >= (8L << 20);   // of one or two heads; figures: k_tile
     }
     char* ws = static_cast<char*>(workspace);
     a.logits = reinterpret_cast<float*>(ws + w.logits);
