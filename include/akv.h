@@ -259,6 +259,11 @@ akv_status akv_unpack(const akv_cache *cache, uint16_t *k_out, uint16_t *v_out, 
  * k, v: device [B][Hkv][Ncap][D] ("Runtime of AlignedKV", the 16-bit
  * baseline), lens: device int32 [B], q / out as above.  workspace: at least
  * akv_sizes.fp16_workspace bytes, 256-B aligned.
+ * The same call gives the same bits.  The order in which a sequence's sums are
+ * added depends on the shape and on max_len (0 = Ncap) and, where Hq/Hkv is 4
+ * or 8, also on the lengths of the other sequences: between such calls a
+ * result may differ in its last bits (float32 results lie within 1e-6 of the
+ * exact ones, 2-norm over 2-norm, on all data measured).
  */
 akv_status akv_fp16_decode_attention(const akv_shape *shape, const uint16_t *k, const uint16_t *v, const int32_t *lens,
                                      const uint16_t *q, void *out, float scale, int32_t out_dtype, int32_t max_len,

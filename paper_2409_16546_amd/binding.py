@@ -350,7 +350,8 @@ def akv_append_decode_attention(cache: Cache, k_new: torch.Tensor, v_new: torch.
 def akv_fp16_decode_attention(k: torch.Tensor, v: torch.Tensor, lens: torch.Tensor, q: torch.Tensor,
                               out: torch.Tensor | None = None, *, scale: float = 0.0, max_len: int = 0,
                               workspace: torch.Tensor | None = None) -> torch.Tensor:
-    """k, v: fp16 [B, Hkv, Ncap, D]; lens: int32 [B]; q: fp16 [B, Hq, D] -- all on the device."""
+    """k, v: fp16 [B, Hkv, Ncap, D]; lens: int32 [B]; q: fp16 [B, Hq, D] -- all on the device.  The same call gives the same bits; the
+    order of a sequence's sums depends on max_len and, in groups of four and eight, on the lengths of the whole batch."""
     B, Hkv, Ncap, D = k.shape
     Hq = q.shape[1]
     assert k.dtype == v.dtype == q.dtype == torch.float16 and lens.dtype == torch.int32 and v.shape == k.shape

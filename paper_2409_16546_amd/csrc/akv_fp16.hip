@@ -17,7 +17,8 @@ constexpr int kFMinChunk = kFTile * kFWaves;        // tokens per workgroup are 
 // groups of eight four, with two resident), so that ragged lengths even out, and not fewer than one tile per wave.  Timed with 4 / 8 / 12 / 16
 // / 32 workgroups per unit: B 8, 32/8, up to 16000 ragged 77 / 78 / 61 / 65 / 73 us, B 8, 32/8, 32768 178 / 178 / 176 / 182 / 194;
 // B 8, 64/8, 8192 58 / 66 / 66 / 84 / 84; B 8, 32/32, 4096 89 / 85 / 87 / 89 / 92.  By the capacity and not by a bound of the
-// lengths, which then does not change the order of the sums.
+// lengths, so that chunks add up in an order the bound does not change (even shares, fp16_even_kernel, in one that the lengths of
+// the whole batch decide).
 // Except: as many pairs as compute units, and a bound of at most 1024: one workgroup for the whole pair, no merge (chunks / one, us:
 // 256 single heads 512 18.0/13.7, 1024 28.6/24.7, 512 of them 1024 47.5/46.3, a third full 26.0/18.4; 256 groups of four 1024
 // 33.1/26.1; 384 single heads 1024, the one call behind, 37.5/39.1).
