@@ -269,6 +269,11 @@ akv_status akv_fp16_decode_attention(const akv_shape *shape, const uint16_t *k, 
                                      const uint16_t *q, void *out, float scale, int32_t out_dtype, int32_t max_len,
                                      void *workspace, size_t workspace_bytes, void *stream);
 
+/* Which kernels akv_fp16_decode_attention takes for this shape: 1 = one workgroup per (sequence, KV head), 2 = chunks of
+ * tokens and a merge, 3 = even shares of the tokens of all sequences and a merge; max_len as there (0 means Ncap).  Host
+ * computation; 0 on a bad shape. */
+int32_t akv_fp16_path(const akv_shape *shape, int32_t max_len);
+
 /*
  * Measurement aid: read `bytes` bytes (16-byte aligned, a multiple of 16) of
  * device memory at buf once with a plain streaming kernel and discard them.

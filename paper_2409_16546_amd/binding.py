@@ -24,7 +24,8 @@ AKV_NEVENTS = 5
 AKV_STATIC_SCRATCH_BYTES = 48 << 20
 EXPORTS = ["akv_version", "akv_last_error", "akv_layout_sizes", "akv_cache_reset", "akv_append", "akv_check_capacity_sync",
            "akv_workspace_init",
-           "akv_decode_attention", "akv_decode_path", "akv_decode_attention_static", "akv_append_decode_attention", "akv_unpack", "akv_fp16_decode_attention", "akv_stream_read",
+           "akv_decode_attention", "akv_decode_path", "akv_decode_attention_static", "akv_append_decode_attention", "akv_unpack", "akv_fp16_decode_attention",
+           "akv_fp16_path", "akv_stream_read",
            "akw_layout_sizes", "akw_workspace_init", "akw_pack", "akw_unpack", "akw_gemv"]
 AKW_MAX_B = 4
 
@@ -116,6 +117,8 @@ def lib() -> C.CDLL:
         L.akv_fp16_decode_attention.argtypes = [C.POINTER(akv_shape), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                                 C.c_void_p, C.c_float, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t,
                                                 C.c_void_p]
+        L.akv_fp16_path.restype = C.c_int32
+        L.akv_fp16_path.argtypes = [C.POINTER(akv_shape), C.c_int32]
         L.akw_layout_sizes.restype = C.c_int
         L.akw_layout_sizes.argtypes = [C.c_int32, C.c_int32, C.POINTER(akw_sizes)]
         L.akw_workspace_init.restype = C.c_int
@@ -367,6 +370,12 @@ def akv_fp16_decode_attention(k: torch.Tensor, v: torch.Tensor, lens: torch.Tens
 
 
 # ------------------------------------------------------------------------------------------ weight GEMV (akw.h)
+
+def akv_fp16_path(B: int, Hq: int, Hkv: int, D: int, Ncap: int, max_len: int = 0) -> int:
+    """1 (one workgroup per pair), 2 (chunks) or 3 (even shares): what akv_fp16_decode_attention takes."""
+    shp = akv_shape(B, Hq, Hkv, D, Ncap)
+    return int(lib().akv_fp16_path(C.byref(shp), max_len))
+
 
 def akw_layout_sizes(K: int, N: int) -> akw_sizes:
     out = akw_sizes()

@@ -379,6 +379,12 @@ int32_t akv_decode_path(const akv_shape* shape, int32_t max_len)
     return akv::head_logits_in_lds(*shape, ml) ? 3 : 1;
 }
 
+int32_t akv_fp16_path(const akv_shape* shape, int32_t max_len)
+{
+    if (!shape || !shape_ok(*shape) || max_len < 0 || max_len > shape->Ncap) return 0;
+    return akv::fp16_path(*shape, max_len > 0 ? max_len : shape->Ncap);
+}
+
 akv_status akv_decode_attention_static(const akv_cache* cache, const uint16_t* q, void* out, const akv_params* params,
                                        void* stream)
 {

@@ -163,6 +163,7 @@ bool head_logits_in_lds(const akv_shape& s, int max_len);   // the head kernel k
 hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v, const int32_t* lens, const uint16_t* q,
                        void* out, float scale, int out_dtype, int max_len, void* ws, hipStream_t st);
 size_t fp16_workspace_bytes(const akv_shape& s);
+int fp16_path(const akv_shape& s, int max_len);   // akv_fp16_path
 
 // Workgroups of a launch are dealt to the eight XCDs in turn: workgroup L of a one-dimensional grid runs on XCD
 // L % 8.  The streaming kernels give every XCD one contiguous eighth of the work instead of every eighth item, so

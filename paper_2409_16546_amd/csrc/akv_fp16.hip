@@ -35,6 +35,29 @@ static int f_chunk(const akv_shape& s, int max_len)
 // workgroups of a compute unit at a time
 constexpr int f_resident(int G) { return G == 8 ? 2 : 3; }
 
+constexpr int kFEvenSeqs = 64;   // sequences the even shares have a lane for
+
+struct F16Plan { int chunk, workgroups; };   // tokens per workgroup; workgroups of fp16_even_kernel, or 0: chunks
+// More chunks than one round of workgroups: even shares, where they are not cut by the pairs' ends too often.  Chunks / even, us:
+// groups of four, ragged (a quarter to all of the bound): 16 pairs 8192 20.9/20.2, 40 pairs 4096 22.8/21.4, 64 pairs 16128
+// 61..70/59..66, 128 pairs 16384 141/128; full: 8 pairs 16384 25.7/23.8, 32 pairs 54.9/55.8, 128 pairs 187/184, 64 pairs 32768 176/176;
+// but 128 pairs 1024 17.4/18.5, 2048 full 34.0/36.9, 256 pairs 2048 53.7/56.7, 96 pairs 5888 40.3/40.9.  Groups of eight, ragged:
+// 64 pairs 16384 88/75, 128 pairs 2048 33.7/34.3, 256 pairs 1280 38.3/38.8; full: 128 pairs 16384 194/183.  Single heads and groups
+// of two lose (8 x 32 of 4096 88/94).
+static F16Plan fp16_plan(const akv_shape& s, int max_len)
+{
+    const int G = s.Hq / s.Hkv, round = f_resident(G) * compute_units(), chunk = f_chunk(s, max_len);
+    const long pairs = long(s.B) * s.Hkv;
+    const bool even = ((G == 8 && max_len >= 32 * pairs) || (G == 4 && max_len >= 64 * pairs)) && s.B <= kFEvenSeqs && chunk < max_len && pairs * ((max_len + chunk - 1) / chunk) > round;
+    return {chunk, even ? round : 0};
+}
+
+int fp16_path(const akv_shape& s, int max_len)
+{
+    const F16Plan p = fp16_plan(s, max_len);
+    return p.workgroups ? 3 : (max_len <= p.chunk ? 1 : 2);
+}
+
 size_t fp16_workspace_bytes(const akv_shape& s)
 {
     const size_t bhq = size_t(s.B) * s.Hq, ns = s.Ncap / kFMinChunk;
@@ -68,10 +91,10 @@ __device__ __forceinline__ float over_rows(float v, F op)
 __device__ __forceinline__ int fp16_len(const F16Args& a, int b) { return max(min(min(a.lens[b], a.s.Ncap), a.max_len), 0); }
 
 // fp16_even_kernel: the tiles of all pairs numbered through, sequence after sequence (at most 64 of them: a lane per sequence), and
-// the tiles a workgroup takes.  A pair of n tiles has room for ceil(n / 4) partial results.  Shares of eight tiles and more may begin
-// anywhere: at most (n - 2) / share + 2 parts.  Below that every pair begins at a multiple of four (its last places may be empty) and
-// shares are a multiple of four: at most one part per four.
-constexpr int kFEvenSeqs = 64;
+// the tiles a workgroup takes.  A pair has room for Ncap / 128 partial results: at least two, as capacities are multiples of 256, and
+// at least ceil(n / 4) for its n tiles.  Shares of eight tiles and more may begin anywhere: one part for one tile, else at most (n - 2)
+// / share + 2 parts, which is two for up to nine tiles and at most ceil(n / 4) for more.  Below that every pair begins at a multiple of
+// four (its last places may be empty) and shares are a multiple of four: at most one part per four.
 struct F16Tiles {
     int len, end;   // of sequence `lane`: its length, the tiles up to and with it
     int share, unit;
@@ -395,18 +418,10 @@ hipError_t launch_fp16(const akv_shape& s, const uint16_t* k, const uint16_t* v,
     a.c = (float)((double)scale * 1.4426950408889634);
     a.out_dtype = out_dtype;
     a.nsplit = s.Ncap / kFMinChunk;
-    a.chunk = f_chunk(s, max_len);
     a.max_len = max_len;
-    // More chunks than one round of workgroups: even shares, where they are not cut by the pairs' ends too often.  Chunks / even, us:
-    // groups of four, ragged (a quarter to all of the bound): 16 pairs 8192 20.9/20.2, 40 pairs 4096 22.8/21.4, 64 pairs 16128
-    // 61..70/59..66, 128 pairs 16384 141/128; full: 8 pairs 16384 25.7/23.8, 32 pairs 54.9/55.8, 128 pairs 187/184, 64 pairs 32768 176/176;
-    // but 128 pairs 1024 17.4/18.5, 2048 full 34.0/36.9, 256 pairs 2048 53.7/56.7, 96 pairs 5888 40.3/40.9.  Groups of eight, ragged:
-    // 64 pairs 16384 88/75, 128 pairs 2048 33.7/34.3, 256 pairs 1280 38.3/38.8; full: 128 pairs 16384 194/183.  Single heads and groups
-    // of two lose (8 x 32 of 4096 88/94).
-    const int G = s.Hq / s.Hkv, round = f_resident(G) * compute_units();
-    const long pairs = long(s.B) * s.Hkv;
-    const bool even = ((G == 8 && max_len >= 32 * pairs) || (G == 4 && max_len >= 64 * pairs)) && s.B <= kFEvenSeqs && a.chunk < max_len && pairs * ((max_len + a.chunk - 1) / a.chunk) > round;
-    a.workgroups = even ? round : 0;
+    const F16Plan plan = fp16_plan(s, max_len);
+    a.chunk = plan.chunk;
+    a.workgroups = plan.workgroups;
     const size_t bhq = size_t(s.B) * s.Hq;
     char* p = reinterpret_cast<char*>(ws);
     a.partO = reinterpret_cast<float*>(p);
