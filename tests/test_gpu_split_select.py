@@ -49,6 +49,30 @@ def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= bound)
 
 
+def test_selection_beyond_the_block_maxima_kept_in_lds(T):
+    """More than 1024 blocks in a sequence: the maxima of the later ones are read from memory.  Tokens of theirs are selected, and one
+    sequence ends with a block of a single token."""
+    from paper_2409_16546_amd import binding as A, workloads
+    from oracle import akv_oracle as O
+    lens, topk, scale = [300000, 262145], 64, 0.02
+    print(f"split selection: lens {lens}", flush=True)
+    w = workloads.make(4, B=2, Hq=2, Hkv=1, N=max(lens), seed=78)
+    w.k[1, :, 262144] = w.k[1, :, :262144].abs().amax(1) * w.q[1, 0].sign()        # the lone token has the largest score of a head
+    Ncap = (max(lens) + 255) // 256 * 256
+    oc = T.oracle_cache(w.k, w.v, lens, Ncap)
+    r = O.decode_attention(oc, T.bits(w.q), topk=topk, scale=scale)
+    assert (r.sel[0] >= 262144).any() and (r.sel[1, 0] == 262144).any()
+    gc = T.gpu_cache(w.k, w.v, lens, 2, Ncap)
+    dbg = A.DebugBuffers.allocate(gc, topk=topk, want_needV=False)
+    dbg.a = None
+    out = A.akv_decode_attention(gc, w.q.to(DEV), dbg=dbg, path=2, topk=topk, scale=scale)
+    torch.cuda.synchronize()
+    assert np.array_equal(dbg.sel.cpu().numpy(), r.sel)
+    assert np.array_equal(dbg.oest.cpu().numpy().view(np.uint32), r.oest.view(np.uint32))
+    assert np.array_equal(dbg.Ehat.cpu().numpy(), r.Ehat)
+    assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= T.out_tolerance(r, lens, scale))
+
+
 @pytest.mark.parametrize("n", [700, 9000])
 def test_selection_stays_in_range_on_infinite_keys(T, n):
     """One sequence holds infinities in K (its logits are infinite or not numbers: results unspecified), the other does not: the
