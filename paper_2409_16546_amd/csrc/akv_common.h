@@ -21,7 +21,7 @@ constexpr int kMaxG = 8;           // query heads per KV head supported
 // K pass: one wave covers one unit of tokens, a 256-token block (4 consecutive tokens per lane) or half of one.
 constexpr int kKWaves = 4;                         // waves per workgroup
 constexpr int kMinUnit = kTB / 2;                  // tokens of the smaller unit
-// V pass: one workgroup covers a chunk of tokens; a wave reads 8 token rows per step.
+// V pass: one workgroup covers a chunk of tokens; a wave takes 16 token rows at a time.
 constexpr int kVWaves = 4;
 constexpr int kVChunk = 512;                       // chunks are at least this long where they are many
 constexpr int kVMinChunk = 128;                    // ... and at least this long where a call has few pairs of short sequences:

@@ -274,7 +274,8 @@ static hipError_t launch_head_t(const DecodeArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-// half blocks per wave where whole ones would leave half of the waves without one
+// half blocks per wave where whole ones would leave at least half of the waves without one (up to NT tokens half of them have none
+// even so)
 template <int G, int NT>
 static hipError_t launch_head_g(const DecodeArgs& a, hipStream_t st)
 {

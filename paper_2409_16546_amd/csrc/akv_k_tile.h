@@ -9,19 +9,22 @@
 
 namespace akv {
 
-// LDS of the K side of one (sequence, KV head)
+// q as binary32 in LDS, for the kernels that read it there (rows of neighbouring heads four banks apart)
+template <int G, bool USED> struct KSharedQ {};
+template <int G> struct KSharedQ<G, true> { alignas(16) float q[G][kD + 4]; };
+// LDS of the K side of one (sequence, KV head).  In groups of eight k_tile multiplies on the matrix cores, which take q from LDS.
 template <int G>
-struct KShared {
+struct KShared : KSharedQ<G, G == 8> {
     static constexpr bool kNew = false;
     static constexpr int kHeads = G;
-    static constexpr bool kMatrix = G == 8;   // k_tile multiplies on the matrix cores
+    static constexpr bool kMatrix = G == 8;
     int emax[2][G];                     // largest addend exponent per query head, of the columns of wave 0 / wave 1
     uint64_t need_mid[2], need_lo[2];   // bit d%64 of word d/64: column d is read at level >= 1 / = 2
-    alignas(16) float q[G][kD + 4];     // as binary32, for kMatrix and kNew (rows of neighbouring heads four banks apart)
 };
 // ... of a kernel that appends a token itself
 template <int G>
-struct KSharedNew : KShared<G> {
+struct KSharedNew : KShared<G>, KSharedQ<G, true> {
+    static_assert(G < 8, "one q");
     static constexpr bool kNew = true;
     float knew[kD];                     // the new token's K row as it will be read at the column levels
     float new_logit[G];                 // q . knew, accumulated in channel order

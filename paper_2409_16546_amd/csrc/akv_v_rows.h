@@ -191,7 +191,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     const int lane = threadIdx.x & 63;
     const int r = lane >> 3, cl = lane & 7;
     // lane j < RB * G computes the score of row j / G of the batch for query head j % G: every (row, head) pair once
-    static_assert(RB * G <= 64 && (G & (G - 1)) == 0, "one lane per (row of the batch, query head)");
+    static_assert(RB * G <= 64 && (G == 1 || G == 2 || G == 4), "one lane per (row of the batch, query head)");
     const int jrow = lane / G, jg = lane % G;
     const bool jlane = lane < RB * G;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
@@ -274,7 +274,6 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
                 zl += pj;
                 if (G >= 2) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
                 if (G >= 4) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
-                if (G >= 8) ahat = max(ahat, __builtin_amdgcn_update_dpp(ahat, ahat, 0x141, 0xF, 0xF, false));   // row_half_mirror
                 ssw = __builtin_amdgcn_perm(0u, uint32_t(ahat + 64), 0x00000000u);   // (Ahat + 64) in every byte
             }
             const int sk = SB ? 64 * k : 0;   // the batch's sixteen score lanes
