@@ -394,8 +394,8 @@ hipError_t launch_unpack(const akv_cache& c, uint16_t* k_out, uint16_t* v_out, h
     const UnpackPlan p = unpack_plan(size_t(c.shape.B) * c.shape.Hkv * (c.shape.Ncap / kTB), k_out != nullptr, v_out != nullptr);
     if (!p.workgroups) return hipErrorInvalidConfiguration;
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)p.workgroups), dim3(256), 0, st, c, k_out, v_out); };
-    if (!k_out) launch(unpack_kernel<0, 2>);
-    else if (!v_out) launch(unpack_kernel<1, 0>);
+    if (!v_out) launch(unpack_kernel<1, 0>);
+    else if (!k_out) p.v_parts == 8 ? launch(unpack_kernel<0, 8>) : (p.v_parts == 4 ? launch(unpack_kernel<0, 4>) : launch(unpack_kernel<0, 2>));
     else if (p.v_parts == 1) launch(unpack_kernel<1, 1>);
     else launch(unpack_kernel<1, 16>);
     return hipGetLastError();

@@ -146,3 +146,19 @@ def test_unpack_of_many_blocks_gives_back_what_was_stored(T, B):
     torch.cuda.synchronize()
     for got, want in ((ku, k), (vu, v)):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("B,H", [(1, 1), (20, 8), (23, 7), (24, 8), (193, 1)])    # 1 and 160 blocks: eight workgroups each; 161 and 192: four; 193: two
+def test_unpack_of_v_alone_gives_back_what_was_stored(T, B, H):
+    from paper_2409_16546_amd import binding as A, workloads
+    print(f"unpack of V: {H * B} blocks", flush=True)
+    k, v = (t.repeat(B, 1, 1, 1).to(DEV) for t in workloads.edge_patterns(1, H, 256, seed=B))
+    v[:, :, :, 5] = torch.arange(B, device=DEV)[:, None, None].half()      # a block or a row that lands in another's place is seen
+    v[:, :, :, 6] = torch.arange(256, device=DEV).half()
+    gc = A.Cache.allocate(B, H, H, 128, 256, DEV)
+    A.akv_append(gc, k, v)
+    out = torch.zeros(B * H * 256 + 1, 128, dtype=torch.float16, device=DEV)      # a row more than the tensor has
+    s = gc.struct()
+    assert A.lib().akv_unpack(C.byref(s), None, out.data_ptr(), torch.cuda.current_stream().cuda_stream) == A.AKV_OK
+    torch.cuda.synchronize()
+    assert torch.equal(out[:-1].view(torch.int16), v.view(-1, 128).view(torch.int16)) and not out[-1].any()
