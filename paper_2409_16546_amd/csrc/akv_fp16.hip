@@ -38,12 +38,14 @@ constexpr int f_resident(int G) { return G == 8 ? 2 : 3; }
 constexpr int kFEvenSeqs = 64;   // sequences the even shares have a lane for
 
 struct F16Plan { int chunk, workgroups; };   // tokens per workgroup; workgroups of fp16_even_kernel, or 0: chunks
-// More chunks than one round of workgroups: even shares, where they are not cut by the pairs' ends too often.  Chunks / even, us:
-// groups of four, ragged (a quarter to all of the bound): 16 pairs 8192 20.9/20.2, 40 pairs 4096 22.8/21.4, 64 pairs 16128
-// 61..70/59..66, 128 pairs 16384 141/128; full: 8 pairs 16384 25.7/23.8, 32 pairs 54.9/55.8, 128 pairs 187/184, 64 pairs 32768 176/176;
-// but 128 pairs 1024 17.4/18.5, 2048 full 34.0/36.9, 256 pairs 2048 53.7/56.7, 96 pairs 5888 40.3/40.9.  Groups of eight, ragged:
-// 64 pairs 16384 88/75, 128 pairs 2048 33.7/34.3, 256 pairs 1280 38.3/38.8; full: 128 pairs 16384 194/183.  Single heads and groups
-// of two lose (8 x 32 of 4096 88/94).
+// More chunks than one round of workgroups: even shares, where they are not cut by the pairs' ends too often.  Chunks / even, us, full and
+// ragged (lengths a quarter to all of the bound): groups of four, 8 pairs 30000 40.5/31.3, 16 pairs 8192 21.3/20.1, 17.4/18.6; 32 pairs
+// 5000 23.3/22.6, 19.4..20.6/18.9..19.8; 64 pairs 5000 38.2/35, 27..29/25..27; 88 pairs 8192 68.0/67.9, 46..49/44..47; 128 pairs 16384
+// 182/170, 123..128/106..113; but of those that the line leaves to chunks 128 pairs 2048 34.0/36.9, 256 pairs 2048 53.7/56.7 (shares that
+// begin anywhere).  Groups of eight, 4 pairs 30000 35.8/27.2, 18.6/20.1; 16 pairs 5000 22.2/20.3, 15.7..21.9/17.2..20.2; 32 pairs 2100
+// 21.1/19.3, 15.6/17.2; 64 pairs 5000 44.8/38.4, 36..38/30; 128 pairs 8192 97.3/102, 77..82/66..70.  Short ragged calls lose up to 1.7 us
+// where the chunks happen to come out even; the host knows a bound of the lengths only.  Single heads and groups of two lose (8 x 32 of
+// 4096 88/94).
 static F16Plan fp16_plan(const akv_shape& s, int max_len)
 {
     const int G = s.Hq / s.Hkv, round = f_resident(G) * compute_units(), chunk = f_chunk(s, max_len);
@@ -90,31 +92,67 @@ __device__ __forceinline__ float over_rows(float v, F op)
 
 __device__ __forceinline__ int fp16_len(const F16Args& a, int b) { return max(min(min(a.lens[b], a.s.Ncap), a.max_len), 0); }
 
-// fp16_even_kernel: the tiles of all pairs numbered through, sequence after sequence (at most 64 of them: a lane per sequence), and
-// the tiles a workgroup takes.  A pair has room for Ncap / 128 partial results: at least two, as capacities are multiples of 256, and
-// at least ceil(n / 4) for its n tiles.  Shares of eight tiles and more may begin anywhere: one part for one tile, else at most (n - 2)
-// / share + 2 parts, which is two for up to nine tiles and at most ceil(n / 4) for more.  Below that every pair begins at a multiple of
-// four (its last places may be empty) and shares are a multiple of four: at most one part per four.
+// What a workgroup of fp16_even_kernel takes, from the lengths of all sequences (at most 64 of them: a lane each).  A wave finds it out
+// by itself, two rounds of scans over the lanes in front of its first load.
+// Whole parts: every pair is cut into parts of `share` tiles, its last one shorter, and a workgroup takes one.  Taken where the even share,
+// or one up to three tiles larger (one from 32 tiles on: 88 ragged pairs, groups of four, share 37, 81 us without, 88 with three more),
+// makes no more parts than there are workgroups.  Groups of four: eight tiles and not five or six, as wide for the waves that have two and
+// fewer parts to merge (6 / 8: 8 pairs of 16384 23.7/21.3, 16 of 8192 21.5/19.8, 40 of 3500 21.2/22.6; groups of eight, 5 / 8: 16 pairs
+// of 5000 20.1/21.9).
+// Else the tiles of all pairs are numbered through, sequence after sequence, and a workgroup takes the next `share` of them, which may
+// be the end of one pair and the beginning of the next: two ranges one after the other, 4 to 6 us where one takes 8.  (Whole parts / these
+// always / chunks, us, groups of eight: 64 pairs 2100 25.7/28.9/27.3, ragged 20.5/25.4/20.7; 32 pairs 5000 25.8/31.1/28.4, ragged
+// 23.2/28.0/21.4; 64 pairs 8192 ragged 38.3/41.2/46.8; groups of four: 16 pairs 30000 47.1/49.7/53.8, 128 pairs 8192 90.7/95.1/98.1.)
+// A pair has room for Ncap / 128 partial results: at least two, as capacities are multiples of 256, and at least ceil(n / 4) for its n
+// tiles.  Whole parts are of four tiles and more, so at most ceil(n / 4).  Shares that begin anywhere are of eight and more: one part for
+// one tile, else at most (n - 2) / share + 2 parts, which is two for up to nine tiles and at most ceil(n / 4) for more.
+// m / d for 0 <= m < 2^21, d >= 1: (m + 1/2) / d lies at least 1 / (2 d) from a whole number, and the two roundings and the reciprocal's
+// last place move it by less than (m + 1/2) / d * 2^-22.  (A sequence has fewer than 2^24 tokens, the descriptors' reach, so 2^19 tiles.)
+__device__ __forceinline__ int small_quotient(int m, int d) { return int((float(m) + 0.5f) * __builtin_amdgcn_rcpf(float(d))); }
 struct F16Tiles {
-    int len, end;   // of sequence `lane`: its length, the tiles up to and with it
-    int share, unit;
+    int len, per, end;   // of sequence `lane`: its length, the places (whole parts, or tiles) of one of its pairs, those up to and with its last
+    int share;
+    bool whole;
     __device__ __forceinline__ F16Tiles(const F16Args& a)
     {
-        const int lane = threadIdx.x & 63;
+        const int lane = threadIdx.x & 63, Hkv = a.s.Hkv;
         len = lane < a.s.B ? fp16_len(a, lane) : 0;
-        unit = 1;
-        end = wave_scan_add(tiles(len) * a.s.Hkv);
+        const int tiles = (len + kFTile - 1) / kFTile;
+        end = wave_scan_add(tiles * Hkv);
         share = (wave_read(end, 63) + a.workgroups - 1) / a.workgroups;
-        if (share < 8) {
-            unit = 4;
-            end = wave_scan_add(tiles(len) * a.s.Hkv);
-            share = (wave_read(end, 63) + 4 * a.workgroups - 1) / (4 * a.workgroups) * 4;
+        // the parts that four shares make, two counts to a word: a sequence adds at most one part a pair to its tiles over the share, so
+        // that all of them are fewer than workgroups + 64
+        const int least = share > 6 || a.s.Hq == 8 * Hkv ? max(share, 4) : (share > 4 ? 8 : 4), most = least + (least < 32 ? 3 : 1);
+        int parts[4], sum[2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) parts[k] = small_quotient(tiles + least + k - 1, least + k);
+#pragma unroll
+        for (int k = 0; k < 4; k += 2) sum[k / 2] = wave_scan_add(parts[k] | parts[k + 1] << 16);
+        whole = false;
+#pragma unroll
+        for (int k = 3; k >= 0; --k) {
+            const int upto = (k & 1) ? int(uint32_t(sum[k / 2]) >> 16) : sum[k / 2] & 0xFFFF;
+            if (wave_read(upto, 63) * Hkv <= a.workgroups && least + k <= most) {   // uniform
+                whole = true;
+                share = least + k;
+                per = parts[k];
+                end = upto * Hkv;
+            }
         }
+        if (whole) return;
+        per = tiles;
+        share = max(share, 8);
     }
-    __device__ __forceinline__ int tiles(int n) const { return (n + kFTile * unit - 1) / (kFTile * unit) * unit; }
     __device__ __forceinline__ int before(int b) const { return b > 0 ? wave_read(end, b - 1) : 0; }   // b uniform
-    __device__ __forceinline__ int len_of(int b) const { return wave_read(len, b); }
-    __device__ __forceinline__ int sequence_of(int tile) const { return __builtin_popcountll(__ballot(end <= tile)); }
+    __device__ __forceinline__ int sequence_of(int place) const { return __builtin_popcountll(__ballot(end <= place)); }
+    // partial results of KV head h of sequence b
+    __device__ __forceinline__ int parts_of(int b, int h) const
+    {
+        const int n = wave_read(per, b);
+        if (whole) return n;
+        const int first = before(b) + h * n;
+        return n > 0 ? (first + n - 1) / share - first / share + 1 : 0;
+    }
 };
 
 __device__ __forceinline__ void store_result(const F16Args& a, size_t at, float v)
@@ -315,29 +353,41 @@ __global__ __launch_bounds__(64 * kFWaves) void fp16_kernel(F16Args a)
     fp16_range<G, ONE, false>(a, b, h, split, c0 + wave * per, min(c0 + (wave + 1) * per, len), len, sm);
 }
 
-// More work than one round of workgroups: every workgroup of that round takes the same number of tiles of 32 tokens, wherever
-// they lie.  The tiles of all (sequence, KV head) pairs are numbered through, sequence after sequence; workgroup i takes tiles i *
-// share .. + share - 1, a range of one pair or the end of one and the beginning of the next.  Chunks by the shape end in a last round
-// that is nearly empty, all the more where lengths differ (times: launch_fp16).  Bound by memory: 5.8 TB/s where lengths are ragged,
-// 6.2 where they are equal.
+// More work than one round of workgroups: one round of them, each with as many tiles of 32 tokens as the others or fewer (F16Tiles).
+// Chunks by the shape end in a last round that is nearly empty, all the more where lengths differ (times: fp16_plan).  Bound by memory: 5.8
+// TB/s where lengths are ragged, 6.2 where they are equal.
 template <int G>
 __global__ __launch_bounds__(64 * kFWaves, f_resident(G)) void fp16_even_kernel(F16Args a)
 {
     __shared__ F16Shared<G> sm;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), Hkv = a.s.Hkv;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const F16Tiles all(a);
     const int total = all.before(64), share = all.share;
-    int tile = blockIdx.x * share;
-    const int tile_end = min(tile + share, total);
-    if (tile >= tile_end) return;   // uniform
-    for (int b = all.sequence_of(tile); tile < tile_end; ++b) {
-        const int len = all.len_of(b), per = all.tiles(len), first = all.before(b);
-        while (tile < tile_end && tile < first + Hkv * per) {   // the pairs of sequence b
-            const int h = (tile - first) / per, pair0 = first + h * per, t0 = tile - pair0, n = min(tile_end, pair0 + per) - tile;
-            fp16_range<G, false, true>(a, b, h, tile / share - pair0 / share, (t0 + n * wave / kFWaves) * kFTile, min((t0 + n * (wave + 1) / kFWaves) * kFTile, len), len, sm);
-            tile += n;
-            if (tile < tile_end) __syncthreads();   // the LDS areas are written again
+    int place = blockIdx.x, place_end = min(place + 1, total);
+    if (!all.whole) {
+        place *= share;
+        place_end = min(place + share, total);
+    }
+    if (place >= place_end) return;   // uniform
+    for (int b = all.sequence_of(place);; b = all.sequence_of(place)) {
+        const int len = wave_read(all.len, b), per = wave_read(all.per, b), first = place - all.before(b);
+        int h, t0, n, part;   // tiles t0 .. t0 + n - 1 of (b, h) are its partial result `part`
+        if (all.whole) {
+            h = small_quotient(first, per);
+            part = first - h * per;
+            t0 = part * share;
+            n = min(share, (len + kFTile - 1) / kFTile - t0);
+            ++place;
+        } else {
+            h = first / per;
+            t0 = first - h * per;
+            n = min(place_end - place, per - t0);
+            part = place / share - (place - t0) / share;
+            place += n;
         }
+        fp16_range<G, false, true>(a, b, h, part, (t0 + n * wave / kFWaves) * kFTile, min((t0 + n * (wave + 1) / kFWaves) * kFTile, len), len, sm);
+        if (place >= place_end) break;
+        __syncthreads();   // the LDS areas are written again
     }
 }
 
@@ -351,9 +401,7 @@ __global__ __launch_bounds__(kD) void fp16_combine_kernel(F16Args a)
     int used;
     if (a.workgroups) {   // uniform
         const F16Tiles all(a);
-        const int share = all.share, per = all.tiles(len);
-        const int pair0 = all.before(b) + (hq_i / (a.s.Hq / a.s.Hkv)) * per;
-        used = per > 0 ? (pair0 + per - 1) / share - pair0 / share + 1 : 0;
+        used = all.parts_of(b, hq_i / (a.s.Hq / a.s.Hkv));
     } else {
         used = (len + a.chunk - 1) / a.chunk;
     }

@@ -164,13 +164,16 @@ def test_decode_path_of_single_heads_in_several_rounds(A, B, Hkv, N, path):
 
 
 def test_fp16_path_query_is_a_host_computation_and_the_gpu_cases_reach_what_they_name(A):
-    from test_gpu_fp16_edges import EVEN, WALKS
+    from test_gpu_fp16_edges import CUTS, EVEN, WALKS, _cut
     assert A.akv_fp16_path(1, 4, 4, 64, 256) == 0 and A.akv_fp16_path(1, 4, 4, 128, 256, 257) == 0
     for G, B, Hkv, Ncap, lens, kernels in WALKS:
         assert len(lens) == B and max(lens) <= Ncap and A.akv_fp16_path(B, Hkv * G, Hkv, 128, Ncap) == kernels, (G, B, Hkv, Ncap)
     for G, B, Hkv, Ncap, lens, max_len in EVEN:
         assert len(lens) == B and max(lens) <= Ncap and A.akv_fp16_path(B, Hkv * G, Hkv, 128, Ncap, max_len) == 3, (G, B, Hkv, Ncap)
-    # the neighbours of the last: a sequence more than lanes, shorter than the line, one or two heads per group
+    for G, B, Hkv, Ncap, lens, whole, share in CUTS:
+        assert len(lens) == B and max(lens) <= Ncap and A.akv_fp16_path(B, Hkv * G, Hkv, 128, Ncap) == 3, (G, B, Hkv, Ncap)
+        assert _cut(G, Hkv, lens) == (whole, share), (G, B, Hkv, Ncap)
+    # the neighbours of the last of EVEN: a sequence more than lanes, shorter than the line, one or two heads per group
     assert A.akv_fp16_path(65, 8, 1, 128, 4096) == 2 and A.akv_fp16_path(64, 8, 1, 128, 1792) == 2
     assert A.akv_fp16_path(2, 6, 3, 128, 32768) == 2 and A.akv_fp16_path(3, 8, 2, 128, 16384) == 2
 

@@ -115,11 +115,11 @@ def test_fp16_walks_of_several_tiles_match_textbook(G, B, Hkv, Ncap, lens, kerne
 
 
 EVEN = [   # G, B, Hkv, Ncap, lens, max_len
-    (4, 2, 3, 32768, [32768, 31999], 0),                                  # shares of eight tiles that begin anywhere
+    (4, 2, 3, 32768, [32768, 31999], 0),                                  # whole parts of eight tiles
     (4, 2, 3, 32768, [32768, 20001], 20000),                              # the bound cuts both
-    (4, 3, 2, 16640, [16640, 0, 40], 0),                                  # shares of four tiles, pairs at multiples of four
+    (4, 3, 2, 16640, [16640, 0, 40], 0),                                  # of four
     (8, 64, 1, 2048, [2048, 0, 0, 1, 33, 129, 2047, 0] * 8, 0),           # a lane per sequence, empty ones between
-    (8, 64, 1, 8192, [8192, 1, 40, 8191, 0, 33, 5000, 64] * 8, 0),        # shares of eleven tiles over several short pairs
+    (8, 64, 1, 8192, [8192, 1, 40, 8191, 0, 33, 5000, 64] * 8, 0),        # of twelve, most pairs shorter than one
     (8, 64, 1, 4096, [0] * 63 + [4096], 0),                               # hardly any work: most workgroups have no tile
     (4, 2, 3, 32768, [0, 0], 0),                                          # none at all
 ]
@@ -150,3 +150,52 @@ def test_fp16_even_shares_match_textbook(G, B, Hkv, Ncap, lens, max_len):
     assert np.all(err <= 2e-5 * size), (err / np.maximum(size, 1e-30)).max()
     assert not got[lens == 0].any()
     assert torch.equal(out, A.akv_fp16_decode_attention(*args, max_len=max_len))
+
+
+CUTS = [   # G, B, Hkv, Ncap, lens, whole parts, tiles of a share
+    (8, 64, 2, 4096, [4096 - (i * 1237) % 2048 for i in range(64)], False, 25),       # shares over the end of a pair
+    (4, 24, 6, 9472, [[9472, 8000, 8100, 1, 8300, 0, 9001, 8500][i % 8] for i in range(24)], False, 38),   # ... of two sequences, empty ones between
+    (8, 64, 3, 6144, [32 * (25, 13, 25)[i % 3] - (i * 5) % 32 for i in range(64)], False, 8),   # the smallest that begin anywhere
+    (8, 64, 2, 4096, [[4096, 289, 300, 1, 0, 33, 2081, 4000][i % 8] for i in range(64)], True, 12),
+    (8, 3, 1, 24576, [24576, 24001, 1], True, 4),                                     # the smallest whole ones
+]
+
+
+def _cut(G, Hkv, lens):
+    """The share of tiles and whether pairs are cut into whole parts, as the rule has it (256 compute units)."""
+    workgroups, tiles = 256 * (2 if G == 8 else 3), [(n + 31) // 32 for n in lens]
+    even = -(-Hkv * sum(tiles) // workgroups)
+    least = 8 if G == 4 and even in (5, 6) else max(even, 4)
+    for share in range(least, least + (4 if least < 32 else 2)):
+        if Hkv * sum(-(-t // share) for t in tiles) <= workgroups:
+            return True, share
+    return False, max(even, 8)
+
+
+@pytest.mark.parametrize("G,B,Hkv,Ncap,lens,whole,share", CUTS)
+def test_fp16_shares_that_span_pairs_and_whole_parts(G, B, Hkv, Ncap, lens, whole, share):
+    """Head by head, to 2e-5 as above; a tile that is left out, taken twice or merged into another head shows."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import akv_testlib as T
+    from oracle import akv_oracle as O
+    from paper_2409_16546_amd import binding as A
+    O.build()
+    print(f"fp16 attention, cuts: G{G} {B}x{Hkv} Ncap {Ncap}", flush=True)
+    assert A.akv_fp16_path(B, Hkv * G, Hkv, 128, Ncap) == 3
+    g = torch.Generator().manual_seed(G + B)
+    most, lens = (max(lens) + 255) // 256 * 256, np.asarray(lens, np.int32)
+    q = torch.randn(B, Hkv * G, 128, generator=g).half()
+    k, v = torch.randn(B, Hkv, most, 128, generator=g).half(), torch.randn(B, Hkv, most, 128, generator=g).half()
+    k *= torch.linspace(0.05, 2.0, most)[:, None].half()
+    kd, vd = (torch.full((B, Hkv, Ncap, 128), float("nan"), dtype=torch.float16, device=DEV) for _ in range(2))      # past the lengths nothing is read
+    for b in range(B):
+        kd[b, :, :lens[b]], vd[b, :, :lens[b]] = k[b, :, :lens[b]].to(DEV), v[b, :, :lens[b]].to(DEV)
+    args = (kd, vd, torch.from_numpy(lens).to(DEV), q.to(DEV))
+    out = A.akv_fp16_decode_attention(*args)
+    got = out.cpu().numpy().astype(np.float64)
+    ref = O.fp16_attention(T.bits(k), T.bits(v), lens, T.bits(q))
+    err, size = np.linalg.norm(got - ref, axis=2), np.linalg.norm(ref, axis=2)
+    assert np.all(err <= 2e-5 * size), (err / np.maximum(size, 1e-30)).max()
+    assert not got[lens == 0].any()
+    assert torch.equal(out, A.akv_fp16_decode_attention(*args))
