@@ -369,13 +369,13 @@ def akv_fp16_decode_attention(k: torch.Tensor, v: torch.Tensor, lens: torch.Tens
     return out
 
 
-# ------------------------------------------------------------------------------------------ weight GEMV (akw.h)
-
 def akv_fp16_path(B: int, Hq: int, Hkv: int, D: int, Ncap: int, max_len: int = 0) -> int:
     """1 (one workgroup per pair), 2 (chunks) or 3 (even shares): what akv_fp16_decode_attention takes."""
     shp = akv_shape(B, Hq, Hkv, D, Ncap)
     return int(lib().akv_fp16_path(C.byref(shp), max_len))
 
+
+# ------------------------------------------------------------------------------------------ weight GEMV (akw.h)
 
 def akw_layout_sizes(K: int, N: int) -> akw_sizes:
     out = akw_sizes()
