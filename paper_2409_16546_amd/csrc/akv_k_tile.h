@@ -381,7 +381,7 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
 
     // ---- logits out, tile maxima -----------------------------------------------------------------
     // Written for other workgroups they go with the non-temporal hint, which is also how the V kernel of a group of four or eight reads
-    // them: B 8, 32/8, 32768 tokens (34 MB) 171 -> 160 us a call, B 4, 32/8, up to 131072 271 -> 265; of one or two heads where there
+    // them: B 8, 32/8, 32768 tokens (34 MB) 169.5 -> 161.5 us a call, B 4, 32/8, up to 131072 246 -> 241; of one or two heads where there
     // are many (a.lg_nt; 17 MB, B 16, 32 heads, 8193 with append 283.5 -> 274; 8 MB equal; 4 MB, which the caches hold until they are
     // read again: B 4, 32 heads, 8192 84.2 -> 85.1).  Groups of four and eight always: few logits lose up to 1.2 % (plain stores and
     // loads / the hint: B 1, 32/8, 1024 25.17/25.35, 8192 33.7/34.0, 32768 (4 MB) 49.8/50.4; B 1, 64/8, 16384 (4 MB) 45.7/45.9; from

@@ -410,11 +410,12 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // Stages L, D, A + matrix product as in v_rows.  Four lanes per row: they are also the lanes that compute the row's scores
 // (lane -> query heads lane % 4, + 4), so that nothing is exchanged but the maximum over a quad, and a MID or LO row takes one
 // 16-byte load per lane: five vector-memory instructions a batch instead of seven, a quarter of the vector instructions less.
-// Measured against eight lanes per row, scores handed over by lane permutes, batches of 8 rows for groups of eight (us a call):
-// B 4, 32/8, up to 131072 tokens 265 -> 257, B 3, 64/8, up to 13000 69.5 -> 65; B 8, 32/8, 32768, every slot of the device full,
-// 159.5 -> 161.  What bounds it now is the loads: without assembly, LDS and matrix products (timing only) the call takes as
-// long, without Rule 2's test and its MID / LO bytes 8 us less, without the logits 10 us less.  The two halves of a lane's 32 HI
-// bytes share a line, so the HI loads keep the line in the caches (temporal: 175 -> 168, at an earlier state).
+// Measured against eight lanes per row, scores handed over by lane permutes, batches of 8 rows for groups of eight (us a call, the
+// non-temporal hint on the logits on both sides): B 8, 32/8, 32768 tokens, few MID and LO rows, 160.6 -> 161.3, with many 190 -> 181; B 4, 32/8,
+// up to 131072 246 -> 236; B 16, 32/8, 5000 80.7 -> 75.9; B 3, 64/8, up to 13000, with the matrix products of its K tile, 67.8 -> 64.2.
+// What bounds it now is the loads: without assembly, LDS and matrix products (timing only) the call takes as long, without Rule 2's test
+// and its MID / LO bytes 8 us less, without the logits 10 us less.  The two halves of a lane's 32 HI bytes share a line, so the HI loads
+// keep the line in the caches (temporal: 175 -> 168, at an earlier state).
 // acc: the wave's two 16x16 result tiles (four words each: rows 4 * (lane / 16) .. + 3 of W, line 16 * (2 w + tile) + lane % 16),
 // scaled by kVWeightScale.  z[s]: this lane's sum of the weights of head lane % 4 + 4 s.
 template <int G, bool DEBUG, int DL>
