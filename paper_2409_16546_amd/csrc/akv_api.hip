@@ -310,14 +310,13 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
             shortest = std::min(shortest, std::max(long(akv::kVMinChunk), ((a.s.Ncap / akv::kVFewChunks + 63) / 64) * 64L));
         a.vslots = akv::v_slots(a.s);
         a.vchunk = int(std::max(shortest, chunk));
-        // K kernel: half blocks where whole ones would leave the device short of waves (the time is then one wave's walk through
-        // its unit): below three waves per compute unit (8 pairs of four heads: 36.2 -> 32.0 us at 2048 tokens, 40.8 -> 36.0 at
-        // 8192; 32 single heads at 4096: 31.0 -> 28.4; from 8 waves per unit on whole blocks are 1-5 % faster, in between equal)
+        // K kernel: a block per wave streams best where the device is full of waves; up to five blocks per compute unit the time is one
+        // wave's walk, and four waves share a block.  Four / one, us a call, full and ragged (a quarter to all of the bound): 8 pairs of
+        // four heads 1024 20.5/30.7, 8192 28.7/38.3, 32768 (4 blocks per unit) 48.5/50.2, 38.9/43.8; 24 pairs of eight 13000 (4.8)
+        // 59.6/61.8, 49.2/57.5; 64 pairs of four 4096 (4) 45.1/46.0, 39.3/42.2; 256 single heads 1024 (4) 52/52; but 64 pairs of four
+        // 8192 (8) 67.4/62.5, 56.3/53.6; 32 pairs of eight 16384 (8) 82.6/77.5, 66.4/64.6; 256 single heads 2048 (8) 52.7/50.3
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
-        a.kunit = waves < 3L * cus && G < 8 ? akv::kMinUnit : akv::kTB;
-        // groups of eight heads: two waves per block instead, four heads each, below 3.5 waves per unit (one / two, us: 8 pairs 2048
-        // 35.8/33.8, 8192 44.4/41.8, 32 pairs 4096 (2 per unit) 43.9/41.8; 24 pairs 13000 (4.8) 65.1/66.7, 32 pairs 16384 (8) 76/85)
-        a.khs = G == 8 && waves < 7L * cus / 2 ? 2 : 1;
+        a.kshort = waves <= 5L * cus;
         a.lg_nt = long(a.s.B) * a.s.Hq * a.max_len * long(sizeof(float)) >= (8L << 20);   // of one or two heads; figures: k_tile
     }
     char* ws = static_cast<char*>(workspace);

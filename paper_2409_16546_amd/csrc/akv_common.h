@@ -18,9 +18,9 @@ constexpr int kAMin = -64;         // floor of the score exponent
 constexpr int kBuckets = 65;       // exponent buckets 0..64 of the approximate top-k
 constexpr int kMaxG = 8;           // query heads per KV head supported
 
-// K pass: one wave covers one unit of tokens, a 256-token block (4 consecutive tokens per lane) or half of one.
+// K pass: one wave covers a 256-token block (4 consecutive tokens per lane), or the four waves of a workgroup do.
 constexpr int kKWaves = 4;                         // waves per workgroup
-constexpr int kMinUnit = kTB / 2;                  // tokens of the smaller unit
+constexpr int kMinUnit = kTB / 2;                  // the workspace has room for a maximum per so many tokens (the sizes callers have been given); one per block is used
 // V pass: one workgroup covers a chunk of tokens; a wave takes 16 token rows at a time.
 constexpr int kVWaves = 4;
 constexpr int kVChunk = 512;                       // chunks are at least this long where they are many
@@ -30,7 +30,7 @@ constexpr int kVFewPairs = 64, kVFewChunks = 16;   // then up to this many chunk
 // Offsets (bytes) into the decode workspace.
 struct WsLayout {
     size_t logits;   // float [B][Hq][Ncap]
-    size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the units of the K pass
+    size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the K blocks (the first half of each row)
     size_t M;        // float [B][Hq]
     size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
     size_t partO;    // float [B][Hq][v_slots][D]
@@ -91,9 +91,8 @@ struct DecodeArgs {
     int32_t* Ehat;
     float* partO;
     float* partZ;
-    int kunit;           // tokens per wave of the K kernel of the token-split path: kTB or kMinUnit
+    int kshort;          // the K kernel of the token-split path gives a block to four waves instead of one
     int lg_nt;           // the K kernel of one or two heads stores its logits with the non-temporal hint
-    int khs;             // waves per unit there, each for its share of the query heads: 1 or 2
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
     int vslots;          // chunks per (sequence, KV head) in partO and partZ
     int32_t* vcount;     // [B][Hkv] arrival counters of the V kernel of the token-split path

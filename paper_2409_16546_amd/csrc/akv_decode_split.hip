@@ -6,43 +6,87 @@
 // Sections "Quantization of K-Cache", "Quantization of V-Cache", "Runtime of AlignedKV".
 #include <type_traits>
 #include "akv_common.h"
+#include "akv_k_short.h"
 #include "akv_k_tile.h"
 #include "akv_mid_step.h"
 #include "akv_v_rows.h"
 
 namespace akv {
 
-// K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one unit of 64*TPL tokens (k_tile) for G / HS
-// of the query heads and leaves its logits and the unit's maxima in the workspace.  HS = 2: neighbouring waves take the same
-// unit for half of the heads each (its bytes come from the caches the second time): in calls of a group of eight heads with fewer
-// units than SIMDs, whose time is one wave's walk through its unit.
-template <int G, int TPL, int HS>
+// K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one 256-token block (k_tile) and leaves its logits and the
+// block's maxima in the workspace.
+template <int G>
 __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 {
     __shared__ __align__(16) uint8_t kstage[kKWaves][kKStage];
     __shared__ KShared<G> ks;
-    constexpr int kUnit = 64 * TPL, kUnits = kKWaves / HS, GW = G / HS;   // units per workgroup, heads per wave
 
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63;
     const int Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int unit = blockIdx.x * kUnits + wave_u / HS;
-    if (blockIdx.x * kUnits * kUnit >= len) return;   // whole workgroup beyond the sequence (uniform)
+    const int blk = blockIdx.x * kKWaves + wave_u;
+    if (blockIdx.x * kKWaves * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
 
     if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
     k_levels<G>(a, b, h, ks, blockIdx.x == 0, len);
-    if (unit * kUnit < len) {                    // else this wave's unit is beyond the sequence
-        float tm[GW];
+    if (blk * kTB < len) {                    // else this wave's block is beyond the sequence
+        float tm[G];
         const u32x4_t zero4 = {0u, 0u, 0u, 0u};
         const u32x4_t none[6] = {zero4, zero4, zero4, zero4, zero4, zero4};
-        float lg[GW][TPL];
-        const size_t hq0 = size_t(b) * Hq + size_t(h) * G + (wave_u % HS) * GW;
-        k_tile<GW, HS == 1, TPL>(a, b, h, hq0, unit, len, ks, tm, none, false, lg, &kstage[wave_u][0], nullptr, 0, (wave_u % HS) * GW);
+        float lg[G][4];
+        const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
+        k_tile<G>(a, b, h, hq0, blk, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
         if (lane == 0)
 #pragma unroll
-            for (int g = 0; g < GW; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + unit] = tm[g];
+            for (int g = 0; g < G; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + blk] = tm[g];
+    }
+}
+
+// The same for calls with few blocks (akv_k_short.h): the four waves of a workgroup take a quarter of its block each, find the levels
+// by themselves and have all their HI bytes in flight meanwhile.
+template <int G>
+__global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs a)
+{
+    static_assert(kKWaves * kSUnit == kTB, "a block per workgroup");
+    __shared__ __align__(16) uint8_t kstage[kKWaves][kKStage];
+    __shared__ KShortQ<G> ks;
+    __shared__ float best_s[kKWaves][G];
+
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int lane = threadIdx.x & 63;
+    const int Hq = a.s.Hq, Ncap = a.s.Ncap;
+    KPairIn<G> in;
+    k_pairs_load<G>(a, b, h, in);
+    const int len = min(min(a.lens[b], Ncap), a.max_len);   // as in split_k_kernel
+    const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int unit = blockIdx.x * kKWaves + wave_u;
+    if (blockIdx.x * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
+    KShortHi hi;
+    k_short_hi(a, b, h, unit, len, hi);
+    if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
+    const KPairLevels lv = k_pair_levels<G>(a, b, h, ks, in, unit == 0, len);
+    const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
+    float best = -INFINITY;   // of head lane / (64 / G)
+    if (unit * kSUnit < len) {                    // else this wave's unit is beyond the sequence
+        float lg[G], m[G];
+        k_short_tile<G>(a, b, h, unit, len, lv, hi, ks, &kstage[wave_u][0], lg);
+        const int t = unit * kSUnit + lane;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            a.logits[(hq0 + g) * Ncap + t] = lg[g];
+            m[g] = t < len ? lg[g] : -INFINITY;
+        }
+        best = wave_max_each<G>(m);
+    }
+    if (lane % (64 / G) == 0) best_s[wave_u][lane / (64 / G)] = best;
+    __syncthreads();
+    if (threadIdx.x < G) {
+        float m = best_s[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < kKWaves; ++w) m = fmaxf(m, best_s[w][threadIdx.x]);
+        a.tilemax[(hq0 + threadIdx.x) * (Ncap / kMinUnit) + blockIdx.x] = m;
     }
 }
 
@@ -80,20 +124,14 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
     const float* tm = a.tilemax + hq * (Ncap / kMinUnit);
-    const int upb = kTB / a.kunit;   // units of the K kernel per block: 1 or 2
-    auto block_max_of = [&](int i) {
-        float m = tm[i * upb];
-        if (upb == 2 && (2 * i + 1) * kMinUnit < len) m = fmaxf(m, tm[2 * i + 1]);
-        return m;
-    };
     // the maxima are looked at up to four times, each a round trip in the chain: those of the first kBest blocks stay in LDS (B 1, 32/8,
     // 8192 tokens 34.8 -> 34.1 us a call, B 4 45.8 -> 45.0, others 0 to 0.6 %)
-    auto block_max = [&](int i) { return i < kBest ? best_s[i] : block_max_of(i); };
+    auto block_max = [&](int i) { return i < kBest ? best_s[i] : tm[i]; };
 
     // ---- the global max logit (exact, order-free) and the bound of the cut
     float m = -INFINITY;
     for (int i = tid; i < nblk; i += NT) {
-        const float bm = block_max_of(i);
+        const float bm = tm[i];
         if (i < kBest) best_s[i] = bm;
         m = fmaxf(m, bm);
     }
@@ -380,11 +418,10 @@ int split_v_workgroups_per_cu(int G) { return G == 2 ? 3 : 4; }
 template <int G>
 static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t k_done_event, hipEvent_t mid_event)
 {
-    const int tile = a.kunit * kKWaves / a.khs;   // tokens per workgroup of the K kernel
+    const int tile = a.kshort ? kTB : kTB * kKWaves;   // tokens per workgroup of the K kernel
     const dim3 kgrid((a.max_len + tile - 1) / tile, a.s.Hkv, a.s.B), kblock(64 * kKWaves);
-    // groups of eight take two waves per block where the others take half blocks
-    if (G == 8 ? a.khs == 2 : a.kunit == kMinUnit) hipLaunchKernelGGL((split_k_kernel<G, G == 8 ? 4 : 2, G == 8 ? 2 : 1>), kgrid, kblock, 0, st, a);
-    else hipLaunchKernelGGL((split_k_kernel<G, 4, 1>), kgrid, kblock, 0, st, a);
+    if (a.kshort) hipLaunchKernelGGL(split_k_short_kernel<G>, kgrid, kblock, 0, st, a);
+    else hipLaunchKernelGGL(split_k_kernel<G>, kgrid, kblock, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;

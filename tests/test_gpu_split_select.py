@@ -147,3 +147,25 @@ def test_token_split_with_half_blocks_and_short_chunks(T, G, lens):
     w = workloads.make(4, B=2, Hq=2 * G, Hkv=2, N=max(lens), seed=600 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
     T.assert_decode_equal(out, dbg, r, lens, G, f"half blocks G{G}")
+
+
+@pytest.mark.parametrize("lens", [[1, 63, 64, 65], [255, 256, 257, 191], [0, 513, 128, 193]])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_token_split_with_four_waves_per_block(T, G, lens):
+    """Few K blocks: the four waves of a workgroup take 64 tokens of its block each; lengths around the edges of waves and blocks."""
+    from paper_2409_16546_amd import workloads
+    print(f"token-split path, four waves per block: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=4, Hq=3 * G, Hkv=3, N=max(lens), seed=700 + G)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2, guard_bits=G % 3)
+    T.assert_decode_equal(out, dbg, r, lens, G, f"four waves per block G{G}")
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_token_split_with_one_wave_per_block(T, G):
+    """Six K blocks per compute unit: a wave takes a whole one."""
+    from paper_2409_16546_amd import workloads
+    lens = [3072, 1, 2049, 300]
+    print(f"token-split path, one wave per block: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=3072, seed=800 + G)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
+    T.assert_decode_equal(out, dbg, r, lens, G, f"one wave per block G{G}")
