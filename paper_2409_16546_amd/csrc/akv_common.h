@@ -33,8 +33,8 @@ struct WsLayout {
     size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the K blocks (the first half of each row)
     size_t M;        // float [B][Hq]
     size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
-    size_t partO;    // float [B][Hq][v_slots][D]
-    size_t partZ;    // float [B][Hq][v_slots]
+    size_t partO;    // float [B][Hkv][v_slots][G][D]: of a chunk, in the order in which the V kernel's lanes hold them
+    size_t partZ;    // float [B][Hkv][v_slots][G]
     size_t control;  // int32 [2][B][Hkv]: unused words (they keep the sizes callers have been given), then the arrival counters of the V kernel per (sequence, KV head); zero between calls
     size_t control_bytes;
     size_t total;
@@ -214,6 +214,7 @@ __device__ __forceinline__ void assemble8(uint32_t H0, uint32_t H1, uint32_t M, 
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
 constexpr uint32_t kSkip = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
 {
@@ -262,6 +263,10 @@ __device__ __forceinline__ void store_agent(float* p, float v)
 __device__ __forceinline__ float load_agent(const float* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void buf_store_b128_agent(u32x4_t v, __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kAuxSc1);
 }
 __device__ __forceinline__ u32x4_t buf_load_b128_agent(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
@@ -325,6 +330,14 @@ __device__ __forceinline__ int score_a(float x)
     return fl >= (float)kAMin ? (int)fl : kAMin;
 }
 
+// the largest whole number not above x (one instruction; x within the range of an int)
+__device__ __forceinline__ int floor_int(float x)
+{
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // Inclusive prefix sum over the 64 lanes of a wave in the vector ALU (six data-parallel-primitive steps: shifts by
 // 1, 2, 4, 8 inside the rows of 16 lanes, then lane 15 of a row added to the next row, then lane 31 to the upper
 // half); a lane without a source adds zero.
@@ -373,6 +386,56 @@ __device__ __forceinline__ int wave_max_int(int v)
     v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));
     v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Sums over lanes in the vector ALU.  A value added to that of the lane 16 / 32 further (mod the pairs of rows / the halves), in both:
+__device__ __forceinline__ float add_lane16(float v)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(float_bits(v), float_bits(v), false, false);
+    return bits_float(s[0]) + bits_float(s[1]);
+}
+__device__ __forceinline__ float add_lane32(float v)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(float_bits(v), float_bits(v), false, false);
+    return bits_float(s[0]) + bits_float(s[1]);
+}
+template <int CTRL> __device__ __forceinline__ float add_dpp(float v)
+{
+    return v + bits_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)float_bits(v), CTRL, 0xF, 0xF, false));
+}
+// ... over the lanes with the same lane % STEP (1, 2, 4, 8), in all of them
+template <int STEP> __device__ __forceinline__ float wave_sum(float v)
+{
+    if (STEP <= 1) v = add_dpp<0xB1>(v);    // quad_perm [1,0,3,2]
+    if (STEP <= 2) v = add_dpp<0x4E>(v);    // quad_perm [2,3,0,1]
+    if (STEP <= 4) v = add_dpp<0x124>(v);   // row_ror:4
+    v = add_dpp<0x128>(v);                  // row_ror:8
+    return add_lane32(add_lane16(v));
+}
+
+// Sums over the 8 row lanes of a wave (lane / 8), two values per exchange: afterwards a lane holds the totals of columns
+// row_lane_column(lane), + 1 of its 16, v[0] and v[1].  (24 instead of 48 exchanges through the LDS unit for 16 values: that
+// unit is shared by the whole compute unit.)
+__device__ __forceinline__ int row_lane_column(int lane) { return 8 * (lane >> 5) + 4 * ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1); }
+__device__ __forceinline__ void sum_row_lanes(const float (&acc)[16], float (&v)[2])
+{
+    float a[8], b[4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {   // lower half of the wave: columns 0..7, upper half: 8..15
+        const auto x = __builtin_amdgcn_permlane32_swap(float_bits(acc[i]), float_bits(acc[i + 8]), false, false);
+        a[i] = bits_float(x[0]) + bits_float(x[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto x = __builtin_amdgcn_permlane16_swap(float_bits(a[i]), float_bits(a[i + 4]), false, false);
+        b[i] = bits_float(x[0]) + bits_float(x[1]);
+    }
+    const bool up = threadIdx.x & 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = up ? b[i + 2] : b[i], send = up ? b[i] : b[i + 2];
+        v[i] = keep + bits_float(__builtin_amdgcn_update_dpp(0, float_bits(send), 0x128, 0xF, 0xF, false));   // row_ror:8
+    }
 }
 
 #endif  // __HIPCC__

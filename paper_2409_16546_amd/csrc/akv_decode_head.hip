@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     if (pair >= a.s.B * Hkv) return;
     const int h = pair % Hkv, b = pair / Hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane >> 3, cl = lane & 7;
+    const int cl = lane & 7;
     const size_t bh = size_t(b) * Hkv + h;
     int ticket = -1;
     // q and K_colmax of the head are asked for first: everything below queues up behind them
@@ -199,10 +199,7 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
 
     // ---- V side: each wave walks its range of batches of 8*KG rows -------------------------------------
     VRule<> vr;
-    v_rule_setup(ms.ehat, a.guard_bits, a.force_level, vr);
-    float Mg[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = ms.M[g];
+    v_rule_load(ms.rule, a.force_level, vr);
     float acc[G][16], z[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -210,15 +207,15 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[g][i] = 0.0f;
     }
-    v_rows<G, KG, DEBUG, kHeadVPre, kHeadVPre>(a, b, h, vb0 * RB, RB, vb1 - vb0, len, vr, Mg, acc, z, pre, pre_ok, lds_lg, lds_tokens);
-    v_reduce_rows<G>(acc, z);
-    if (r == 0) {
+    v_rows<G, KG, DEBUG, kHeadVPre, kHeadVPre, false>(a, b, h, vb0 * RB, RB, vb1 - vb0, len, vr, ms.M[lane % G], acc, z, pre, pre_ok, lds_lg, lds_tokens, [] {});
+    float sum[G][2];
+    v_reduce_rows<G>(acc, z, sum);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) red_s[wave][g][cl * 16 + i] = acc[g][i];
-            if (cl == 0) red_s[wave][g][kD] = z[g];
-        }
+    for (int g = 0; g < G; ++g) {
+        const int d = cl * 16 + row_lane_column(lane);
+        red_s[wave][g][d] = sum[g][0];
+        red_s[wave][g][d + 1] = sum[g][1];
+        if (lane == 0) red_s[wave][g][kD] = z[g];
     }
     __syncthreads();
     for (int idx = tid; idx < G * kD; idx += NT) {

@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
     if (unit * kSUnit < len) {                    // else this wave's unit is beyond the sequence
         float lg[G], m[G];
         k_short_tile<G>(a, b, h, unit, len, lv, hi, ks, &kstage[wave_u][0], lg);
-        const int t = unit * kSUnit + lane;
+        const int t = unit * kSUnit + k_short_token(lane);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             a.logits[(hq0 + g) * Ncap + t] = lg[g];
@@ -91,29 +91,29 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
 }
 
 // Mid step: one workgroup per (sequence, query head) does all of it -- the global max logit, the approximate top-k, O_est
-// and the result exponents of its head.  It reads only the K blocks that can hold a selected token: every block maximum
-// the K kernel left behind is itself a token, so the bucket Jb in which the running count of block maxima reaches k' is
-// an upper bound of the cut bucket, and a block whose best token lies beyond Jb holds nothing that counts (fewer than k'
-// blocks: all are read).  Each wave takes a contiguous range of the blocks, in token order:
-//   pass 1  the histogram of its tokens in buckets <= Jb (LDS; the floor bucket is what is left of the range, uncounted);
+// and the result exponents of its head.  Each wave finds M by itself and takes a contiguous range of the blocks, in token order:
+//   pass 1  the histogram of its tokens' score exponents (LDS);
 //   cut     from the totals, and from the waves in front of it how many selected tokens precede its range;
-//   pass 2  the blocks up to the cut once more (from L2), in order: ballots place the selected tokens.  A block whose best
-//           token is in the cut bucket itself is passed over once enough tokens of that bucket have been seen.
-// Bound by its chain of dependent round trips to memory (maxima, pass 1, pass 2, V rows), about a microsecond each, not by
-// bytes; so a head has a workgroup of its own, with 32 blocks in flight in each pass.
-// Measured on whole calls, against a pass over every logit (1024-token slices, histograms and candidates through memory)
-// followed by one selecting workgroup per KV head: 198 -> 181 us (B 8, 32/8 heads, 32768 tokens), 301 -> 273 us (B 4, 32/8,
-// up to 131072), 101 -> 80 us (B 3, 64/8, up to 13000); no call got slower.
-// NT: 512 threads, or 1024 where every head can have a compute unit to itself and has more than 16 blocks (B 8, 32/8, 32768
-// tokens 173.4 -> 171.6 us a call, B 3, 64/8, up to 13000 69.8 -> 68.9; with 512 heads of 33 blocks 283.3 -> 284.7, with 32 heads
-// of 8 blocks 27.2 -> 28.0).
+//   pass 2  ballots place the selected tokens.
+// Up to kKeep blocks per wave it reads all of them at the start, beside the maxima, and keeps their logits in registers.  Of longer sequences
+// it reads only the K blocks that can hold a selected token: every block maximum the K kernel left behind is itself a token, and so is the
+// largest of those that fall on one lane (block i on lane i % 64); the bucket Jb in which the running count of the lanes' maxima reaches k'
+// is an upper bound of the cut bucket, and a block whose best token lies beyond Jb holds nothing that counts (the floor bucket needs no
+// count: it is what is left of the range).  Pass 2 fetches the blocks up to the cut again (from L2) only where a wave had more than kKeep, or
+// the cut is the floor bucket; a block whose best token is in the cut bucket itself is then passed over once enough tokens of it have been seen.
+// Bound by its chain of dependent steps, not by bytes: a wave takes 4.5 to 5.5 cycles an instruction, 25 to 30 where a scalar one needs the
+// result of a vector one, and two or three round trips to memory of some 900 cycles; so a head has a workgroup of its own, and its
+// loops run over blocks that are there only.
+// Measured against a histogram of the block maxima by LDS atomics, two barriers more, and code for every slot whether it held a block or
+// not: B 1, 32/8, 1024 tokens 18.4 -> 16.9 us a call, 4096 22.3 -> 21.0, 8192 27.0 -> 24.8, B 3, 64/8, 13000 57.0 -> 55.6; longer ones equal.
+// NT: 512 threads, or 1024 where every head can have a compute unit to itself and has more than 16 blocks (512 / 1024: B 1, 32/8, 1024 tokens
+// 16.9/17.6, 4096 21.0/21.0, 32768 47.1/45.9, B 3, 64/8, 13000 57.4/55.6; with 512 heads of 16 blocks 57.7/61.1).
 template <int NT>
 __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
 {
-    constexpr int kWaves = NT / 64, kAhead = 32 / kWaves;   // kAhead: blocks of a wave in flight
+    constexpr int kWaves = NT / 64, kKeep = 8;   // kKeep: blocks of a wave in flight
     __shared__ MidShared ms;
-    constexpr int kBest = 1024;
-    __shared__ float red_s[kWaves], best_s[kBest];
+    __shared__ int hist_s[kWaves][64 + 64];      // per wave: buckets 0..63, and a place per lane for tokens that need no count
 
     const int hq_i = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -123,132 +123,190 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / (Hq / Hkv);
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
-    const float* tm = a.tilemax + hq * (Ncap / kMinUnit);
-    // the maxima are looked at up to four times, each a round trip in the chain: those of the first kBest blocks stay in LDS (B 1, 32/8,
-    // 8192 tokens 34.8 -> 34.1 us a call, B 4 45.8 -> 45.0, others 0 to 0.6 %)
-    auto block_max = [&](int i) { return i < kBest ? best_s[i] : tm[i]; };
-
-    // ---- the global max logit (exact, order-free) and the bound of the cut
-    float m = -INFINITY;
-    for (int i = tid; i < nblk; i += NT) {
-        const float bm = tm[i];
-        if (i < kBest) best_s[i] = bm;
-        m = fmaxf(m, bm);
-    }
-    m = wave_max(m);
-    if (lane == 0) red_s[wave] = m;
-    if (tid < kBuckets) ms.cnt[tid] = 0;
-    for (int i = tid; i < kWaves * (kBuckets + 1); i += NT) (&ms.cntw[0][0])[i] = 0;
-    __syncthreads();
-    float M = red_s[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) M = fmaxf(M, red_s[w]);
-    int Jb = 64;
-    if (nblk >= kk) {   // uniform
-        int n64 = 0;
-        for (int i0 = 0; i0 < nblk; i0 += NT) mid_hist_add(ms.cnt, i0 + tid < nblk ? -score_a(score_x(block_max(i0 + tid), M, a.c)) : 1000, n64);
-        __syncthreads();
-        int below;
-        mid_find_cut(ms.cnt[lane], kk, Jb, below);   // the floor bucket is not counted: 64 if none before it is
-    }
-
     const int b0 = int((long long)nblk * wave / kWaves), b1 = int((long long)nblk * (wave + 1) / kWaves);   // the wave's blocks
+    const bool all = nblk <= kKeep / 2 * kWaves;   // every wave reads all of its blocks, and keeps them
+    const __amdgpu_buffer_rsrc_t rs_tm = make_rsrc(a.tilemax + hq * (Ncap / kMinUnit), uint32_t(Ncap / kTB) * 4u);
     const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
-    // bucket of the best token of block c0 + lane (1000 past the range)
-    auto best_of = [&](int c0) { return c0 + lane < b1 ? -score_a(score_x(block_max(c0 + lane), M, a.c)) : 1000; };
-    // takes up to kAhead blocks off the mask and asks for their logits (lane -> four consecutive tokens)
-    auto fetch = [&](int c0, uint64_t& mask, int (&blk)[kAhead], u32x4_t (&w)[kAhead]) {
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            blk[u] = mask ? c0 + __builtin_ctzll(mask) : -1;
-            mask &= mask - 1;
-            w[u] = buf_load_b128(rs_lg, blk[u] >= 0 ? uint32_t(blk[u] * kTB + lane * 4) * 4u : kSkip);
-        }
+    int nb = 0, blk[kKeep];   // the blocks at hand (uniform) and their logits (lane -> four consecutive tokens)
+    u32x4_t w[kKeep];
+    auto ask = [&](int u, int block) {
+        blk[u] = block;
+        w[u] = buf_load_b128(rs_lg, uint32_t(block) * (kTB * 4u) + uint32_t(lane) * 16u);
     };
-    auto score4 = [&](int blk, const u32x4_t& w, float (&x)[4], int (&j)[4]) {
-        const float lv[4] = {bits_float(w.x), bits_float(w.y), bits_float(w.z), bits_float(w.w)};
-        const int t0 = blk * kTB + lane * 4;
+
+    // ---- the global max logit (exact, order-free)
+    float m = -INFINITY;   // of the blocks of this lane
+    for (int i0 = 0; i0 < nblk; i0 += 4 * 64) {
+        float t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = bits_float(buf_load_b32(rs_tm, uint32_t(i0 + 64 * i + lane) * 4u));
+        if (all) {   // nothing to decide first: the logits are on their way beside the maxima (one turn: nblk <= 64)
+            nb = b1 - b0;
+#pragma unroll
+            for (int u = 0; u < kKeep; ++u)
+                if (u < nb) ask(u, b0 + u);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = fmaxf(m, i0 + 64 * i + lane < nblk ? t[i] : -INFINITY);
+    }
+    hist_s[wave][lane] = 0;   // read and written by this wave alone up to the cut
+    const float M = wave_max(m);
+    // score and score exponent of the tokens of block blk[u] (score_x, score_a); -1000 past the sequence
+    auto score4 = [&](int u, float (&x)[4], int (&e)[4]) {
+        const float lv[4] = {bits_float(w[u].x), bits_float(w[u].y), bits_float(w[u].z), bits_float(w[u].w)};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             x[i] = score_x(lv[i], M, a.c);
-            j[i] = t0 + i < len ? -score_a(x[i]) : 1000;
+            e[i] = floor_int(fmaxf(x[i], (float)kAMin));   // the maximum passes over a score that is not a number
         }
+        if ((blk[u] + 1) * kTB > len)   // uniform
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = blk[u] * kTB + lane * 4 + i < len ? e[i] : -1000;
     };
-    // ---- pass 1.  Bucket Jb is counted in the lanes: where scores are flat nearly all tokens are in it, and LDS atomics of a whole
-    // wave on one address take a cycle per lane (B 1, 32/8, 131072 tokens of equal scores: 214 -> 126 us a call; where scores spread, 0.2 to 0.9 % more).
+    // buckets before `top` are counted by LDS atomics, bucket `top` in the lanes (n_top), later ones not at all: atomics of a whole wave on one
+    // address take a cycle per lane, and where scores are flat nearly all tokens of a long sequence are in the cut bucket (B 1, 32/8, 131072
+    // tokens of equal scores: every bucket by atomics 217 us a call, so 125)
     int n_top = 0;
-    for (int c0 = b0; c0 < b1; c0 += 64) {
-        const int best = best_of(c0);
-        uint64_t mask = __ballot(a.dbg.a ? best <= 64 : best <= min(Jb, 63));   // the export wants every token
-        while (mask) {
-            int blk[kAhead];
-            u32x4_t w[kAhead];
-            fetch(c0, mask, blk, w);
+    auto count = [&](int top) {
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                if (blk[u] < 0) continue;   // uniform
-                float x[4];
-                int j[4];
-                score4(blk[u], w[u], x, j);
+        for (int u = 0; u < kKeep; ++u) {
+            if (u >= nb) break;   // uniform
+            float x[4];
+            int e[4];
+            score4(u, x, e);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (j[i] <= Jb) {
-                        if (j[i] == Jb) ++n_top;
-                        else atomicAdd(&ms.cntw[wave][j[i]], 1);
-                    }
-                    if (j[i] <= 64 && a.dbg.a) a.dbg.a[hq * Ncap + blk[u] * kTB + lane * 4 + i] = (int8_t)(-j[i]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                atomicAdd(&hist_s[wave][e[i] > -top ? -e[i] : 64 + lane], 1);
+                n_top += e[i] == -top;
+                if (a.dbg.a && e[i] >= kAMin) a.dbg.a[hq * Ncap + blk[u] * kTB + lane * 4 + i] = (int8_t)e[i];
             }
         }
+    };
+    // bucket of the best token of block c0 + lane (1000 past the range)
+    auto best_of = [&](int c0) {
+        const float best = bits_float(buf_load_b32(rs_tm, uint32_t(c0 + lane) * 4u));
+        return c0 + lane < b1 ? -score_a(score_x(best, M, a.c)) : 1000;
+    };
+    // takes up to kKeep blocks off the mask
+    auto take = [&](int c0, uint64_t& mask) {
+        nb = min((int)__builtin_popcountll(mask), kKeep);
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u) {
+            if (u >= nb) break;   // uniform
+            ask(u, c0 + __builtin_ctzll(mask));
+            mask &= mask - 1;
+        }
+    };
+    // ---- pass 1
+    bool kept = all;
+    if (all) {
+        count(64);
+    } else {
+        // the bound of the cut: the smallest bucket that k' lanes reach, each with a token of its own (64 if fewer do)
+        const int j = lane < nblk ? -score_a(score_x(m, M, a.c)) : 1000;
+        int Jb = 0;
+#pragma unroll
+        for (int step = 64; step > 0; step >>= 1) Jb += __builtin_popcountll(__ballot(j < Jb + step)) < kk ? step : 0;
+        Jb = min(Jb, 64);
+        for (int c0 = b0; c0 < b1; c0 += 64) {
+            const int best = best_of(c0);
+            uint64_t mask = __ballot(a.dbg.a ? best <= 64 : best <= min(Jb, 63));   // the export wants every token
+            kept = b1 - b0 <= 64 && __builtin_popcountll(mask) <= kKeep;
+            while (mask) {
+                take(c0, mask);
+                count(Jb);
+            }
+        }
+        if (Jb < 64) {
+            n_top = wave_read(wave_scan_add(n_top), 63);
+            if (lane == 0) hist_s[wave][Jb] = n_top;
+        }
     }
-    n_top = wave_read(wave_scan_add(n_top), 63);
-    if (lane == 0 && Jb < 64) ms.cntw[wave][Jb] = n_top;   // the floor bucket stays uncounted
     __syncthreads();
     // ---- the cut, and the selected tokens of each kind in the waves before this one
     int tot = 0, before = 0;   // bucket `lane`: all waves / the waves before this one
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int c = ms.cntw[w][lane];
+    for (int v = 0; v < kWaves; ++v) {
+        const int c = hist_s[v][lane];
         tot += c;
-        before += w < wave ? c : 0;
+        before += v < wave ? c : 0;
     }
-    int J, below;
-    mid_find_cut(tot, kk, J, below);
-    const int fromcut = kk - below;
-    int n_lt0 = wave_read(wave_scan_add(lane < J ? before : 0), 63);
-    int n_eq0 = J < 64 ? wave_read(before, J) : min(b0 * kTB, len) - n_lt0;   // the cut in the floor bucket: all buckets before it are counted
-    // ---- pass 2
-    for (int c0 = b0; c0 < b1; c0 += 64) {
-        const int best = best_of(c0);
-        uint64_t mask = __ballot(best <= J);
-        while (mask) {
-            if (n_eq0 >= fromcut) mask &= __ballot(best < J);   // blocks that could only add to the cut bucket
-            if (!mask) break;
-            int blk[kAhead];
-            u32x4_t w[kAhead];
-            fetch(c0, mask, blk, w);
+    // both running counts in one scan, sixteen bits each: neither is told apart above k' <= 64, in 64 buckets
+    const int upto = wave_scan_add(min(tot, AKV_MAX_TOPK) | min(before, AKV_MAX_TOPK) << 16);
+    const uint64_t reached = __ballot((upto & 0xFFFF) >= kk);
+    const int J = reached ? __builtin_ctzll(reached) : 64;   // 64, the floor bucket, if none before it is the cut
+    const int sum = J == 0 ? 0 : wave_read(upto, J - 1);      // of the buckets before the cut, none of which holds k' tokens
+    const int fromcut = kk - (sum & 0xFFFF);
+    int n_lt0 = sum >> 16;
+    int n_eq0 = J < 64 ? wave_read(before, J) : min(b0 * kTB, len) - n_lt0;   // the cut in the floor bucket: all tokens before it are in buckets before it or in it
+    // ---- pass 2.  Selected tokens go to their places in sel and score (place AKV_MAX_TOPK takes the others)
+    auto emit = [&](int u, int i, float x, int pos, bool on) {
+        pos = on ? pos : AKV_MAX_TOPK;
+        ms.sel[pos] = blk[u] * kTB + lane * 4 + i;
+        ms.phat[pos] = x;
+    };
+    auto place = [&] {
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                if (blk[u] < 0) continue;   // uniform
-                float x[4];
-                int j[4], n_lt, n_eq, w_lt, w_eq;
-                score4(blk[u], w[u], x, j);
+        for (int u = 0; u < kKeep; ++u) {
+            if (u >= nb) break;   // uniform
+            float x[4];
+            int e[4], w_eq = 0, w_all = 0, n = 0;
+            score4(u, x, e);
+            if (!__ballot(max(max(e[0], e[1]), max(e[2], e[3])) >= -J)) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w_eq += __builtin_popcountll(__ballot(e[i] == -J));
+            if (n_eq0 >= fromcut || n_eq0 + w_eq <= fromcut) {   // the tokens of bucket J are all left out or all in: one kind
+                const int least = n_eq0 >= fromcut ? 1 - J : -J;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint64_t on = __ballot(e[i] >= least);
+                    n = __builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, n));
+                    w_all += __builtin_popcountll(on);
+                }
+                n += n_lt0 + min(n_eq0, fromcut);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    emit(u, i, x[i], n, e[i] >= least);
+                    n += e[i] >= least;
+                }
+                n_lt0 += n_eq0 >= fromcut ? w_all : w_all - w_eq;
+            } else {
+                int j[4], n_lt, n_eq, w_lt;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) j[i] = -e[i];
                 mid_wave_order(j, J, n_lt, n_eq, w_lt, w_eq);
                 n_lt += n_lt0;
                 n_eq += n_eq0;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const bool is_lt = j[i] < J, is_eq = j[i] == J;
-                    if (is_lt || (is_eq && n_eq < fromcut)) mid_emit(ms, n_lt + (n_eq < fromcut ? n_eq : fromcut), blk[u] * kTB + lane * 4 + i, x[i], j[i]);
-                    n_lt += is_lt;
-                    n_eq += is_eq;
+                    emit(u, i, x[i], n_lt + min(n_eq, fromcut), j[i] < J || (j[i] == J && n_eq < fromcut));
+                    n_lt += j[i] < J;
+                    n_eq += j[i] == J;
                 }
                 n_lt0 += w_lt;
-                n_eq0 += w_eq;
+            }
+            n_eq0 += w_eq;
+        }
+    };
+    if (kept && (all || J < 64)) {   // the blocks of pass 1, which are those up to the cut and perhaps more; the floor bucket may be in any block
+        place();
+    } else {
+        for (int c0 = b0; c0 < b1; c0 += 64) {
+            const int best = best_of(c0);
+            uint64_t mask = __ballot(best <= J);
+            while (mask) {
+                if (n_eq0 >= fromcut) mask &= __ballot(best < J);   // blocks that could only add to the cut bucket
+                if (!mask) break;
+                take(c0, mask);
+                place();
             }
         }
     }
     __syncthreads();
+    if (tid < kk) {   // the weight: 2^x with a linear mantissa, the exponent floored at -64
+        const float x = ms.phat[tid], fl = floorf(x);
+        ms.phat[tid] = ldexpf(1.0f + (x - fl), score_a(x));
+    }
     int ehat = 32767;
     mid_oest<NT>(a, bh, hq, kk, ms, ehat);
     if (tid < kD) a.Ehat[hq * kD + tid] = ehat;
@@ -266,18 +324,18 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     constexpr bool SHARED = v_shared<G>();
     constexpr int KG = 2, RB = 8 * KG;                      // rows of a batch
     static_assert(RB == kSRows && (kVMinChunk % (RB * kVWaves)) == 0, "a chunk is whole rounds");
-    // the combining workgroup: a thread sums four neighbouring outputs over every kSub-th chunk
+    // a chunk's partial sums are kCols vectors of four; the combining workgroup: a thread takes one of them over every kSub-th chunk
     constexpr int kCols = G * kD / 4, kSub = 64 * kVWaves / kCols;
     struct Private { union { float red[kVWaves][G][kD]; f32x4_t comb[kSub][kCols]; }; };
-    struct Shared { union { VShare rows; float red[G][kD]; f32x4_t comb[kSub][kCols]; }; };   // the sums are laid down when the last round has been read
+    struct Shared { union { VShare rows; f32x4_t comb[kSub][kCols]; }; };
     __shared__ __align__(16) std::conditional_t<SHARED, Shared, Private> lds_s;
     __shared__ float z_s[kVWaves][G];
-    __shared__ int ehat_s[kD];
+    __shared__ VRuleShared rule_s;
     __shared__ int last_s;
 
     const int h = blockIdx.y, b = blockIdx.z, split = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane >> 3, cl = lane & 7;
+    const int cl = lane & 7;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
     const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
     const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of 64 chosen at launch
@@ -291,48 +349,58 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
         return;
     }
 
-    if (tid < kD) {   // Rule 2 aligns to the smallest result exponent of the group
-        int e = 32767;
+    // Rule 2 aligns to the smallest result exponent of the group.  Asked for in front of the rows; worked out (ready()) when the first
+    // rows are on their way
+    const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
+    int eg[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) e = min(e, a.Ehat[(size_t(b) * Hq + size_t(h) * G + g) * kD + tid]);
-        ehat_s[tid] = e;
-        if (a.dbg.Ehat && split == 0) a.dbg.Ehat[bh * kD + tid] = (int16_t)e;
-    }
-    float Mg[G];
+    for (int g = 0; g < G; ++g) eg[g] = a.Ehat[(hq0 + g) * kD + tid % kD];
+    float Ml[SHARED ? G / 4 : 1];   // the global max of this lane's query heads (one load per lane: taken for all heads at once they went through scratch memory, a round trip each)
 #pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = a.M[size_t(b) * Hq + size_t(h) * G + g];
-    __syncthreads();
+    for (int s = 0; s < (SHARED ? G / 4 : 1); ++s) Ml[s] = a.M[hq0 + 4 * s + lane % (SHARED ? 4 : G)];
+    auto ready = [&](auto& vr) {
+        if (tid < kD) {
+            int e = eg[0];
+#pragma unroll
+            for (int g = 1; g < G; ++g) e = min(e, eg[g]);
+            v_rule_store(rule_s, tid, e, a.guard_bits);
+            if (a.dbg.Ehat && split == 0) a.dbg.Ehat[bh * kD + tid] = (int16_t)e;
+        }
+        lds_barrier();
+        v_rule_load(rule_s, a.force_level, vr);
+    };
+    const __amdgpu_buffer_rsrc_t rs_o = make_rsrc(a.partO + bh * G * nsplit * kD, uint32_t(G) * uint32_t(nsplit) * kD * 4u);
+    float* const part_z = a.partZ + bh * G * nsplit;
     // HI bytes fetched three or four batches ahead in the private mode (few waves per SIMD: each keeps more bytes in
-    // flight), two in the shared mode (four waves per SIMD; three and four measured 1.5 % and 3 % slower)
+    // flight), two in the shared mode (four waves per SIMD; three and four measured 1.5 % and 3 % slower;
+    // where waves are few, four ahead with the decisions three ahead gains nothing: a round of a wave by itself is 2300 cycles of instructions).
     constexpr int DL = SHARED ? 2 : (G == 2 ? 4 : 3);
     if constexpr (SHARED) {
         VRule<4> vr;
-        v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
         float acc[8], z[G / 4];
 #pragma unroll
         for (int s = 0; s < G / 4; ++s) z[s] = 0.0f;
-        v_rows_shared<G, DEBUG, DL>(a, b, h, c0 + wave * RB, vchunk / (RB * kVWaves), len, vr, Mg, acc, z, lds_s.rows);
+        v_rows_shared<G, DEBUG, DL>(a, b, h, c0 + wave * RB, vchunk / (RB * kVWaves), len, vr, Ml, acc, z, lds_s.rows, [&] { ready(vr); });
 #pragma unroll
         for (int s = 0; s < G / 4; ++s) {   // over the lanes of the same query heads
-            for (int o = 4; o < 64; o <<= 1) z[s] += __shfl_xor(z[s], o);
+            z[s] = wave_sum<4>(z[s]);
             if (lane < 4) z_s[wave][lane + 4 * s] = z[s];
         }
         // a result tile holds the high parts of the weights in its rows 0 .. G-1 and the low parts in rows G .. 2G-1:
-        // lanes 16 * (G / 4) apart hold the two parts of one (query head, line)
-        float part[8];
+        // lanes 16 * (G / 4) apart hold the two parts of one (query head, line).  A lane's four words are those of four query heads for
+        // one line, and as such they go out: vector 128 (lane / 16) + line of the chunk
+        f32x4_t part[2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) part[i] = (acc[i] + __shfl(acc[i], (lane + 4 * G) & 63)) * (1.0f / kVWeightScale);
-        __syncthreads();   // every wave is done with the rows of the last round: the same LDS now takes the sums
+        for (int i = 0; i < 8; ++i) part[i / 4][i % 4] = (G == 4 ? add_lane16(acc[i]) : add_lane32(acc[i])) * (1.0f / kVWeightScale);
         if (lane < 4 * G) {
 #pragma unroll
             for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) lds_s.red[4 * (lane >> 4) + i][line_channel(32 * wave + 16 * t + (lane & 15))] = part[4 * t + i];
+                buf_store_b128_agent(__builtin_bit_cast(u32x4_t, part[t]), rs_o, (uint32_t(split) * kCols + kD * uint32_t(lane >> 4) + uint32_t(32 * wave + 16 * t + (lane & 15))) * 16u);
         }
+        __syncthreads();
     } else {
         VRule<> vr;
-        v_rule_setup(ehat_s, a.guard_bits, a.force_level, vr);
-        float acc[G][16], z[G];
+        float acc[G][16], z[G], sum[G][2];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             z[g] = 0.0f;
@@ -340,73 +408,84 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
             for (int i = 0; i < 16; ++i) acc[g][i] = 0.0f;
         }
         const u32x4_t none[1][KG] = {};
-        v_rows<G, KG, DEBUG, 0, DL, true>(a, b, h, c0 + wave * RB, RB * kVWaves, vchunk / (RB * kVWaves), len, vr, Mg, acc, z, none, false);
-        v_reduce_rows<G>(acc, z);
-        if (r == 0) {
+        v_rows<G, KG, DEBUG, 0, DL, true>(a, b, h, c0 + wave * RB, RB * kVWaves, vchunk / (RB * kVWaves), len, vr, Ml[0], acc, z, none, false, nullptr, 0, [&] { ready(vr); });
+        v_reduce_rows<G>(acc, z, sum);
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) lds_s.red[wave][g][cl * 16 + i] = acc[g][i];
+        for (int g = 0; g < G; ++g) {
+            *reinterpret_cast<float2*>(&lds_s.red[wave][g][cl * 16 + row_lane_column(lane)]) = make_float2(sum[g][0], sum[g][1]);
+            if (lane == 0) z_s[wave][g] = z[g];
         }
-        if (lane == 0) {
+        __syncthreads();
+        if (tid < kCols) {
+            f32x4_t o = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int g = 0; g < G; ++g) z_s[wave][g] = z[g];
+            for (int w = 0; w < kVWaves; ++w) o += *reinterpret_cast<const f32x4_t*>(&lds_s.red[w][0][4 * tid]);
+            buf_store_b128_agent(__builtin_bit_cast(u32x4_t, o), rs_o, (uint32_t(split) * kCols + uint32_t(tid)) * 16u);
         }
     }
-    __syncthreads();
-    for (int idx = tid; idx < G * (kD + 1); idx += 64 * kVWaves) {
-        const int g = idx / (kD + 1), d = idx % (kD + 1);
-        float s = 0.0f;
+    if (tid < G) {
+        float z = z_s[0][tid];
 #pragma unroll
-        for (int w = 0; w < kVWaves; ++w) {
-            if (d == kD) s += z_s[w][g];
-            else if constexpr (SHARED) s += w == 0 ? lds_s.red[g][d] : 0.0f;
-            else s += lds_s.red[w][g][d];
-        }
-        const size_t hq = size_t(b) * Hq + size_t(h) * G + g;
-        if (d < kD) store_agent(&a.partO[(hq * nsplit + split) * kD + d], s);
-        else store_agent(&a.partZ[hq * nsplit + split], s);
+        for (int w = 1; w < kVWaves; ++w) z += z_s[w][tid];
+        store_agent(&part_z[split * G + tid], z);
     }
 
     // ---- the workgroup that finishes last for this (sequence, KV head) combines the chunks -------------
     // out = sum_chunks O / sum_chunks Z: every chunk used the same global max, so nothing is rescaled.  All threads take part
-    // with 16-byte loads, eight chunks each in flight (one word per thread and output before: 5-7 us at the end of a call of
-    // eight heads per group, now 4; the round trips of stores, ticket and loads are what is left).
+    // with 16-byte loads, eight chunks each in flight, the weights' sums beside them; the round trips of stores, ticket and loads are
+    // what is left.  (The waves' sums by exchanges in the vector ALU and straight to memory as the lanes hold them, Rule 2's constants by a
+    // thread per channel, no trip through scratch memory for the maxima: B 1, 32/8, 1024 tokens 20.0 -> 18.4 us a call, 4096 24.2 -> 22.3, B 8, 32/8,
+    // 32768 188 -> 182, B 4, 131072 346 -> 336.)
     const int used = (len + vchunk - 1) / vchunk;
     stores_done();
     __syncthreads();
     if (tid == 0) last_s = take_ticket(&a.vcount[bh]) == used - 1;
     __syncthreads();
     if (!last_s) return;
-    const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
-    const int c = tid % kCols, sub = tid / kCols, g_out = c / (kD / 4);
-    const __amdgpu_buffer_rsrc_t rs_o = make_rsrc(a.partO + hq0 * nsplit * kD, uint32_t(G) * uint32_t(nsplit) * kD * 4u);
+    const int c = tid % kCols, sub = tid / kCols;
+    constexpr int kZ = 64 / G;   // chunks a wave's lanes take at a time: lane -> query head lane % G
+    const __amdgpu_buffer_rsrc_t rs_z = make_rsrc(part_z, uint32_t(G) * uint32_t(used) * 4u);
+    float zs = 0.0f;
     f32x4_t o = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int sp0 = sub; sp0 < used; sp0 += 8 * kSub) {   // eight chunks' words in flight; the additions stay in chunk order
+    for (int sp0 = 0; sp0 < used; sp0 += 8 * kSub) {   // eight chunks' words in flight; the additions stay in chunk order
+        static_assert(kZ == 8 * kSub, "one word of the weights' sums per lane and turn");
         u32x4_t po[8];
+        const float pz = bits_float(__builtin_amdgcn_raw_buffer_load_b32(rs_z, uint32_t((sp0 + lane / G) * G + lane % G) * 4u, 0, kAuxSc1));   // chunks past the last one: zeros
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int sp = sp0 + i * kSub;
-            po[i] = buf_load_b128_agent(rs_o, sp < used ? (uint32_t(g_out) * uint32_t(nsplit) + uint32_t(sp)) * (kD * 4u) + uint32_t(c % (kD / 4)) * 16u : kSkip);
+            const int sp = sp0 + sub + i * kSub;
+            po[i] = buf_load_b128_agent(rs_o, sp < used ? (uint32_t(sp) * kCols + uint32_t(c)) * 16u : kSkip);
         }
+        zs += pz;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[k] += bits_float(po[i][k]);
     }
-    for (int g = wave; g < G; g += kVWaves) {   // the weights' sums: a wave per query head, lane -> chunks
-        float zs = 0.0f;
-        for (int sp = lane; sp < used; sp += 64) zs += load_agent(&a.partZ[(hq0 + g) * nsplit + sp]);
-        for (int k = 1; k < 64; k <<= 1) zs += __shfl_xor(zs, k);
-        if (lane == 0) z_s[0][g] = zs;
+    zs = wave_sum<G>(zs);   // of query head lane % G
+    if (kSub > 1) {
+        lds_s.comb[sub][c] = o;
+        __syncthreads();
     }
-    if (kSub > 1) lds_s.comb[sub][c] = o;
-    __syncthreads();
-    if (sub == 0) {
+    if (sub == 0) {   // whole waves (kCols of 32, single heads: the lower half of one)
 #pragma unroll
         for (int u = 1; u < kSub; ++u) o += lds_s.comb[u][c];
+        float zg[G];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) store_out(a, hq0 + g_out, (c % (kD / 4)) * 4 + k, o[k] / z_s[0][g_out]);
+        for (int g = 0; g < G; ++g) zg[g] = bits_float((uint32_t)__builtin_amdgcn_readlane((int)float_bits(zs), g));
+        if constexpr (SHARED) {   // four query heads of one line
+            const int quad = c / kD, d = line_channel(c % kD);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float zk = G == 4 ? zg[k] : (quad ? zg[4 % G + k] : zg[k]);
+                store_out(a, hq0 + 4 * quad + k, d, o[k] / zk);
+            }
+        } else {
+            const int g = c / (kD / 4);
+            const float zk = G == 1 || g == 0 ? zg[0] : zg[G - 1];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) store_out(a, hq0 + g, (c % (kD / 4)) * 4 + k, o[k] / zk);
+        }
     }
     if (tid == 0) store_agent(&a.vcount[bh], 0);   // ready for the next call
 }

@@ -145,7 +145,8 @@ __device__ __forceinline__ void k_short_hi(const DecodeArgs& a, int b, int h, in
     }
 }
 
-// acc[g]: the logit of token unit * 64 + lane for query head g, by the same multiply-adds in the same order as in k_tile
+// acc[g]: the logit of token unit * 64 + k_short_token(lane) for query head g, by the same multiply-adds in the same order as in k_tile
+__device__ __forceinline__ int k_short_token(int lane) { return (lane & ~3) | ((lane & 1) << 1) | ((lane >> 1) & 1); }
 template <int G>
 __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, int unit, int len, const KPairLevels& lv, const KShortHi& hi,
                                              const KShortQ<G>& ks, uint8_t* stage, float (&acc)[G])
@@ -172,12 +173,14 @@ __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, 
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = 0.0f;
     // LDS: column c of the group is a row of 64 halves in pieces of eight tokens (16 bytes); the pieces of a row are permuted by its
-    // number, so that the lanes of a store meet on few banks.  Inside a piece tokens lie as 0 2 1 3 4 6 5 7 (assemble8_fill).
+    // number, so that the lanes of a store meet on few banks.  Inside a piece tokens lie as 0 2 1 3 4 6 5 7 (assemble8_fill).  The transposing
+    // read hands a lane the values of four columns at its own place: lane n of sixteen reads four values of row n / 4 and receives value n of all
+    // four rows.
     constexpr uint32_t kRow = kSUnit * 2;
-    const uint32_t at = (uint32_t(lane) & ~3u) | ((lane & 1) << 1) | ((lane >> 1) & 1);   // place of the lane's token in a row
-    uint32_t rd[8], wr[4];
+    const uint32_t n = lane & 15, piece = 2 * (lane >> 4) + ((n & 3) >> 1);
+    uint32_t rd[2], wr[4];   // rd: of rows 8 v .. 8 v + 3 and of the next four
 #pragma unroll
-    for (int k = 0; k < 8; ++k) rd[k] = (((at >> 3) ^ uint32_t(k)) << 4) | ((at & 7) * 2);
+    for (int e = 0; e < 2; ++e) rd[e] = (4 * e + (n >> 2)) * kRow + ((piece ^ (4 * e + (n >> 2))) << 4) + 8 * (n & 1);
 #pragma unroll
     for (int k = 0; k < 4; ++k) wr[k] = col * kRow + (((t / 8 + k) ^ (col & 7)) << 4);
 #pragma unroll
@@ -192,9 +195,12 @@ __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, 
             *reinterpret_cast<u32x4_t*>(stage + wr[k]) = u32x4_t{w[0], w[1], w[2], w[3]};
         }
         __builtin_amdgcn_wave_barrier();
-        uint16_t x[kSCols];
+        short4_t x[kSCols / 4];   // of four columns each
 #pragma unroll
-        for (int u = 0; u < kSCols; ++u) x[u] = *reinterpret_cast<const uint16_t*>(stage + u * kRow + rd[u & 7]);
+        for (int v = 0; v < kSCols / 4; ++v) {
+            typedef __attribute__((address_space(3))) short4_t* lds_ptr;
+            x[v] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)reinterpret_cast<short4_t*>(stage + rd[v & 1] + (v >> 1) * 8 * kRow));
+        }
 #pragma unroll
         for (int v = 0; v < kSCols / 4; ++v) {
             f32x4_t qx[MX ? S : G];   // four columns of head lane % 4 (+ 4 s), or of every head
@@ -202,7 +208,7 @@ __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, 
             for (int s = 0; s < (MX ? S : G); ++s) qx[s] = *reinterpret_cast<const f32x4_t*>(&ks.q[MX ? 4 * s + (lane & 3) : s][i * kSCols + 4 * v]);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float k = half_bits_to_float(x[4 * v + u]);
+                const float k = half_bits_to_float((uint16_t)x[v][u]);
                 if constexpr (MX) {
 #pragma unroll
                     for (int s = 0; s < S; ++s) dx[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(qx[s][u], k, dx[s], 0, 0, 0);

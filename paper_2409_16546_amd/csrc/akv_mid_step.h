@@ -3,7 +3,10 @@
 // "Quantization of V-Cache": the scores differ by orders of magnitude, so the product of a few of the
 // largest scores with their V rows estimates the result (O_est); an approximate top-k picks them.
 #pragma once
+#include <type_traits>
+
 #include "akv_common.h"
+#include "akv_v_rows.h"
 
 namespace akv {
 
@@ -12,12 +15,12 @@ constexpr int kMidMaxWaves = 16;
 // LDS of the mid step (declared __shared__ by the kernel that runs it)
 struct MidShared {
     float M[kMaxG];              // in: global max logit of every query head of the group (set by the caller)
-    int ehat[kD];                // out: result exponent per channel, min over the group
+    VRuleShared rule;            // out: Rule 2's constants per channel, from the smallest result exponent of the group
     int cnt[kBuckets];           // histogram of score exponents (several chunks of tokens per thread)
     int cntw[kMidMaxWaves][kBuckets + 1];   // ... per wave (one chunk: every thread owns four tokens)
     int wlt[kMidMaxWaves], weq[kMidMaxWaves];
-    int sel[AKV_MAX_TOPK];                   // selected tokens of one query head, ascending
-    alignas(16) float phat[AKV_MAX_TOPK];    // their weights
+    int sel[AKV_MAX_TOPK + 1];               // selected tokens of one query head, ascending (the last place: of the selection kernel)
+    alignas(16) float phat[AKV_MAX_TOPK + 1];   // their weights
     alignas(16) uint32_t v2[AKV_MAX_TOPK / 2][kD];   // fp16 bits of the selected V rows: rows 2i (low half) and 2i+1 of channel d
 };
 
@@ -174,7 +177,8 @@ __device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, 
     if (tid < kD) {
         const int d = tid;
         float acc = 0.0f;
-        for (int i0 = 0; i0 < kk; i0 += 16) {   // the additions stay in selection order
+        // sixteen rows at a time, the additions in selection order; ALL: none of them lies past the selection
+        auto rows16 = [&](int i0, auto all) {
             float pv[16];
             uint32_t vv[8];
 #pragma unroll
@@ -186,10 +190,13 @@ __device__ __forceinline__ void mid_oest_finish(const DecodeArgs& a, size_t hq, 
             for (int i = 0; i < 8; ++i) vv[i] = sm.v2[(i0 >> 1) + i][d];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                if (i0 + 2 * i < kk) acc = fmaf(pv[2 * i], lo_half(vv[i]), acc);
-                if (i0 + 2 * i + 1 < kk) acc = fmaf(pv[2 * i + 1], hi_half(vv[i]), acc);
+                if (all() || i0 + 2 * i < kk) acc = fmaf(pv[2 * i], lo_half(vv[i]), acc);
+                if (all() || i0 + 2 * i + 1 < kk) acc = fmaf(pv[2 * i + 1], hi_half(vv[i]), acc);
             }
-        }
+        };
+        int i0 = 0;
+        for (; i0 + 16 <= kk; i0 += 16) rows16(i0, std::true_type());
+        if (i0 < kk) rows16(i0, std::false_type());
         const int E = float_exp_field(acc) - 127;
         ehat = E < ehat ? E : ehat;
         if (a.dbg.oest) a.dbg.oest[hq * kD + d] = acc;
@@ -214,7 +221,7 @@ __device__ __forceinline__ void mid_oest(const DecodeArgs& a, size_t bh, size_t 
 // per-wave histograms give every wave the cut bucket and the number of selected tokens in the waves before it
 // without a second barrier; ballots order the tokens inside the wave.  The selected V rows are fetched by all
 // threads at once into LDS so that O_est costs one memory latency, then each channel runs its ordered FMA chain
-// from operands fetched up front.  Result: sm.ehat (LDS).
+// from operands fetched up front.  Result: sm.rule (LDS).
 // lds_lg / lds_stride: the logits in LDS as k_tile left them, or NULL (they are read from a.logits).
 template <int G, int NT>
 __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int len, MidShared& sm,
@@ -351,7 +358,7 @@ __device__ __forceinline__ void mid_step(const DecodeArgs& a, int b, int h, int 
         mid_oest<NT>(a, bh, hq, kk, sm, ehat);
     }
     if (tid < kD) {
-        sm.ehat[tid] = ehat;
+        v_rule_store(sm.rule, tid, ehat, a.guard_bits);
         if (a.dbg.Ehat) a.dbg.Ehat[bh * kD + tid] = (int16_t)ehat;
     }
     __syncthreads();

@@ -26,30 +26,33 @@ struct VRule {
     int force;      // -1, or the level every row is read at (then B = 4: no byte ever reaches bit 7)
 };
 
-// ehat: the 128 result exponents of the KV head (global memory or LDS)
+// The constants in LDS: thread d < 128 of the workgroup (two waves) lays down those of its channel, v_rule_load takes them up behind a
+// barrier (a lane working out its 16 or 32 channels by itself took 600 or 1500 cycles of every workgroup)
+struct VRuleShared {
+    alignas(16) uint8_t B[kD];
+    int wmax[2];    // of channels 0..63, 64..127
+    int ehat[kD];
+};
+__device__ __forceinline__ void v_rule_store(VRuleShared& sh, int d, int ehat, int guard_bits)
+{
+    const int w = guard_bits - 5 - ehat;
+    sh.B[d] = (uint8_t)clamp_byte(w + 61);
+    sh.ehat[d] = ehat;
+    sh.wmax[d >> 6] = wave_max_int(w);
+}
 template <int LPR>
-__device__ __forceinline__ void v_rule_setup(const int* ehat, int guard_bits, int force_level, VRule<LPR>& vr)
+__device__ __forceinline__ void v_rule_load(const VRuleShared& sh, int force_level, VRule<LPR>& vr)
 {
     const int cl = threadIdx.x % LPR;
-    int wmax = -100000;
 #pragma unroll
-    for (int i = 0; i < vr.kWords; ++i) {
-        vr.B[i] = 0;
+    for (int i = 0; i < vr.kWords; i += 4) {
+        const u32x4_t w = *reinterpret_cast<const u32x4_t*>(&sh.B[(cl * vr.kWords + i) * 4]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int e = ehat[(cl * vr.kWords + i) * 4 + k];
-            vr.ehat[i * 4 + k] = e;
-            const int w = guard_bits - 5 - e;
-            wmax = w > wmax ? w : wmax;
-            vr.B[i] |= clamp_byte(w + 61) << (8 * k);
-        }
-        if (force_level >= 0) vr.B[i] = 0x04040404u;
+        for (int k = 0; k < 4; ++k) vr.B[i + k] = force_level >= 0 ? 0x04040404u : w[k];
     }
-    for (int o = 1; o < LPR; o <<= 1) {
-        const int other = __shfl_xor(wmax, o);
-        wmax = other > wmax ? other : wmax;
-    }
-    vr.wmax = wmax;
+#pragma unroll
+    for (int i = 0; i < 4 * vr.kWords; ++i) vr.ehat[i] = sh.ehat[cl * vr.kWords * 4 + i];   // dead but in the variant that exports
+    vr.wmax = max(sh.wmax[0], sh.wmax[1]);
     vr.force = force_level;
 }
 
@@ -93,7 +96,7 @@ __device__ __forceinline__ void v_row_needs(const uint32_t (&hw)[32 / LPR], cons
 
 // HI bytes of the first NPRE batches of a wave, issued early by a caller that has idle time before the V side can
 // start (they depend on nothing but the row range).  Rows at or past len are not fetched.
-template <int KG, int NPRE>
+template <int KG, int NPRE, bool NT = false>
 __device__ __forceinline__ void v_prefetch_hi(const DecodeArgs& a, int b, int h, int t_first, int batch_stride, int len,
                                               u32x4_t (&hi)[NPRE][KG])
 {
@@ -104,7 +107,7 @@ __device__ __forceinline__ void v_prefetch_hi(const DecodeArgs& a, int b, int h,
 #pragma unroll
     for (int n = 0; n < NPRE; ++n)
 #pragma unroll
-        for (int gr = 0; gr < KG; ++gr) hi[n][gr] = buf_load_b128(rs_hi, voff + uint32_t(n * batch_stride + gr * 8) * kD);
+        for (int gr = 0; gr < KG; ++gr) hi[n][gr] = NT ? buf_load_b128_nt(rs_hi, voff + uint32_t(n * batch_stride + gr * 8) * kD) : buf_load_b128(rs_hi, voff + uint32_t(n * batch_stride + gr * 8) * kD);
 }
 
 // DEBUG: what a lane has counted for akv_stats (rows at each level; elements in all and those that need levels 1 and 2), added
@@ -174,20 +177,24 @@ __device__ __forceinline__ void v_export(const DecodeArgs& a, size_t bh, int t, 
 // over waves, by the caller); z accumulates sum_t p_t per lane (to be summed over all 64 lanes).
 // NPRE > 0: pre holds the HI bytes of batches 0 .. NPRE-1 (v_prefetch_hi) if pre_ok.
 // lds_lg / lds_stride: the logits in LDS (query head g at lds_lg + g * lds_stride, token t at index t), or NULL: a.logits.
+// Mlane: the global max of query head lane % G.  ready(): called when the first loads are on their way; vr is read after it.
 // NT: the HI bytes are read with the non-temporal hint (measured: it pays in the token-split V kernel, where the logits
 // and the chunk partials of other workgroups share the caches, and costs in the head-per-workgroup kernel); the MID
 // and LO bytes always are (it pays in both).
-template <int G, int KG, bool DEBUG, int NPRE, int DL = 2, bool NT = false>
+template <int G, int KG, bool DEBUG, int NPRE, int DL, bool NT, typename READY>
 __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_first, int batch_stride, int nbatches,
-                                       int len, const VRule<>& vr, const float (&Mg)[G], float (&acc)[G][16],
+                                       int len, const VRule<>& vr, float Mlane, float (&acc)[G][16],
                                        float (&z)[G], const u32x4_t (&pre)[NPRE > 0 ? NPRE : 1][KG], bool pre_ok,
-                                       const float* lds_lg = nullptr, int lds_stride = 0)
+                                       const float* lds_lg, int lds_stride, READY ready)
 {
     constexpr int RB = 8 * KG;
     // wave-uniform by contract: scalar registers, scalar loop control
     nbatches = __builtin_amdgcn_readfirstlane(nbatches);
     t_first = __builtin_amdgcn_readfirstlane(t_first);
-    if (nbatches <= 0) return;
+    if (nbatches <= 0) {
+        ready();
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int r = lane >> 3, cl = lane & 7;
     // lane j < RB * G computes the score of row j / G of the batch for query head j % G: every (row, head) pair once
@@ -202,16 +209,13 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.v_hi + bh * Ncap * kD, uint32_t(len) * kD);
     const __amdgpu_buffer_rsrc_t rs_mid = make_rsrc(a.v_mid + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
     const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(a.v_lo + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
-    const uint32_t row1 = v_bound_word(vr, 3, 1), row2 = v_bound_word(vr, 7, 2);
+    uint32_t row1 = 0, row2 = 0;
     const uint32_t voff_hi = uint32_t(r) * kD + uint32_t(cl) * 16;
     const uint32_t voff_nib = uint32_t(r) * (kD / 2) + uint32_t(cl) * 8;
     const uint32_t voff_lg = (uint32_t(jg) * uint32_t(Ncap) + uint32_t(jrow)) * 4u;
     int src[KG];                                   // byte address of the first score lane of row gr*8 + r, for the lane permutes
 #pragma unroll
     for (int gr = 0; gr < KG; ++gr) src[gr] = (gr * 8 + r) * G * 4;
-    float Mlane = Mg[0];                           // the global max of this lane's query head
-#pragma unroll
-    for (int g = 1; g < G; ++g) Mlane = jg == g ? Mg[g] : Mlane;
     float zl = 0.0f;                               // sum of this lane's weights (rows j / G of the batches, head j % G)
     unsigned st_rows[3] = {0u, 0u, 0u}, st_need[3] = {0u, 0u, 0u};   // DEBUG: this lane's counts for akv_stats
 
@@ -248,7 +252,7 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     };
     auto sb_scores = [&](int b0) {
         const int bt = b0 + (lane >> 4);
-        const float x = score_x(lg_n, Mg[0], a.c);
+        const float x = score_x(lg_n, Mlane, a.c);
         sb_p = bt < nbatches && row0(bt) + (lane & 15) < len ? __builtin_amdgcn_exp2f(x) : 0.0f;
         zl += sb_p;
         const int ahat = score_a(x);
@@ -339,10 +343,11 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
         }
         if (!SB) Llg(ring[k], k);
     }
-    if (SB) {
-        sb_load(0);
-        sb_scores(0);
-    }
+    if (SB) sb_load(0);
+    ready();
+    row1 = v_bound_word(vr, 3, 1);
+    row2 = v_bound_word(vr, 7, 2);
+    if (SB) sb_scores(0);
     D(ring[0], 0, 0);
 #pragma unroll 1
     for (int i = 0; i < nbatches; i += R) {   // rounds past the last batch issue nothing and compute nothing
@@ -361,18 +366,15 @@ __device__ __forceinline__ void v_rows(const DecodeArgs& a, int b, int h, int t_
     if (DEBUG && a.stats) v_add_stats(a, st_rows, st_need);
 }
 
-// sum acc over the 8 row lanes of a wave (lanes with the same lane % 8) and z over all lanes; afterwards
-// lanes 0..7 hold the wave's totals for their channel slices and every lane holds the wave's z
+// Sum acc over the 8 row lanes of a wave (lanes with the same lane % 8) and z over all lanes: afterwards a lane holds the wave's totals of
+// channels 16 (lane % 8) + row_lane_column(lane), + 1 in sum and every lane the wave's z
 template <int G>
-__device__ __forceinline__ void v_reduce_rows(float (&acc)[G][16], float (&z)[G])
+__device__ __forceinline__ void v_reduce_rows(const float (&acc)[G][16], float (&z)[G], float (&sum)[G][2])
 {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        for (int o = 1; o < 64; o <<= 1) z[g] += __shfl_xor(z[g], o);
-        for (int o = 8; o < 64; o <<= 1) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[g][i] += __shfl_xor(acc[g][i], o);
-        }
+        z[g] = wave_sum<1>(z[g]);
+        sum_row_lanes(acc[g], sum[g]);
     }
 }
 
@@ -387,7 +389,6 @@ constexpr int kSRows = 16;        // rows of a wave's batch: lane -> row lane / 
 // way out, so that a lane lays a row down with 16-byte stores.  The words of a row are permuted by its number
 // (v_word_turn), so that neither side has bank conflicts.  Two buffers alternate by round.
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
 struct VShare {
     static constexpr int kRows = kVWaves * kSRows;   // rows of a round
     alignas(16) u32x4_t vr[2][kRows][16];
@@ -417,10 +418,10 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // and its MID / LO bytes 8 us less, without the logits 10 us less.  The two halves of a lane's 32 HI bytes share a line, so the HI loads
 // keep the line in the caches (temporal: 175 -> 168, at an earlier state).
 // acc: the wave's two 16x16 result tiles (four words each: rows 4 * (lane / 16) .. + 3 of W, line 16 * (2 w + tile) + lane % 16),
-// scaled by kVWeightScale.  z[s]: this lane's sum of the weights of head lane % 4 + 4 s.
-template <int G, bool DEBUG, int DL>
+// scaled by kVWeightScale.  Ml[s]: the global max of query head lane % 4 + 4 s.  ready(): as in v_rows.  z[s]: this lane's sum of the weights of head lane % 4 + 4 s.
+template <int G, bool DEBUG, int DL, typename READY>
 __device__ __forceinline__ void v_rows_shared(const DecodeArgs& a, int b, int h, int t_first, int nbatches, int len, const VRule<4>& vr,
-                                              const float (&Mg)[G], float (&acc)[8], float (&z)[G / 4], VShare& sh)
+                                              const float (&Ml)[G / 4], float (&acc)[8], float (&z)[G / 4], VShare& sh, READY ready)
 {
     static_assert(G == 4 || G == 8, "high and low parts of all heads are the 16 rows of W");
     static_assert(kVWaves * 32 == kD, "four waves share the 128 lines");
@@ -436,16 +437,9 @@ __device__ __forceinline__ void v_rows_shared(const DecodeArgs& a, int b, int h,
     const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.v_hi + bh * Ncap * kD, uint32_t(len) * kD);
     const __amdgpu_buffer_rsrc_t rs_mid = make_rsrc(a.v_mid + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
     const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(a.v_lo + bh * Ncap * (kD / 2), uint32_t(len) * (kD / 2));
-    const uint32_t row1 = v_bound_word(vr, 3, 1), row2 = v_bound_word(vr, 7, 2);
+    uint32_t row1 = 0, row2 = 0;
     const uint32_t voff_hi = uint32_t(r) * kD + uint32_t(c) * 32, voff_nib = uint32_t(r) * (kD / 2) + uint32_t(c) * 16;
     const uint32_t voff_lg = (uint32_t(c) * uint32_t(Ncap) + uint32_t(r)) * 4u;
-    float Ml[S];                                   // the global max of this lane's query heads
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        Ml[s] = Mg[4 * s];
-#pragma unroll
-        for (int g = 1; g < 4; ++g) Ml[s] = c == g ? Mg[4 * s + g] : Ml[s];
-    }
     unsigned st_rows[3] = {0u, 0u, 0u}, st_need[3] = {0u, 0u, 0u};   // DEBUG: this lane's counts for akv_stats
 
     struct Batch {
@@ -529,6 +523,10 @@ __device__ __forceinline__ void v_rows_shared(const DecodeArgs& a, int b, int h,
             d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w8, __builtin_bit_cast(half8_t, __builtin_shufflevector(v[1][0], v[1][1], 0, 1, 2, 3, 4, 5, 6, 7)), d1, 0, 0, 0);
         }
     };
+    constexpr int R = DL + 1;   // rounds and buffers as in v_rows
+    Batch ring[R];
+#pragma unroll
+    for (int k = 0; k < DL; ++k) L(ring[k], k);
     if constexpr (2 * G < 16) {   // the rows of W no head uses stay zero in both buffers (ordered before the first read by the first barrier)
         constexpr int kRows = VShare::kRows;
         for (int idx = threadIdx.x; idx < 2 * (16 - 2 * G) * kRows; idx += 64 * kVWaves) {
@@ -536,10 +534,9 @@ __device__ __forceinline__ void v_rows_shared(const DecodeArgs& a, int b, int h,
             sh.pt[bf][2 * G + rest / kRows][rest % kRows] = 0;
         }
     }
-    constexpr int R = DL + 1;   // rounds and buffers as in v_rows
-    Batch ring[R];
-#pragma unroll
-    for (int k = 0; k < DL; ++k) L(ring[k], k);
+    ready();
+    row1 = v_bound_word(vr, 3, 1);
+    row2 = v_bound_word(vr, 7, 2);
     D(ring[0], 0);
 #pragma unroll 1
     for (int i = 0; i < nbatches; i += R) {   // rounds past the last batch issue nothing and compute nothing

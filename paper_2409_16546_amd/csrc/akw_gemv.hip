@@ -42,31 +42,6 @@ struct GemvArgs {
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 
-// Sums over the 8 row lanes of a wave (lane / 8) in the vector ALU, two values per exchange: afterwards a lane holds the
-// totals of columns row_lane_column(lane), + 1 of its 16, v[0] and v[1].  (24 instead of 48 exchanges through the LDS unit for
-// 16 values: that unit is shared by the whole compute unit.)
-__device__ __forceinline__ int row_lane_column(int lane) { return 8 * (lane >> 5) + 4 * ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1); }
-__device__ __forceinline__ void sum_row_lanes(const float (&acc)[16], float (&v)[2])
-{
-    float a[8], b[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {   // lower half of the wave: columns 0..7, upper half: 8..15
-        const auto x = __builtin_amdgcn_permlane32_swap(float_bits(acc[i]), float_bits(acc[i + 8]), false, false);
-        a[i] = bits_float(x[0]) + bits_float(x[1]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const auto x = __builtin_amdgcn_permlane16_swap(float_bits(a[i]), float_bits(a[i + 4]), false, false);
-        b[i] = bits_float(x[0]) + bits_float(x[1]);
-    }
-    const bool up = threadIdx.x & 8;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const float keep = up ? b[i + 2] : b[i], send = up ? b[i] : b[i + 2];
-        v[i] = keep + bits_float(__builtin_amdgcn_update_dpp(0, float_bits(send), 0x128, 0xF, 0xF, false));   // row_ror:8
-    }
-}
-
 // two fp16 magnitudes, each at least the smallest normal
 __device__ __forceinline__ uint32_t at_least_smallest_normal(uint32_t w)
 {

@@ -169,3 +169,21 @@ def test_token_split_with_one_wave_per_block(T, G):
     w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=3072, seed=800 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
     T.assert_decode_equal(out, dbg, r, lens, G, f"one wave per block G{G}")
+
+
+@pytest.mark.parametrize("cfg,scale", [(3, 0.0), (2, 1e-6), (2, 0.01)])          # the cut in the floor bucket, in the first, between
+@pytest.mark.parametrize("lens", [[16384, 16385, 4097], [5000, 129, 33]])
+def test_selection_where_every_wave_reads_all_of_its_blocks(T, cfg, scale, lens):
+    """Up to 64 blocks the sixteen waves read and keep all of them; one block more and they read those up to a bound."""
+    from paper_2409_16546_amd import binding as A, workloads
+    from oracle import akv_oracle as O
+    print(f"split selection: cfg{cfg} scale {scale} lens {lens}", flush=True)
+    w = workloads.make(cfg, B=3, Hq=2, Hkv=2, N=max(lens), seed=60 + cfg)
+    Ncap = (max(lens) + 255) // 256 * 256
+    r = O.decode_attention(T.oracle_cache(w.k, w.v, lens, Ncap), T.bits(w.q), topk=64, scale=scale)
+    gc = T.gpu_cache(w.k, w.v, lens, 2, Ncap)
+    dbg = A.DebugBuffers.allocate(gc, topk=64, want_needV=False)
+    dbg.a = None
+    A.akv_decode_attention(gc, w.q.to(DEV), dbg=dbg, path=2, topk=64, scale=scale)
+    torch.cuda.synchronize()
+    assert np.array_equal(dbg.sel.cpu().numpy(), r.sel) and np.array_equal(dbg.Ehat.cpu().numpy(), r.Ehat)
