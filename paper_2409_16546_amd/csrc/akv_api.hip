@@ -287,6 +287,8 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
     a.v_hi = cache->v_hi; a.v_mid = cache->v_mid; a.v_lo = cache->v_lo;
     a.colmax = cache->colmax; a.lens = cache->lens; a.q = q; a.out = out;
     a.flags = cache->flags;
+    a.k_new = k_new;   // the kernels of either path store the new token themselves
+    a.v_new = v_new;
     const double scale = p.scale > 0.0f ? (double)p.scale : 1.0 / std::sqrt((double)a.s.D);
     a.c = (float)(scale * 1.4426950408889634);
     a.topk = p.topk; a.guard_bits = p.guard_bits; a.force_level = p.force_level; a.out_dtype = p.out_dtype;
@@ -345,12 +347,8 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         if (p.events)
             for (int i = 1; i < 4; ++i)
                 if (hipError_t e = hipEventRecord(ev(i), s)) return hip_fail(e, "hipEventRecord");
-        a.k_new = k_new;   // the head kernel stores the new token itself
-        a.v_new = v_new;
         if (hipError_t e = akv::launch_decode_head(a, s)) return hip_fail(e, "decode (head path) launch");
     } else {
-        if (k_new)
-            if (hipError_t e = akv::launch_append(*cache, k_new, v_new, nullptr, 1, s)) return hip_fail(e, "append launch");
         if (p.events)
             if (hipError_t e = hipEventRecord(ev(1), s)) return hip_fail(e, "hipEventRecord");
         if (hipError_t e = akv::launch_decode_split(a, s, ev(2), ev(3))) return hip_fail(e, "decode (split path) launch");

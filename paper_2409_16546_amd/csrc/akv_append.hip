@@ -66,12 +66,6 @@ __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t
 // tokens onto 6 x 8 heads: 155 -> 17 us (partly covered blocks used to be walked token by token).
 constexpr int kHalf = kD / 2;   // channels per turn
 
-typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t max_halves(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
-}
 // K_colmax of two neighbouring channels
 __device__ __forceinline__ void colmax_update(uint32_t* word, uint32_t mags)
 {

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/akv.h"
 
@@ -30,7 +31,7 @@ constexpr int kVFewPairs = 64, kVFewChunks = 16;   // then up to this many chunk
 // Offsets (bytes) into the decode workspace.
 struct WsLayout {
     size_t logits;   // float [B][Hq][Ncap]
-    size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the K blocks (the first half of each row)
+    size_t tilemax;  // float [B][Hq][Ncap / 128]: maxima of the K blocks (the first half of each row), then the attended length (selection kernel to V kernel)
     size_t M;        // float [B][Hq]
     size_t Ehat;     // int32 [B][Hq][D]: result exponents per query head (the V kernel takes the minimum over the group)
     size_t partO;    // float [B][Hkv][v_slots][G][D]: of a chunk, in the order in which the V kernel's lanes hold them
@@ -80,7 +81,7 @@ struct DecodeArgs {
     const uint16_t* colmax;
     const int32_t* lens;
     const uint16_t* q;
-    const uint16_t *k_new, *v_new;   // fused append of one token per sequence ([B][Hkv][D] each), or NULL
+    const uint16_t *k_new, *v_new;   // fused append of one token per sequence ([B][Hkv][D] each), or NULL; the token-split kernels store it in the K kernel and move the length in the V kernel
     int32_t* flags;                  // cache flags (append arrival counters, overflow count); used with k_new
     void* out;
     float c;             // (float)(scale * log2(e))
@@ -174,6 +175,25 @@ inline unsigned xcd_grid(size_t items) { return (unsigned)((items + kXcds - 1) /
 
 // ------------------------------------------------------------------ device helpers
 #if defined(__HIPCC__)
+// The lengths of sequence b in a decode call.  A sequence longer than the caller's bound max_len is attended over its first max_len tokens,
+// consistently in all kernels; the token of a fused append is stored in any case where there is room.
+struct SeqLen {
+    int stored;      // tokens stored when the call begins
+    bool appended;   // the call stores one more, at place `stored`
+    int old, len;    // stored tokens that are attended, and with the new one
+    __device__ __forceinline__ SeqLen(const DecodeArgs& a, int b)
+    {
+        stored = min(a.lens[b], a.s.Ncap);
+        appended = a.k_new && stored < a.s.Ncap;
+        old = min(stored, a.max_len);
+        len = min(stored + (appended ? 1 : 0), a.max_len);
+    }
+    __device__ __forceinline__ bool attend_new() const { return len > old; }
+    // the workgroup of the K kernel that stores the new token: the one that walks its block, or the last where the bound ends before it
+    __device__ __forceinline__ bool owner(int tile) const { return appended && int(blockIdx.x) == min(stored / tile, int(gridDim.x) - 1); }
+};
+// the bits of a stored value as they are read at a level ("Dynamic Quantization": bits that are not read are filled with 100...)
+__device__ __forceinline__ uint32_t read_at(uint32_t bits, int level) { return level == 2 ? bits : (level == 1 ? ((bits & 0xFFF0u) | 0x0008u) : ((bits & 0xFF00u) | 0x0080u)); }
 __device__ __forceinline__ int xcd_work_index(int L, int nwg) { return (L % kXcds) * (nwg / kXcds) + L / kXcds; }
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -208,6 +228,13 @@ __device__ __forceinline__ void assemble8(uint32_t H0, uint32_t H1, uint32_t M, 
     p[3] = __builtin_amdgcn_perm(H1, od, 0x07030502u);
 }
 
+// the larger of two pairs of 16-bit words
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t max_halves(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
 // Raw buffer loads (the hardware range check makes predication free): a load whose byte offset is at or
 // beyond the buffer's size returns zero and fetches nothing, so "do not read this plane" is an offset of
 // kSkip instead of a branch, and every load of a loop can be issued unconditionally and early.
@@ -436,6 +463,27 @@ __device__ __forceinline__ void sum_row_lanes(const float (&acc)[16], float (&v)
         const float keep = up ? b[i + 2] : b[i], send = up ? b[i] : b[i + 2];
         v[i] = keep + bits_float(__builtin_amdgcn_update_dpp(0, float_bits(send), 0x128, 0xF, 0xF, false));   // row_ror:8
     }
+}
+
+// the same for N integers side by side
+template <int N> __device__ __forceinline__ void wave_max_ints(int (&v)[N])
+{
+    auto step = [&](auto ctrl, auto rows) {
+        int t[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = __builtin_amdgcn_update_dpp(v[i], v[i], ctrl(), rows(), 0xF, false);
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = max(v[i], t[i]);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());
+    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_readlane(v[i], 63);
 }
 
 #endif  // __HIPCC__

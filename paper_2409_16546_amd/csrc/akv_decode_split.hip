@@ -13,6 +13,39 @@
 
 namespace akv {
 
+// Fused append: one token per sequence, stored by the workgroup that walks its block.  Its K row is in no plane yet when the tiles run: they
+// take its values from k_new.  Thread d < 128 owns channel d.
+__device__ __forceinline__ void count_flags(const DecodeArgs& a, const SeqLen& sl, int h)
+{
+    if (blockIdx.x || h || threadIdx.x) return;
+    if (sl.stored + (sl.appended ? 1 : 0) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
+    if (a.k_new && !sl.appended) atomicAdd(&a.flags[AKV_FLAG_OVERFLOW], 1);   // a full sequence keeps its tokens
+}
+struct NewToken {
+    int k_bits = -1;                  // of channel threadIdx.x
+    uint32_t old_m = 0, old_l = 0;    // the nibble bytes the new token shares with its neighbour
+    __device__ __forceinline__ void load(const DecodeArgs& a, const SeqLen& sl, size_t bh, bool owner)
+    {
+        const int d = threadIdx.x;
+        if (!sl.appended || d >= kD) return;
+        k_bits = a.k_new[bh * kD + d];
+        if (owner && (sl.stored & 1)) {   // an even place opens its nibble byte
+            const size_t nib = k_nibble_index(bh, a.s.Ncap, sl.stored, d);
+            old_m = a.k_mid[nib];
+            old_l = a.k_lo[nib];
+        }
+    }
+    // colmax: K_colmax of the channel with the new token in it (0: the caller stores it)
+    __device__ __forceinline__ void store(const DecodeArgs& a, const SeqLen& sl, size_t bh, uint32_t colmax) const
+    {
+        const int d = threadIdx.x;
+        if (d >= kD) return;
+        store_token_rmw(const_cast<uint8_t*>(a.k_hi), const_cast<uint8_t*>(a.k_mid), const_cast<uint8_t*>(a.k_lo), const_cast<uint8_t*>(a.v_hi),
+                        const_cast<uint8_t*>(a.v_mid), const_cast<uint8_t*>(a.v_lo), bh, a.s.Ncap, sl.stored, d, a.k_new + bh * kD, a.v_new + bh * kD, old_m, old_l);
+        if (colmax) const_cast<uint16_t*>(a.colmax)[bh * kD + d] = (uint16_t)colmax;
+    }
+};
+
 // K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one 256-token block (k_tile) and leaves its logits and the
 // block's maxima in the workspace.
 template <int G>
@@ -24,24 +57,33 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63;
     const int Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
+    const SeqLen sl(a, b);
+    const int len = sl.len;
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int blk = blockIdx.x * kKWaves + wave_u;
     if (blockIdx.x * kKWaves * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
 
-    if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
-    k_levels<G>(a, b, h, ks, blockIdx.x == 0, len);
+    const size_t bh = size_t(b) * a.s.Hkv + h;
+    count_flags(a, sl, h);
+    KLevelsIn<G> in;
+    k_levels_load<G>(a, b, h, in);
+    NewToken nt;
+    const bool owner = sl.owner(kTB * kKWaves);
+    nt.load(a, sl, bh, owner);
+    const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, blockIdx.x == 0, nt.k_bits, in, len);
     if (blk * kTB < len) {                    // else this wave's block is beyond the sequence
         float tm[G];
         const u32x4_t zero4 = {0u, 0u, 0u, 0u};
         const u32x4_t none[6] = {zero4, zero4, zero4, zero4, zero4, zero4};
         float lg[G][4];
         const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
-        k_tile<G>(a, b, h, hq0, blk, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
+        if (sl.attend_new() && blk == sl.stored / kTB) k_tile<G, true, 4, true>(a, b, h, hq0, blk, len, ks, tm, none, false, lg, &kstage[wave_u][0], nullptr, 0, sl.stored % kTB);
+        else k_tile<G>(a, b, h, hq0, blk, len, ks, tm, none, false, lg, &kstage[wave_u][0]);
         if (lane == 0)
 #pragma unroll
             for (int g = 0; g < G; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + blk] = tm[g];
     }
+    if (owner) nt.store(a, sl, bh, colmax_used);
 }
 
 // The same for calls with few blocks (akv_k_short.h): the four waves of a workgroup take a quarter of its block each, find the levels
@@ -59,19 +101,28 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
     const int Hq = a.s.Hq, Ncap = a.s.Ncap;
     KPairIn<G> in;
     k_pairs_load<G>(a, b, h, in);
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // as in split_k_kernel
+    const SeqLen sl(a, b);
+    const int len = sl.len;
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int unit = blockIdx.x * kKWaves + wave_u;
     if (blockIdx.x * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
     KShortHi hi;
     k_short_hi(a, b, h, unit, len, hi);
-    if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0 && min(a.lens[b], Ncap) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
+    const size_t bh = size_t(b) * a.s.Hkv + h;
+    count_flags(a, sl, h);
+    const bool owner = sl.owner(kTB);
+    NewToken nt;
+    nt.load(a, sl, bh, owner);
+    if (sl.appended) in.cm = max_halves(in.cm, in.knew & 0x7FFF7FFFu);
     const KPairLevels lv = k_pair_levels<G>(a, b, h, ks, in, unit == 0, len);
     const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
     float best = -INFINITY;   // of head lane / (64 / G)
     if (unit * kSUnit < len) {                    // else this wave's unit is beyond the sequence
         float lg[G], m[G];
-        k_short_tile<G>(a, b, h, unit, len, lv, hi, ks, &kstage[wave_u][0], lg);
+        uint32_t knew[kSGroups] = {};
+        const int at_new = sl.attend_new() && unit == sl.stored / kSUnit ? sl.stored % kSUnit : -1;   // uniform
+        if (at_new >= 0) k_pair_read(in.knew, lv, knew);
+        k_short_tile<G>(a, b, h, unit, len, lv, hi, ks, &kstage[wave_u][0], lg, at_new, knew);
         const int t = unit * kSUnit + k_short_token(lane);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -87,6 +138,10 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
 #pragma unroll
         for (int w = 1; w < kKWaves; ++w) m = fmaxf(m, best_s[w][threadIdx.x]);
         a.tilemax[(hq0 + threadIdx.x) * (Ncap / kMinUnit) + blockIdx.x] = m;
+    }
+    if (owner) {
+        nt.store(a, sl, bh, 0);
+        if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(const_cast<uint16_t*>(a.colmax + bh * kD))[lane] = in.cm;
     }
 }
 
@@ -118,7 +173,8 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const int hq_i = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
+    const int len = SeqLen(a, b).len;
+    if (tid == 0) a.tilemax[(size_t(b) * Hq + hq_i) * (Ncap / kMinUnit) + Ncap / kTB] = bits_float((uint32_t)len);   // for the V kernel, which moves lens
     if (len <= 0) return;   // uniform: an empty sequence has no selection (the V kernel writes its zeros)
     const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / (Hq / Hkv);
     const int nblk = (len + kTB - 1) / kTB;
@@ -337,7 +393,11 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cl = lane & 7;
     const int Hkv = a.s.Hkv, Hq = a.s.Hq, Ncap = a.s.Ncap;
-    const int len = min(min(a.lens[b], Ncap), a.max_len);   // a hint below the true length: the tokens past it are left out, consistently in all kernels
+    const int len = __builtin_amdgcn_readfirstlane((int)float_bits(a.tilemax[(size_t(b) * Hq + size_t(h) * G) * (Ncap / kMinUnit) + Ncap / kTB]));   // the attended length
+    if (a.k_new && split == 0 && h == 0 && tid == 0) {   // fused append: nothing else of this kernel reads lens
+        int32_t* const stored = const_cast<int32_t*>(a.lens) + b;
+        if (*stored < Ncap) *stored += 1;
+    }
     const int vchunk = a.vchunk;   // tokens per workgroup: a multiple of 64 chosen at launch
     const int c0 = split * vchunk;
     const size_t bh = size_t(b) * Hkv + h;

@@ -11,12 +11,13 @@ namespace akv {
 template <int G> struct KShortQ { alignas(16) float q[G][kD + 4]; };
 
 // What a lane asks for at the start: K_colmax and q of channels 2 lane, 2 lane + 1 (fp16 pairs).
-template <int G> struct KPairIn { uint32_t cm, q[G]; };
+template <int G> struct KPairIn { uint32_t cm, knew, q[G]; };
 template <int G>
 __device__ __forceinline__ void k_pairs_load(const DecodeArgs& a, int b, int h, KPairIn<G>& in)
 {
     const int lane = threadIdx.x & 63;
     in.cm = reinterpret_cast<const uint32_t*>(a.colmax + (size_t(b) * a.s.Hkv + h) * kD)[lane];
+    in.knew = a.k_new ? reinterpret_cast<const uint32_t*>(a.k_new + (size_t(b) * a.s.Hkv + h) * kD)[lane] : 0u;   // uniform; fused append
 #pragma unroll
     for (int g = 0; g < G; ++g) in.q[g] = reinterpret_cast<const uint32_t*>(a.q + (size_t(b) * a.s.Hq + size_t(h) * G + g) * kD)[lane];
 }
@@ -30,7 +31,7 @@ struct KPairLevels { uint64_t mid[2], lo[2]; };
 // q goes to ks.q for the multiply-adds of the same wave.  stat_len, export_levels: as in k_levels_finish (one wave of the pair).
 template <int G>
 __device__ __forceinline__ KPairLevels k_pair_levels(const DecodeArgs& a, int b, int h, KShortQ<G>& ks, const KPairIn<G>& in, bool export_levels, int stat_len)
-{
+{   // in.cm with the appended token's magnitudes already in it
     typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
     const int lane = threadIdx.x & 63;
     const uint32_t cm = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, in.cm), u16x2_t{0x0400, 0x0400}));
@@ -44,25 +45,11 @@ __device__ __forceinline__ KPairLevels k_pair_levels(const DecodeArgs& a, int b,
         m1[g] = int(float_bits(q1 * c1) & 0x7FFFFFFFu);
         mx[g] = max(m0[g], m1[g]);
     }
-    // the steps of wave_max_int for all heads side by side
-    auto step = [&](auto ctrl, auto rows) {
-        int t[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_update_dpp(mx[g], mx[g], ctrl(), rows(), 0xF, false);
-#pragma unroll
-        for (int g = 0; g < G; ++g) mx[g] = max(mx[g], t[g]);
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());
-    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());
+    wave_max_ints(mx);
     int gap0 = -1000, gap1 = -1000;   // largest (exponent of the addend - that of the head's coarsest)
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        int em = __builtin_amdgcn_readlane(mx[g], 63) >> 23;
+        int em = mx[g] >> 23;
         em = em == 0 ? 1000 : em;       // a head whose products are all zero asks for nothing
         gap0 = max(gap0, (m0[g] >> 23) - em);   // a zero product lies 89 and more below any other
         gap1 = max(gap1, (m1[g] >> 23) - em);
@@ -89,6 +76,19 @@ __device__ __forceinline__ KPairLevels k_pair_levels(const DecodeArgs& a, int b,
         }
     }
     return lv;
+}
+
+// fused append: the new token's K row (pairs: channels 2 lane, 2 lane + 1) as it is read at the column levels, channel 32 i + lane % 32 in word i
+__device__ __forceinline__ void k_pair_read(uint32_t pairs, const KPairLevels& lv, uint32_t (&knew)[4])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = 32 * i + lane % 32;
+        const uint64_t mid = (c & 1) ? lv.mid[1] : lv.mid[0], lo = (c & 1) ? lv.lo[1] : lv.lo[0];
+        const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (c / 2), (int)pairs);
+        knew[i] = read_at((c & 1) ? w >> 16 : w & 0xFFFFu, int((mid >> (c / 2)) & 1u) + int((lo >> (c / 2)) & 1u));
+    }
 }
 
 // maximum over the 64 lanes for every one of G values: afterwards lane l holds that of value l / (64 / G)
@@ -145,11 +145,14 @@ __device__ __forceinline__ void k_short_hi(const DecodeArgs& a, int b, int h, in
     }
 }
 
-// acc[g]: the logit of token unit * 64 + k_short_token(lane) for query head g, by the same multiply-adds in the same order as in k_tile
+// the token of a lane, and the place of a token in an LDS row (assemble8_fill's order; the exchange is its own inverse)
 __device__ __forceinline__ int k_short_token(int lane) { return (lane & ~3) | ((lane & 1) << 1) | ((lane >> 1) & 1); }
+
+// acc[g]: the logit of token unit * 64 + k_short_token(lane) for query head g, by the same multiply-adds in the same order as in k_tile
+// at_new: the token of the unit that is being appended, or -1; its values come from knew, channel 32 i + lane % 32 in word i, and not from the planes.
 template <int G>
 __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, int unit, int len, const KPairLevels& lv, const KShortHi& hi,
-                                             const KShortQ<G>& ks, uint8_t* stage, float (&acc)[G])
+                                             const KShortQ<G>& ks, uint8_t* stage, float (&acc)[G], int at_new, const uint32_t (&knew)[kSGroups])
 {
     constexpr bool MX = G % 4 == 0;       // groups of four and eight: matrix products of depth one, as in k_tile
     constexpr int S = MX ? G / 4 : 1;
@@ -193,6 +196,10 @@ __device__ __forceinline__ void k_short_tile(const DecodeArgs& a, int b, int h, 
             uint32_t w[4];
             assemble8_fill(hi.w[i][k >> 1][2 * (k & 1)], hi.w[i][k >> 1][2 * (k & 1) + 1], m[i][k], l[i][k], fill, w);
             *reinterpret_cast<u32x4_t*>(stage + wr[k]) = u32x4_t{w[0], w[1], w[2], w[3]};
+        }
+        if (at_new >= 0 && lane < kSCols) {   // behind the stores above: LDS serves a wave's accesses in order
+            const uint32_t c = uint32_t(lane), place = k_short_token(at_new);
+            *reinterpret_cast<uint16_t*>(stage + c * kRow + (((place >> 3) ^ (c & 7)) << 4) + 2 * (place & 7)) = (uint16_t)knew[i];
         }
         __builtin_amdgcn_wave_barrier();
         short4_t x[kSCols / 4];   // of four columns each

@@ -20,6 +20,7 @@ struct KShared : KSharedQ<G, G == 8> {
     static constexpr bool kMatrix = G == 8;
     int emax[2][G];                     // largest addend exponent per query head, of the columns of wave 0 / wave 1
     uint64_t need_mid[2], need_lo[2];   // bit d%64 of word d/64: column d is read at level >= 1 / = 2
+    uint16_t kread[kD];                 // fused append: the new token's K row as it is read at the column levels
 };
 // ... of a kernel that appends a token itself
 template <int G>
@@ -33,9 +34,8 @@ struct KSharedNew : KShared<G>, KSharedQ<G, true> {
 // Rule 1 for the 128 columns of (b, h), in two steps so that a caller can put other loads in flight between the
 // issue of the loads here and their first use.  Both are called by every thread of a workgroup of at least 128
 // threads (the second contains barriers); afterwards ks holds the level masks.
-// k_new_bits: fp16 bits of channel tid of a token that is being appended in the same kernel (fused append; ks is a
-// KSharedNew), else -1: K_colmax then counts that token, and q as fp32 and the token's row, read at the column levels, are
-// left in ks.q and ks.knew for new_token_logit().
+// k_new_bits: fp16 bits of channel tid of a token that is being appended in the same kernel, else -1: K_colmax then counts that token, and
+// its row, read at the column levels, is left in ks.kread for k_tile (ks a KSharedNew: with q as fp32 in ks.knew and ks.q for new_token_logit()).
 template <int G>
 struct KLevelsIn {
     uint32_t cm;         // K_colmax of channel tid as stored
@@ -108,23 +108,14 @@ __device__ __forceinline__ uint32_t k_levels_finish(const DecodeArgs& a, int b, 
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->k_elems[1]), n1 * n);
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats->k_elems[2]), n2 * n);
         }
-        if constexpr (KS::kNew) {
-            if (k_new_bits >= 0) {   // "Dynamic Quantization": bits that are not read are filled with 100...
-                const uint32_t kb = uint32_t(k_new_bits);
-                ks.knew[tid] = half_bits_to_float(lv == 2 ? kb : (lv == 1 ? ((kb & 0xFFF0u) | 0x0008u) : ((kb & 0xFF00u) | 0x0080u)));
-            }
+        if (k_new_bits >= 0) {
+            const uint32_t kb = read_at(uint32_t(k_new_bits), lv);
+            if constexpr (KS::kNew) ks.knew[tid] = half_bits_to_float(kb);
+            else ks.kread[tid] = (uint16_t)kb;
         }
     }
     __syncthreads();
     return colmax_used;
-}
-
-template <int G>
-__device__ __forceinline__ void k_levels(const DecodeArgs& a, int b, int h, KShared<G>& ks, bool export_levels, int stat_len)
-{
-    KLevelsIn<G> in;
-    k_levels_load<G>(a, b, h, in);
-    k_levels_finish<G>(a, b, h, ks, export_levels, -1, in, stat_len);
 }
 
 // Fused append: the logit of the token that is being appended, from ks.knew, with the same arithmetic as a
@@ -205,11 +196,12 @@ __device__ __forceinline__ void k_tile_pre(const DecodeArgs& a, int b, int h, in
 // lds_lg: where a kernel keeps the logits of its (sequence, KV head) in LDS (query head g at lds_lg + g * lds_stride
 // floats, token t at index t), or NULL: they go to a.logits.  With LDS logits a.logits is written as well only if it
 // is the caller's export buffer (a.dbg.logits).
-// hq0, g0: first of the G consecutive query heads whose logits are computed (all heads of the group, or part of it), and its place in the group.
-template <int G, bool NT = true, int TPL = 4, typename KS>
+// hq0: first of the G consecutive query heads whose logits are computed.
+// NEW: token at_new of the unit is being appended; its values come from ks.kread and not from the planes (whose bytes may be stored meanwhile).
+template <int G, bool NT = true, int TPL = 4, bool NEW = false, typename KS>
 __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t hq0, int unit, int len, const KS& ks,
                                        float (&tile_max)[G], const u32x4_t (&pre)[6], bool use_pre,
-                                       float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0, int g0 = 0)
+                                       float (&acc)[G][TPL], uint8_t* stage, float* lds_lg = nullptr, int lds_stride = 0, int at_new = 0)
 {
     static_assert(TPL == 4 || TPL == 2, "");
     constexpr int U = 32 / TPL;       // columns per group
@@ -302,6 +294,11 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
         *reinterpret_cast<u32x4_t*>(stage + 1024 + voff) = gr.h1;
         *reinterpret_cast<u32x4_t*>(stage + 2048 + 2 * voff) = u32x4_t{low[0], low[1], low[2], low[3]};
         *reinterpret_cast<u32x4_t*>(stage + 2048 + 2 * voff + 16) = u32x4_t{low[4], low[5], low[6], low[7]};
+        if (NEW && lane < U) {   // behind the stores above: LDS serves a wave's accesses in order
+            const uint32_t kb = ks.kread[d0 + lane];
+            stage[lane * kUnit + at_new] = (uint8_t)(kb >> 8);
+            stage[2048 + lane * kUnit + at_new] = (uint8_t)kb;
+        }
         __builtin_amdgcn_wave_barrier();
         typedef std::conditional_t<TPL == 4, uint32_t, uint16_t> word_t;   // TPL bytes
         uint32_t hh[U], ll[U];
@@ -315,7 +312,7 @@ __device__ __forceinline__ void k_tile(const DecodeArgs& a, int b, int h, size_t
 #pragma unroll
             for (int s = 0; s < S; ++s)
 #pragma unroll
-                for (int v = 0; v < U / 4; ++v) qx[s][v] = *reinterpret_cast<const f32x4_t*>(&ks.q[g0 + 4 * s + (lane & 3)][d0 + 4 * v]);
+                for (int v = 0; v < U / 4; ++v) qx[s][v] = *reinterpret_cast<const f32x4_t*>(&ks.q[4 * s + (lane & 3)][d0 + 4 * v]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float k[TPL];

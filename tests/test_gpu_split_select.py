@@ -187,3 +187,32 @@ def test_selection_where_every_wave_reads_all_of_its_blocks(T, cfg, scale, lens)
     A.akv_decode_attention(gc, w.q.to(DEV), dbg=dbg, path=2, topk=64, scale=scale)
     torch.cuda.synchronize()
     assert np.array_equal(dbg.sel.cpu().numpy(), r.sel) and np.array_equal(dbg.Ehat.cpu().numpy(), r.Ehat)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("Hkv,Ncap,lens,max_len", [
+    (3, 1024, [0, 1, 63, 64, 255, 256, 1023, 1024], 0),          # four waves per block; the last sequence is full
+    (3, 1024, [0, 511, 512, 513, 700, 1023, 767, 1024], 512),    # the new token at, behind and far behind the bound
+    (40, 1280, [0, 255, 256, 1023, 1024, 1025, 1279, 1280], 0),  # 1600 blocks: a wave per block
+    (40, 1280, [1100, 1101, 1102, 1150, 1200, 1024, 1279, 1280], 1101),
+])
+def test_token_split_step_is_append_then_attention(T, G, Hkv, Ncap, lens, max_len):
+    """The token-split kernels store the new token themselves: cache, flags and result are those of an append followed by attention."""
+    from paper_2409_16546_amd import binding as A, workloads
+    print(f"token-split step: G{G} Hkv{Hkv} Ncap{Ncap} lens{lens} max_len{max_len}", flush=True)
+    B = len(lens)
+    w = workloads.make(2, B=B, Hq=Hkv * G, Hkv=Hkv, N=Ncap, seed=900 + G)
+    gen = torch.Generator().manual_seed(G)
+    kn, vn = ((torch.randn(B, Hkv, 1, 128, generator=gen) * 3).half().to(DEV) for _ in range(2))
+    q = w.q.to(DEV)
+    one, two = (T.gpu_cache(w.k, w.v, lens, Hkv * G, Ncap) for _ in range(2))
+    for turn in range(2):   # an even place, then an odd one
+        if turn:
+            kn, vn = kn.flip(0).contiguous(), vn.flip(1).contiguous()
+        out = A.akv_append_decode_attention(one, kn, vn, q, path=2, max_len=max_len)
+        A.akv_append(two, kn, vn)
+        ref = A.akv_decode_attention(two, q, path=2, max_len=max_len)
+        torch.cuda.synchronize()
+        for name in ("k_hi", "k_mid", "k_lo", "v_hi", "v_mid", "v_lo", "colmax", "lens", "flags"):
+            assert torch.equal(getattr(one, name), getattr(two, name)), f"{name}, turn {turn}"
+        assert torch.equal(out, ref)
