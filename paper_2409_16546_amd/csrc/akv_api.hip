@@ -205,17 +205,23 @@ void* static_scratch_for_current_device(hipStream_t s)
 // full enough, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written
 // bytes cost several times what read bytes cost).
 // The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
-// path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step
-// (append and attention in one call) costs it a launch more; the head kernel stores the new token itself.  So the lines lie
+// path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step (append and
+// attention in one call) costs it more as well.  So the lines lie
 // where the head kernel wins on attention over full sequences, or where it is behind by a few per cent there and ahead by more
-// over sequences a third full and in steps.  Timed on MI355X over 8..512 pairs, bounds 256..8192, group sizes 1, 2, 4 (head /
-// split, us, full and a third):
-//   single heads  8 pairs 1024 22.0/22.5; 64 pairs 2048 36.2/34.6 and 23.4/29.7, step 37.0/39.5; 96 pairs 1536 32.5/33.5 and
-//                 22.7/28.0; 128 pairs 2048 37.7/38.3 and 24.0/33.5; 128 pairs 4096 52.9/51.7, 160 pairs 58.5/69.9; 160 pairs 8192
-//                 102/102; 512 pairs 512 44.4/37.9, 768 49.5/50.5 (step 54.7/60.1), 1536 70.5/78.3, 4096 135/145
-//   groups of 2   128 pairs 2048 39.6/38.6, 192 pairs 41.2/50.5, 4096 71.6/79.1, 8192 141/132
-//   groups of 4   64 pairs 256 32.3/27.4; 128 pairs 512 30.6/32.4; 160 pairs 2048 61.7/57.8 and 43.2/50.2, step 62.7/63.4 and
-//                 46.2/55.6; 192 pairs 1024 43.8/44.7, 2048 62.2/60.1 and 43.7/50.8, step 63.2/67.2; 200 pairs 2048 63.0/66.5; 224 pairs 4096 106/113 and 56/88; 256 pairs 6144 166/165 and 65/104
+// over sequences that are not full and in steps.  Timed on MI355X over 8..256 pairs, bounds 128..8192, group sizes 1, 2, 4 (head /
+// split, us: full, lengths a quarter to all of the bound, step):
+//   single heads  64 pairs 256 16.5/16.7, 15.6/16.5, 19.9/20.3; 64 pairs 512 18.2/17.8, 18.1/17.4, 22.3/21.9, 96 pairs 18.3/19.8,
+//                 17.8/19.4, 23.1/25.2; 32 pairs 1024 20.4/18.1, 17.5/16.7, 23.7/21.2, 96 pairs 21.4/22.3, 20.4/21.8, 25.5/26.9; 128 pairs
+//                 2048 32.5/30.7, 28.9/29.2, 34.8/37.1; 96 pairs 3072 38.2/35.1, 33.0/30.3, 42.3/38.8, 128 pairs 39.2/41.1, 37.1/36.7,
+//                 42.5/48.6; 128 pairs 4096 49.3/48.3, 45.5/42.4, 53.9/60.3, 160 pairs 51.1/59.1, 38.7/48.2, 55.8/69.4; 128 pairs 8192
+//                 92/79, 79/76, 99/90, 192 pairs 113/111, 89/99, 118/125
+//   groups of 2   64 pairs 256 18.4/17.8, 17.6/17.7, 22.4/21.7, 96 pairs 18.5/21.1, 18.1/21.1, 23.4/24.8; 64 pairs 512 20.5/19.2, 20.2/19.0,
+//                 25.1/23.0, 96 pairs 20.7/22.2, 20.1/21.4, 26.4/28.8; 96 pairs 1024 26.3/26.3, 24.9/25.8, 33.7/32.4, 128 pairs 26.4/27.7,
+//                 25.9/27.0, 33.4/35.6; 96 pairs 2048 36.8/35.0, 33.6/33.8, 42.1/41.9, 128 pairs 37.0/39.7, 34.3/38.2, 41.7/48.2; 128 pairs
+//                 4096 65.4/55.6, 61.9/47.8, 70.6/65.4, 160 pairs 66.6/68.8, 53.6/59.0, 71.8/80.3; 192 pairs 6144 105/101, 83/84, 108/113
+//   groups of 4   128 pairs 128 23.4/22.7, 23.4/22.9, 28.7/25.7, 160 pairs 23.5/25.5, 23.5/25.9, 29.7/29.2; 128 pairs 512 29.5/24.6, 28.1/23.8,
+//                 33.9/29.5, 192 pairs 29.7/30.6, 29.2/30.0, 36.0/38.0; 192 pairs 1024 36.4/36.2, 35.4/35.0, 45.0/44.5, 224 pairs 36.9/40.1,
+//                 35.6/36.9, 46.0/48.8; 192 pairs 2048 53.9/53.3, 50.4/49.1, 60.4/67.6; 224 pairs 4096 97.4/98.2, 92.2/85.1, 105.9/111.5
 //   two rounds of single heads, step and attention over full sequences and partly full ones: 448 pairs 10000 298/307, 12288 354/367;
 //                 512 pairs 8448 291/300, 10000 321/335 (half full 172/236), 12288 384/401, step of 11000 0.7 full 291/323
 //   more rounds, full / step / lengths a quarter to all of the bound: an idle part of the last round is shared by all rounds.  4096
@@ -232,15 +238,15 @@ bool head_path_pays(long pairs, int G, int max_len)
     if (rounds == 2) return G == 1 && max_len <= 12288 && fill >= 0.85 && max_len > 512;
     if (rounds > 2) return G == 1 && max_len <= 12288 && fill >= 0.83 && max_len >= 4096 && (max_len == 4096 || last >= 0.5);
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
-    static constexpr Rule g1[] = {{1024, 0.0}, {2048, 0.2}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
-                          g2[] = {{512, 0.0}, {1024, 0.25}, {2048, 0.53}, {4096, 0.65}, {8192, 0.9}},
-                          g4[] = {{512, 0.47}, {2048, 0.6}, {4096, 0.85}, {6144, 0.97}};
+    static constexpr Rule g1[] = {{256, 0.0}, {1024, 0.3}, {2048, 0.25}, {3072, 0.5}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
+                          g2[] = {{128, 0.0}, {512, 0.3}, {2048, 0.4}, {4096, 0.6}, {6144, 0.85}, {8192, 0.9}},
+                          g4[] = {{128, 0.6}, {512, 0.7}, {1024, 0.8}, {2048, 0.6}, {4096, 0.85}, {6144, 0.97}};
     auto pays = [&](const Rule* r, int n) {
         for (int i = 0; i < n; ++i)
             if (max_len <= r[i].len) return fill >= r[i].fill;
         return false;
     };
-    return G == 1 ? pays(g1, 5) : (G == 2 ? pays(g2, 5) : pays(g4, 4));
+    return G == 1 ? pays(g1, 7) : (G == 2 ? pays(g2, 6) : pays(g4, 6));
 }
 
 // decode attention, optionally preceded by the append of one token per sequence (k_new, v_new: [B][Hkv][D])

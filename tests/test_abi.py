@@ -188,3 +188,12 @@ def test_misaligned_weight_arrays_are_refused(A):
     assert L.akw_unpack(C.byref(A.akw_weights(64, 32, 0x10008, 0x20000, 0x30000, 0x40000)), x, None) == A.AKV_EINVAL
     assert "aligned" in L.akv_last_error().decode()
     assert L.akw_gemv(C.byref(w), x, 1, y, None, ws + 8, 1 << 30, None) == A.AKV_EWORKSPACE
+
+
+@pytest.mark.parametrize("pairs,G,N,path", [
+    (8, 1, 256, 3), (64, 1, 512, 2), (96, 1, 512, 3), (32, 1, 1024, 2), (96, 1, 1024, 3), (60, 1, 2048, 2), (120, 1, 3072, 2), (128, 1, 3072, 3),
+    (8, 2, 128, 3), (64, 2, 256, 2), (96, 2, 512, 3), (96, 2, 2048, 2), (128, 2, 2048, 3), (160, 2, 4096, 3), (192, 2, 6144, 2),
+    (128, 4, 128, 2), (160, 4, 128, 3), (176, 4, 512, 2), (192, 4, 512, 3), (192, 4, 1024, 2), (224, 4, 1024, 3)])
+def test_decode_path_of_short_calls(A, pairs, G, N, path):
+    """Either side of the lines between the head kernel (1, 3) and the token-split kernels (2), on 256 compute units."""
+    assert A.akv_decode_path(pairs // 4, 4 * G, 4, 128, N) in ((2,) if path == 2 else (1, 3))
