@@ -7,7 +7,7 @@
 // eight groups of 8 rows; lane -> row lane/8 of the group and the 16-column slice lane%8, so one 16-byte load per
 // lane fetches the 128 contiguous HI bytes of each of 8 rows (the MID and LO bytes: 8 bytes per lane; a row whose
 // level does not need a plane is asked for out of range and fetches nothing).  All of a wave's loads are in flight
-// at once: the HI bytes go first, before anything is known about the levels.  Every workgroup derives the largest
+// at once: the HI bytes go before anything is known about the levels.  Every workgroup derives the largest
 // addend exponent of each activation row from x and rowmax itself (K products, from L2) -- cheaper than a launch
 // of its own in front of a kernel that runs for a few microseconds.  One activation row is multiplied on the vector ALU, two
 // to four by 4x4x4 matrix products (the weights stay where the lanes hold them; four fp16 rows of a column are two byte
@@ -53,9 +53,8 @@ template <int B>
 __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two workgroups per compute unit at least
 {
     __shared__ int pmax_s[B][kWWaves];   // bits of magnitudes: integer order
-    __shared__ int lvl_s[kWSlab];
-    __shared__ float xs[B == 1 ? kWSlab : 1];
-    __shared__ __align__(16) uint16_t xh[4][kWWaves][8][kWGroups];   // B > 1: x of row (group g, row lane r) of a wave, as the matrix instruction takes it
+    __shared__ __align__(8) uint8_t lvl_s[kWWaves][8][kWGroups];                  // of row (group g, row lane r) of a wave
+    __shared__ __align__(16) uint16_t xh[B == 1 ? 1 : 4][kWWaves][8][kWGroups];   // x of that row, as the matrix instruction takes it
     __shared__ __align__(16) float red_s[kWWaves][B][kWCols];
     __shared__ int last_s;
 
@@ -64,26 +63,32 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
     const int r = lane >> 3, cl = lane & 7;
     const int strip = blockIdx.x, slab_i = blockIdx.y;
     const int K = a.K, N = a.N;
-    const int col = strip * kWCols + cl * 16, k0 = slab_i * kWSlab;
+    const int col = strip * kWCols + cl * 16, k0 = (slab_i * kWWaves + wave) * kWGroups * 8;   // the wave's first row
     const bool lane_ok = col < N;                                   // N % 16 == 0: a lane is inside or outside as a whole
 
     const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.hi, uint32_t(K) * uint32_t(N));
     const __amdgpu_buffer_rsrc_t rs_mid = make_rsrc(a.mid, uint32_t(K) * uint32_t(N / 2));
     const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(a.lo, uint32_t(K) * uint32_t(N / 2));
-    auto local_row = [&](int g) { return (wave * kWGroups + g) * 8 + r; };   // row of the slab this lane reads in group g
+    const __amdgpu_buffer_rsrc_t rs_rm = make_rsrc(a.rowmax, uint32_t(K) * 2u), rs_x = make_rsrc(a.x, uint32_t(B) * uint32_t(K) * 2u);
 
-    // ---- the wave's HI bytes: in flight before anything is known about the levels (asked for first: the sooner the
-    // stream of weights starts, the sooner it ends -- putting the few loads of the exponents in front of them
-    // measured slower)
-    u32x4_t H[kWGroups];
+    // ---- x and rowmax of the first features, and of this thread's row of the slab.  In front of the weights: loads come back in the order
+    // they were asked for, and a wave that has these waits for none of its HI bytes before it knows its levels and asks for MID / LO bytes.
+    // Behind the weights they cost a round trip more.  us a call, 1 / 2 / 4 rows, behind -> in front: 4096x4096 10.7/11.6/12.7 ->
+    // 9.7/10.5/10.7, 4096x11008 17.1/21.5/24.5 -> 16.1/19.3/20.8, 11008x4096 19.8/25.2/28.6 -> 18.4/22.5/24.2, 8192x28672 69.7/91.5/102.8 ->
+    // 66.4/83.3/90.8.  (Only with as many of them as registers hold until the weights have been asked for: a loop that adds them up as they
+    // come, in front of the weights, held the stream up.)
+    constexpr int kPre = B == 1 ? 3 : 2;   // rounds of 4096 features
+    const uint32_t nvec = uint32_t(K) / 8;
+    u32x4_t rm_pre[kPre], x_pre[kPre][B];
+    auto load_x = [&](uint32_t v, u32x4_t& rm, u32x4_t (&xv)[B]) {   // eight features; past the last: zeros
+        rm = buf_load_b128(rs_rm, v < nvec ? v * 16 : kSkip);
 #pragma unroll
-    for (int g = 0; g < kWGroups; ++g) {
-        const int k = k0 + local_row(g);
-        H[g] = buf_load_b128(rs_hi, lane_ok && k < K ? uint32_t(k) * uint32_t(N) + uint32_t(col) : kSkip);
-    }
-
-    // rowmax and x of this thread's row of the slab: used once the exponents are known, asked for now
-    const int k_row = k0 + tid;
+        for (int b = 0; b < B; ++b) xv[b] = buf_load_b128(rs_x, v < nvec ? (uint32_t(b) * nvec + v) * 16 : kSkip);
+    };
+#pragma unroll
+    for (int i = 0; i < kPre; ++i)
+        if (i == 0 || i * kWThreads < (int)nvec) load_x(uint32_t(tid) + i * kWThreads, rm_pre[i], x_pre[i]);   // uniform
+    const int g_row = lane >> 3, r_row = lane & 7, k_row = k0 + g_row * 8 + r_row;   // the row of the slab whose level this thread finds
     uint32_t r16_row = 0, x16_row[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) x16_row[b] = 0;
@@ -92,27 +97,41 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
 #pragma unroll
         for (int b = 0; b < B; ++b) x16_row[b] = a.x[size_t(b) * K + k_row];
     }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- the wave's HI bytes, before anything is known about the levels
+    // K % 8 == 0: a group is inside or outside as a whole
+    auto group_in = [&](int g) { return k0 + g * 8 < K; };
+    const uint32_t lane_hi = lane_ok ? uint32_t(r) * uint32_t(N) + uint32_t(col) : kSkip, lane_low = uint32_t(r) * uint32_t(N / 2) + uint32_t(col / 2);
+    u32x4_t H[kWGroups];
+#pragma unroll
+    for (int g = 0; g < kWGroups; ++g)
+        H[g] = __builtin_amdgcn_raw_buffer_load_b128(rs_hi, group_in(g) ? lane_hi : kSkip, group_in(g) ? (k0 + g * 8) * N : 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- Rule 1: largest addend exponent of every activation row, over all K input features (8 per thread and round)
     if (B > 1 && B < 4)   // activation rows that are not there
-        for (int i = tid; i < (4 - B) * kWSlab; i += kWThreads) (&xh[B][0][0][0])[i] = 0;
+        for (int i = tid; i < (4 - B) * kWSlab; i += kWThreads) (&xh[B == 1 ? 0 : B][0][0][0])[i] = 0;
     // (the exponent of the largest product: one multiply and one maximum per product; a product that is not a number, of an infinite
     // weight and a zero, counts as larger than all, as its exponent says: the maximum that returns such an operand)
     float pmax[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) pmax[b] = 0.0f;
-    const int nvec = K / 8;
-    for (int v = tid; v < nvec; v += kWThreads) {
-        const uint4 rm = reinterpret_cast<const uint4*>(a.rowmax)[v];
+    auto products = [&](const u32x4_t& rm, const u32x4_t (&xv)[B]) {
         const uint32_t rw[4] = {at_least_smallest_normal(rm.x), at_least_smallest_normal(rm.y), at_least_smallest_normal(rm.z), at_least_smallest_normal(rm.w)};
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const uint4 xv = reinterpret_cast<const uint4*>(a.x)[size_t(b) * nvec + v];
-            const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
+        for (int b = 0; b < B; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i)                             // exact products
-                pmax[b] = __builtin_elementwise_maximum(pmax[b], __builtin_elementwise_maximum(fabsf(lo_half(xw[i]) * lo_half(rw[i])), fabsf(hi_half(xw[i]) * hi_half(rw[i]))));
-        }
+                pmax[b] = __builtin_elementwise_maximum(pmax[b], __builtin_elementwise_maximum(fabsf(lo_half(xv[b][i]) * lo_half(rw[i])), fabsf(hi_half(xv[b][i]) * hi_half(rw[i]))));
+    };
+#pragma unroll
+    for (int i = 0; i < kPre; ++i)
+        if (i == 0 || i * kWThreads < (int)nvec) products(rm_pre[i], x_pre[i]);   // uniform
+    for (uint32_t v = uint32_t(tid) + kPre * kWThreads; v < nvec; v += kWThreads) {
+        u32x4_t rm, xv[B];
+        load_x(v, rm, xv);
+        products(rm, xv);
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
@@ -120,7 +139,7 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
         if (lane == 0) pmax_s[b][wave] = m;
     }
     __syncthreads();
-    {                                                               // thread -> row k0 + tid of the slab: level and activations
+    {                                                               // thread -> row k_row: level and activations
         int level = 0;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
@@ -128,39 +147,36 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
 #pragma unroll
             for (int w = 1; w < kWWaves; ++w) pm = max(pm, pmax_s[b][w]);
             const int em = pm >> 23;
-            const float xf = half_bits_to_float(x16_row[b]);        // rows at or past K: 0
-            const float P = xf * half_bits_to_float(r16_row < 0x0400u ? 0x0400u : r16_row);
+            const float P = half_bits_to_float(x16_row[b]) * half_bits_to_float(r16_row < 0x0400u ? 0x0400u : r16_row);   // rows at or past K: 0
             if (P != 0.0f) {
                 const int l = level_for_mantissa_bits(10 + a.guard_bits - (em - float_exp_field(P)));
                 level = l > level ? l : level;
             }
-            if (B == 1) xs[B == 1 ? tid : 0] = xf;
-            else xh[b][tid >> 6][tid & 7][(tid >> 3) & 7] = (uint16_t)x16_row[b];
+            xh[b][wave][r_row][g_row] = (uint16_t)x16_row[b];
         }
         if (a.force_level >= 0) level = a.force_level;
-        lvl_s[tid] = level;
+        lvl_s[wave][r_row][g_row] = (uint8_t)level;
         if (a.lvl_out && strip == 0 && k_row < K) a.lvl_out[k_row] = (uint8_t)level;
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();   // a wave's rows are its own: LDS serves its accesses in order
 
     // ---- the planes the levels ask for, then the multiply-adds
     u32x2_t M[kWGroups], L[kWGroups];
-    int lv[kWGroups];
+    const u32x2_t lv_w = *reinterpret_cast<const u32x2_t*>(&lvl_s[wave][r][0]);   // a byte per group
+    auto lv = [&](int g) { return int((lv_w[g / 4] >> (8 * (g % 4))) & 0xFFu); };
 #pragma unroll
     for (int g = 0; g < kWGroups; ++g) {
-        const int lr = local_row(g), k = k0 + lr;
-        lv[g] = lvl_s[lr];
-        const uint32_t off = uint32_t(k) * uint32_t(N / 2) + uint32_t(col / 2);
-        const bool in = lane_ok && k < K;
-        M[g] = buf_load_b64(rs_mid, in && lv[g] >= 1 ? off : kSkip);
-        L[g] = buf_load_b64(rs_lo, in && lv[g] >= 2 ? off : kSkip);
+        const int need = lane_ok && group_in(g) ? lv(g) : 0, at = group_in(g) ? (k0 + g * 8) * (N / 2) : 0;
+        M[g] = __builtin_amdgcn_raw_buffer_load_b64(rs_mid, need >= 1 ? lane_low : kSkip, at, 0);
+        L[g] = __builtin_amdgcn_raw_buffer_load_b64(rs_lo, need >= 2 ? lane_low : kSkip, at, 0);
     }
     float acc[B][16];
     auto assemble = [&](int g, uint32_t (&pa)[4], uint32_t (&pb)[4]) {
-        const uint32_t fill = fill_for_level(lv[g]);
+        const uint32_t fill = fill_for_level(lv(g));
         assemble8_fill(H[g].x, H[g].y, M[g].x, L[g].x, fill, pa);   // columns 0..7 of the lane
         assemble8_fill(H[g].z, H[g].w, M[g].y, L[g].y, fill, pb);   // columns 8..15
     };
+    const u32x4_t xa = *reinterpret_cast<const u32x4_t*>(&xh[B == 1 ? 0 : lane & 3][wave][r][0]);   // eight groups' rows, of activation row lane % 4
     if constexpr (B == 1) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[0][i] = 0.0f;
@@ -172,7 +188,7 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
                                  lo_half(pa[2]), lo_half(pa[3]), hi_half(pa[2]), hi_half(pa[3]),
                                  lo_half(pb[0]), lo_half(pb[1]), hi_half(pb[0]), hi_half(pb[1]),
                                  lo_half(pb[2]), lo_half(pb[3]), hi_half(pb[2]), hi_half(pb[3])};
-            const float xf = xs[local_row(g)];
+            const float xf = (g & 1) ? hi_half(xa[g / 2]) : lo_half(xa[g / 2]);
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[0][i] = fmaf(xf, v[i], acc[0][i]);
         }
@@ -180,7 +196,6 @@ __global__ __launch_bounds__(kWThreads, 4) void gemv_kernel(GemvArgs a)   // two
         // Two to four activation rows: sixteen 4x4x4 products per instruction.  A block is four lanes of one row lane r, its
         // four k are four groups' rows, its four columns one column of each of the four lanes, its four rows the activation
         // rows (those that are not there are zero): D[b] of the instruction for column i is this lane's acc[b][i].
-        const u32x4_t xa = *reinterpret_cast<const u32x4_t*>(&xh[lane & 3][wave][r][0]);   // A: activation row lane % 4, eight groups
         f32x4_t d[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) d[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};

@@ -61,3 +61,28 @@ def test_gemv_levels_with_infinite_weights_match_oracle(B):
         fin = np.isfinite(r.y)
         assert np.array_equal(np.isnan(y), np.isnan(r.y)) and np.array_equal(y[~fin & ~np.isnan(r.y)], r.y[~fin & ~np.isnan(r.y)])
         assert fin.sum() == B * (N - 2) and np.all(np.abs(y[fin] - r.y[fin]) <= 1.3e-6 * r.abs_sum[fin])
+
+
+@pytest.mark.parametrize("B,K", [(1, 4104), (2, 4088), (4, 4104), (1, 8200), (3, 8192), (4, 8200), (1, 12288), (1, 12304), (2, 12304)])
+def test_gemv_rounds_of_features_match_oracle(B, K):
+    """The largest product is found 4096 features a round, the first rounds (three for one activation row, two for more) in flight together
+    and the others one after the other: sizes at the edges of the rounds, the largest product in the last feature."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import akw_oracle as OW
+    from paper_2409_16546_amd import binding as A, workloads
+    OW.build()
+    N = 144
+    print(f"gemv rounds: K{K} N{N} B{B}", flush=True)
+    bits = lambda t: np.ascontiguousarray(t.contiguous().view(torch.int16).numpy().view(np.uint16))
+    wl = workloads.make_weights((K, N), B, outliers=2, seed=K + B)
+    wl.x[:, K - 1] = 300.0
+    gw = A.Weights.allocate(K, N, DEV)
+    A.akw_pack(gw, wl.W.to(DEV))
+    lvl = torch.empty(K, dtype=torch.uint8, device=DEV)
+    y = A.akw_gemv(gw, wl.x.to(DEV), lvl_out=lvl)
+    torch.cuda.synchronize()
+    r = OW.gemv(OW.pack(bits(wl.W)), bits(wl.x))
+    assert np.array_equal(lvl.cpu().numpy(), r.lvl)
+    # 19 + K / 512 binary32 additions of a running sum no larger than S_n = sum |x w|, 2^-24 of it each
+    assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - r.y) <= (19 + (K + 511) // 512) * 2.0 ** -24 * r.abs_sum)
