@@ -110,24 +110,27 @@ __device__ __forceinline__ size_t k_nibble_index(size_t bh, int Ncap, int t, int
 {
     return ((bh * (Ncap / kTB) + t / kTB) * kD + d) * (kTB / 2) + (t % kTB) / 2;
 }
-// old_m, old_l: the current bytes at k_nibble_index (read by the caller, possibly long before)
-__device__ __forceinline__ uint32_t store_token_rmw(uint8_t* k_hi, uint8_t* k_mid, uint8_t* k_lo, uint8_t* v_hi,
-                                                    uint8_t* v_mid, uint8_t* v_lo, size_t bh, int Ncap, int t, int d,
-                                                    const uint16_t* krow, const uint16_t* vrow, uint32_t old_m,
-                                                    uint32_t old_l)
+// kx: the fp16 bits of channel d; old_m, old_l: the current bytes at k_nibble_index (read by the caller, possibly long before);
+// nt: with the non-temporal hint
+__device__ __forceinline__ uint32_t store_token_k(uint8_t* k_hi, uint8_t* k_mid, uint8_t* k_lo, size_t bh, int Ncap, int t, int d,
+                                                  uint32_t kx, uint32_t old_m, uint32_t old_l, bool nt = false)
 {
-    const int NB = Ncap / kTB, blk = t / kTB, j = t % kTB;
-    const uint32_t kx = krow[d];
-    const size_t col = (bh * NB + blk) * kD + d;
-    k_hi[col * kTB + j] = (uint8_t)(kx >> 8);
-    const size_t nib = k_nibble_index(bh, Ncap, t, d);
-    if (j & 1) {
-        k_mid[nib] = (uint8_t)((old_m & 0x0F) | (((kx >> 4) & 15u) << 4));
-        k_lo[nib] = (uint8_t)((old_l & 0x0F) | ((kx & 15u) << 4));
+    const uint32_t shift = (t & 1) ? 4 : 0, keep = (t & 1) ? 0x0Fu : 0xF0u;
+    const size_t nib = k_nibble_index(bh, Ncap, t, d), at = ((bh * (Ncap / kTB) + t / kTB) * kD + d) * kTB + t % kTB;
+    const uint8_t hi = (uint8_t)(kx >> 8), mid = (uint8_t)((old_m & keep) | (((kx >> 4) & 15u) << shift)), lo = (uint8_t)((old_l & keep) | ((kx & 15u) << shift));
+    if (nt) {
+        __builtin_nontemporal_store(hi, k_hi + at);
+        __builtin_nontemporal_store(mid, k_mid + nib);
+        __builtin_nontemporal_store(lo, k_lo + nib);
     } else {
-        k_mid[nib] = (uint8_t)((old_m & 0xF0) | ((kx >> 4) & 15u));
-        k_lo[nib] = (uint8_t)((old_l & 0xF0) | (kx & 15u));
+        k_hi[at] = hi;
+        k_mid[nib] = mid;
+        k_lo[nib] = lo;
     }
+    return kx & 0x7FFFu;   // |k| as bits: integer order is magnitude order
+}
+__device__ __forceinline__ void store_token_v(uint8_t* v_hi, uint8_t* v_mid, uint8_t* v_lo, size_t bh, int Ncap, int t, int d, const uint16_t* vrow)
+{
     const size_t row = bh * Ncap + t;
     const uint32_t vx = vrow[d];
     v_hi[row * kD + d] = (uint8_t)(vx >> 8);
@@ -136,7 +139,15 @@ __device__ __forceinline__ uint32_t store_token_rmw(uint8_t* k_hi, uint8_t* k_mi
         v_mid[row * (kD / 2) + d] = (uint8_t)(((v0 >> 4) & 15u) | (((v1 >> 4) & 15u) << 4));
         v_lo[row * (kD / 2) + d] = (uint8_t)((v0 & 15u) | ((v1 & 15u) << 4));
     }
-    return kx & 0x7FFFu;   // |k| as bits: integer order is magnitude order
+}
+__device__ __forceinline__ uint32_t store_token_rmw(uint8_t* k_hi, uint8_t* k_mid, uint8_t* k_lo, uint8_t* v_hi,
+                                                    uint8_t* v_mid, uint8_t* v_lo, size_t bh, int Ncap, int t, int d,
+                                                    const uint16_t* krow, const uint16_t* vrow, uint32_t old_m,
+                                                    uint32_t old_l)
+{
+    const uint32_t mag = store_token_k(k_hi, k_mid, k_lo, bh, Ncap, t, d, krow[d], old_m, old_l);   // first: its bytes take longest
+    store_token_v(v_hi, v_mid, v_lo, bh, Ncap, t, d, vrow);
+    return mag;
 }
 __device__ __forceinline__ uint32_t store_token(uint8_t* k_hi, uint8_t* k_mid, uint8_t* k_lo, uint8_t* v_hi,
                                                 uint8_t* v_mid, uint8_t* v_lo, size_t bh, int Ncap, int t, int d,

@@ -68,8 +68,8 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     const bool appended = a.k_new && len_old + 1 <= Ncap;   // a full sequence keeps its tokens (counted at the end)
     // Fused append of one token: this workgroup owns every byte of (b, h).  The K side below runs over the
     // len_old tokens already stored and takes the new token's logit from its fp16 row directly, so nothing
-    // waits for the plane stores; they are issued after the K tiles and are long complete when the V side
-    // reads row len_old.
+    // waits for the plane stores; the V row's are issued after the K tiles and are long complete when the V side
+    // reads row len_old, the K bytes' at the end.
     int k_new_bits = -1;
     uint32_t old_m = 0, old_l = 0;   // the nibble bytes the new token shares with its neighbour
     if (appended && tid < kD) {
@@ -111,6 +111,7 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
         if (blk / kPerBlk == keep_blk) k_tile_pre<false, TPL>(a, b, h, blk, len_k, kpre);
         else k_tile_pre<true, TPL>(a, b, h, blk, len_k, kpre);
     }
+    const uint32_t new_k = uint32_t(k_new_bits) << 16 | old_l << 8 | old_m;   // for the stores at the end, in one register
     const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, true, k_new_bits, lin, len);
     float wm[G];
 #pragma unroll
@@ -162,13 +163,11 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     const bool pre_ok = !(appended && len_old < (vb0 + kHeadVPre) * RB);   // false only where the new row lies in the rows fetched here
     u32x4_t pre[kHeadVPre][KG];
     v_prefetch_hi<KG, kHeadVPre>(a, b, h, vb0 * RB, RB, pre_ok ? len : 0, pre);
-    if (appended && tid < kD) {   // the new token goes into the planes (the block's lines were just read: they are in L2), K_colmax follows
-        store_token_rmw(const_cast<uint8_t*>(a.k_hi), const_cast<uint8_t*>(a.k_mid), const_cast<uint8_t*>(a.k_lo),
-                        const_cast<uint8_t*>(a.v_hi), const_cast<uint8_t*>(a.v_mid), const_cast<uint8_t*>(a.v_lo), bh,
-                        Ncap, len_old, tid, a.k_new + bh * kD, a.v_new + bh * kD, old_m, old_l);
+    if (appended && tid < kD) {   // the new token's V row goes into the planes, K_colmax follows
+        store_token_v(const_cast<uint8_t*>(a.v_hi), const_cast<uint8_t*>(a.v_mid), const_cast<uint8_t*>(a.v_lo), bh, Ncap, len_old, tid, a.v_new + bh * kD);
         const_cast<uint16_t*>(a.colmax)[bh * kD + tid] = (uint16_t)colmax_used;
     }
-    __syncthreads();   // also: every logit store and the new token's bytes have completed (same CU, same L2)
+    __syncthreads();   // also: every logit store and the new token's V row have completed (same CU, same L2)
     if (tid < G) {
         float m = -INFINITY;
         if (attend_new) {   // after the barrier: the tile that covers position len_old has stored its vector
@@ -228,6 +227,13 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
         }
         store_out(a, size_t(b) * Hq + size_t(h) * G + g, d, o / zsum);
     }
+    // The new token's K bytes, a line each for 128 channels and three planes, which nothing in this kernel reads: last, and with the
+    // non-temporal hint.  Among the streams of loads their lines left the caches at any time, and each turned the memory from reading to
+    // writing and back: step of 16 x 32 heads 8192 stored 278 us (8193 272; 252 without these stores), last 277 (278), between the
+    // sides with the hint 269 (274), last with the hint 262 (265); 8 x 32 heads 4096 78.5, 77, 78, 74.
+    if (appended && tid < kD)
+        store_token_k(const_cast<uint8_t*>(a.k_hi), const_cast<uint8_t*>(a.k_mid), const_cast<uint8_t*>(a.k_lo), bh, Ncap, len_old, tid,
+                      new_k >> 16, new_k & 0xFFu, (new_k >> 8) & 0xFFu, true);
     finish_append(a, b, len_old, ticket);
 }
 
