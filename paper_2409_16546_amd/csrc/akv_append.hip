@@ -49,16 +49,17 @@ __global__ __launch_bounds__(128) void append_kernel(akv_cache c, const uint16_t
     }
 }
 
-// Bulk append (prefill, chunks): two workgroups of 256 threads per (sequence, KV head, 256-token K block touched), one for
-// the block's K rows and one for its V rows.  Bound by memory (2 bytes in, 2 bytes out per element), so both keep all their
+// Bulk append (prefill, chunks): 2 S workgroups of 256 threads per (sequence, KV head, 256-token K block touched): S for the block's K,
+// two of them 64 channels each, and S for its V, two of them 128 rows each (twice the workgroups with half the chain each: launch_append).
+// Bound by memory (2 bytes in, 2 bytes out per element), so both keep all their
 // loads in flight at once and store whole 16-byte pieces.
 //   V: no transposition; a thread turns 16 channels of a row (32 bytes in) into 16 + 8 + 8 bytes of the three planes.
-//   K: 64 channels at a time (the second half is in flight while the first is turned).  A thread holds 8 tokens x 8
+//   K: 64 channels at a time (one workgroup for all: the second half is in flight while the first is turned).  A thread holds 8 tokens x 8
 //      channels (rows 128 bytes apart in lanes, whole lines) and turns them in registers with byte permutes into two HI words
 //      and one MID and one LO word per channel, which go to LDS channel-major; from there they leave as 16-byte pieces of
 //      the channel-major runs.  The 16-byte pieces of a channel's LDS row are permuted by the channel's octet, so that neither
 //      side has bank conflicts.  A piece that the new tokens cover only partly (the ends of the range) is merged with the
-//      bytes that are there: no other workgroup writes that block.
+//      bytes that are there: no other workgroup writes those channels of the block.
 // K_colmax: two channels at a time by compare-and-swap on their word, at the very end, when nothing of the workgroup waits for
 // it (all blocks of a head meet there: per channel and between the halves it had cost a third of the launch).  The length
 // moves in a launch of its own behind this one (every workgroup reads the old one), or by ticket where the workgroups are few.  Plain loads and non-temporal stores measured best of the four combinations.
@@ -109,6 +110,7 @@ __device__ __forceinline__ void store_piece(uint8_t* dst, u32x4_t v, int t, int 
     __builtin_nontemporal_store(v, p);
 }
 
+template <int S>
 __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const uint16_t* __restrict__ k_new,
                                                            const uint16_t* __restrict__ v_new,
                                                            const int32_t* __restrict__ n_new, int n, int ticketed)
@@ -134,12 +136,12 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
         if (tid == 0) ticket = atomicAdd(&c.flags[AKV_NFLAGS + b], 1);
     }
     auto leave = [&] {
-        if (ticket == append_tickets(gridDim.x / 2, Hkv) - 1) {   // the last: every wave of the sequence's workgroups has read the length
+        if (ticket == append_tickets(gridDim.x / (2 * S), Hkv, S) - 1) {   // the last: every wave of the sequence's workgroups has read the length
             c.flags[AKV_NFLAGS + b] = 0;
             c.lens[b] = len + cnt;
         }
     };
-    const AppendBlock ab = append_block(len, cnt, blockIdx.x >> 1);
+    const AppendBlock ab = append_block(len, cnt, blockIdx.x / (2 * S));
     const int blk = ab.blk, t_lo = ab.t_lo, t_hi = ab.t_hi;   // tokens of this block: [t_lo, t_hi)
     if (t_lo >= t_hi) {
         leave();
@@ -147,22 +149,24 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
     }
     const size_t bh = size_t(b) * Hkv + h;
     const bool is_v = blockIdx.x & 1;
+    const int sub = S == 1 ? 0 : (blockIdx.x >> 1) % S;   // which rows of V, or channels of K
     // row i of the input is token len + i; rows outside the range are asked for out of range and read as zeros
     const __amdgpu_buffer_rsrc_t rs = make_rsrc((is_v ? v_new : k_new) + bh * n * kD, uint32_t(n) * (kD * 2u));
 
-    if (is_v) {   // thread -> (row tid/8 + 32 i, 16 channels)
-        const int cl = tid & 7;
-        u32x4_t x[8][2];
+    if (is_v) {   // thread -> (row tid/8 + 32 i of the part, 16 channels)
+        constexpr int kRows = 8 / S;
+        const int cl = tid & 7, t_first = blk * kTB + sub * (32 * kRows) + (tid >> 3);
+        u32x4_t x[kRows][2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int t = blk * kTB + (tid >> 3) + 32 * i;
+        for (int i = 0; i < kRows; ++i) {
+            const int t = t_first + 32 * i;
             const uint32_t off = t >= t_lo && t < t_hi ? uint32_t(t - len) * (kD * 2u) + uint32_t(cl) * 32u : kSkip;
             x[i][0] = buf_load_b128(rs, off);
             x[i][1] = buf_load_b128(rs, off + 16);
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int t = blk * kTB + (tid >> 3) + 32 * i;
+        for (int i = 0; i < kRows; ++i) {
+            const int t = t_first + 32 * i;
             u32x4_t hi;
             uint32_t low[4];
 #pragma unroll
@@ -190,26 +194,29 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
 
     const int lane = tid & 63, wave = tid >> 6;
     const int p = lane & 7, oct = wave * 8 + (lane >> 3);   // channels 8p .. 8p+7 of the half, tokens 8 oct .. 8 oct + 7 of the block
-    u32x4_t x[2][8];
-    auto fetch = [&](int half) {
+    constexpr int kTurns = 2 / S;   // halves this workgroup turns
+    u32x4_t x[kTurns][8];
+    auto fetch = [&](int turn) {
+        const int half = turn + sub;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int t = blk * kTB + 8 * oct + i;
-            x[half][i] = buf_load_b128(rs, t >= t_lo && t < t_hi ? uint32_t(t - len) * (kD * 2u) + uint32_t(half) * kD + uint32_t(p) * 16u : kSkip);
+            x[turn][i] = buf_load_b128(rs, t >= t_lo && t < t_hi ? uint32_t(t - len) * (kD * 2u) + uint32_t(half) * kD + uint32_t(p) * 16u : kSkip);
         }
     };
     fetch(0);
     const size_t colbase = (bh * NB + blk) * kD;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        if (half == 0) fetch(1);
+    for (int turn = 0; turn < kTurns; ++turn) {
+        const int half = turn + sub;
+        if (turn + 1 < kTurns) fetch(turn + 1);
 #pragma unroll
         for (int w = 0; w < 4; ++w) {   // channel pair 8p + 2w, 8p + 2w + 1
             uint32_t hi[2][2], low[2][2];   // [channel of the pair][tokens 0..3, 4..7]
             uint32_t mx = 0;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const uint32_t w0 = x[half][4 * q][w], w1 = x[half][4 * q + 1][w], w2 = x[half][4 * q + 2][w], w3 = x[half][4 * q + 3][w];
+                const uint32_t w0 = x[turn][4 * q][w], w1 = x[turn][4 * q + 1][w], w2 = x[turn][4 * q + 2][w], w3 = x[turn][4 * q + 3][w];
                 const uint32_t ha = __builtin_amdgcn_perm(w1, w0, 0x07030501u), hb = __builtin_amdgcn_perm(w3, w2, 0x07030501u);
                 const uint32_t la = __builtin_amdgcn_perm(w1, w0, 0x06020400u), lb = __builtin_amdgcn_perm(w3, w2, 0x06020400u);
                 hi[0][q] = __builtin_amdgcn_perm(hb, ha, 0x05040100u);
@@ -228,7 +235,7 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
                 reinterpret_cast<uint32_t*>(&lo_s[ch][(oct >> 2) ^ p])[oct & 3] = lo;
             }
             for (int o = 8; o < 64; o <<= 1) mx = max_halves(mx, (uint32_t)__shfl_xor((int)mx, o));
-            if (lane < 8) max_s[wave][half * (kHalf / 2) + 4 * p + w] = mx;
+            if (lane < 8) max_s[wave][turn * (kHalf / 2) + 4 * p + w] = mx;
         }
         __syncthreads();
 #pragma unroll
@@ -243,10 +250,10 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
             store_piece(c.k_mid + at, mid_s[ch][g ^ (ch >> 3)], blk * kTB + g * 32, t_lo, t_hi, 4);
             store_piece(c.k_lo + at, lo_s[ch][g ^ (ch >> 3)], blk * kTB + g * 32, t_lo, t_hi, 4);
         }
-        if (half == 0) __syncthreads();   // the LDS areas are written again
+        if (turn + 1 < kTurns) __syncthreads();   // the LDS areas are written again
     }
-    if (tid < kD / 2)   // last, when nothing of this workgroup waits for it any more
-        colmax_update(reinterpret_cast<uint32_t*>(c.colmax + bh * kD) + tid, max_halves(max_halves(max_s[0][tid], max_s[1][tid]), max_halves(max_s[2][tid], max_s[3][tid])));
+    if (tid < kTurns * (kHalf / 2))   // last, when nothing of this workgroup waits for it any more
+        colmax_update(reinterpret_cast<uint32_t*>(c.colmax + bh * kD) + sub * (kHalf / 2) + tid, max_halves(max_halves(max_s[0][tid], max_s[1][tid]), max_halves(max_s[2][tid], max_s[3][tid])));
     leave();
 }
 
@@ -275,12 +282,19 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
     if (n <= (pairs >= 3072 ? 6 : 5) || (n <= (pairs < 128 ? 15 : 16) && pairs * n <= 4608)) {
         hipLaunchKernelGGL(append_kernel, dim3(c.shape.Hkv, c.shape.B), dim3(128), 0, st, c, k_new, v_new, n_new, n);
     } else {
-        const dim3 grid(2 * append_grid_blocks(n), c.shape.Hkv, c.shape.B);
+        // two workgroups per block's K and two per its V (one / two, us with the copy that sets the lengths: 1 x 8 heads 100 tokens 9.5/8.7,
+        // 8 x 8 100 14.6/11.9, 2 x 32 512 19.1/15.4, chunks of 777 onto 6 x 8 19.0/15.9, 4 x 8 4096 26.6/24.8, 16 x 32 512 75.8/72.0,
+        // 2048 197/192, 8192 783/758), unless few tokens go to so many heads that most have nothing to do (16 x 32 100 tokens 44.9/46.5;
+        // 10 x 32 20 tokens, 1280 workgroups, 24.8/23.7, 8 x 32 64, 1024, 21.8/21.9)
+        const int blocks = append_grid_blocks(n);
+        const int parts = n < kTB && 2 * blocks * pairs > 1536 ? 1 : 2;
+        const dim3 grid(2 * parts * blocks, c.shape.Hkv, c.shape.B);
         // few workgroups move the length by ticket: a launch less, but tickets on one cache line cost more than the launch where they
-        // are many (launch / tickets, us with the copy that sets the lengths: 32 workgroups 12.8/10.0, 128 13.7/11.7, 256 15.3/15.3,
-        // 320 on one sequence 13.4/12.4, 384 17.4/18.7, 480 16.5/19.0, 1024 22.7/31.1)
-        const bool ticketed = long(grid.x) * grid.y * grid.z <= 320;
-        hipLaunchKernelGGL(append_block_kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0);
+        // are many (launch / tickets, us: 64 workgroups 11.5/8.7, 256 11.6/10.9, 288 11.7/10.2, 320 12.0/12.7, 512 13.3/15.7)
+        const bool ticketed = long(grid.x) * grid.y * grid.z <= 288;
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0); };
+        if (parts == 2) launch(append_block_kernel<2>);
+        else launch(append_block_kernel<1>);
         if (ticketed) return hipGetLastError();
         if (hipError_t e = hipGetLastError()) return e;
         hipLaunchKernelGGL(append_lens_kernel, dim3(1), dim3(256), 0, st, c, n_new, n);

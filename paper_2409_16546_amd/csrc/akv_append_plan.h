@@ -23,9 +23,9 @@ AKV_HOST_DEVICE inline AppendBlock append_block(int len, int cnt, int i)
     return {blk, len > lo ? len : lo, len + cnt < hi ? len + cnt : hi};
 }
 
-// Tickets of a sequence: one of every workgroup of the launch (K and V of each block of each head), also of those whose block
+// Tickets of a sequence: one of every workgroup of the launch (`parts` each for K and V of each block of each head), also of those whose block
 // the tokens do not touch.  Such a workgroup only knows so from the length: were the length to move before it has read it, it
 // would find work that is not there.
-AKV_HOST_DEVICE inline int append_tickets(int grid_blocks, int Hkv) { return 2 * grid_blocks * Hkv; }
+AKV_HOST_DEVICE inline int append_tickets(int grid_blocks, int Hkv, int parts = 1) { return 2 * parts * grid_blocks * Hkv; }
 
 }  // namespace akv
