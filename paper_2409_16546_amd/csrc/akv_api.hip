@@ -201,8 +201,8 @@ void* static_scratch_for_current_device(hipStream_t s)
 // Head-per-workgroup or token-split kernels, when the caller leaves the choice to the library.  One head kernel
 // workgroup occupies a compute unit, so `pairs` (sequence, KV head) pairs run in ceil(pairs / CUs) rounds of equal
 // length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
-// that the single launch outweighs idle units; for single query heads also at two nearly full rounds, and at more whose last one is
-// full enough, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written
+// that the single launch outweighs idle units; for single query heads, which go two to a unit where there are more than units, also for
+// up to two of them per unit, and at more rounds whose last one is full enough, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written
 // bytes cost several times what read bytes cost).
 // The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
 // path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step (append and
@@ -222,9 +222,14 @@ void* static_scratch_for_current_device(hipStream_t s)
 //   groups of 4   128 pairs 128 23.4/22.7, 23.4/22.9, 28.7/25.7, 160 pairs 23.5/25.5, 23.5/25.9, 29.7/29.2; 128 pairs 512 29.5/24.6, 28.1/23.8,
 //                 33.9/29.5, 192 pairs 29.7/30.6, 29.2/30.0, 36.0/38.0; 192 pairs 1024 36.4/36.2, 35.4/35.0, 45.0/44.5, 224 pairs 36.9/40.1,
 //                 35.6/36.9, 46.0/48.8; 192 pairs 2048 53.9/53.3, 50.4/49.1, 60.4/67.6; 224 pairs 4096 97.4/98.2, 92.2/85.1, 105.9/111.5
-//   two rounds of single heads, step and attention over full sequences and partly full ones: 448 pairs 10000 298/307, 12288 354/367;
-//                 512 pairs 8448 291/300, 10000 321/335 (half full 172/236), 12288 384/401, step of 11000 0.7 full 291/323
-//   more rounds, full / step / lengths a quarter to all of the bound: an idle part of the last round is shared by all rounds.  4096
+//   257 to 512 pairs of single heads, two to a unit up to 11264 tokens, full, step, lengths a quarter to all of the bound: 264 pairs 256
+//                 16.4/22.2, 21.7/26.4, 16.2/21.5, 1024 32.4/35.4, 37.3/43.6, 28.2/32.9, 2048 51.4/56.7, 55.5/61.4, 36.0/48.0, 4096
+//                 97.8/92.1, 103.0/101.8, 78.4/76.8; 352 pairs 4096 102/108, 105/119, 75/88, 8192 215/197, 221/219, 155/163; 416 pairs
+//                 8192 233/236, 241/260, 177/196, 11264 311/318, 320/332, 226/243; 512 pairs 512 25.2/31.3, 2048 65.4/80.5, 8192
+//                 250/270.  (From 257 to 512 tokens the head kernel is ahead as well; there the choice is as it was.)  Longer ones, one
+//                 after the other: 448 pairs 12288 354/367, 512 pairs 12288 384/401
+//   more rounds (timed one after the other), full / step / lengths a quarter to all of the bound: an idle part of the last round is
+//                 shared by all rounds.  4096
 //                 tokens: 640 pairs 191/193, 207/221, 133/155; 860 255/258, 283/291, 170/202; 1100 322/321, 356/363, 218/244; 1312
 //                 374/377, 420/425, 261/286; 1536 400/413; but 1024 pairs 2048 172/152, 768 pairs 1024 79/70.  Above that full
 //                 sequences and steps lose where the last round is less than half full: 5000 tokens 860 pairs 315/302, 337/327, 209/231; 1312
@@ -235,8 +240,10 @@ bool head_path_pays(long pairs, int G, int max_len)
 {
     const long cus = compute_units(), rounds = (pairs + cus - 1) / cus;
     const double fill = double(pairs) / double(rounds * cus), last = double(pairs - (rounds - 1) * cus) / double(cus);   // of all rounds, of the last one
-    if (rounds == 2) return G == 1 && max_len <= 12288 && fill >= 0.85 && max_len > 512;
-    if (rounds > 2) return G == 1 && max_len <= 12288 && fill >= 0.83 && max_len >= 4096 && (max_len == 4096 || last >= 0.5);
+    if (rounds == 2 && G == 1)
+        return max_len <= 256 || (max_len > 512 && (max_len <= 3072 || (max_len <= 4096 && fill >= 0.6) || (max_len <= 8192 && fill >= 0.75) ||
+                                                    (max_len <= 11264 && fill >= 0.8) || (max_len <= 12288 && fill >= 0.85)));
+    if (rounds >= 2) return G == 1 && max_len <= 12288 && fill >= 0.83 && max_len >= 4096 && (max_len == 4096 || last >= 0.5);
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
     static constexpr Rule g1[] = {{256, 0.0}, {1024, 0.3}, {2048, 0.25}, {3072, 0.5}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
                           g2[] = {{128, 0.0}, {512, 0.3}, {2048, 0.4}, {4096, 0.6}, {6144, 0.85}, {8192, 0.9}},

@@ -32,23 +32,39 @@ __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int le
 // (three where the registers allow it: 1.7 % faster than two on 4096 tokens; four spill)
 template <int G> constexpr int head_v_pre() { return G == 1 ? 3 : 2; }
 // groups of 8 rows per batch of the V side: what the register budget of the launch shape allows
-template <int G, int NT> constexpr int head_v_groups() { return NT <= 512 && G <= 2 ? 4 : 2; }
+template <int G, int NT> constexpr int head_v_groups() { return G == 2 ? 4 : 2; }
 
+// Single heads have two launch shapes.  Up to a pair per compute unit a workgroup of 1024 threads has the unit to itself.  More pairs than
+// units go two to a unit, in workgroups of 512 threads (kPairs): what a workgroup spends without a load in flight (entry, levels, mid
+// step, barriers, the waves that are done first: 15 to 23 us) is spent once and not in every round, and one streams while the other
+// does not.  For that both have to fit the LDS, so that what is used behind the K side shares the staging areas' place.  One after the
+// other / two to a unit, us: 512 pairs 600 tokens 40.7/28.9, 1024 51.0/40.8, 2048 76.7/63.9, 4096 129/121, 8192 267/250, 11000 354/342;
+// 1024 pairs 4096 269/253; lengths a quarter to all of the bound 512 pairs 2048 62/50, 8192 203/200 (768 pairs 4096 the one call behind,
+// 135.8/139.9).
 // LDSLG: the logits of the pair stay in LDS (lds_tokens floats per query head, dynamic shared memory) between the K
 // side, the mid step and the V side instead of going through the workspace: nothing of them is written to memory
 // (16 MB of logits written during a 0.8 GB stream cost as much time as 100 MB of reads on this machine).
 extern __shared__ __align__(16) float head_lds_logits[];
 
 template <int G, int NT, bool DEBUG, bool LDSLG, int TPL>
-__global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
+__global__ __launch_bounds__(NT, G == 1 ? 4 : 2) void head_kernel(DecodeArgs a, int lds_tokens)
 {
     constexpr int kWaves = NT / 64;
     float* const lds_lg = LDSLG ? head_lds_logits : nullptr;
     __shared__ KSharedNew<G> ks;
-    __shared__ MidShared ms;
+    // the staging areas of the K tiles, and what is used behind the barrier after them
+    union Areas {
+        uint8_t kstage[kWaves][kKStage];
+        struct {
+            MidShared mid;
+            float red[kWaves][G][kD + 1];
+        } v;
+    };
+    __shared__ __align__(16) Areas areas;
     __shared__ float wmax_s[G][kWaves];
-    __shared__ float red_s[kWaves][G][kD + 1];
-    __shared__ __align__(16) uint8_t kstage[kWaves][kKStage];
+    MidShared& ms = areas.v.mid;
+    auto& red_s = areas.v.red;
+    auto& kstage = areas.kstage;
 
     const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap;
     const int pair = xcd_work_index(blockIdx.x, gridDim.x);   // an XCD takes consecutive heads
@@ -237,9 +253,10 @@ __global__ __launch_bounds__(NT) void head_kernel(DecodeArgs a, int lds_tokens)
     finish_append(a, b, len_old, ticket);
 }
 
-// bytes of LDS a head workgroup may spend on logits beside its static arrays (staging areas of the K tiles, mid step,
-// reduction): 160 KB per compute unit, one workgroup of 1024 threads or two of 512
-template <int NT> constexpr size_t head_lds_logit_budget() { return NT >= 1024 ? 48 * 1024 : 32 * 1024; }
+// bytes of LDS a head workgroup may spend on logits beside its static arrays (staging areas of the K tiles, or mid step and
+// reduction): 160 KB per compute unit, of which a workgroup of 1024 threads takes 67 KB without, one of 512 threads 34 KB (two of single
+// heads fit with 44 KB of logits each, 11264 tokens) or up to 42 KB (groups of two and four)
+template <int G, int NT> constexpr size_t head_lds_logit_budget() { return (NT >= 1024 ? 48 : (G == 1 ? 44 : 32)) * 1024; }
 
 static int head_lds_tokens(const akv_shape& s, int max_len) { return (std::min(max_len, s.Ncap) + kTB - 1) / kTB * kTB; }   // the K tiles write whole blocks
 
@@ -247,7 +264,13 @@ bool head_logits_in_lds(const akv_shape& s, int max_len)
 {
     const int G = s.Hq / s.Hkv;
     const size_t bytes = size_t(G) * head_lds_tokens(s, max_len) * sizeof(float);
-    return bytes <= (G == 1 ? head_lds_logit_budget<1024>() : head_lds_logit_budget<512>());
+    return bytes <= (G == 1 ? head_lds_logit_budget<1, 1024>() : head_lds_logit_budget<2, 512>());
+}
+
+// single heads, two workgroups of 512 threads to a compute unit: more pairs than units, the logits of both in LDS
+static bool head_paired(const akv_shape& s, int max_len)
+{
+    return long(s.B) * s.Hkv > compute_units() && head_lds_tokens(s, max_len) * sizeof(float) <= head_lds_logit_budget<1, 512>();
 }
 
 template <int G, int NT, int TPL>
@@ -257,20 +280,21 @@ static hipError_t launch_head_t(const DecodeArgs& a, hipStream_t st)
     const bool debug = a.dbg.needV || a.dbg.appliedV || a.stats;
     const int lds_tokens = head_lds_tokens(a.s, a.max_len);
     const size_t lds_bytes = size_t(G) * lds_tokens * sizeof(float);
-    if (head_logits_in_lds(a.s, a.max_len)) {
+    constexpr bool kPairs = G == 1 && NT == 512;
+    if (kPairs || head_logits_in_lds(a.s, a.max_len)) {
         static bool raised[64] = {};   // per instantiation and device: allow the dynamic part beside the static arrays
         auto kd = head_kernel<G, NT, true, true, TPL>;
         auto kp = head_kernel<G, NT, false, true, TPL>;
         int dev = 0;
         if (hipError_t e = hipGetDevice(&dev)) return e;
         if (dev < 0 || dev >= 64 || !raised[dev]) {
-            if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kd), hipFuncAttributeMaxDynamicSharedMemorySize, (int)head_lds_logit_budget<NT>())) return e;
-            if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kp), hipFuncAttributeMaxDynamicSharedMemorySize, (int)head_lds_logit_budget<NT>())) return e;
+            if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kd), hipFuncAttributeMaxDynamicSharedMemorySize, (int)head_lds_logit_budget<G, NT>())) return e;
+            if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kp), hipFuncAttributeMaxDynamicSharedMemorySize, (int)head_lds_logit_budget<G, NT>())) return e;
             if (dev >= 0 && dev < 64) raised[dev] = true;
         }
         if (debug) hipLaunchKernelGGL(kd, grid, block, lds_bytes, st, a, lds_tokens);
         else hipLaunchKernelGGL(kp, grid, block, lds_bytes, st, a, lds_tokens);
-    } else {
+    } else if constexpr (!kPairs) {
         if (debug) hipLaunchKernelGGL((head_kernel<G, NT, true, false, 4>), grid, block, 0, st, a, 0);
         else hipLaunchKernelGGL((head_kernel<G, NT, false, false, 4>), grid, block, 0, st, a, 0);
     }
@@ -290,7 +314,7 @@ bool head_path_supported(const akv_shape& s) { return s.Hq / s.Hkv <= 4; }
 hipError_t launch_decode_head(const DecodeArgs& a, hipStream_t st)
 {
     switch (a.s.Hq / a.s.Hkv) {
-        case 1: return launch_head_g<1, 1024>(a, st);
+        case 1: return head_paired(a.s, a.max_len) ? launch_head_g<1, 512>(a, st) : launch_head_g<1, 1024>(a, st);
         case 2: return launch_head_g<2, 512>(a, st);
         case 4: return launch_head_g<4, 512>(a, st);
         default: return hipErrorInvalidValue;
