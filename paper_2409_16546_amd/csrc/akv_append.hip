@@ -119,12 +119,17 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
     __shared__ uint32_t max_s[4][kD / 2];
     const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int Hkv = c.shape.Hkv, Ncap = c.shape.Ncap, NB = Ncap / kTB;
+    // Workgroups go to the XCDs in turn: were a head's parts always in the same order, those without tokens (the last block's, mostly) would
+    // leave the same XCDs idle where the parts are a multiple of two, four or eight.  So they begin at another one in every head (as they
+    // were / turned, us: 8 x 32 heads 600 tokens 50.9/39.8, 16 x 32 100 46.5/33.3, 512 72.0/66.7; long sequences stream worse, 16 x 32
+    // 8192 783/808 with one workgroup per side, and there few blocks are empty).
+    const unsigned turned = blockIdx.x + (S == 1 ? 0u : unsigned(b * Hkv + h) % gridDim.x), part = turned < gridDim.x ? turned : turned - gridDim.x;
     const int len = c.lens[b];
     int cnt = n_new ? n_new[b] : n;
     cnt = cnt < 0 ? 0 : (cnt > n ? n : cnt);
     if (cnt == 0) return;
     if (len + cnt > Ncap) {                     // the sequence is left unchanged
-        if (ticketed && blockIdx.x == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
+        if (ticketed && part == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
         return;
     }
     // ticketed: every workgroup of the sequence draws one once all its waves have read the length (each has taken the branches
@@ -141,15 +146,15 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
             c.lens[b] = len + cnt;
         }
     };
-    const AppendBlock ab = append_block(len, cnt, blockIdx.x / (2 * S));
+    const AppendBlock ab = append_block(len, cnt, int(part / (2 * S)));
     const int blk = ab.blk, t_lo = ab.t_lo, t_hi = ab.t_hi;   // tokens of this block: [t_lo, t_hi)
     if (t_lo >= t_hi) {
         leave();
         return;
     }
     const size_t bh = size_t(b) * Hkv + h;
-    const bool is_v = blockIdx.x & 1;
-    const int sub = S == 1 ? 0 : (blockIdx.x >> 1) % S;   // which rows of V, or channels of K
+    const bool is_v = part & 1;
+    const int sub = S == 1 ? 0 : int(part >> 1) % S;   // which rows of V, or channels of K
     // row i of the input is token len + i; rows outside the range are asked for out of range and read as zeros
     const __amdgpu_buffer_rsrc_t rs = make_rsrc((is_v ? v_new : k_new) + bh * n * kD, uint32_t(n) * (kD * 2u));
 
@@ -282,16 +287,18 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
     if (n <= (pairs >= 3072 ? 6 : 5) || (n <= (pairs < 128 ? 15 : 16) && pairs * n <= 4608)) {
         hipLaunchKernelGGL(append_kernel, dim3(c.shape.Hkv, c.shape.B), dim3(128), 0, st, c, k_new, v_new, n_new, n);
     } else {
-        // two workgroups per block's K and two per its V (one / two, us with the copy that sets the lengths: 1 x 8 heads 100 tokens 9.5/8.7,
-        // 8 x 8 100 14.6/11.9, 2 x 32 512 19.1/15.4, chunks of 777 onto 6 x 8 19.0/15.9, 4 x 8 4096 26.6/24.8, 16 x 32 512 75.8/72.0,
-        // 2048 197/192, 8192 783/758), unless few tokens go to so many heads that most have nothing to do (16 x 32 100 tokens 44.9/46.5;
-        // 10 x 32 20 tokens, 1280 workgroups, 24.8/23.7, 8 x 32 64, 1024, 21.8/21.9)
+        // Two workgroups per block's K and two per its V where that is one round or two of them and a head has few blocks.  One / two, us with
+        // the copy that sets the lengths: 1 x 8 heads 100 tokens 9.5/8.6, 8 x 8 100 14.6/11.5, 2 x 32 512 19.1/15.2, chunks of 777 onto 6 x
+        // 8 19.0/15.8, 8 x 32 600 50.8/39.8, 16 x 32 100 44.9/33.3, 512 75.8/66.7, 16 x 8 3000 82.5/78.5, with K_colmax from zero 88/82.
+        // Not beyond: 16 x 32 2048 (9216 workgroups of one) 197/200, and from zero all blocks of a head meet at its K_colmax, the more
+        // of them the shorter they run: 1 x 32 8192 54/57, 16 x 32 8192 798/1012.
         const int blocks = append_grid_blocks(n);
-        const int parts = n < kTB && 2 * blocks * pairs > 1536 ? 1 : 2;
+        const int parts = blocks <= 16 && 2 * blocks * pairs <= 4096 ? 2 : 1;
         const dim3 grid(2 * parts * blocks, c.shape.Hkv, c.shape.B);
         // few workgroups move the length by ticket: a launch less, but tickets on one cache line cost more than the launch where they
-        // are many (launch / tickets, us: 64 workgroups 11.5/8.7, 256 11.6/10.9, 288 11.7/10.2, 320 12.0/12.7, 512 13.3/15.7)
-        const bool ticketed = long(grid.x) * grid.y * grid.z <= 288;
+        // are many (launch / tickets, us: 64 workgroups 11.5/8.7, 256 11.6/10.9, 288 11.7/10.2, 320 12.0/12.7, 512 13.3/15.7; one per
+        // side 320 on one sequence 13.4/12.4, 384 17.4/18.7)
+        const bool ticketed = long(grid.x) * grid.y * grid.z <= (parts == 2 ? 288 : 320);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0); };
         if (parts == 2) launch(append_block_kernel<2>);
         else launch(append_block_kernel<1>);
