@@ -274,17 +274,18 @@ def main():
         if one_kernel:
             entry["path"] = "head-per-workgroup (one kernel" + ("; logits in LDS)" if path == 3 else ")")
             entry["kernel_us"] = {"head_kernel": round(us_events, 2)}
-            nt = 1024 if Hq == Hkv else 512
+            nt = 1024 if Hq == Hkv and (B * Hkv <= torch.cuda.get_device_properties(0).multi_processor_count or maxlen > 11264) else 512
             dom_name = f"akv::head_kernel<{Hq // Hkv}, {nt}, false, {'true, ' + ('2' if maxlen <= 2 * nt else '4') if path == 3 else 'false, 4'}>"
             dom_tag, dom_us, dom_bytes = "head_kernel", us_events, by["total"]
         else:
-            entry["path"] = "token-split (K, selection, V kernels" + ("; append kernel in front)" if append else ")")
+            entry["path"] = "token-split (K, selection, V kernels)"
             entry["kernel_us"] = {"append": round(seg[0], 2), "k_kernel": round(seg[1], 2), "selection_kernel": round(seg[2], 2),
                                   "v_kernel": round(seg[3], 2),
                                   "how": f"HIP events recorded by the library between its kernels, mean over {prof_steps} steps run right "
                                          f"after the timed ones, minus the {gap:.2f} us two back-to-back events lie apart"}
             if by["k_kernel"] >= by["v_kernel"]:
-                dom_name, dom_tag, dom_us, dom_bytes = f"akv::split_k_kernel<{Hq // Hkv}, 4, 1>", "split_k_kernel", seg[1], by["k_kernel"]
+                short = B * Hkv * ((maxlen + 255) // 256) <= 5 * torch.cuda.get_device_properties(0).multi_processor_count
+                dom_name, dom_tag, dom_us, dom_bytes = f"akv::split_k_{'short_' if short else ''}kernel<{Hq // Hkv}>", "split_k_kernel", seg[1], by["k_kernel"]
             else:
                 dom_name, dom_tag, dom_us, dom_bytes = f"akv::split_v_kernel<{Hq // Hkv}, false>", "split_v_kernel", seg[3], by["v_kernel"]
             entry["kernel_frac_of_peak"] = {"k_kernel": round(by["k_kernel"] / seg[1] / 1e3 / HBM_PEAK_GBS, 4),
