@@ -31,7 +31,7 @@ __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int le
 // batches of V rows whose HI bytes a wave fetches while it waits for the mid step, and keeps in flight afterwards
 // (three where the registers allow it: 1.7 % faster than two on 4096 tokens; four spill)
 template <int G> constexpr int head_v_pre() { return G == 1 ? 3 : 2; }
-// groups of 8 rows per batch of the V side: what the register budget of the launch shape allows
+// groups of 8 rows per batch of the V side: what the register budget allows
 template <int G, int NT> constexpr int head_v_groups() { return G == 2 ? 4 : 2; }
 
 // Single heads have two launch shapes.  Up to a pair per compute unit a workgroup of 1024 threads has the unit to itself.  More pairs than
