@@ -530,19 +530,16 @@ __global__ __launch_bounds__(64 * kVWaves) void split_v_kernel(DecodeArgs a)
     if (sub == 0) {   // whole waves (kCols of 32, single heads: the lower half of one)
 #pragma unroll
         for (int u = 1; u < kSub; ++u) o += lds_s.comb[u][c];
-        float zg[G];
+        // the sum of a query head's weights, from the lane that holds it: by a lane number and not from an array, whose index the compiler
+        // would take through scratch memory
+        auto z_of = [&](int g) { return bits_float((uint32_t)wave_read((int)float_bits(zs), g)); };
+        if constexpr (SHARED) {   // four query heads of one line; whole waves have the same four
+            const int quad = __builtin_amdgcn_readfirstlane(c / kD), d = line_channel(c % kD);
 #pragma unroll
-        for (int g = 0; g < G; ++g) zg[g] = bits_float((uint32_t)__builtin_amdgcn_readlane((int)float_bits(zs), g));
-        if constexpr (SHARED) {   // four query heads of one line
-            const int quad = c / kD, d = line_channel(c % kD);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float zk = G == 4 ? zg[k] : (quad ? zg[4 % G + k] : zg[k]);
-                store_out(a, hq0 + 4 * quad + k, d, o[k] / zk);
-            }
+            for (int k = 0; k < 4; ++k) store_out(a, hq0 + 4 * quad + k, d, o[k] / z_of(4 * quad + k));
         } else {
             const int g = c / (kD / 4);
-            const float zk = G == 1 || g == 0 ? zg[0] : zg[G - 1];
+            const float z0 = z_of(0), z1 = z_of(G - 1), zk = g == 0 ? z0 : z1;
 #pragma unroll
             for (int k = 0; k < 4; ++k) store_out(a, hq0 + g, (c % (kD / 4)) * 4 + k, o[k] / zk);
         }

@@ -1,0 +1,58 @@
+"""What the compiler gave the kernels, read from the metadata of the built library's code objects: no kernel of a plain call may pass
+values through scratch memory (a round trip each, in chains whose round trips are what a short call takes)."""
+import os
+import re
+import struct
+
+import msgpack
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def code_objects(lib):
+    """The gfx950 code objects of the library: entries of its offload bundles."""
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", lib):
+        at = m.end()
+        (n,) = struct.unpack_from("<Q", lib, at)
+        at += 8
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", lib, at)
+            name = lib[at + 24:at + 24 + idlen]
+            at += 24 + idlen
+            if b"gfx950" in name:
+                yield lib[m.start() + off:m.start() + off + size]
+
+
+def kernels(elf):
+    """The entries of `amdhsa.kernels` in the code object's metadata note."""
+    shoff, = struct.unpack_from("<Q", elf, 0x28)
+    size, count = struct.unpack_from("<HH", elf, 0x3A)
+    for i in range(count):
+        kind, = struct.unpack_from("<I", elf, shoff + i * size + 4)
+        if kind != 7:   # SHT_NOTE
+            continue
+        at, length = struct.unpack_from("<QQ", elf, shoff + i * size + 0x18)
+        end = at + length
+        while at + 12 <= end:
+            nlen, dlen, ntype = struct.unpack_from("<III", elf, at)
+            body = at + 12 + (nlen + 3) // 4 * 4
+            if ntype == 32:   # NT_AMDGPU_METADATA
+                yield from msgpack.unpackb(elf[body:body + dlen])["amdhsa.kernels"]
+            at = body + (dlen + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def table():
+    with open(os.path.join(ROOT, "paper_2409_16546_amd", "libakv.so"), "rb") as f:
+        lib = f.read()
+    t = {k[".name"]: k for o in code_objects(lib) for k in kernels(o)}
+    assert len(t) > 50
+    return t
+
+
+def test_no_kernel_of_a_plain_call_uses_scratch_memory(table):
+    # the variants that export masks and counters (head_kernel<1, NT, true, ...>) have the register limit of the plain ones and may spill
+    exports = re.compile(r"head_kernelILi1ELi\d+ELb1E")
+    bad = {n: k[".private_segment_fixed_size"] for n, k in table.items() if k[".private_segment_fixed_size"] and not exports.search(n)}
+    assert not bad
