@@ -161,12 +161,15 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
 // loops run over blocks that are there only.
 // Measured against a histogram of the block maxima by LDS atomics, two barriers more, and code for every slot whether it held a block or
 // not: B 1, 32/8, 1024 tokens 18.4 -> 16.9 us a call, 4096 22.3 -> 21.0, 8192 27.0 -> 24.8, B 3, 64/8, 13000 57.0 -> 55.6; longer ones equal.
+// kKeep: four blocks of a wave leave 54 registers, four workgroups of 512 threads to a compute unit; eight took 86 and two workgroups, and calls
+// of many heads paid for it (eight / four, us a call: 4096 heads 256 tokens 70.9/63.3, 2048 214.5/205.3, 2048 heads 1024 72.3/68.2, 1024 heads
+// 512 51.2/50.3; fewer heads and long sequences equal).
 // NT: 512 threads, or 1024 where every head can have a compute unit to itself and has more than 16 blocks (512 / 1024: B 1, 32/8, 1024 tokens
 // 16.9/17.6, 4096 21.0/21.0, 32768 47.1/45.9, B 3, 64/8, 13000 57.4/55.6; with 512 heads of 16 blocks 57.7/61.1).
 template <int NT>
 __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
 {
-    constexpr int kWaves = NT / 64, kKeep = 8;   // kKeep: blocks of a wave in flight
+    constexpr int kWaves = NT / 64, kKeep = 4;   // kKeep: blocks of a wave in flight
     __shared__ MidShared ms;
     __shared__ int hist_s[kWaves][64 + 64];      // per wave: buckets 0..63, and a place per lane for tokens that need no count
 
@@ -180,7 +183,7 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
     const int b0 = int((long long)nblk * wave / kWaves), b1 = int((long long)nblk * (wave + 1) / kWaves);   // the wave's blocks
-    const bool all = nblk <= kKeep / 2 * kWaves;   // every wave reads all of its blocks, and keeps them
+    const bool all = nblk <= kKeep * kWaves;   // every wave reads all of its blocks, and keeps them
     const __amdgpu_buffer_rsrc_t rs_tm = make_rsrc(a.tilemax + hq * (Ncap / kMinUnit), uint32_t(Ncap / kTB) * 4u);
     const __amdgpu_buffer_rsrc_t rs_lg = make_rsrc(a.logits + hq * Ncap, uint32_t(Ncap) * 4u);
     int nb = 0, blk[kKeep];   // the blocks at hand (uniform) and their logits (lane -> four consecutive tokens)
