@@ -332,6 +332,14 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         // 8192 (8) 67.4/62.5, 56.3/53.6; 32 pairs of eight 16384 (8) 82.6/77.5, 66.4/64.6; 256 single heads 2048 (8) 52.7/50.3
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
         a.kshort = waves <= 5L * cus;
+        // Fused append: the new token's K bytes are a line each for 128 channels in three planes.  Where the planes are more than the caches hold,
+        // their lines leave the caches at any time among the K kernel's loads, and each turns the memory from reading to writing and back.  From
+        // 32 blocks per compute unit on (0.5 GB of bounds) the selection kernel stores them, with the device nearly idle.  Stored by the K
+        // kernel / the selection kernel, us a step, full and ragged: 128 single heads 32768 tokens 305.1/289.6, 213.6/213.4; 64 pairs of four
+        // heads 32768 190.6/182.7, 146.2/146.8; 512 pairs of four 8192 418/398, 287/286; 1024 pairs of eight 4096 525/488, 399/381.  With fewer
+        // blocks (256 single heads 6656 tokens 126.5/132.2, 98.2/101.8) and in more workgroups of shorter bounds (4096 single heads 512
+        // 230/241) the K kernel is ahead.
+        a.k_late = waves >= 32L * cus && a.max_len >= 4096;
         a.lg_nt = long(a.s.B) * a.s.Hq * a.max_len * long(sizeof(float)) >= (8L << 20);   // of one or two heads; figures: k_tile
     }
     char* ws = static_cast<char*>(workspace);

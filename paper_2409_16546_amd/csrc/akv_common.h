@@ -81,7 +81,7 @@ struct DecodeArgs {
     const uint16_t* colmax;
     const int32_t* lens;
     const uint16_t* q;
-    const uint16_t *k_new, *v_new;   // fused append of one token per sequence ([B][Hkv][D] each), or NULL; the token-split kernels store it in the K kernel and move the length in the V kernel
+    const uint16_t *k_new, *v_new;   // fused append of one token per sequence ([B][Hkv][D] each), or NULL; the token-split kernels store it in the K kernel (see k_late) and move the length in the V kernel
     int32_t* flags;                  // cache flags (append arrival counters, overflow count); used with k_new
     void* out;
     float c;             // (float)(scale * log2(e))
@@ -93,6 +93,7 @@ struct DecodeArgs {
     float* partO;
     float* partZ;
     int kshort;          // the K kernel of the token-split path gives a block to four waves instead of one
+    int k_late;          // fused append of the token-split path: the new token's K bytes and K_colmax are stored by the selection kernel, not by the K kernel
     int lg_nt;           // the K kernel of one or two heads stores its logits with the non-temporal hint
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
     int vslots;          // chunks per (sequence, KV head) in partO and partZ

@@ -13,8 +13,9 @@
 
 namespace akv {
 
-// Fused append: one token per sequence, stored by the workgroup that walks its block.  Its K row is in no plane yet when the tiles run: they
-// take its values from k_new.  Thread d < 128 owns channel d.
+// Fused append: one token per sequence.  Its K row is in no plane yet when the tiles run: they take its values from k_new.  The workgroup of the
+// K kernel that walks its block stores its V row, which the kernels behind read; its K bytes and K_colmax, which they do not, are stored by that
+// workgroup as well or by the selection kernel (a.k_late).  The V kernel moves the length.
 __device__ __forceinline__ void count_flags(const DecodeArgs& a, const SeqLen& sl, int h)
 {
     if (blockIdx.x || h || threadIdx.x) return;
@@ -22,29 +23,28 @@ __device__ __forceinline__ void count_flags(const DecodeArgs& a, const SeqLen& s
     if (a.k_new && !sl.appended) atomicAdd(&a.flags[AKV_FLAG_OVERFLOW], 1);   // a full sequence keeps its tokens
 }
 struct NewToken {
-    int k_bits = -1;                  // of channel threadIdx.x
+    int k_bits = -1;                  // of one channel
     uint32_t old_m = 0, old_l = 0;    // the nibble bytes the new token shares with its neighbour
-    __device__ __forceinline__ void load(const DecodeArgs& a, const SeqLen& sl, size_t bh, bool owner)
+    __device__ __forceinline__ void load(const DecodeArgs& a, const SeqLen& sl, size_t bh, int d, bool stores)
     {
-        const int d = threadIdx.x;
-        if (!sl.appended || d >= kD) return;
+        if (!sl.appended || d < 0 || d >= kD) return;
         k_bits = a.k_new[bh * kD + d];
-        if (owner && (sl.stored & 1)) {   // an even place opens its nibble byte
+        if (stores && (sl.stored & 1)) {   // an even place opens its nibble byte
             const size_t nib = k_nibble_index(bh, a.s.Ncap, sl.stored, d);
             old_m = a.k_mid[nib];
             old_l = a.k_lo[nib];
         }
     }
-    // colmax: K_colmax of the channel with the new token in it (0: the caller stores it)
-    __device__ __forceinline__ void store(const DecodeArgs& a, const SeqLen& sl, size_t bh, uint32_t colmax) const
+    __device__ __forceinline__ uint32_t store_k(const DecodeArgs& a, const SeqLen& sl, size_t bh, int d, bool nt) const
     {
-        const int d = threadIdx.x;
-        if (d >= kD) return;
-        store_token_rmw(const_cast<uint8_t*>(a.k_hi), const_cast<uint8_t*>(a.k_mid), const_cast<uint8_t*>(a.k_lo), const_cast<uint8_t*>(a.v_hi),
-                        const_cast<uint8_t*>(a.v_mid), const_cast<uint8_t*>(a.v_lo), bh, a.s.Ncap, sl.stored, d, a.k_new + bh * kD, a.v_new + bh * kD, old_m, old_l);
-        if (colmax) const_cast<uint16_t*>(a.colmax)[bh * kD + d] = (uint16_t)colmax;
+        return store_token_k(const_cast<uint8_t*>(a.k_hi), const_cast<uint8_t*>(a.k_mid), const_cast<uint8_t*>(a.k_lo), bh, a.s.Ncap, sl.stored, d,
+                             uint32_t(k_bits), old_m, old_l, nt);
     }
 };
+__device__ __forceinline__ void store_new_v(const DecodeArgs& a, const SeqLen& sl, size_t bh, int d)
+{
+    store_token_v(const_cast<uint8_t*>(a.v_hi), const_cast<uint8_t*>(a.v_mid), const_cast<uint8_t*>(a.v_lo), bh, a.s.Ncap, sl.stored, d, a.v_new + bh * kD);
+}
 
 // K kernel: workgroup = kKWaves waves of one (sequence, KV head).  A wave walks one 256-token block (k_tile) and leaves its logits and the
 // block's maxima in the workspace.
@@ -67,9 +67,10 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
     count_flags(a, sl, h);
     KLevelsIn<G> in;
     k_levels_load<G>(a, b, h, in);
+    const int d = threadIdx.x;
     NewToken nt;
     const bool owner = sl.owner(kTB * kKWaves);
-    nt.load(a, sl, bh, owner);
+    nt.load(a, sl, bh, d, owner && !a.k_late);
     const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, blockIdx.x == 0, nt.k_bits, in, len);
     if (blk * kTB < len) {                    // else this wave's block is beyond the sequence
         float tm[G];
@@ -83,7 +84,13 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
 #pragma unroll
             for (int g = 0; g < G; ++g) a.tilemax[(hq0 + g) * (Ncap / kMinUnit) + blk] = tm[g];
     }
-    if (owner) nt.store(a, sl, bh, colmax_used);
+    if (owner && d < kD) {
+        if (!a.k_late) {
+            nt.store_k(a, sl, bh, d, false);
+            const_cast<uint16_t*>(a.colmax)[bh * kD + d] = (uint16_t)colmax_used;
+        }
+        store_new_v(a, sl, bh, d);
+    }
 }
 
 // The same for calls with few blocks (akv_k_short.h): the four waves of a workgroup take a quarter of its block each, find the levels
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
     count_flags(a, sl, h);
     const bool owner = sl.owner(kTB);
     NewToken nt;
-    nt.load(a, sl, bh, owner);
+    nt.load(a, sl, bh, threadIdx.x, owner);
     if (sl.appended) in.cm = max_halves(in.cm, in.knew & 0x7FFF7FFFu);
     const KPairLevels lv = k_pair_levels<G>(a, b, h, ks, in, unit == 0, len);
     const size_t hq0 = size_t(b) * Hq + size_t(h) * G;
@@ -139,8 +146,11 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
         for (int w = 1; w < kKWaves; ++w) m = fmaxf(m, best_s[w][threadIdx.x]);
         a.tilemax[(hq0 + threadIdx.x) * (Ncap / kMinUnit) + blockIdx.x] = m;
     }
-    if (owner) {
-        nt.store(a, sl, bh, 0);
+    if (owner) {   // a.k_late is for calls of many blocks
+        if (threadIdx.x < kD) {
+            nt.store_k(a, sl, bh, threadIdx.x, false);
+            store_new_v(a, sl, bh, threadIdx.x);
+        }
         if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(const_cast<uint16_t*>(a.colmax + bh * kD))[lane] = in.cm;
     }
 }
@@ -166,8 +176,9 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
 // 512 51.2/50.3; fewer heads and long sequences equal).
 // NT: 512 threads, or 1024 where every head can have a compute unit to itself and has more than 16 blocks (512 / 1024: B 1, 32/8, 1024 tokens
 // 16.9/17.6, 4096 21.0/21.0, 32768 47.1/45.9, B 3, 64/8, 13000 57.4/55.6; with 512 heads of 16 blocks 57.7/61.1).
-template <int NT>
-__global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
+// LATE: a.k_late (a variant of its own: other calls run nothing of it)
+template <int NT, bool LATE>
+__global__ __launch_bounds__(NT, LATE && NT == 512 ? 8 : 1) void split_select_kernel(DecodeArgs a)
 {
     constexpr int kWaves = NT / 64, kKeep = 4;   // kKeep: blocks of a wave in flight
     __shared__ MidShared ms;
@@ -176,10 +187,23 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     const int hq_i = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Hq = a.s.Hq, Hkv = a.s.Hkv, Ncap = a.s.Ncap;
-    const int len = SeqLen(a, b).len;
+    const SeqLen sl(a, b);
+    const int len = sl.len;
     if (tid == 0) a.tilemax[(size_t(b) * Hq + hq_i) * (Ncap / kMinUnit) + Ncap / kTB] = bits_float((uint32_t)len);   // for the V kernel, which moves lens
     if (len <= 0) return;   // uniform: an empty sequence has no selection (the V kernel writes its zeros)
-    const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / (Hq / Hkv);
+    const int G = Hq / Hkv;
+    const size_t hq = size_t(b) * Hq + hq_i, bh = size_t(b) * Hkv + hq_i / G;
+    // fused append, a.k_late: the workgroups of a group's heads store an equal share of the new token's channels each, by waves 2 and 3, which have
+    // nothing to do while O_est is added up
+    static_assert(NT >= 2 * kD, "");
+    const int d_new = tid - kD;
+    const bool stores = LATE && sl.appended && d_new >= 0 && d_new < kD && d_new * G / kD == hq_i % G;
+    NewToken nt;
+    uint32_t colmax = 0;
+    if (stores) {
+        nt.load(a, sl, bh, d_new, true);
+        colmax = a.colmax[bh * kD + d_new];
+    }
     const int nblk = (len + kTB - 1) / kTB;
     const int kk = a.topk < len ? a.topk : len;
     const int b0 = int((long long)nblk * wave / kWaves), b1 = int((long long)nblk * (wave + 1) / kWaves);   // the wave's blocks
@@ -368,6 +392,10 @@ __global__ __launch_bounds__(NT) void split_select_kernel(DecodeArgs a)
     }
     int ehat = 32767;
     mid_oest<NT>(a, bh, hq, kk, ms, ehat);
+    if (stores) {
+        const uint32_t mag = nt.store_k(a, sl, bh, d_new, true);
+        if (mag > colmax) const_cast<uint16_t*>(a.colmax)[bh * kD + d_new] = (uint16_t)mag;
+    }
     if (tid < kD) a.Ehat[hq * kD + tid] = ehat;
     if (tid == 0) a.M[hq] = M;
 }
@@ -564,8 +592,10 @@ static hipError_t launch_split_g(const DecodeArgs& a, hipStream_t st, hipEvent_t
     if (hipError_t e = hipGetLastError()) return e;
     if (k_done_event)
         if (hipError_t e = hipEventRecord(k_done_event, st)) return e;
-    if (a.max_len > 16 * kTB && long(a.s.B) * a.s.Hq <= compute_units()) hipLaunchKernelGGL(split_select_kernel<1024>, dim3(a.s.Hq, a.s.B), dim3(1024), 0, st, a);
-    else hipLaunchKernelGGL(split_select_kernel<512>, dim3(a.s.Hq, a.s.B), dim3(512), 0, st, a);
+    const int nt = a.max_len > 16 * kTB && long(a.s.B) * a.s.Hq <= compute_units() ? 1024 : 512;
+    auto select = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.s.Hq, a.s.B), dim3(nt), 0, st, a); };
+    if (a.k_new && a.k_late) nt == 1024 ? select(split_select_kernel<1024, true>) : select(split_select_kernel<512, true>);
+    else nt == 1024 ? select(split_select_kernel<1024, false>) : select(split_select_kernel<512, false>);
     if (hipError_t e = hipGetLastError()) return e;
     if (mid_event)
         if (hipError_t e = hipEventRecord(mid_event, st)) return e;

@@ -216,3 +216,30 @@ def test_token_split_step_is_append_then_attention(T, G, Hkv, Ncap, lens, max_le
         for name in ("k_hi", "k_mid", "k_lo", "v_hi", "v_mid", "v_lo", "colmax", "lens", "flags"):
             assert torch.equal(getattr(one, name), getattr(two, name)), f"{name}, turn {turn}"
         assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("max_len", [0, 131072 + 5])                             # every token attended; tokens at and behind the bound
+def test_token_split_step_of_many_blocks_is_append_then_attention(T, G, max_len):
+    """From 32 blocks per compute unit on the selection kernel stores the new token's K bytes, the workgroups of a group's heads a share of the
+    channels each: cache, flags and result are those of an append followed by attention."""
+    from paper_2409_16546_amd import binding as A
+    B, Hkv, Ncap, n = 9, 2, 262144, 1100
+    lens = [0, 1, 255, 256, 1023, 70000, Ncap - 1, Ncap, 131072 + 4]
+    print(f"token-split step of many blocks: G{G} max_len {max_len}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(G)
+    randn = lambda *s: torch.randn(*s, generator=gen, device=DEV).half()
+    k, v, q = randn(B, Hkv, n, 128), randn(B, Hkv, n, 128), randn(B, Hkv * G, 128)
+    one, two = (A.Cache.allocate(B, Hkv * G, Hkv, 128, Ncap, DEV) for _ in range(2))
+    for c in (one, two):
+        A.akv_append(c, k, v, torch.tensor([min(x, n) for x in lens], dtype=torch.int32, device=DEV))
+        c.lens.copy_(torch.tensor(lens, dtype=torch.int32))                      # rows of zeros behind the first 1100 tokens
+    for turn in range(2):   # an even place, then an odd one
+        kn, vn = randn(B, Hkv, 1, 128) * 9, randn(B, Hkv, 1, 128)
+        out = A.akv_append_decode_attention(one, kn, vn, q, path=2, max_len=max_len)
+        A.akv_append(two, kn, vn)
+        ref = A.akv_decode_attention(two, q, path=2, max_len=max_len)
+        torch.cuda.synchronize()
+        for name in ("k_hi", "k_mid", "k_lo", "v_hi", "v_mid", "v_lo", "colmax", "lens", "flags"):
+            assert torch.equal(getattr(one, name), getattr(two, name)), f"{name}, turn {turn}"
+        assert torch.equal(out, ref)
