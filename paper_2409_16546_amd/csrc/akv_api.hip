@@ -332,6 +332,14 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
         // 8192 (8) 67.4/62.5, 56.3/53.6; 32 pairs of eight 16384 (8) 82.6/77.5, 66.4/64.6; 256 single heads 2048 (8) 52.7/50.3
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
         a.kshort = waves <= 5L * cus;
+        // Workgroups go to the XCDs and their units in turn: where a pair has 64 or 128 of them the first blocks of all pairs meet on a few units, and
+        // where sequences are far shorter than their bound those are the ones with work.  There the pairs begin at equal distances.  As they
+        // were / turned, us, full, ragged, a tenth of the bound: 8 pairs 32768 single heads 37.8/37.7, 29.3/28.0, 22.6/19.9, groups of two
+        // 41.4/41.4, 37.2/37.5, 26.4/23.0, of eight 51.8/51.8, 48.8/49.1, 33.1/25.7; 16 single heads 16384 36.0/36.0, 31.3/30.8, 23.0/20.4.
+        // (Other counts lie differently from pair to pair by themselves: 64 pairs of four heads 5120, turned, 23.4 -> 26.1 a tenth full, 24
+        // pairs of eight 13000 ragged 44.4 -> 45.2.)
+        const long kgrid = (a.max_len + akv::kTB - 1) / akv::kTB;
+        a.kturn = a.kshort && kgrid % 64 == 0 ? int(kgrid / pairs) : 0;
         // Fused append: the new token's K bytes are a line each for 128 channels in three planes.  Where the planes are more than the caches hold,
         // their lines leave the caches at any time among the K kernel's loads, and each turns the memory from reading to writing and back.  From
         // 32 blocks per compute unit on (0.5 GB of bounds) the selection kernel stores them, with the device nearly idle.  Stored by the K

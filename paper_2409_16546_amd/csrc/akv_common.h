@@ -93,6 +93,7 @@ struct DecodeArgs {
     float* partO;
     float* partZ;
     int kshort;          // the K kernel of the token-split path gives a block to four waves instead of one
+    int kturn;           // ... and the pairs' first blocks lie this many workgroups further from pair to pair (0: each pair begins with its first block)
     int k_late;          // fused append of the token-split path: the new token's K bytes and K_colmax are stored by the selection kernel, not by the K kernel
     int lg_nt;           // the K kernel of one or two heads stores its logits with the non-temporal hint
     int vchunk;          // tokens per workgroup of the V kernel of the token-split path (a multiple of 64: whole batches of rows for every wave)
@@ -202,7 +203,7 @@ struct SeqLen {
     }
     __device__ __forceinline__ bool attend_new() const { return len > old; }
     // the workgroup of the K kernel that stores the new token: the one that walks its block, or the last where the bound ends before it
-    __device__ __forceinline__ bool owner(int tile) const { return appended && int(blockIdx.x) == min(stored / tile, int(gridDim.x) - 1); }
+    __device__ __forceinline__ bool owner(int tile, int at) const { return appended && at == min(stored / tile, int(gridDim.x) - 1); }   // workgroup `at` of the pair
 };
 // the bits of a stored value as they are read at a level ("Dynamic Quantization": bits that are not read are filled with 100...)
 __device__ __forceinline__ uint32_t read_at(uint32_t bits, int level) { return level == 2 ? bits : (level == 1 ? ((bits & 0xFFF0u) | 0x0008u) : ((bits & 0xFF00u) | 0x0080u)); }

@@ -16,9 +16,9 @@ namespace akv {
 // Fused append: one token per sequence.  Its K row is in no plane yet when the tiles run: they take its values from k_new.  The workgroup of the
 // K kernel that walks its block stores its V row, which the kernels behind read; its K bytes and K_colmax, which they do not, are stored by that
 // workgroup as well or by the selection kernel (a.k_late).  The V kernel moves the length.
-__device__ __forceinline__ void count_flags(const DecodeArgs& a, const SeqLen& sl, int h)
+__device__ __forceinline__ void count_flags(const DecodeArgs& a, const SeqLen& sl, int h, int at)
 {
-    if (blockIdx.x || h || threadIdx.x) return;
+    if (at || h || threadIdx.x) return;
     if (sl.stored + (sl.appended ? 1 : 0) > a.max_len) atomicAdd(&a.flags[AKV_FLAG_MAXLEN], 1);
     if (a.k_new && !sl.appended) atomicAdd(&a.flags[AKV_FLAG_OVERFLOW], 1);   // a full sequence keeps its tokens
 }
@@ -64,12 +64,12 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_kernel(DecodeArgs a)
     if (blockIdx.x * kKWaves * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
 
     const size_t bh = size_t(b) * a.s.Hkv + h;
-    count_flags(a, sl, h);
+    count_flags(a, sl, h, blockIdx.x);
     KLevelsIn<G> in;
     k_levels_load<G>(a, b, h, in);
     const int d = threadIdx.x;
     NewToken nt;
-    const bool owner = sl.owner(kTB * kKWaves);
+    const bool owner = sl.owner(kTB * kKWaves, blockIdx.x);
     nt.load(a, sl, bh, d, owner && !a.k_late);
     const uint32_t colmax_used = k_levels_finish<G>(a, b, h, ks, blockIdx.x == 0, nt.k_bits, in, len);
     if (blk * kTB < len) {                    // else this wave's block is beyond the sequence
@@ -111,13 +111,15 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
     const SeqLen sl(a, b);
     const int len = sl.len;
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int unit = blockIdx.x * kKWaves + wave_u;
-    if (blockIdx.x * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
+    const unsigned turned = blockIdx.x + unsigned(b * a.s.Hkv + h) * unsigned(a.kturn);
+    const int at = int(turned < gridDim.x ? turned : turned - gridDim.x);   // the block of this workgroup
+    const int unit = at * kKWaves + wave_u;
+    if (at * kTB >= len) return;   // whole workgroup beyond the sequence (uniform)
     KShortHi hi;
     k_short_hi(a, b, h, unit, len, hi);
     const size_t bh = size_t(b) * a.s.Hkv + h;
-    count_flags(a, sl, h);
-    const bool owner = sl.owner(kTB);
+    count_flags(a, sl, h, at);
+    const bool owner = sl.owner(kTB, at);
     NewToken nt;
     nt.load(a, sl, bh, threadIdx.x, owner);
     if (sl.appended) in.cm = max_halves(in.cm, in.knew & 0x7FFF7FFFu);
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(64 * kKWaves) void split_k_short_kernel(DecodeArgs 
         float m = best_s[0][threadIdx.x];
 #pragma unroll
         for (int w = 1; w < kKWaves; ++w) m = fmaxf(m, best_s[w][threadIdx.x]);
-        a.tilemax[(hq0 + threadIdx.x) * (Ncap / kMinUnit) + blockIdx.x] = m;
+        a.tilemax[(hq0 + threadIdx.x) * (Ncap / kMinUnit) + at] = m;
     }
     if (owner) {   // a.k_late is for calls of many blocks
         if (threadIdx.x < kD) {

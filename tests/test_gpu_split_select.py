@@ -243,3 +243,24 @@ def test_token_split_step_of_many_blocks_is_append_then_attention(T, G, max_len)
         for name in ("k_hi", "k_mid", "k_lo", "v_hi", "v_mid", "v_lo", "colmax", "lens", "flags"):
             assert torch.equal(getattr(one, name), getattr(two, name)), f"{name}, turn {turn}"
         assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_token_split_step_where_the_pairs_begin_at_equal_distances(T, G):
+    """64 K blocks per pair, four waves per block: the workgroups of a pair begin with another block in every pair, and the one that stores
+    the new token and the one that counts move with them."""
+    from paper_2409_16546_amd import binding as A, workloads
+    from oracle import akv_oracle as O
+    B, Hkv, N, lens = 2, 3, 16384, [16384, 4099]
+    print(f"token-split step, turned: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=B, Hq=Hkv * G, Hkv=Hkv, N=N, seed=1000 + G)
+    oc, gc = T.oracle_cache(w.k, w.v, lens, N), T.gpu_cache(w.k, w.v, lens, Hkv * G, N)
+    gen = torch.Generator().manual_seed(G)
+    kn, vn = (torch.randn(B, Hkv, 1, 128, generator=gen).half() for _ in range(2))
+    refused = O.append(oc, T.bits(kn), T.bits(vn), np.array([1] * B, np.int32))
+    dbg = A.DebugBuffers.allocate(gc, want_needV=False)
+    out = A.akv_append_decode_attention(gc, kn.to(DEV), vn.to(DEV), w.q.to(DEV), dbg=dbg, path=2)
+    torch.cuda.synchronize()
+    T.assert_cache_equal(gc, oc)
+    T.assert_decode_equal(out, dbg, O.decode_attention(oc, T.bits(w.q)), oc.lens.tolist(), G, f"turned G{G}")
+    assert refused == 1 and int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == 1

@@ -67,3 +67,11 @@ def test_four_workgroups_of_the_selection_kernel_share_a_compute_unit(table):
         waves = k[".max_flat_workgroup_size"] // 64   # per SIMD: those of four workgroups on four SIMDs
         assert (k[".vgpr_count"] + 7) // 8 * 8 * waves <= 512 and k[".sgpr_count"] * waves <= 800
         assert 4 * k[".group_segment_fixed_size"] <= 160 * 1024
+
+
+def test_four_workgroups_of_the_short_k_kernel_share_a_compute_unit(table):
+    """Up to five workgroups of four waves per unit: a wave per SIMD each."""
+    variants = [k for n, k in table.items() if "split_k_short_kernel" in n]
+    assert len(variants) == 4
+    for k in variants:
+        assert k[".vgpr_count"] <= 128 and 4 * k[".group_segment_fixed_size"] <= 160 * 1024
