@@ -119,17 +119,16 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
     __shared__ uint32_t max_s[4][kD / 2];
     const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int Hkv = c.shape.Hkv, Ncap = c.shape.Ncap, NB = Ncap / kTB;
-    // Workgroups go to the XCDs in turn: were a head's parts always in the same order, those without tokens (the last block's, mostly) would
-    // leave the same XCDs idle where the parts are a multiple of two, four or eight.  So they begin at another one in every head (as they
-    // were / turned, us: 8 x 32 heads 600 tokens 50.9/39.8, 16 x 32 100 46.5/33.3, 512 72.0/66.7; long sequences stream worse, 16 x 32
-    // 8192 783/808 with one workgroup per side, and there few blocks are empty).
-    const unsigned turned = blockIdx.x + (S == 1 ? 0u : unsigned(b * Hkv + h) % gridDim.x), part = turned < gridDim.x ? turned : turned - gridDim.x;
+    // A head's parts begin at another one in every head (append_part).  As they were / turned, us: 8 x 32 heads 600 tokens 50.9/39.8, 16 x 32
+    // 100 46.5/33.3, 512 72.0/66.7; long sequences stream worse (16 x 32 8192 783/808 with one workgroup per side), and there few blocks are
+    // empty.
+    const AppendPart part = append_part<S>(blockIdx.x, gridDim.x, unsigned(b * Hkv + h));
     const int len = c.lens[b];
     int cnt = n_new ? n_new[b] : n;
     cnt = cnt < 0 ? 0 : (cnt > n ? n : cnt);
     if (cnt == 0) return;
     if (len + cnt > Ncap) {                     // the sequence is left unchanged
-        if (ticketed && part == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
+        if (ticketed && part.i == 0 && part.v == 0 && part.sub == 0 && h == 0 && tid == 0) atomicAdd(&c.flags[AKV_FLAG_OVERFLOW], 1);
         return;
     }
     // ticketed: every workgroup of the sequence draws one once all its waves have read the length (each has taken the branches
@@ -146,15 +145,15 @@ __global__ __launch_bounds__(256) void append_block_kernel(akv_cache c, const ui
             c.lens[b] = len + cnt;
         }
     };
-    const AppendBlock ab = append_block(len, cnt, int(part / (2 * S)));
+    const AppendBlock ab = append_block(len, cnt, part.i);
     const int blk = ab.blk, t_lo = ab.t_lo, t_hi = ab.t_hi;   // tokens of this block: [t_lo, t_hi)
     if (t_lo >= t_hi) {
         leave();
         return;
     }
     const size_t bh = size_t(b) * Hkv + h;
-    const bool is_v = part & 1;
-    const int sub = S == 1 ? 0 : int(part >> 1) % S;   // which rows of V, or channels of K
+    const bool is_v = part.v;
+    const int sub = part.sub;   // which rows of V, or channels of K
     // row i of the input is token len + i; rows outside the range are asked for out of range and read as zeros
     const __amdgpu_buffer_rsrc_t rs = make_rsrc((is_v ? v_new : k_new) + bh * n * kD, uint32_t(n) * (kD * 2u));
 

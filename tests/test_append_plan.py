@@ -1,5 +1,5 @@
-"""The arithmetic of the block append (csrc/akv_append_plan.h) on the CPU: the blocks of a launch cover the new tokens once, and the
-length of a sequence cannot move while any workgroup of the launch has still to read it."""
+"""The arithmetic of the block append (csrc/akv_append_plan.h) on the CPU: the blocks of a launch cover the new tokens once, its
+workgroups every part of a block once, and the length of a sequence cannot move while any workgroup of the launch has still to read it."""
 import os
 import shutil
 import subprocess
@@ -11,8 +11,21 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 DRIVER = r"""
 #include <cstdio>
 #include <initializer_list>
+#include <vector>
 #include "akv_append_plan.h"
 using namespace akv;
+template <int S> bool each_once(int blocks, unsigned head)
+{
+    std::vector<int> seen(2 * S * blocks);
+    for (int x = 0; x < 2 * S * blocks; ++x) {
+        const AppendPart p = append_part<S>(unsigned(x), unsigned(2 * S * blocks), head);
+        if (p.i < 0 || p.i >= blocks || p.v < 0 || p.v > 1 || p.sub < 0 || p.sub >= S) return false;
+        ++seen[(p.i * 2 + p.v) * S + p.sub];
+    }
+    for (int n : seen)
+        if (n != 1) return false;
+    return true;
+}
 int main()
 {
     long would_stray = 0;
@@ -30,19 +43,24 @@ int main()
                     at = x.t_hi;
                 }
                 if (at != len + cnt) return printf("n %d len %d: %d of %d tokens\n", n, len, at - len, cnt), 1;
-                // Any one workgroup of the launch (block i, K or V, head h) is held back until all others have read the length
+                // Any one workgroup of the launch (block i, K or V, part, head h) is held back until all others have read the length
                 // and drawn: the draws so far must not be enough to move it.
-                for (int Hkv : {1, 8}) {
-                    const int others = 2 * blocks * Hkv - 1;
-                    if (others >= append_tickets(blocks, Hkv)) return printf("n %d len %d Hkv %d: the length moves before the last read\n", n, len, Hkv), 1;
-                    if (others + 1 != append_tickets(blocks, Hkv)) return printf("n %d len %d Hkv %d: the length never moves\n", n, len, Hkv), 1;
-                }
+                for (int Hkv : {1, 8})
+                    for (int parts : {1, 2}) {
+                        const int others = 2 * parts * blocks * Hkv - 1;   // the grid's x and y extents, less one
+                        if (others >= append_tickets(blocks, Hkv, parts)) return printf("n %d len %d Hkv %d parts %d: the length moves before the last read\n", n, len, Hkv, parts), 1;
+                        if (others + 1 != append_tickets(blocks, Hkv, parts)) return printf("n %d len %d Hkv %d parts %d: the length never moves\n", n, len, Hkv, parts), 1;
+                    }
                 // why those without tokens count: with the moved length some of them would find tokens
                 for (int i = 0; i < blocks; ++i) {
                     const AppendBlock x = append_block(len, cnt, i), late = append_block(len + cnt, cnt, i);
                     would_stray += x.t_lo >= x.t_hi && late.t_lo < late.t_hi;
                 }
             }
+    // the workgroups of a head are every part of both sides of every block, once, wherever the head begins
+    for (int blocks = 1; blocks <= 40; ++blocks)
+        for (unsigned head = 0; head < 200; ++head)
+            if (!each_once<1>(blocks, head) || !each_once<2>(blocks, head)) return printf("blocks %d head %u\n", blocks, head), 1;
     if (!would_stray) return puts("no length shows the hazard"), 1;
     puts("clean");
 }
