@@ -49,8 +49,8 @@ def test_selection_matches_oracle(T, cfg, G, scale, lens, topk):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - r.out).max(axis=2) <= bound)
 
 
-def test_selection_beyond_the_block_maxima_kept_in_lds(T):
-    """More than 1024 blocks in a sequence: the maxima of the later ones are read from memory.  Tokens of theirs are selected, and one
+def test_selection_of_more_than_1024_blocks(T):
+    """More than 1024 blocks in a sequence: a wave's share is more than 64 of them, a ballot each.  Tokens of the later ones are selected, and one
     sequence ends with a block of a single token."""
     from paper_2409_16546_amd import binding as A, workloads
     from oracle import akv_oracle as O
@@ -114,21 +114,19 @@ def test_selection_of_many_heads(T):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
-def test_token_split_with_whole_blocks_per_wave(T, G):
-    """Groups of one, two and four: enough K blocks that every wave of the K kernel takes a whole one (small calls take half blocks);
-    groups of eight one for all eight heads.  More pairs than those the V kernel cuts into short chunks; ragged lengths
-    down to one token."""
+def test_token_split_with_four_blocks_per_unit(T, G):
+    """1024 K blocks, four waves each: four workgroups of the K kernel to a compute unit.  More pairs than those the V kernel cuts into short
+    chunks; ragged lengths down to one token."""
     from paper_2409_16546_amd import workloads
     lens = [2048, 1, 1027, 300]
-    print(f"token-split path, whole blocks: G{G} lens {lens}", flush=True)
+    print(f"token-split path, four blocks per unit: G{G} lens {lens}", flush=True)
     w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=2048, seed=500 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
-    T.assert_decode_equal(out, dbg, r, lens, G, f"whole blocks G{G}")
+    T.assert_decode_equal(out, dbg, r, lens, G, f"four blocks per unit G{G}")
 
 
 def test_token_split_with_one_wave_per_block_of_eight_heads(T):
-    """Groups of eight, 128 pairs of 12 blocks: six waves per compute unit; a wave of the K kernel takes a block for all eight heads
-    (two waves share one below 3.5 per unit)."""
+    """Groups of eight, 128 pairs of 12 blocks: six blocks per compute unit; a wave of the K kernel takes a whole one for all eight heads."""
     from paper_2409_16546_amd import workloads
     lens = [3072, 1025, 256, 2817]
     print(f"token-split path, one wave per block: G8 lens {lens}", flush=True)
@@ -138,15 +136,13 @@ def test_token_split_with_one_wave_per_block_of_eight_heads(T):
 
 
 @pytest.mark.parametrize("G,lens", [(1, [1024, 129]), (2, [2048, 127]), (4, [4100, 128]), (8, [700, 385])])
-def test_token_split_with_half_blocks_and_short_chunks(T, G, lens):
-    """Few pairs of short sequences: half a block per wave of the K kernel (lengths around 128; groups of eight: two waves per
-    block, four heads each), chunks of the V kernel below
-    512 tokens (128, 128, 320 and 128 of them)."""
+def test_token_split_with_short_chunks(T, G, lens):
+    """Few pairs of short sequences: chunks of the V kernel below 512 tokens (128, 128, 320 and 128 of them), lengths around 128."""
     from paper_2409_16546_amd import workloads
-    print(f"token-split path, half blocks: G{G} lens {lens}", flush=True)
+    print(f"token-split path, short chunks: G{G} lens {lens}", flush=True)
     w = workloads.make(4, B=2, Hq=2 * G, Hkv=2, N=max(lens), seed=600 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
-    T.assert_decode_equal(out, dbg, r, lens, G, f"half blocks G{G}")
+    T.assert_decode_equal(out, dbg, r, lens, G, f"short chunks G{G}")
 
 
 @pytest.mark.parametrize("lens", [[1, 63, 64, 65], [255, 256, 257, 191], [0, 513, 128, 193]])
@@ -263,4 +259,25 @@ def test_token_split_step_where_the_pairs_begin_at_equal_distances(T, G):
     torch.cuda.synchronize()
     T.assert_cache_equal(gc, oc)
     T.assert_decode_equal(out, dbg, O.decode_attention(oc, T.bits(w.q)), oc.lens.tolist(), G, f"turned G{G}")
+    assert refused == 1 and int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == 1
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_token_split_step_with_one_wave_per_block(T, G):
+    """1600 K blocks: a wave per block, and the one whose block the new token joins takes its values from the token's row.  Cache and decisions
+    against the oracle; the new token is the first of a block, the last, between, at odd and even places, and refused."""
+    from paper_2409_16546_amd import binding as A, workloads
+    from oracle import akv_oracle as O
+    B, Hkv, N, lens = 8, 40, 1280, [0, 255, 256, 1023, 1024, 1025, 1279, 1280]
+    print(f"token-split step, one wave per block: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=B, Hq=Hkv * G, Hkv=Hkv, N=N, seed=1100 + G)
+    oc, gc = T.oracle_cache(w.k, w.v, lens, N), T.gpu_cache(w.k, w.v, lens, Hkv * G, N)
+    gen = torch.Generator().manual_seed(G)
+    kn, vn = ((torch.randn(B, Hkv, 1, 128, generator=gen) * 3).half() for _ in range(2))
+    refused = O.append(oc, T.bits(kn), T.bits(vn), np.array([1] * B, np.int32))
+    dbg = A.DebugBuffers.allocate(gc, want_needV=False)
+    out = A.akv_append_decode_attention(gc, kn.to(DEV), vn.to(DEV), w.q.to(DEV), dbg=dbg, path=2)
+    torch.cuda.synchronize()
+    T.assert_cache_equal(gc, oc)
+    T.assert_decode_equal(out, dbg, O.decode_attention(oc, T.bits(w.q)), oc.lens.tolist(), G, f"step, one wave per block G{G}")
     assert refused == 1 and int(gc.flags.cpu()[A.AKV_FLAG_OVERFLOW]) == 1
