@@ -146,9 +146,10 @@ typedef struct akv_params {
     const akv_debug *dbg; /* host pointer to a struct of device pointers, or NULL                    */
     void *const *events;  /* host pointer to AKV_NEVENTS hipEvent_t, or NULL: the library records them on the
                              stream so that a caller can time the kernels in place -- [0] before its first
-                             kernel, [1] in front of the K kernel (after the append kernel where
-                             akv_append_decode_attention runs one), [2] after the K kernel, [3] in front of
-                             the V kernel, [4] after its last kernel.  On the head-per-workgroup path, which
+                             kernel, [1] in front of the K kernel, [2] after it, [3] in front of the V
+                             kernel, [4] after its last kernel.  [1] follows [0] at once: the kernels store
+                             the new token of akv_append_decode_attention themselves, its K and V bytes in
+                             front of [3] and the length behind it.  On the head-per-workgroup path, which
                              is one kernel, [1], [2] and [3] follow [0] at once                        */
     int32_t path;         /* 0: choose; 1: head-per-workgroup path (one kernel; needs Hq/Hkv <= 4);
                              2: token-split path (three kernels).  Both give the same decisions.       */
