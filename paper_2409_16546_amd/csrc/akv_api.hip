@@ -325,13 +325,17 @@ akv_status decode_impl(const akv_cache* cache, const uint16_t* k_new, const uint
             shortest = std::min(shortest, std::max(long(akv::kVMinChunk), ((a.s.Ncap / akv::kVFewChunks + 63) / 64) * 64L));
         a.vslots = akv::v_slots(a.s);
         a.vchunk = int(std::max(shortest, chunk));
-        // K kernel: a block per wave streams best where the device is full of waves; up to five blocks per compute unit the time is one
-        // wave's walk, and four waves share a block.  Four / one, us a call, full and ragged (a quarter to all of the bound): 8 pairs of
-        // four heads 1024 20.5/30.7, 8192 28.7/38.3, 32768 (4 blocks per unit) 48.5/50.2, 38.9/43.8; 24 pairs of eight 13000 (4.8)
-        // 59.6/61.8, 49.2/57.5; 64 pairs of four 4096 (4) 45.1/46.0, 39.3/42.2; 256 single heads 1024 (4) 52/52; but 64 pairs of four
-        // 8192 (8) 67.4/62.5, 56.3/53.6; 32 pairs of eight 16384 (8) 82.6/77.5, 66.4/64.6; 256 single heads 2048 (8) 52.7/50.3
+        // K kernel: a block per wave streams best where the device is full of waves; with few blocks per compute unit the time is one wave's
+        // walk, and four waves share a block.  Both timed at 3 to 10 blocks per unit over 16 to 768 pairs, full, ragged (a quarter to all of
+        // the bound) and a tenth full.  Four / one, us a call, 128 pairs:
+        //   single heads     5 blocks 35.4/38.0, 32.1/35.0, 20.7/23.6; 6 38.6/40.6, 34.4/36.3, 23.2/25.0; 7 46.2/46.5, 38.0/39.8, 22.7/26.9; 8
+        //                    50.8/48.1, 41.0/41.7, 35.9/35.6 (256 pairs, 7: 46.5/46.0; 8: 50.5/47.7, 44.4/41.3)
+        //   groups of two    5 40.5/43.5, 36.4/40.3, 23.2/26.5; 6 45.2/46.4, 39.0/41.7, 25.7/27.8; 7 51.7/50.5, 41.4/43.5, 26.2/32.1
+        //   groups of four   5 46.0/47.0, 38.4/43.4, 25.6/30.8; 6 51.2/49.6, 42.5/45.2, 29.0/32.5 (768 pairs, 6: 66.1/64.5, 61.1/60.4)
+        //   groups of eight  5 55.3/58.9, 47.9/55.2, 32.2/37.8; 6 61.7/61.8, 52.3/57.2, 37.3/39.2; 7 69.9/68.2, 57.4/60.7, 36.1/47.3
+        // Where full sequences are the slower ones the block stays with one wave.
         const long waves = pairs * ((a.max_len + akv::kTB - 1) / akv::kTB);
-        a.kshort = waves <= 5L * cus;
+        a.kshort = waves <= (G == 4 ? 5L : 6L) * cus;
         // Workgroups go to the XCDs and their units in turn: where a pair has 64 or 128 of them the first blocks of all pairs meet on a few units, and
         // where sequences are far shorter than their bound those are the ones with work.  There the pairs begin at equal distances.  As they
         // were / turned, us, full, ragged, a tenth of the bound: 8 pairs 32768 single heads 37.8/37.7, 29.3/28.0, 22.6/19.9, groups of two

@@ -1,6 +1,6 @@
 // Decode attention, token-split path: the tokens of every (sequence, KV head) are spread over many
 // workgroups (long contexts, few heads).  Three kernels:
-//   K kernel          Rule 1 levels + q.K~, a 256-token block per wave, half of one, or a block per two waves;
+//   K kernel          Rule 1 levels + q.K~, a 256-token block per wave, or a quarter of one in calls of few blocks (akv_k_short.h);
 //   selection kernel  one workgroup per (sequence, query head): max, approximate top-k, O_est and the result exponents;
 //   V kernel          Rule 2 + S.V~ over chunks of tokens; the workgroup that finishes last combines the chunks.
 // Sections "Quantization of K-Cache", "Quantization of V-Cache", "Runtime of AlignedKV".

@@ -126,11 +126,11 @@ def test_token_split_with_four_blocks_per_unit(T, G):
 
 
 def test_token_split_with_one_wave_per_block_of_eight_heads(T):
-    """Groups of eight, 128 pairs of 12 blocks: six blocks per compute unit; a wave of the K kernel takes a whole one for all eight heads."""
+    """Groups of eight, 128 pairs of 13 blocks: more than six blocks per compute unit; a wave of the K kernel takes a whole one for all eight heads."""
     from paper_2409_16546_amd import workloads
-    lens = [3072, 1025, 256, 2817]
+    lens = [3328, 1025, 256, 2817]
     print(f"token-split path, one wave per block: G8 lens {lens}", flush=True)
-    w = workloads.make(3, B=4, Hq=256, Hkv=32, N=3072, seed=508)
+    w = workloads.make(3, B=4, Hq=256, Hkv=32, N=3328, seed=508)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
     T.assert_decode_equal(out, dbg, r, lens, 8, "one wave per block G8")
 
@@ -158,13 +158,24 @@ def test_token_split_with_four_waves_per_block(T, G, lens):
 
 @pytest.mark.parametrize("G", [1, 2, 4])
 def test_token_split_with_one_wave_per_block(T, G):
-    """Six K blocks per compute unit: a wave takes a whole one."""
+    """More than six K blocks per compute unit: a wave takes a whole one."""
     from paper_2409_16546_amd import workloads
-    lens = [3072, 1, 2049, 300]
+    lens = [3328, 1, 2049, 300]
     print(f"token-split path, one wave per block: G{G} lens {lens}", flush=True)
-    w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=3072, seed=800 + G)
+    w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=3328, seed=800 + G)
     gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
     T.assert_decode_equal(out, dbg, r, lens, G, f"one wave per block G{G}")
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_token_split_with_six_blocks_per_unit(T, G):
+    """Six K blocks per compute unit, the last count that goes to four waves each (groups of four: a wave each)."""
+    from paper_2409_16546_amd import workloads
+    lens = [3072, 3, 2049, 1281]
+    print(f"token-split path, six blocks per unit: G{G} lens {lens}", flush=True)
+    w = workloads.make(2, B=4, Hq=32 * G, Hkv=32, N=3072, seed=820 + G)
+    gc, oc, out, dbg, r = T.run_both(w.k, w.v, w.q, lens, path=2)
+    T.assert_decode_equal(out, dbg, r, lens, G, f"six blocks per unit G{G}")
 
 
 @pytest.mark.parametrize("cfg,scale", [(3, 0.0), (2, 1e-6), (2, 0.01)])          # the cut in the floor bucket, in the first, between

@@ -70,7 +70,7 @@ def test_four_workgroups_of_the_selection_kernel_share_a_compute_unit(table):
 
 
 def test_four_workgroups_of_the_short_k_kernel_share_a_compute_unit(table):
-    """Up to five workgroups of four waves per unit: a wave per SIMD each."""
+    """Up to six workgroups of four waves per unit: a wave per SIMD each."""
     variants = [k for n, k in table.items() if "split_k_short_kernel" in n]
     assert len(variants) == 4
     for k in variants:
