@@ -201,9 +201,9 @@ void* static_scratch_for_current_device(hipStream_t s)
 // Head-per-workgroup or token-split kernels, when the caller leaves the choice to the library.  One head kernel
 // workgroup occupies a compute unit, so `pairs` (sequence, KV head) pairs run in ceil(pairs / CUs) rounds of equal
 // length: the path pays when there is one round and it is full enough for the length, or when the sequences are so short
-// that the single launch outweighs idle units; for single query heads, which go two to a unit where there are more than units, also for
-// up to two of them per unit, and at more rounds whose last one is full enough, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and written
-// bytes cost several times what read bytes cost).
+// that the single launch outweighs idle units; for single query heads, which go two to a unit where there are more pairs than units, also
+// with any number of them, as long as the logits of a pair fit its LDS, 12288 tokens (the token-split kernels write theirs to memory, and
+// written bytes cost several times what read bytes cost).
 // The host knows a bound of the lengths only (max_len, or the capacity), and sequences that are not full cost the token-split
 // path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step (append and
 // attention in one call) costs it more as well.  So the lines lie
@@ -222,28 +222,34 @@ void* static_scratch_for_current_device(hipStream_t s)
 //   groups of 4   128 pairs 128 23.4/22.7, 23.4/22.9, 28.7/25.7, 160 pairs 23.5/25.5, 23.5/25.9, 29.7/29.2; 128 pairs 512 29.5/24.6, 28.1/23.8,
 //                 33.9/29.5, 192 pairs 29.7/30.6, 29.2/30.0, 36.0/38.0; 192 pairs 1024 36.4/36.2, 35.4/35.0, 45.0/44.5, 224 pairs 36.9/40.1,
 //                 35.6/36.9, 46.0/48.8; 192 pairs 2048 53.9/53.3, 50.4/49.1, 60.4/67.6; 224 pairs 4096 97.4/98.2, 92.2/85.1, 105.9/111.5
-//   257 to 512 pairs of single heads, two to a unit up to 11264 tokens, full, step, lengths a quarter to all of the bound: 264 pairs 256
-//                 16.4/22.2, 21.7/26.4, 16.2/21.5, 1024 32.4/35.4, 37.3/43.6, 28.2/32.9, 2048 51.4/56.7, 55.5/61.4, 36.0/48.0, 4096
-//                 97.8/92.1, 103.0/101.8, 78.4/76.8; 352 pairs 4096 102/108, 105/119, 75/88, 8192 215/197, 221/219, 155/163; 416 pairs
-//                 8192 233/236, 241/260, 177/196, 11264 311/318, 320/332, 226/243; 512 pairs 512 25.2/31.3, 2048 65.4/80.5, 8192
-//                 250/270.  (From 257 to 512 tokens the head kernel is ahead as well; there the choice is as it was.)  Longer ones, one
-//                 after the other: 448 pairs 12288 354/367, 512 pairs 12288 384/401
-//   more rounds (timed one after the other), full / step / lengths a quarter to all of the bound: an idle part of the last round is
-//                 shared by all rounds.  4096
-//                 tokens: 640 pairs 191/193, 207/221, 133/155; 860 255/258, 283/291, 170/202; 1100 322/321, 356/363, 218/244; 1312
-//                 374/377, 420/425, 261/286; 1536 400/413; but 1024 pairs 2048 172/152, 768 pairs 1024 79/70.  Above that full
-//                 sequences and steps lose where the last round is less than half full: 5000 tokens 860 pairs 315/302, 337/327, 209/231; 1312
-//                 459/443, 502/474; 6144 860 384/362, 1312 547/515; 8192 860 488/473, 527/508; 1312 742/712, 782/741; 12280 1312
-//                 1047/1008; from half full on they are even: 6144 704 293/300, 311/324, 210/229; 1408 568/570, 607/616, 376/426;
-//                 8192 704 377/371, 409/399, 275/288; 928 485/493, 538/530, 342/367; 1216 638/646, 692/676, 427/458; 1536 757/781
+// Single heads with more pairs than units, two to a unit up to 11264 tokens (full, lengths a quarter to all of the bound, step):
+//   257 to 512    264 pairs 128 15.3/22.0, 14.9/21.6, 21.4/26.5, 384 19.3/25.5, 17.6/24.6, 24.4/29.1, 1024 32.3/33.8, 26.6/31.2, 36.4/49.3,
+//                 2048 51.6/56.7, 41.6/47.6, 56.3/67.0, 3072 74.6/71.6, 62.6/60.8, 80.4/85.8, 4096 100.7/90.1, 80.4/77.0, 107/103; 320 pairs
+//                 4096 104/97, 76/79, 111/114; 384 pairs 3072 82/87, 72/73, 91/104, 6144 160/156, 120/118, 169/175, 8192 211/201,
+//                 166/169, 224/221; 448 pairs 8192 223/239, 172/203, 239/263, 11008 299/320, 230/251, 316/337; 512 pairs 512 24.0/30.7,
+//                 22.8/29.0, 32.6/49.4, 2048 65.8/79.0, 48.5/67.2, 77/102, 8192 241/265, 183/222, 258/287
+//   more          520 pairs 1024 50.3/57.3, 42.0/49.6, 62.2/75.0, 5000 196/195, 123/152, 214/210, 8192 311/305, 205/261, 332/326; 768 pairs
+//                 1024 57.9/64.1, 50.9/52.5, 80.4/90.7, 4096 182/204, 127/166, 209/232; 1040 pairs 1024 86/90, 67/76, 112/125, 4096
+//                 273/289, 193/237, 313/321, 8192 532/551, 376/467, 590/586; 1312 pairs 5000 403/430, 269/317, 470/455, 8192 640/673,
+//                 472/569, 726/717; 2080 pairs 512 97/95, 84/83, 141/147, 1024 154/161, 120/130, 208/227, 8192 986/1042, 686/871,
+//                 1129/1116; 4096 pairs 512 175/177, 152/151, 262/288, 2048 474/545, 332/436, 628/691.
+//                 A block or two, not quite filled: 520 pairs 320 tokens 32.0/32.8, 29.2/30.4, 39.6/36.9; 640 pairs 128 26.8/27.8, 25.6/27.4,
+//                 36.0/33.5, 384 32.5/35.5, 30.7/33.6, 43.0/44.8; 1040 pairs 128 39.6/38.8, 37.8/37.9, 50.8/51.0; 1792 pairs 256
+//                 61.0/63.4, 58.2/60.6, 85.9/96.6; 2080 pairs 256 75.9/72.3, 72.1/68.9, 108/115, 448 97/94, 82/82, 133/125; 4096 pairs 256
+//                 139/125, 130/119, 213/217, 384 160/157, 140/133, 240/239
+// Longer ones run one after the other, and an idle part of the last round is shared by all rounds: 12288 tokens 384 pairs 320/296, 231/218,
+// 512 368/383, 249/285, 544 475/457, 304/342, 768 543/573, 386/427, 896 671/686, 462/521, 1312 993/995, 669/735 (its step in an earlier
+// state 5 per cent behind).
 bool head_path_pays(long pairs, int G, int max_len)
 {
     const long cus = compute_units(), rounds = (pairs + cus - 1) / cus;
     const double fill = double(pairs) / double(rounds * cus), last = double(pairs - (rounds - 1) * cus) / double(cus);   // of all rounds, of the last one
-    if (rounds == 2 && G == 1)
-        return max_len <= 256 || (max_len > 512 && (max_len <= 3072 || (max_len <= 4096 && fill >= 0.6) || (max_len <= 8192 && fill >= 0.75) ||
-                                                    (max_len <= 11264 && fill >= 0.8) || (max_len <= 12288 && fill >= 0.85)));
-    if (rounds >= 2) return G == 1 && max_len <= 12288 && fill >= 0.83 && max_len >= 4096 && (max_len == 4096 || last >= 0.5);
+    if (rounds >= 2 && G != 1) return false;
+    if (rounds == 2)
+        return max_len <= 3072 || (max_len <= 4096 && fill >= 0.6) || (max_len <= 8192 && fill >= 0.75) || (max_len <= 11264 && fill >= 0.8) ||
+               (max_len <= 12288 && fill >= 0.85);
+    if (rounds > 2 && max_len <= 11264) return max_len > 448 || (pairs > 5 * cus / 2 && pairs <= 7 * cus);
+    if (rounds > 2) return max_len <= 12288 && fill >= 0.83 && last >= 0.5;
     struct Rule { int len; double fill; };   // up to len tokens from this fill on
     static constexpr Rule g1[] = {{256, 0.0}, {1024, 0.3}, {2048, 0.25}, {3072, 0.5}, {4096, 0.53}, {8192, 0.65}, {12288, 0.85}},
                           g2[] = {{128, 0.0}, {512, 0.3}, {2048, 0.4}, {4096, 0.6}, {6144, 0.85}, {8192, 0.9}},

@@ -39,8 +39,9 @@ template <int G, int NT> constexpr int head_v_groups() { return G == 2 ? 4 : 2; 
 // step, barriers, the waves that are done first: 15 to 23 us) is spent once and not in every round, and one streams while the other
 // does not.  For that both have to fit the LDS, so that what is used behind the K side shares the staging areas' place.  One after the
 // other / two to a unit, us: 512 pairs 600 tokens 40.7/28.9, 1024 51.0/40.8, 2048 76.7/63.9, 4096 129/121, 8192 267/250, 11000 354/342;
-// 1024 pairs 4096 269/253; lengths a quarter to all of the bound 512 pairs 2048 62/50, 8192 203/200 (768 pairs 4096 the one call behind,
-// 135.8/139.9).
+// 1024 pairs 4096 269/253; lengths a quarter to all of the bound 512 pairs 2048 62/50, 8192 203/200.  More pairs than two per unit, 544 to
+// 1536 of them, 1024 to 11008 tokens: 0.89 of the time over full sequences, 0.94 in steps (none slower).  Ragged ones depend on how the drawn
+// lengths fall into rounds: 544 to 768 pairs of 3072 to 8192 tokens, ten draws each, 0.96 on average, 0.87 to 1.18 in single ones.
 // LDSLG: the logits of the pair stay in LDS (lds_tokens floats per query head, dynamic shared memory) between the K
 // side, the mid step and the V side instead of going through the workspace: nothing of them is written to memory
 // (16 MB of logits written during a 0.8 GB stream cost as much time as 100 MB of reads on this machine).

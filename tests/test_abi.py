@@ -147,18 +147,21 @@ def test_decode_path_keeps_the_head_kernel_where_sequences_may_be_short(A):
     for B, Hkv, G, N in [(28, 8, 4, 2304), (28, 8, 4, 4096), (32, 8, 4, 6144), (20, 8, 4, 2048), (2, 32, 1, 2048), (12, 8, 1, 1536),
                          (16, 32, 1, 1536), (16, 32, 1, 1024)]:
         assert A.akv_decode_path(B, Hkv * G, Hkv, 128, N) in (1, 3), (B, Hkv, G, N)
-    for B, Hkv, G, N in [(8, 8, 4, 1024), (4, 8, 4, 256), (16, 32, 1, 512), (4, 8, 1, 2048), (32, 8, 4, 8192), (8, 32, 1, 8448 + 4096)]:
+    for B, Hkv, G, N in [(8, 8, 4, 1024), (4, 8, 4, 256), (4, 8, 1, 2048), (32, 8, 4, 8192), (8, 32, 1, 8448 + 4096)]:
         assert A.akv_decode_path(B, Hkv * G, Hkv, 128, N) == 2, (B, Hkv, G, N)
 
 
 @pytest.mark.parametrize("B,Hkv,N,path", [
-    (16, 32, 8448, 3), (14, 32, 12288, 3), (16, 32, 12544, 2),        # two rounds: as long as the logits fit the LDS
-    (24, 32, 4096, 3), (20, 32, 4096, 3), (48, 32, 12288, 3),          # more rounds, all of them 83 % full together
-    (18, 32, 4096, 2), (32, 32, 2048, 2), (24, 32, 3840, 2),
-    # a last round that is less than half full (860 pairs 36 %, 1100 30 %, 1312 12 %): up to 4096 tokens only
-    (215, 4, 4096, 3), (275, 4, 4096, 3), (41, 32, 4096, 3),
-    (215, 4, 4352, 2), (215, 4, 8192, 2), (275, 4, 8192, 2), (41, 32, 8192, 2), (41, 32, 12288, 2),
-    (176, 4, 8192, 3), (352, 4, 8192, 3), (20, 32, 8192, 3)])          # from half full on: longer ones too
+    (16, 32, 8448, 3), (14, 32, 12288, 3), (16, 32, 12544, 2),        # up to 512 pairs: as long as the logits fit the LDS
+    (16, 32, 256, 3), (16, 32, 512, 3), (66, 4, 512, 3), (16, 32, 768, 3),
+    (66, 4, 3072, 3), (66, 4, 3328, 2), (77, 4, 4096, 3), (76, 4, 4096, 2), (96, 4, 8192, 3), (95, 4, 8192, 2),   # 60 and 75 % of them
+    (103, 4, 11264, 3), (102, 4, 11264, 2), (109, 4, 12288, 3), (108, 4, 12288, 2),                           # 80 and 85 %
+    # more, two to a unit: everything above a block or two
+    (24, 32, 4096, 3), (20, 32, 4096, 3), (18, 32, 4096, 3), (32, 32, 2048, 3), (24, 32, 3840, 3), (65, 8, 1024, 3), (129, 4, 512, 3),
+    (215, 4, 4352, 3), (215, 4, 8192, 3), (275, 4, 11264, 3), (41, 32, 8192, 3), (128, 32, 512, 3),
+    (160, 4, 256, 2), (161, 4, 256, 3), (448, 4, 256, 3), (449, 4, 256, 2), (128, 32, 256, 2),
+    # longer, one after the other: all rounds 83 % full together, the last one half full
+    (48, 32, 12288, 3), (41, 32, 12288, 2), (17, 32, 12288, 2), (24, 32, 12288, 3), (28, 32, 12288, 3), (24, 32, 12544, 2)])
 def test_decode_path_of_single_heads_in_several_rounds(A, B, Hkv, N, path):
     assert A.akv_decode_path(B, Hkv, Hkv, 128, N) == path
 

@@ -9,15 +9,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("Ncap", [1024, 1280, 11264, 11520])
-def test_more_single_heads_than_units_match_oracle(Ncap):
+@pytest.mark.parametrize("Ncap,B", [(1024, 65), (1280, 65), (11264, 65), (11520, 65), (1280, 131)])   # 131: more than two pairs per unit
+def test_more_single_heads_than_units_match_oracle(Ncap, B):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from oracle import akv_oracle as O
     O.build()
     import akv_testlib as T
     from paper_2409_16546_amd import binding as A, workloads
-    B, Hkv = 65, 4
+    Hkv = 4
     print(f"head kernel: {B * Hkv} pairs, room for {Ncap}", flush=True)
     n = min(Ncap, 1280)
     w = workloads.make(2, B=B, Hq=Hkv, Hkv=Hkv, N=n, seed=Ncap)
