@@ -294,10 +294,12 @@ hipError_t launch_append(const akv_cache& c, const uint16_t* k_new, const uint16
         const int blocks = append_grid_blocks(n);
         const int parts = blocks <= 16 && 2 * blocks * pairs <= 4096 ? 2 : 1;
         const dim3 grid(2 * parts * blocks, c.shape.Hkv, c.shape.B);
-        // few workgroups move the length by ticket: a launch less, but tickets on one cache line cost more than the launch where they
-        // are many (launch / tickets, us: 64 workgroups 11.5/8.7, 256 11.6/10.9, 288 11.7/10.2, 320 12.0/12.7, 512 13.3/15.7; one per
-        // side 320 on one sequence 13.4/12.4, 384 17.4/18.7)
-        const bool ticketed = long(grid.x) * grid.y * grid.z <= (parts == 2 ? 288 : 320);
+        // few workgroups move the length by ticket: a launch less, but tickets on one cache line cost more than the launch where they are
+        // many.  Launch / tickets, two per side, us for the copy that sets the lengths and K_colmax cleared in front (where the launches set the
+        // pace), and what the tickets cost in device time behind a long kernel: 256 workgroups 15.6/12.8, +0.4; 320 15.6/13.5, +0.8; 384
+        // 15.5/14.2, +1.5; 480 15.2/15.2, +2.1; 640 15.7/18.7, +4.5.  One per side (the copy alone): 320 on one sequence 13.4/12.4, 384
+        // 17.4/18.7.
+        const bool ticketed = long(grid.x) * grid.y * grid.z <= 320;
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, c, k_new, v_new, n_new, n, ticketed ? 1 : 0); };
         if (parts == 2) launch(append_block_kernel<2>);
         else launch(append_block_kernel<1>);

@@ -166,6 +166,7 @@ def test_unpack_of_v_alone_gives_back_what_was_stored(T, B, H):
 
 @pytest.mark.parametrize("B,Hkv,n", [
     (25, 16, 256),                # two workgroups per side, the length by a launch
+    (10, 4, 36), (41, 1, 36),     # 320 and 328 workgroups of two per side: the length by ticket, by a launch
     (32, 32, 60), (33, 32, 60),   # 4096 workgroups of one per side, the last with two; one more sequence
     (3, 3, 3841), (3, 3, 3842),   # 16 blocks, the last with two per side; 17, and the length by ticket
 ])
