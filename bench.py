@@ -88,15 +88,20 @@ class HipEvents:
         return float(ms.value)
 
 
-def measured_traffic(kernel_tag: str, cfg: int):
-    """HBM bytes per launch of a kernel from the committed rocprofv3 --pmc summary of that kernel and configuration
-    (profiles/<kernel_tag>_cfg<cfg>_pmc.txt), or None.  Not measured in this run: counters need rocprofv3."""
+def measured_traffic(kernel_tag: str, cfg: int, names: list[str]):
+    """HBM bytes per launch of a kernel, where from, and which of `names` it is, from the committed rocprofv3 --pmc summary of that kernel
+    and configuration (profiles/<kernel_tag>_cfg<cfg>_pmc.txt); None where there is none or it is of another kernel.  Not measured
+    in this run: counters need rocprofv3."""
     path = os.path.join(ROOT, "profiles", f"{kernel_tag}_cfg{cfg}_pmc.txt")
     try:
-        m = re.search(r"^traffic_bytes_per_launch:\s*([0-9.eE+]+)", open(path).read(), flags=re.M)
-        return (int(float(m.group(1))), os.path.relpath(path, ROOT)) if m else (None, None)
+        text = open(path).read()
     except OSError:
-        return None, None
+        return None, None, None
+    of = re.match(r"HBM traffic of (.+) on benchmark configuration", text)
+    m = re.search(r"^traffic_bytes_per_launch:\s*([0-9.eE+]+)", text, flags=re.M)
+    if not of or not m or of.group(1) not in names:
+        return None, None, None
+    return int(float(m.group(1))), os.path.relpath(path, ROOT), of.group(1)
 
 
 def main():
@@ -275,26 +280,27 @@ def main():
             entry["path"] = "head-per-workgroup (one kernel" + ("; logits in LDS)" if path == 3 else ")")
             entry["kernel_us"] = {"head_kernel": round(us_events, 2)}
             nt = 1024 if Hq == Hkv and (B * Hkv <= torch.cuda.get_device_properties(0).multi_processor_count or maxlen > 11264) else 512
-            dom_name = f"akv::head_kernel<{Hq // Hkv}, {nt}, false, {'true, ' + ('2' if maxlen <= 2 * nt else '4') if path == 3 else 'false, 4'}>"
+            dom_names = [f"akv::head_kernel<{Hq // Hkv}, {nt}, false, {'true, ' + ('2' if maxlen <= 2 * nt else '4') if path == 3 else 'false, 4'}>"]
             dom_tag, dom_us, dom_bytes = "head_kernel", us_events, by["total"]
         else:
             entry["path"] = "token-split (K, selection, V kernels)"
-            entry["kernel_us"] = {"append": round(seg[0], 2), "k_kernel": round(seg[1], 2), "selection_kernel": round(seg[2], 2),
-                                  "v_kernel": round(seg[3], 2),
+            entry["kernel_us"] = {"k_kernel": round(seg[1], 2), "selection_kernel": round(seg[2], 2), "v_kernel": round(seg[3], 2),
                                   "how": f"HIP events recorded by the library between its kernels, mean over {prof_steps} steps run right "
                                          f"after the timed ones, minus the {gap:.2f} us two back-to-back events lie apart"}
-            if by["k_kernel"] >= by["v_kernel"]:
-                short = B * Hkv * ((maxlen + 255) // 256) <= 5 * torch.cuda.get_device_properties(0).multi_processor_count
-                dom_name, dom_tag, dom_us, dom_bytes = f"akv::split_k_{'short_' if short else ''}kernel<{Hq // Hkv}>", "split_k_kernel", seg[1], by["k_kernel"]
+            if by["k_kernel"] >= by["v_kernel"]:             # one wave per block, or four in short calls: the library chooses
+                dom_names = [f"akv::split_k_kernel<{Hq // Hkv}>", f"akv::split_k_short_kernel<{Hq // Hkv}>"]
+                dom_tag, dom_us, dom_bytes = "split_k_kernel", seg[1], by["k_kernel"]
             else:
-                dom_name, dom_tag, dom_us, dom_bytes = f"akv::split_v_kernel<{Hq // Hkv}, false>", "split_v_kernel", seg[3], by["v_kernel"]
+                dom_names = [f"akv::split_v_kernel<{Hq // Hkv}, false>"]
+                dom_tag, dom_us, dom_bytes = "split_v_kernel", seg[3], by["v_kernel"]
             entry["kernel_frac_of_peak"] = {"k_kernel": round(by["k_kernel"] / seg[1] / 1e3 / HBM_PEAK_GBS, 4),
                                             "v_kernel": round(by["v_kernel"] / seg[3] / 1e3 / HBM_PEAK_GBS, 4)}
         entry["algorithmic_bytes"] = by
         entry["reduction_vs_fp16"] = round(1.0 - by["total"] / by["fp16"], 4)
         entry["step_GBps"] = round(by["total"] / us_step / 1e3, 1)
         entry["step_frac_of_peak"] = round(by["total"] / us_step / 1e3 / HBM_PEAK_GBS, 4)
-        traffic, traffic_src = measured_traffic(dom_tag, cfg)
+        traffic, traffic_src, dom_name = measured_traffic(dom_tag, cfg, dom_names)
+        dom_name = dom_name or " or ".join(dom_names)
         roof = {"bound": "hbm", "kernel": dom_name, "achieved": round(dom_bytes / dom_us / 1e3, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(dom_bytes / dom_us / 1e3 / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "traffic_source": (traffic_src + " (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a plain copy; a committed "
