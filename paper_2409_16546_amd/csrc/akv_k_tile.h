@@ -146,8 +146,8 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 
 // One wave, one unit of 64*TPL tokens of (b, h): lane -> tokens TPL*lane .. TPL*lane+TPL-1 of the unit; the logit of a
 // token is accumulated in fp32 over channels in ascending order inside its lane (no reduction).  TPL = 4: a unit is a
-// 256-token block, the form that streams best (2-KB and 1-KB runs).  TPL = 2: half a block, for calls with so few blocks
-// that the time is one wave's walk through its unit: twice the waves, half as many dependent groups each (the call above: 24.8 -> 22.3 us).
+// 256-token block, the form that streams best (2-KB and 1-KB runs).  TPL = 2: half a block, in the head kernel, for calls with so few blocks
+// that the time is one wave's walk through its unit: twice the waves, half as many dependent groups each (the call below: 24.8 -> 22.3 us).
 // Channels are processed U = 32 / TPL at a time, 4 KB per group in either form.  For TPL = 4 the wave fetches per group the 2-KB run of K_hi (8 columns x 256 B,
 // contiguous in the channel-major block) with two 16-B loads per lane, and the 1-KB runs of K_mid / K_lo with one
 // 16-B load per lane each, lane -> (column lane/8, 16 bytes): a column whose level does not ask for a plane is
