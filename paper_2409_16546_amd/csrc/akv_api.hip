@@ -208,20 +208,27 @@ void* static_scratch_for_current_device(hipStream_t s)
 // path more: its workgroups past the lengths are launched all the same, and those that have work fall on few XCDs.  A step (append and
 // attention in one call) costs it more as well.  So the lines lie
 // where the head kernel wins on attention over full sequences, or where it is behind by a few per cent there and ahead by more
-// over sequences that are not full and in steps.  Timed on MI355X over 8..256 pairs, bounds 128..8192, group sizes 1, 2, 4 (head /
-// split, us: full, lengths a quarter to all of the bound, step):
-//   single heads  64 pairs 256 16.5/16.7, 15.6/16.5, 19.9/20.3; 64 pairs 512 18.2/17.8, 18.1/17.4, 22.3/21.9, 96 pairs 18.3/19.8,
-//                 17.8/19.4, 23.1/25.2; 32 pairs 1024 20.4/18.1, 17.5/16.7, 23.7/21.2, 96 pairs 21.4/22.3, 20.4/21.8, 25.5/26.9; 128 pairs
-//                 2048 32.5/30.7, 28.9/29.2, 34.8/37.1; 96 pairs 3072 38.2/35.1, 33.0/30.3, 42.3/38.8, 128 pairs 39.2/41.1, 37.1/36.7,
-//                 42.5/48.6; 128 pairs 4096 49.3/48.3, 45.5/42.4, 53.9/60.3, 160 pairs 51.1/59.1, 38.7/48.2, 55.8/69.4; 128 pairs 8192
-//                 92/79, 79/76, 99/90, 192 pairs 113/111, 89/99, 118/125
-//   groups of 2   64 pairs 256 18.4/17.8, 17.6/17.7, 22.4/21.7, 96 pairs 18.5/21.1, 18.1/21.1, 23.4/24.8; 64 pairs 512 20.5/19.2, 20.2/19.0,
-//                 25.1/23.0, 96 pairs 20.7/22.2, 20.1/21.4, 26.4/28.8; 96 pairs 1024 26.3/26.3, 24.9/25.8, 33.7/32.4, 128 pairs 26.4/27.7,
-//                 25.9/27.0, 33.4/35.6; 96 pairs 2048 36.8/35.0, 33.6/33.8, 42.1/41.9, 128 pairs 37.0/39.7, 34.3/38.2, 41.7/48.2; 128 pairs
-//                 4096 65.4/55.6, 61.9/47.8, 70.6/65.4, 160 pairs 66.6/68.8, 53.6/59.0, 71.8/80.3; 192 pairs 6144 105/101, 83/84, 108/113
-//   groups of 4   128 pairs 128 23.4/22.7, 23.4/22.9, 28.7/25.7, 160 pairs 23.5/25.5, 23.5/25.9, 29.7/29.2; 128 pairs 512 29.5/24.6, 28.1/23.8,
-//                 33.9/29.5, 192 pairs 29.7/30.6, 29.2/30.0, 36.0/38.0; 192 pairs 1024 36.4/36.2, 35.4/35.0, 45.0/44.5, 224 pairs 36.9/40.1,
-//                 35.6/36.9, 46.0/48.8; 192 pairs 2048 53.9/53.3, 50.4/49.1, 60.4/67.6; 224 pairs 4096 97.4/98.2, 92.2/85.1, 105.9/111.5
+// over sequences that are not full (a tenth of the bound counts too: there it is ahead nearly everywhere) and in steps.  Timed on MI355X
+// over 8..256 pairs, bounds 128..11008, group sizes 1, 2, 4 (head / split, us: full, lengths a quarter to all of the bound, step, a tenth full):
+//   single heads  64 pairs 256 16.5/16.3, 16.0/16.2, 20.4/19.1, 13.4/15.6; 64 pairs 512 18.1/17.7, 17.8/17.3, 22.0/20.6, 14.2/16.0, 80 pairs
+//                 18.2/19.3, 18.0/19.1, 22.7/23.0, 14.2/17.9; 64 pairs 1024 20.9/20.5, 20.5/18.8, 24.5/24.3, 14.1/17.6, 80 pairs 21.3/22.1,
+//                 20.5/21.6, 25.3/24.8, 14.2/19.5; 64 pairs 2048 31.2/25.3, 28.7/23.0, 33.3/28.9, 15.9/19.1, 128 pairs 32.8/30.2,
+//                 30.6/28.7, 34.6/36.2, 16.2/26.2; 96 pairs 3072 38.4/34.5, 36.9/31.2, 41.6/36.9, 20.7/21.6, 128 pairs 39.7/39.1,
+//                 37.2/34.5, 43.1/48.3, 20.8/23.3; 128 pairs 4096 49.7/48.3, 45.1/41.2, 54.0/60.4, 21.2/35.2, 144 pairs 50.6/56.8,
+//                 45.7/48.1, 55.8/62.9, 21.2/28.8; 160 pairs 8192 103/96, 91/85, 107/108, 24/56, 176 pairs 105/107, 93/95, 110/119, 25/58;
+//                 224 pairs 11008 155/167, 131/139, 161/178, 28/81
+//   groups of 2   64 pairs 128 17.0/17.0, 16.8/16.9, 20.8/20.1, 15.7/16.3; 64 pairs 256 18.7/17.5, 18.3/17.3, 22.9/20.3, 16.4/16.8, 80 pairs
+//                 18.8/20.7, 18.4/20.6, 23.5/23.8, 16.4/19.8; 64 pairs 512 20.7/18.9, 20.4/18.4, 25.0/22.4, 16.8/17.1, 80 pairs 20.9/21.5,
+//                 20.6/21.3, 25.6/24.4, 16.9/20.2; 128 pairs 1024 26.5/25.4, 25.7/24.3, 33.3/31.8, 17.2/22.0, 160 pairs 26.7/30.0,
+//                 26.0/29.1, 33.7/35.0, 17.3/26.3; 128 pairs 2048 37.2/33.7, 36.0/32.4, 42.3/40.7, 21.6/29.6, 160 pairs 37.5/41.0,
+//                 36.7/38.6, 43.0/46.2, 21.8/35.2; 144 pairs 4096 66.1/63.7, 62.9/53.9, 72.7/70.2, 23.9/35.2, 160 pairs 67.1/69.0,
+//                 63.3/59.0, 73.3/80.3, 24.3/48.1; 208 pairs 6144 110/112, 92/92, 115/125, 26/46; 240 pairs 8192 156/156, 135/136, 161/170,
+//                 29/85
+//   groups of 4   128 pairs 128 23.5/22.4, 23.5/22.2, 27.5/24.8, 21.9/21.2, 256 pairs 24.2/26.3, 23.9/26.3, 29.2/30.0, 22.0/24.4; 176 pairs
+//                 512 29.5/27.9, 29.1/27.4, 34.5/35.0, 23.5/23.7, 224 pairs 29.7/30.5, 29.2/30.0, 34.8/37.4, 23.6/26.1; 192 pairs 1024
+//                 35.8/33.8, 34.8/32.1, 44.6/40.9, 23.6/28.5, 208 pairs 35.9/38.2, 35.2/36.0, 45.3/44.9, 23.8/31.4; 144 pairs 2048
+//                 53.2/44.3, 52.9/40.2, 59.8/51.8, 30.4/36.9, 192 pairs 54.0/49.9, 52.4/46.0, 60.4/63.7, 30.7/37.5; 208 pairs 4096 101/97,
+//                 91/79, 107/110, 34/58, 256 pairs 108/106, 93/87, 114/121, 34/61; 256 pairs 6144 157/148, 132/114, 161/169, 37/78
 // Single heads with more pairs than units, two to a unit up to 11264 tokens (full, lengths a quarter to all of the bound, step):
 //   257 to 512    264 pairs 128 15.3/22.0, 14.9/21.6, 21.4/26.5, 384 19.3/25.5, 17.6/24.6, 24.4/29.1, 1024 32.3/33.8, 26.6/31.2, 36.4/49.3,
 //                 2048 51.6/56.7, 41.6/47.6, 56.3/67.0, 3072 74.6/71.6, 62.6/60.8, 80.4/85.8, 4096 100.7/90.1, 80.4/77.0, 107/103; 320 pairs
